@@ -144,6 +144,45 @@ struct TileFetch {
   uint32_t gam[QJL ? 1 : 0]; // the token's stored residual norm
 };
 
+// Scores of the uncompressed tail (the newest tokens of every head, binary16, not yet a full block):
+// row[h][t] = <q[h], tail[t]> / sqrt(d) for the tokens t0 .. t0 + TAIL_TOK - 1 of one (sequence, KV head).  16 lanes share a
+// token (16 bytes each), float32 accumulation of exact binary16 products.  These are further workgroups of the scores
+// kernel, 64 tokens each: a kernel of their own cost a launch, and with one workgroup per head 32 us at 12 heads and 389
+// tokens.
+constexpr int TAIL_TOK = 64;
+__device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, int t0, int tail_len,
+                                            const uint16_t* __restrict__ q, int group, float* __restrict__ row, size_t T, float* qs,
+                                            int tid) {
+  const int l16 = tid & 15;
+  float x[TAIL_TOK / 16][8];
+#pragma unroll
+  for (int i = 0; i < TAIL_TOK / 16; ++i) {
+    const int t = t0 + 16 * i + (tid >> 4);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[i][e] = 0.0f;
+    if (t < tail_len) load8(tail, EOQ_F16, (size_t)t * D + 8 * l16, x[i]);
+  }
+  for (int e = tid; e < group * D; e += THREADS) qs[e] = half_bits_to_float(q[e]);
+  __syncthreads();
+  const float inv_sqrt_d = 1.0f / sqrtf((float)D);
+  for (int h = 0; h < group; ++h) {
+    const float4 q0 = *reinterpret_cast<const float4*>(qs + h * D + 8 * l16), q1 = *reinterpret_cast<const float4*>(qs + h * D + 8 * l16 + 4);
+    const float qv[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+#pragma unroll
+    for (int i = 0; i < TAIL_TOK / 16; ++i) {
+      const int t = t0 + 16 * i + (tid >> 4);
+      float acc = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc = fmaf(x[i][e], qv[e], acc);
+      acc += dpp_mov<0xB1>(acc);
+      acc += dpp_mov<0x4E>(acc);
+      acc += dpp_mov<0x141>(acc);
+      acc += dpp_mov<0x140>(acc);
+      if (l16 == 0 && t < tail_len) row[h * T + t] = acc * inv_sqrt_d;
+    }
+  }
+}
+
 // One workgroup per (sequence, KV head, run of blocks); every wave works on 32-token tiles of its own (tile u of the
 // run: tokens 32 (u % tpb) .. of block u / tpb; wave w takes the tiles w, w + 4, ...), the record bytes of the next
 // tile on their way while this one is worked on.  NQ = query heads a lane finishes per token (2 for groups up to 4).
@@ -156,7 +195,8 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     const float* __restrict__ tab, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms,
     const int32_t* __restrict__ rank_in, const uint16_t* __restrict__ lfac, const uint16_t* __restrict__ rfac,
     const uint16_t* __restrict__ q, float* __restrict__ scores, const uint16_t* __restrict__ phih,
-    const uint8_t* __restrict__ qsigns, const uint16_t* __restrict__ qnorms) {
+    const uint8_t* __restrict__ qsigns, const uint16_t* __restrict__ qnorms, int runs, const uint16_t* __restrict__ tail,
+    int64_t tail_capacity, int tail_len) {
   constexpr int TYPES = 1 << (BITS - 1);
   constexpr int NMM = 4 * TYPES;   // matrix instructions per tile: 64 coordinates x TYPES bytes per lane, 16 at a time
   constexpr int WH = 2 * NQ;       // heads the run's w table holds
@@ -187,6 +227,11 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   const size_t T = (size_t)score_stride;   // entries per score row (>= blocks_per_head * n)
   constexpr int ROWB = BITS * D / 8;
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
+  if ((int)blockIdx.x >= runs) {   // a workgroup of the tail
+    tail_scores(tail + sg * (size_t)tail_capacity * D, TAIL_TOK * ((int)blockIdx.x - runs), tail_len, q + q0, group,
+                scores + (sq * n_q_heads + kv * group) * T + (size_t)blocks_per_head * n, T, qraw, tid);
+    return;
+  }
 
   {
     const int tn = tid & 15, xn = tid >> 4;
@@ -518,37 +563,6 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
 #undef EOQ_SC_WORK
 }
 
-// Scores of the uncompressed tail (the newest tokens of every head, binary16, not yet a full block):
-// scores[s][h][offset + t] = <q[s][h], tail[s][g][t]> / sqrt(d).  One workgroup per (sequence, KV head); 16 lanes
-// share a token (16 bytes each), float32 accumulation of exact binary16 products.
-__global__ __launch_bounds__(THREADS) void eoq_scores_tail_kernel(
-    int n_kv_heads, int group, int64_t tail_capacity, int tail_len, const uint16_t* __restrict__ tail,
-    const uint16_t* __restrict__ q, float* __restrict__ scores, int64_t score_stride, int64_t offset) {
-  __shared__ float qs[SC_MAXG * D];
-  const int tid = threadIdx.x, l16 = tid & 15;
-  const size_t sg = blockIdx.x;
-  const size_t sq = sg / n_kv_heads, kv = sg % n_kv_heads;
-  const int n_q_heads = n_kv_heads * group;
-  for (int e = tid; e < group * D; e += THREADS) qs[e] = half_bits_to_float(q[(sq * n_q_heads + kv * group) * D + e]);
-  __syncthreads();
-  const float inv_sqrt_d = 1.0f / sqrtf((float)D);
-  for (int t0 = 0; t0 < tail_len; t0 += THREADS / 16) {   // uniform trip count: the row sums need whole rows
-    const int t = t0 + (tid >> 4);
-    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (t < tail_len) load8(tail, EOQ_F16, (sg * (size_t)tail_capacity + t) * D + 8 * l16, x);
-    for (int h = 0; h < group; ++h) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc = fmaf(x[e], qs[h * D + 8 * l16 + e], acc);
-      acc += dpp_mov<0xB1>(acc);
-      acc += dpp_mov<0x4E>(acc);
-      acc += dpp_mov<0x141>(acc);
-      acc += dpp_mov<0x140>(acc);
-      if (l16 == 0 && t < tail_len) scores[(sq * n_q_heads + kv * group + h) * (size_t)score_stride + offset + t] = acc * inv_sqrt_d;
-    }
-  }
-}
-
 hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl* qjl, int64_t n_seq, int n_kv_heads,
                               int64_t blocks_per_head, const void* q_fp16, int n_q_heads, float* scores,
                               int64_t block_capacity, int64_t score_stride, const void* tail_fp16,
@@ -557,21 +571,14 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   if (block_capacity <= 0) block_capacity = blocks_per_head;
   if (score_stride <= 0) score_stride = blocks_per_head * L.n;
   if (L.ev) (void)hipEventRecord(L.ev[6], L.stream);
-  if (tail_len > 0)
-    hipLaunchKernelGGL(eoq_scores_tail_kernel, dim3((unsigned)sg_total), dim3(THREADS), 0, L.stream, n_kv_heads,
-                       n_q_heads / n_kv_heads, tail_capacity, tail_len, static_cast<const uint16_t*>(tail_fp16),
-                       static_cast<const uint16_t*>(q_fp16), scores, score_stride, blocks_per_head * L.n);
-  if (blocks_per_head == 0) {
-    if (L.ev) (void)hipEventRecord(L.ev[7], L.stream);
-    return hipGetLastError();
-  }
   // blocks per workgroup: the query set-up is paid once per workgroup, so runs are as long as they can be (16) while the
   // grid still has a workgroup for each of the 4 x 256 places on the chip
   int64_t run = (sg_total * blocks_per_head + 1023) / 1024;
   run = run < 1 ? 1 : (run > SC_RUN_MAX ? SC_RUN_MAX : run);
   const int64_t runs = (blocks_per_head + run - 1) / run;
-  if (sg_total > 65535 || runs > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)runs, (unsigned)sg_total), block(THREADS);
+  const int64_t tail_groups = (tail_len + TAIL_TOK - 1) / TAIL_TOK;
+  if (sg_total > 65535 || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(runs + tail_groups), (unsigned)sg_total), block(THREADS);
   const uint16_t* q = static_cast<const uint16_t*>(q_fp16);
   const int group = n_q_heads / n_kv_heads;
 #define EOQ_SCORES_ARGS                                                                                              \
@@ -580,10 +587,12 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
 #define EOQ_SCORES(BITS, NQ)                                                                                         \
   do {                                                                                                               \
     if (qjl)                                                                                                         \
-      hipLaunchKernelGGL((eoq_scores_i8_kernel<BITS, true, NQ>), EOQ_SCORES_ARGS, L.phih, qjl->signs, qjl->norms); \
+      hipLaunchKernelGGL((eoq_scores_i8_kernel<BITS, true, NQ>), EOQ_SCORES_ARGS, L.phih, qjl->signs, qjl->norms,  \
+                         (int)runs, (const uint16_t*)nullptr, (int64_t)0, 0);                                        \
     else                                                                                                             \
       hipLaunchKernelGGL((eoq_scores_i8_kernel<BITS, false, NQ>), EOQ_SCORES_ARGS, (const uint16_t*)nullptr,      \
-                         (const uint8_t*)nullptr, (const uint16_t*)nullptr);                                         \
+                         (const uint8_t*)nullptr, (const uint16_t*)nullptr, (int)runs,                              \
+                         static_cast<const uint16_t*>(tail_fp16), tail_capacity, tail_len);                          \
   } while (0)
 #define EOQ_SCORES_BITS(NQ)                 \
   switch (L.bits) {                         \
