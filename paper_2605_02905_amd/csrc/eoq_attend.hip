@@ -17,255 +17,571 @@ using namespace eoqdev;
 constexpr int D = EOQ_D;
 constexpr int THREADS = 256;
 constexpr int MAXG = 8;      // query heads per KV head
-constexpr int CHUNK = 128;   // tokens staged per pass (n is a multiple of 128)
+constexpr int PAIR = 64;     // tokens of one pass of a wave: two tiles of 32
 
-// One workgroup: blocks [blockIdx.x * run, ...) of (sequence, KV head) blockIdx.y.
-// Codebook term: lane (cg, tg) = (tid % 32, tid / 32) owns the four coordinates 4 cg .. 4 cg + 3 and the tokens tg,
-// tg + 8, ... of every chunk.  Per token it reads one byte of every bit-plane, and for codes of up to 2 bits one entry
-// of a 256-entry table indexed by (nibble of plane 0 | nibble of plane 1 << 4) gives the four centroids at once; the
-// weights of the token's heads are one or two 16-byte reads shared by the whole token group; 4 x GH multiply-adds.
-// Low-rank term: lane (c, th) = (tid % 128, tid / 128) owns output coordinate c.
-// GH: heads accumulated per lane (4 when the group has at most four query heads: half the multiply-adds and LDS reads).
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+union H8 {
+  half8 h;
+  u32x4 u;
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(bytes > 0x7FFFFFFFu ? 0x7FFFFFFFu : bytes),
+                                           0x00020000);
+}
+__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
+
+// Partial sums of the attention output.  Every wave is a worker of its own: wave number w of a head takes the tokens
+// [w, w + 1) * 64 ppw of it, 64 at a time, without a barrier; the four waves of a workgroup meet once at the end.
+//
+// Codebook term, a_h[c] = sum_t w'_ht centroid[code_tc] with w' = w rho / sqrt(d): a contraction over TOKENS, on the
+// integer matrix cores and exact there.  The matrix instruction wants sixteen consecutive tokens of one coordinate in a
+// lane, the record holds eight coordinates of one token in a byte.  Matrix instructions turn the one into the other: the
+// lane that owns a token turns the nibbles of its bit-planes into the code numbers of its coordinates, one byte each
+// (one or two reads of a 256-entry LDS table per four coordinates), and v_mfma_i32_32x32x32_i8 multiplies 32 tokens x
+// 32 coordinates by the identity: lane (coordinate, half) receives the codes of sixteen tokens of ITS coordinate.  The
+// second tile of 32 tokens goes into the same accumulator with its codes in the second byte (table of 4 code, identity
+// of 64), so two registers make one word of four code bytes with one instruction.  v_perm_b32 with a table of eight
+// bytes then turns four codes into four operand bytes at once:
+//   up to 2 bits  centroid = s (c_0 + m (c_1 - c_0)) with s = +-1, m = 0/1: terms s and s m in {-1, 0, 1}, the coefficient
+//                 is multiplied into the weights; with at most four heads (16 operand rows of 32) the second term has
+//                 the rows 16 .. 31 to itself instead and the coefficients come in at the end;
+//   3 and 4 bits  the centroid as a 32-bit integer of four signed bytes (exact: unit 2^-28), term p = byte p.
+// The weights are 32-bit fixed point too, four signed bytes (rows of the A operand): a power-of-two unit per head,
+// chosen from the weights at hand so that they take 28 bits or more, one rounding each.  With byte terms row (head, e)
+// holds for term p the weight's byte e - p: the bytes of the product 2^(8 e) meet in one accumulator.  Sums over all
+// tokens of a wave are exact in int32 (a byte is at most 128: 4 x 2^14 per token at most, a wave has at most 6144
+// tokens); when a weight comes that does not fit the unit any more, the sums so far go to float32 and a new unit is
+// chosen.
+// Low-rank term: B_hi = sum_t w_ht C_ti per block on the f16 matrix cores (the coefficient rows are contiguous in t: the
+// operand is a 16-byte load), the weight as three binary16 parts of 11 bits each; then lin_h[c] += sum_i B_hi V_ic.
+//
+// What bounds it (2 bits, 4 heads, 8.4 M tokens: 0.15 ms, 0.36 ms in the float32 version this replaces, which spent 16
+// multiply-adds per token and lane): per pair of tiles 333 vector, 47 LDS and 26 matrix instructions, which take 0.10 ms
+// by themselves, beside 0.49 GB from memory, which takes 0.11 ms by itself (4.5 TB/s): the two overlap in part only, at
+// the two waves per SIMD that the registers allow.
 template <int BITS, int GH>
-__global__ __launch_bounds__(THREADS) void eoq_attend_partial_kernel(
+struct AttendShape {
+  static constexpr bool BYTES = BITS >= 3;                   // byte terms of the centroid
+  static constexpr bool SPLIT = BITS == 2 && GH == 4;        // the two terms in the two halves of the operand rows
+  static constexpr int TERMS = BYTES ? 4 : BITS;
+  static constexpr int NQ = BYTES ? 4 : GH / 2;              // groups of four accumulator registers in use
+  static constexpr int SETS = GH / 4;                        // groups of four heads of the low-rank product
+  static constexpr int SETS_OF_BYTES = BYTES || SPLIT ? 1 : TERMS;   // how often the weights are cut into bytes
+  // weight bytes: [row][64 tokens] and, where operand rows are left out, a row of zeros
+  static constexpr int DIG_BYTES = BYTES || SPLIT ? 4 * 4 * PAIR + PAIR : TERMS * 32 * PAIR;
+  static constexpr int PART_LD = 2 * PAIR + 16;              // bytes per row of binary16 parts
+  static constexpr int PART_BYTES = SETS * 12 * PART_LD;
+  static constexpr int STAGE_BYTES = DIG_BYTES + PART_BYTES;
+  static constexpr int LIN_BYTES = GH * D * 4;               // at the end the staging memory takes the low-rank sums
+  // low-rank sums of a block on their way: three parts, then the finished ones of the last RING blocks
+  static constexpr int RING = GH == 4 ? 8 : 4;
+  static constexpr int PARTS3_BYTES = SETS * 3 * EOQ_RMAX_CAP * 4 * 4;
+  static constexpr int RING_BYTES = SETS * EOQ_RMAX_CAP * 4 * 4;     // of one block
+  static constexpr int BS_BYTES = PARTS3_BYTES + RING * RING_BYTES;
+  static constexpr int BASE_BYTES = STAGE_BYTES > LIN_BYTES ? STAGE_BYTES : LIN_BYTES;
+  static constexpr int WAVE_BYTES = BASE_BYTES + BS_BYTES + GH * D * 4 + 64;
+  static constexpr int NTAB = BITS <= 2 ? 2 : 3;
+  static constexpr bool AHEAD = BITS == 1 || SPLIT;          // registers left to work ahead of a coordinate tile
+};
+
+template <int BITS, int GH>
+__global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     int n, int r_max, int n_kv_heads, int group, int64_t blocks_per_head, int64_t block_capacity, int64_t weight_stride,
-    int run, const float* __restrict__ tab, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms,
+    int ppw, const float* __restrict__ tab, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms,
     const int32_t* __restrict__ rank_in, const uint16_t* __restrict__ lfac, const uint16_t* __restrict__ rfac,
     const float* __restrict__ weights, float* __restrict__ partial) {
+  using S = AttendShape<BITS, GH>;
+  constexpr bool BYTES = S::BYTES;
+  constexpr int TERMS = S::TERMS, NQ = S::NQ, SETS = S::SETS;
   constexpr int ROWB = BITS * D / 8;
-  // staging of a chunk; after the last chunk the same memory takes the four waves' sums of the codebook term
-  constexpr int STAGE_BYTES = CHUNK * ROWB + 2 * CHUNK * MAXG * 4 + EOQ_RMAX_CAP * CHUNK * 2;
-  constexpr int FOLD_BYTES = 4 * GH * D * 4;
-  __shared__ __align__(16) uint8_t stage_s[STAGE_BYTES > FOLD_BYTES ? STAGE_BYTES : FOLD_BYTES];
-  uint8_t* code_s = stage_s;
-  float* wr_s = reinterpret_cast<float*>(stage_s + CHUNK * ROWB);                        // [t][h]: w_ht rho_t / sqrt(d)
-  float* w_s = wr_s + CHUNK * MAXG;                                                      // [h][t]: w_ht
-  uint16_t* cf_s = reinterpret_cast<uint16_t*>(w_s + MAXG * CHUNK);                      // [i][t]: stored coefficients C_ti of the chunk
-  float* fold4_s = reinterpret_cast<float*>(stage_s);                                    // [wave][h][c]
-  __shared__ __align__(16) float4 cen4_s[BITS <= 2 ? 256 : 1];
-  __shared__ float cent_s[1 << BITS];
-  __shared__ float bsum_s[4 * MAXG * EOQ_RMAX_CAP];      // [token segment][h][i]: sum_t w_ht C_ti of the current block
-  __shared__ float fold_s[MAXG * D];
+  __shared__ __align__(16) unsigned char mem[4 * S::WAVE_BYTES];
+  __shared__ __align__(16) uint32_t tab_s[S::NTAB * 256];   // code bytes of four coordinates by two nibbles, times 1, 4 (and 16)
 
-  const int tid = threadIdx.x;
-  const int c = tid & (D - 1), th = tid >> 7;
-  const int cg = tid & 31, tg = tid >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hf = lane >> 5, l16 = lane & 15, kg = lane >> 4;
   const size_t sg = blockIdx.y;
   const size_t sq = sg / n_kv_heads, kv = sg % n_kv_heads;
   const int n_q_heads = n_kv_heads * group;
+  const int h0 = 4 * blockIdx.z;                             // first head of this workgroup (byte terms: four heads each)
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
-  if (tid < (1 << BITS)) cent_s[tid] = tab[tid];
-  if constexpr (BITS <= 2) {
-    const int n0 = tid & 15, n1 = tid >> 4;
-    float cv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) cv[e] = tab[((n0 >> e) & 1) | ((BITS == 2) ? (((n1 >> e) & 1) << 1) : 0)];
-    cen4_s[tid] = make_float4(cv[0], cv[1], cv[2], cv[3]);
-  }
 
-  float rot[GH][4], lin[GH];
-#pragma unroll
-  for (int h = 0; h < GH; ++h) {
-    lin[h] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) rot[h][e] = 0.0f;
-  }
+  unsigned char* mine = mem + wave * S::WAVE_BYTES;
+  unsigned char* dig = mine;
+  unsigned char* parts = mine + S::DIG_BYTES;
+  float* bs = reinterpret_cast<float*>(mine + S::BASE_BYTES);                 // [set][part][component][head]
+  float* ring = bs + S::PARTS3_BYTES / 4;                                     // [block][set][component][head]
+  float* rot = reinterpret_cast<float*>(mine + S::BASE_BYTES + S::BS_BYTES);  // [head][coordinate]
+  float* unit_s = rot + GH * D;                                               // value of one integer unit, per head
+  float* winv_s = unit_s + GH;                                                // 1 / scale of the binary16 parts, per head
 
-  // What a lane fetches of a chunk of 128 tokens; the next chunk's (of this block or the next) is requested before
-  // this one is worked on, so the loads travel during the arithmetic instead of in front of a barrier.
-  constexpr int NC = (CHUNK * ROWB / 16 + THREADS - 1) / THREADS;   // 16-byte pieces of the codes per lane
-  struct Fetch {
-    uint4 code[NC];
-    float w[4];      // weights of heads th, 2 + th, 4 + th, 6 + th at token tid % 128
-    uint16_t rho;    // stored norm of that token
-    uint4 cf[2];     // stored coefficients: piece tid + 256 k of the chunk's [component][token] rows
-  };
-  __shared__ int rank_s[16];
-  const int64_t j_begin = (int64_t)blockIdx.x * run;
-  const int64_t j_end = min(j_begin + run, blocks_per_head);
-  if (tid < (int)(j_end - j_begin)) rank_s[tid] = min(max(rank_in[sg * (size_t)block_capacity + j_begin + tid], 0), r_max);
+  {
+    uint32_t v = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v |= (((tid >> e) & 1) | (BITS >= 2 ? ((tid >> (4 + e)) & 1) << 1 : 0)) << (8 * e);
+#pragma unroll
+    for (int k = 0; k < S::NTAB; ++k) tab_s[k * 256 + tid] = v << (2 * k);
+  }
+  for (int e = lane; e < S::DIG_BYTES / 4; e += 64) reinterpret_cast<uint32_t*>(dig)[e] = 0u;
+  for (int e = lane; e < GH * D; e += 64) rot[e] = 0.0f;
   __syncthreads();
-  auto fetch = [&](Fetch& f, int64_t jb, int t0) __attribute__((always_inline)) {
-    const size_t blk = sg * (size_t)block_capacity + jb;
-    const int r = rank_s[jb - j_begin];
-#pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int e = tid + THREADS * k;
-      f.code[k] = (e < CHUNK * ROWB / 16) ? reinterpret_cast<const uint4*>(codes + (blk * (size_t)n + t0) * ROWB)[e] : make_uint4(0u, 0u, 0u, 0u);
+
+  // operand tables: four codes to four bytes of term t, entry i for code i (low register: codes 0 .. 3)
+  uint32_t lut[TERMS][BITS == 4 ? 4 : 2];
+  float coef[TERMS];
+  if constexpr (!BYTES) {
+    lut[0][0] = BITS == 1 ? 0x000001FFu : 0x0101FFFFu;       // the sign
+    lut[0][1] = 0u;
+    coef[0] = tab[TERMS];                                    // smallest positive centroid
+    if constexpr (BITS == 2) {
+      lut[1][0] = 0x010000FFu;                               // the sign where the magnitude bit is set
+      lut[1][1] = 0u;
+      coef[1] = tab[3] - tab[2];
     }
-    const int t = tid & (CHUNK - 1);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int h = 2 * k + th;
-      f.w[k] = (h < group) ? weights[(sq * n_q_heads + kv * group + h) * (size_t)weight_stride + (size_t)jb * n + t0 + t] : 0.0f;
-    }
-    f.rho = norms[blk * (size_t)n + t0 + t];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int e = tid + THREADS * k, i = e >> 4;
-      f.cf[k] = (i < r) ? *reinterpret_cast<const uint4*>(lfac + (blk * r_max + i) * (size_t)n + t0 + 8 * (e & 15)) : make_uint4(0u, 0u, 0u, 0u);
-    }
-  };
-  Fetch cur, nxt;
-  if (j_begin < j_end) fetch(cur, j_begin, 0);
-  for (int64_t jb = j_begin; jb < j_end; ++jb) {
-    const size_t blk = sg * (size_t)block_capacity + jb;
-    const int r = rank_s[jb - j_begin];
-    // low-rank weights of this block: lane (segment, i, h) = (tid / 64, (tid / 8) % 8, tid % 8) sums the 32 tokens
-    // 32 segment .. of every chunk for the components i, i + 8, ... and head h
-    const int bs = tid >> 6, bi = (tid >> 3) & 7, bh = tid & 7;
-    float bacc[EOQ_RMAX_CAP / 8];
-#pragma unroll
-    for (int g = 0; g < EOQ_RMAX_CAP / 8; ++g) bacc[g] = 0.0f;
-    for (int t0 = 0; t0 < n; t0 += CHUNK) {
-      __syncthreads();  // the previous chunk has been consumed
-      // stage the chunk: codes, weights, weights times norm, coefficients
-#pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        const int e = tid + THREADS * k;
-        if (e < CHUNK * ROWB / 16) reinterpret_cast<uint4*>(code_s)[e] = cur.code[k];
-      }
-      {
-        const int t = tid & (CHUNK - 1);
-        const float rs = half_bits_to_float(cur.rho) * inv_sqrt_d;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int h = 2 * k + th;
-          w_s[h * CHUNK + t] = cur.w[k];
-          wr_s[t * MAXG + h] = cur.w[k] * rs;
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int e = tid + THREADS * k;
-        if ((e >> 4) < r) reinterpret_cast<uint4*>(cf_s)[e] = cur.cf[k];
-      }
-      // the next chunk's bytes are requested here
-      {
-        const bool last_chunk = t0 + CHUNK >= n;
-        const int64_t jn = last_chunk ? jb + 1 : jb;
-        if (jn < j_end) fetch(nxt, jn, last_chunk ? 0 : t0 + CHUNK);
-      }
-      __syncthreads();
-      // codebook term: this lane's four coordinates, every eighth token of the chunk
-      const int cbyte = cg >> 1, cshift = 4 * (cg & 1);
-#pragma unroll 4
-      for (int t = tg; t < CHUNK; t += 8) {
-        float cv[4];
-        if constexpr (BITS <= 2) {
-          uint32_t idx = ((uint32_t)code_s[t * ROWB + cbyte] >> cshift) & 0xFu;
-          if constexpr (BITS == 2) idx |= (((uint32_t)code_s[t * ROWB + 16 + cbyte] >> cshift) & 0xFu) << 4;
-          const float4 c4 = cen4_s[idx];
-          cv[0] = c4.x; cv[1] = c4.y; cv[2] = c4.z; cv[3] = c4.w;
-        } else {
-          uint32_t nib[BITS];
-#pragma unroll
-          for (int p = 0; p < BITS; ++p) nib[p] = ((uint32_t)code_s[t * ROWB + 16 * p + cbyte] >> cshift) & 0xFu;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            uint32_t idx = 0;
-#pragma unroll
-            for (int p = 0; p < BITS; ++p) idx |= ((nib[p] >> e) & 1u) << p;
-            cv[e] = cent_s[idx];
+  } else {
+    EOQ_SFOR(t, 4, EOQ_SFOR(i, BITS == 4 ? 4 : 2, lut[t][i] = 0u;););
+    EOQ_SFOR(c, 1 << BITS,
+      const int I = (int)(tab[c] * 0x1.0p28f);               // |centroid| < 4
+      const uint32_t dg = ((uint32_t)I + 0x80808080u) ^ 0x80808080u;
+      EOQ_SFOR(t, 4, lut[t][c >> 2] |= ((dg >> (8 * t)) & 0xFFu) << (8 * (c & 3)););
+    );
+    EOQ_SFOR(t, 4, coef[t] = 1.0f;);
+  }
+
+  // identity operands: k = 16 hf + i meets column l32
+  v4i id1, id64;
+  EOQ_SFOR(w, 4,
+    const int at = l32 - 16 * hf - 4 * w;
+    const uint32_t one = (at >= 0 && at < 4) ? 1u << (8 * at) : 0u;
+    id1[w] = (int)one;
+    id64[w] = (int)(one << 6);
+  );
+
+  // this wave's tokens
+  const int ppb = n / PAIR;
+  const int64_t pairs = blocks_per_head * ppb;
+  const int64_t p_begin = ((int64_t)blockIdx.x * 4 + wave) * ppw;
+  const int count = (int)(min(p_begin + ppw, pairs) - p_begin);   // may be <= 0
+  float lin[GH][2];
+  EOQ_SFOR(h, GH, lin[h][0] = 0.0f; lin[h][1] = 0.0f;);
+  const int c2 = 2 * lane;                                   // this lane's coordinates of the low-rank sums
+
+  if (count > 0) {
+    const int64_t b_first = p_begin / ppb;
+    const size_t blk0 = sg * (size_t)block_capacity + b_first;
+    const int in_first = (int)(p_begin - b_first * ppb);     // pair inside the first block
+    const int nblk = (in_first + count - 1) / ppb + 1;
+    const int rk_all = min(max(rank_in[blk0 + min(lane, nblk - 1)], 0), r_max);
+    auto rank_of = [&](int b) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(rk_all, b); };
+    const size_t tok0 = sg * (size_t)block_capacity * n + (size_t)p_begin * PAIR;   // first token in the record arrays
+    const uint8_t* code_p = codes + (tok0 + l32) * ROWB + 8 * hf;
+    // a staging item: four tokens whose bytes sit side by side in an operand word (tokens tt, tt + 1 of either tile) and
+    // one head; word u of a row is [m][half][4 bytes]: see the pack below
+    const int u = l16;
+    const int tt = 16 * (u >> 3) + 8 * ((u >> 1) & 1) + 4 * ((u >> 2) & 1) + 2 * (u & 1);
+    const uint16_t* rho_p = norms + tok0 + tt;
+    const float* w_p[SETS];
+    bool head_live[SETS];
+    EOQ_SFOR(s, SETS,
+      const int h = h0 + 4 * s + kg;
+      head_live[s] = h < group;
+      w_p[s] = weights + (sq * n_q_heads + kv * group + (head_live[s] ? h : 0)) * (size_t)weight_stride + (size_t)p_begin * PAIR + tt;
+    );
+    const uint32_t vo_cf = (uint32_t)((l16 * n + 8 * kg) * 2);
+    auto coef_buffer = [&](int b) __attribute__((always_inline)) {
+      return buffer_of(lfac + (blk0 + b) * (size_t)r_max * n, (size_t)rank_of(b) * n * 2);
+    };
+
+    struct Fetch {
+      u32x2 pl[2][BITS];       // the lane's 8 bytes of every bit-plane, tokens l32 of both tiles
+      float w[SETS][4];        // weights of the staging item: tokens tt, 32 + tt, tt + 1, 33 + tt
+      uint32_t rho[2];         // norms of tokens tt, tt + 1 and 32 + tt, 33 + tt
+      u32x4 cf[2];             // coefficients: component l16, tokens 8 kg .. + 7 of either tile; zero at and above the rank
+    };
+    struct __attribute__((packed, aligned(4))) F2 { float x, y; };
+    auto request = [&](Fetch& f, int p, int b, int in_b) __attribute__((always_inline)) {   // pair p of the wave: pair in_b of block b
+      const size_t t = (size_t)p * PAIR;
+      EOQ_SFOR(i, 2, EOQ_SFOR(k, BITS,
+        f.pl[i][k] = *reinterpret_cast<const u32x2*>(code_p + (t + 32 * i) * ROWB + 16 * k);););
+      EOQ_SFOR(s, SETS,
+        const F2 a = *reinterpret_cast<const F2*>(w_p[s] + t); const F2 c = *reinterpret_cast<const F2*>(w_p[s] + t + 32);
+        f.w[s][0] = a.x; f.w[s][1] = c.x; f.w[s][2] = a.y; f.w[s][3] = c.y;
+      );
+      EOQ_SFOR(i, 2, f.rho[i] = *reinterpret_cast<const uint32_t*>(rho_p + t + 32 * i););
+      const __amdgpu_buffer_rsrc_t cfd = coef_buffer(b);
+      EOQ_SFOR(i, 2, f.cf[i] = __builtin_amdgcn_raw_buffer_load_b128(cfd, vo_cf, (in_b * PAIR + 32 * i) * 2, 0););
+    };
+
+    v16i acc[4];               // coordinates 64 (l32 / 16) + 16 j + l32 % 16
+    EOQ_SFOR(j, 4, EOQ_SFOR(v, 16, acc[j][v] = 0;););
+    float4v lr[SETS][2];       // row 4 part + head, column = component l16 / 16 + l16
+    EOQ_SFOR(s, SETS, EOQ_SFOR(k, 2, EOQ_SFOR(v, 4, lr[s][k][v] = 0.0f;);););
+    float inv[SETS], sw[SETS]; // units of the staging item's head: integers = w' inv, binary16 parts of w sw
+    EOQ_SFOR(s, SETS, inv[s] = INFINITY; sw[s] = INFINITY;);
+    bool any = false;
+
+    auto flush_rot = [&]() __attribute__((always_inline)) {
+      EOQ_SFOR(j, 4,
+        const int c = 64 * (l32 >> 4) + 16 * j + l16;
+        EOQ_SFOR(q, NQ,
+          double v = fma(fma(fma((double)acc[j][4 * q + 3], 256.0, (double)acc[j][4 * q + 2]), 256.0, (double)acc[j][4 * q + 1]), 256.0,
+                         (double)acc[j][4 * q]);
+          if constexpr (BYTES) {
+            if (hf) v *= 0x1.0p32;                           // planes 4 .. 7
+            v += __shfl_xor(v, 32, 64);
+            if (!hf) rot[q * D + c] += (float)(v * (double)unit_s[q] * 0x1.0p-28);
+          } else if constexpr (!S::SPLIT) {
+            rot[(2 * q + hf) * D + c] += (float)(v * (double)unit_s[2 * q + hf]);
+          } else {
+            const double v1 = fma(fma(fma((double)acc[j][8 + 4 * q + 3], 256.0, (double)acc[j][8 + 4 * q + 2]), 256.0, (double)acc[j][8 + 4 * q + 1]), 256.0,
+                                  (double)acc[j][8 + 4 * q]);
+            rot[(2 * q + hf) * D + c] += (float)(fma(v, (double)coef[0], v1 * (double)coef[1]) * (double)unit_s[2 * q + hf]);
           }
-        }
-        const float4 wa = *reinterpret_cast<const float4*>(wr_s + t * MAXG);
-        const float wv[4] = {wa.x, wa.y, wa.z, wa.w};
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) rot[h][e] = fmaf(wv[h], cv[e], rot[h][e]);
-        if constexpr (GH == 8) {
-          const float4 wb = *reinterpret_cast<const float4*>(wr_s + t * MAXG + 4);
-          const float wu[4] = {wb.x, wb.y, wb.z, wb.w};
-#pragma unroll
-          for (int h = 0; h < 4; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) rot[4 + h][e] = fmaf(wu[h], cv[e], rot[4 + h][e]);
-        }
+        );
+        EOQ_SFOR(v, 16, acc[j][v] = 0;);
+      );
+    };
+    // The low-rank sums of block b: parts joined, kept in LDS; the V rows of RING blocks are then read in one go (per
+    // block their latency was 12 us of 160 on 8.4 M tokens).
+    int n_ring = 0, b_ring = 0;     // blocks in the ring; the first of them (consecutive; one of rank 0 counts, too)
+    // `rows` rows of every block of the ring on their way at a time; rows at and above a block's rank read as zero
+    // through its descriptor (its sums there are zero)
+    auto drain_ring = [&](auto rows_ic) __attribute__((always_inline)) {
+      constexpr int ROWS = decltype(rows_ic)::value;
+      int top = 0;
+      EOQ_SFOR(k, S::RING, if (k < n_ring) top = max(top, rank_of(b_ring + k)););
+      for (int i0 = 0; i0 < top; i0 += ROWS) {
+        uint32_t vv[S::RING][ROWS];
+        EOQ_SFOR(k, S::RING,
+          const int bk = b_ring + min(k, n_ring - 1);
+          const __amdgpu_buffer_rsrc_t vb = buffer_of(rfac + (blk0 + bk) * (size_t)r_max * D, k < n_ring ? (size_t)rank_of(bk) * D * 2 : 0);
+          EOQ_SFOR(i, ROWS, vv[k][i] = __builtin_amdgcn_raw_buffer_load_b32(vb, lane * 4 + (i0 + i) * (D * 2), 0, 0););
+        );
+        EOQ_SFOR(k, S::RING,
+          if (k < n_ring && i0 < rank_of(b_ring + k)) {
+            EOQ_SFOR(i, ROWS,
+              const float v0 = half_bits_to_float((uint16_t)(vv[k][i] & 0xFFFFu)); const float v1 = half_bits_to_float((uint16_t)(vv[k][i] >> 16));
+              EOQ_SFOR(s, SETS,
+                const float4v w4 = *reinterpret_cast<const float4v*>(ring + k * (S::RING_BYTES / 4) + (s * EOQ_RMAX_CAP + i0 + i) * 4);
+                EOQ_SFOR(h, 4,
+                  lin[4 * s + h][0] = fmaf(w4[h], v0, lin[4 * s + h][0]);
+                  lin[4 * s + h][1] = fmaf(w4[h], v1, lin[4 * s + h][1]);
+                );
+              );
+            );
+          });
       }
-      // low-rank weights: components bi + 8 g, head bh, the segment's 32 tokens, 8 per load
-#pragma unroll
-      for (int g = 0; g < EOQ_RMAX_CAP / 8; ++g) {
-        if (8 * g < r) {   // uniform
-          const int i = bi + 8 * g;
-          if (i < r) {
-            const uint16_t* crow = cf_s + i * CHUNK;
-#pragma unroll
-            for (int t = 32 * bs; t < 32 * bs + 32; t += 8) {
-              float cf[8];
-              load8(crow, EOQ_F16, t, cf);
-              const float4 wa = *reinterpret_cast<const float4*>(w_s + bh * CHUNK + t);
-              const float4 wb = *reinterpret_cast<const float4*>(w_s + bh * CHUNK + t + 4);
-              bacc[g] = fmaf(wa.x, cf[0], bacc[g]);
-              bacc[g] = fmaf(wa.y, cf[1], bacc[g]);
-              bacc[g] = fmaf(wa.z, cf[2], bacc[g]);
-              bacc[g] = fmaf(wa.w, cf[3], bacc[g]);
-              bacc[g] = fmaf(wb.x, cf[4], bacc[g]);
-              bacc[g] = fmaf(wb.y, cf[5], bacc[g]);
-              bacc[g] = fmaf(wb.z, cf[6], bacc[g]);
-              bacc[g] = fmaf(wb.w, cf[7], bacc[g]);
+      b_ring += n_ring;
+      n_ring = 0;
+      __builtin_amdgcn_wave_barrier();
+    };
+    auto flush_lin = [&](int b, bool last) __attribute__((always_inline)) {
+      const int r = rank_of(b);
+      if (r > 0) {
+        EOQ_SFOR(s, SETS, EOQ_SFOR(k, 2,
+          if (kg < 3) *reinterpret_cast<float4v*>(bs + ((s * 3 + kg) * EOQ_RMAX_CAP + 16 * k + l16) * 4) = lr[s][k];
+        ););
+        __builtin_amdgcn_wave_barrier();
+        const int hh = lane & 3;
+        EOQ_SFOR(s, SETS,
+          const float winv = winv_s[4 * s + hh];
+          EOQ_SFOR(k, 2,
+            if (16 * k < r) {
+              const float* e = bs + (s * 3 * EOQ_RMAX_CAP + 16 * k) * 4 + lane;   // component 16 k + lane / 4, head lane % 4
+              ring[(n_ring * SETS + s) * (EOQ_RMAX_CAP * 4) + 16 * k * 4 + lane] =
+                  fmaf(fmaf(e[2 * EOQ_RMAX_CAP * 4], 0x1.0p-11f, e[EOQ_RMAX_CAP * 4]), 0x1.0p-11f, *e) * winv;
+            });
+        );
+        __builtin_amdgcn_wave_barrier();
+        EOQ_SFOR(s, SETS, EOQ_SFOR(k, 2, EOQ_SFOR(v, 4, lr[s][k][v] = 0.0f;);););
+      }
+      ++n_ring;
+      if (n_ring == S::RING && !last) drain_ring(std::integral_constant<int, 2>{});
+    };
+
+    // New units for the heads whose weights (sums of magnitudes tr, tw over four tokens each, with rho / without) do not
+    // fit the ones they have.  The low-rank sums so far are brought to the new scale (a power of two).
+    auto choose_units = [&](const float (&mr)[SETS], const float (&mw)[SETS]) __attribute__((always_inline)) {
+      EOQ_SFOR(s, SETS,
+        float tr = mr[s]; float tw = mw[s];
+        EOQ_SFOR(x, 4,
+          constexpr int ctrl = x == 0 ? 0xB1 : (x == 1 ? 0x4E : (x == 2 ? 0x141 : 0x140));
+          const float a = dpp_mov<ctrl>(tr); const float c = dpp_mov<ctrl>(tw);
+          tr = (a > tr || !(a == a)) ? a : tr;             // a NaN stays
+          tw = (c > tw || !(c == c)) ? c : tw;
+        );
+        const bool bad = !(tr < INFINITY) || !(tw < INFINITY);
+        const int er = min(max((int)(__float_as_uint(tr) >> 23) - 127, -90), 126);
+        const int ew = min(max((int)(__float_as_uint(tw) >> 23) - 127, -90), 126);
+        if (bad || !(tr * inv[s] < 1.85f * 0x1.0p30f)) {
+          inv[s] = bad ? 0.0f : __uint_as_float((uint32_t)(28 - er + 127) << 23);     // integers below 2^29
+          if (l16 == 0) unit_s[4 * s + kg] = bad ? 0.0f : __uint_as_float((uint32_t)(er - 28 + 127) << 23);
+        }
+        float turn = 1.0f;
+        if (bad || !(tw * sw[s] < 0x1.0p15f)) {
+          const float fresh = bad ? 0.0f : __uint_as_float((uint32_t)(12 - ew + 127) << 23);      // parts below 2^13
+          turn = any ? fresh * winv_s[4 * s + kg] : 1.0f;
+          sw[s] = fresh;
+          __builtin_amdgcn_wave_barrier();
+          if (l16 == 0) winv_s[4 * s + kg] = bad ? 0.0f : __uint_as_float((uint32_t)(ew - 12 + 127) << 23);
+        }
+        EOQ_SFOR(v, 4,
+          const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(turn), 16 * v));
+          EOQ_SFOR(k, 2, lr[s][k][v] *= f;);
+        );
+        if (bad) {   // Inf or NaN among the weights: so is the head's output
+          EOQ_SFOR(i, 8, rot[(4 * s + kg) * D + 16 * i + l16] = NAN;);
+        }
+      );
+      __builtin_amdgcn_wave_barrier();
+    };
+    // Two register sets in turn.  A pair's registers are free as soon as its weights are staged and its code nibbles
+    // sorted, and the pair after the next is requested into them there: one to two pairs are on their way all the time
+    // (with one: 0.16 instead of 0.13 ms on 8.4 M tokens).  Behind the last pair that one is fetched once more, so there
+    // is no branch around the requests.
+    int pr = 0, br = 0, in_br = in_first;   // next pair to request, its block of the wave's range and place inside it
+    auto request_next = [&](Fetch& f) __attribute__((always_inline)) {
+      request(f, pr, br, in_br);
+      const bool more = pr + 1 < count, turn = in_br + 1 == ppb;
+      pr += more ? 1 : 0;
+      br += (more && turn) ? 1 : 0;
+      in_br = !more ? in_br : (turn ? 0 : in_br + 1);
+    };
+    int b = 0, in_b = in_first;             // the same for the pair to work on
+    auto work = [&](Fetch& f, bool last) __attribute__((always_inline)) {
+      const int r = rank_of(b);
+      const bool last_in_block = in_b + 1 == ppb;
+      // ---- weights: do they fit the units?  (sums of four magnitudes: NaN and Inf fail the test) ----
+      float wr[SETS][4], mr[SETS], mw[SETS];
+      bool fits = true;
+      {
+        const float ra[2] = {half_bits_to_float((uint16_t)(f.rho[0] & 0xFFFFu)) * inv_sqrt_d, half_bits_to_float((uint16_t)(f.rho[0] >> 16)) * inv_sqrt_d};
+        const float rb[2] = {half_bits_to_float((uint16_t)(f.rho[1] & 0xFFFFu)) * inv_sqrt_d, half_bits_to_float((uint16_t)(f.rho[1] >> 16)) * inv_sqrt_d};
+        EOQ_SFOR(s, SETS,
+          EOQ_SFOR(e, 4,
+            f.w[s][e] = head_live[s] ? f.w[s][e] : 0.0f;
+            wr[s][e] = f.w[s][e] * ((e & 1) ? rb[e >> 1] : ra[e >> 1]);
+          );
+          mr[s] = (fabsf(wr[s][0]) + fabsf(wr[s][1])) + (fabsf(wr[s][2]) + fabsf(wr[s][3]));
+          mw[s] = (fabsf(f.w[s][0]) + fabsf(f.w[s][1])) + (fabsf(f.w[s][2]) + fabsf(f.w[s][3]));
+          fits = fits && mr[s] * inv[s] < 1.85f * 0x1.0p30f && mw[s] * sw[s] < 0x1.0p15f;
+        );
+      }
+      if (__ballot(!fits) != 0ull) {   // wave-uniform, rare: new units
+        if (any) flush_rot();
+        choose_units(mr, mw);
+      }
+      any = true;
+      // ---- staging: weight bytes and binary16 parts ----
+      EOQ_SFOR(s, SETS,
+        EOQ_SFOR(t, S::SETS_OF_BYTES,
+          uint32_t dg[4];
+          const float sc = (BYTES || S::SPLIT) ? inv[s] : coef[t] * inv[s];
+          EOQ_SFOR(e, 4, dg[e] = ((uint32_t)__float2int_rn(wr[s][e] * sc) + 0x80808080u) ^ 0x80808080u;);
+          uint32_t pl[4];
+          transpose_bytes(dg[0], dg[1], dg[2], dg[3], pl);
+          EOQ_SFOR(e, 4, *reinterpret_cast<uint32_t*>(dig + t * (32 * PAIR) + (4 * (4 * s + kg) + e) * PAIR + 4 * u) = pl[e];);
+        );
+        if (r > 0) {
+          float x[4];
+          EOQ_SFOR(e, 4, x[e] = f.w[s][e] * sw[s];);
+          EOQ_SFOR(part, 3,
+            unsigned char* dst = parts + (s * 12 + 4 * part + kg) * S::PART_LD + 2 * tt;
+            const uint32_t pa = pack_half2(x[0], x[2]); const uint32_t pb = pack_half2(x[1], x[3]);
+            *reinterpret_cast<uint32_t*>(dst) = pa;
+            *reinterpret_cast<uint32_t*>(dst + PAIR) = pb;
+            if constexpr (part < 2) {
+              x[0] = (x[0] - half_bits_to_float((uint16_t)(pa & 0xFFFFu))) * 0x1.0p11f;
+              x[2] = (x[2] - half_bits_to_float((uint16_t)(pa >> 16))) * 0x1.0p11f;
+              x[1] = (x[1] - half_bits_to_float((uint16_t)(pb & 0xFFFFu))) * 0x1.0p11f;
+              x[3] = (x[3] - half_bits_to_float((uint16_t)(pb >> 16))) * 0x1.0p11f;
             }
-          }
+          );
         }
+      );
+      __builtin_amdgcn_wave_barrier();   // one wave: its LDS operations complete in order
+      // ---- A operands: row l32, tokens [m][half] ----
+      v4i A[TERMS][2];
+      EOQ_SFOR(t, TERMS,
+        const unsigned char* src;
+        if constexpr (BYTES) {
+          const int e = (l32 & 7) - t;
+          src = dig + ((e >= 0 && e < 4) ? ((l32 >> 3) * 4 + e) * PAIR : 16 * PAIR);
+        } else if constexpr (S::SPLIT) {
+          src = dig + ((l32 >> 4) == t ? l16 : 16) * PAIR;
+        } else {
+          src = dig + t * (32 * PAIR) + l32 * PAIR;
+        }
+        EOQ_SFOR(m, 2, A[t][m] = *reinterpret_cast<const v4i*>(src + 32 * m + 16 * hf););
+      );
+      // ---- codes: bytes, transposed, translated, multiplied ----
+      // even / odd: byte = (nibble of plane 0 | nibble of plane 1 << 4) of the low / high nibbles
+      uint32_t ev[2][2][BITS > 2 ? 2 : 1]; uint32_t od[2][2][BITS > 2 ? 2 : 1];
+      EOQ_SFOR(i, 2, EOQ_SFOR(w, 2, EOQ_SFOR(k, (BITS > 2 ? 2 : 1),
+        const uint32_t x = f.pl[i][2 * k][w];
+        if constexpr (2 * k + 1 < BITS) {
+          const uint32_t y = f.pl[i][2 * k + 1][w];
+          ev[i][w][k] = bfi(0x0F0F0F0Fu, x, y << 4);
+          od[i][w][k] = bfi(0x0F0F0F0Fu, x >> 4, y);
+        } else {
+          ev[i][w][k] = x & 0x0F0F0F0Fu;
+          od[i][w][k] = (x >> 4) & 0x0F0F0F0Fu;
+        }
+      );););
+      // ---- low-rank sums of this block ----
+      if (r > 0) {
+        EOQ_SFOR(s, SETS, EOQ_SFOR(i, 2,
+          H8 wa;
+          H8 ca;
+          wa.u = *reinterpret_cast<const u32x4*>(parts + (s * 12 + min(l16, 11)) * S::PART_LD + PAIR * i + 16 * kg);
+          ca.u = f.cf[i];
+          lr[s][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa.h, ca.h, lr[s][0], 0, 0, 0);   // rows 12 .. 15: never read
+          if (r > 16) {
+            // components 16 .. 31 (rare): fetched here
+            ca.u = __builtin_amdgcn_raw_buffer_load_b128(coef_buffer(b), vo_cf + (uint32_t)(16 * n * 2), (in_b * PAIR + 32 * i) * 2, 0);
+            lr[s][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa.h, ca.h, lr[s][1], 0, 0, 0);
+          }
+        ););
+        __builtin_amdgcn_wave_barrier();
       }
-      cur = nxt;
-    }
-    // low-rank term of the block: lin_h[c] += sum_i bsum[h][i] V[i][c]; the two lane halves take alternate components
-    __syncthreads();
-#pragma unroll
-    for (int g = 0; g < EOQ_RMAX_CAP / 8; ++g) bsum_s[(bs * MAXG + bh) * EOQ_RMAX_CAP + bi + 8 * g] = bacc[g];
-    __syncthreads();
-    for (int i = th; i < r; i += 2) {
-      const float v = half_bits_to_float(rfac[(blk * r_max + i) * D + c]);
-#pragma unroll
-      for (int h = 0; h < GH; ++h) {
-        // the four token segments in order
-        const float bsum = ((bsum_s[(0 * MAXG + h) * EOQ_RMAX_CAP + i] + bsum_s[(1 * MAXG + h) * EOQ_RMAX_CAP + i]) +
-                            bsum_s[(2 * MAXG + h) * EOQ_RMAX_CAP + i]) + bsum_s[(3 * MAXG + h) * EOQ_RMAX_CAP + i];
-        lin[h] = fmaf(bsum, v, lin[h]);
+      if (last_in_block || last) flush_lin(b, last);
+      request_next(f);
+      // coordinate tile j: where registers allow, the table reads of tile j + 2 and the transposing products of tile j + 1
+      // are issued before tile j is packed, so a wave has work while they are on their way
+      auto code_bytes = [&](auto jc, v4i (&X)[2]) __attribute__((always_inline)) {
+        constexpr int j = decltype(jc)::value;
+        EOQ_SFOR(i, 2, EOQ_SFOR(w, 4,
+          constexpr int sh = 8 * ((2 * j + (w >> 1)) & 3);
+          const uint32_t src0 = ((w & 1) ? od[i][j >> 1][0] : ev[i][j >> 1][0]) >> sh;
+          uint32_t x = tab_s[i * 256 + (src0 & 0xFFu)];
+          if constexpr (BITS > 2) {
+            const uint32_t src1 = ((w & 1) ? od[i][j >> 1][1] : ev[i][j >> 1][1]) >> sh;
+            x |= tab_s[(i + 1) * 256 + (src1 & 0xFFu)];
+          }
+          X[i][w] = (int)x;
+        ););
+      };
+      auto transpose = [&](const v4i (&X)[2]) __attribute__((always_inline)) {
+        v16i cd;
+        EOQ_SFOR(v, 16, cd[v] = 0;);
+        cd = __builtin_amdgcn_mfma_i32_32x32x32_i8(X[0], id1, cd, 0, 0, 0);
+        return __builtin_amdgcn_mfma_i32_32x32x32_i8(X[1], id64, cd, 0, 0, 0);
+      };
+      v4i X[2][2];
+      v16i cd[2];
+      if constexpr (S::AHEAD) {
+        code_bytes(std::integral_constant<int, 0>{}, X[0]);
+        code_bytes(std::integral_constant<int, 1>{}, X[1]);
+        cd[0] = transpose(X[0]);
       }
+      EOQ_SFOR(j, 4,
+        if constexpr (S::AHEAD) {
+          if constexpr (j + 2 < 4) code_bytes(std::integral_constant<int, j + 2>{}, X[j & 1]);
+          if constexpr (j + 1 < 4) cd[(j + 1) & 1] = transpose(X[(j + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+        } else {
+          code_bytes(std::integral_constant<int, j>{}, X[j & 1]);
+          cd[j & 1] = transpose(X[j & 1]);
+        }
+        // register v: token 8 (v / 4) + 4 hf + v % 4 of the first tile in byte 0, of the second in byte 1
+        uint32_t pk[8];
+        EOQ_SFOR(v, 8, pk[v] = (uint32_t)cd[j & 1][2 * v] | ((uint32_t)cd[j & 1][2 * v + 1] << 16););
+        EOQ_SFOR(m, 2,
+          uint32_t sel[4]; uint32_t top[4];
+          EOQ_SFOR(w, 4,
+            sel[w] = pk[4 * m + w];
+            if constexpr (BITS == 4) {
+              const uint32_t up = (sel[w] >> 3) & 0x01010101u;
+              top[w] = (up << 8) - up;                       // 255 in the bytes whose code is 8 or more
+              sel[w] &= 0x07070707u;
+            }
+          );
+          EOQ_SFOR(t, TERMS,
+            v4i Bt;
+            EOQ_SFOR(w, 4,
+              const uint32_t lo = __builtin_amdgcn_perm(lut[t][1], lut[t][0], sel[w]);
+              if constexpr (BITS == 4)
+                Bt[w] = (int)bfi(top[w], __builtin_amdgcn_perm(lut[t][3], lut[t][2], sel[w]), lo);
+              else
+                Bt[w] = (int)lo;
+            );
+            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[t][m], Bt, acc[j], 0, 0, 0);
+          );
+        );
+        if constexpr (S::AHEAD) __builtin_amdgcn_sched_barrier(0);
+      );
+      if (last_in_block) {
+        ++b;
+        in_b = 0;
+      } else {
+        ++in_b;
+      }
+    };
+    Fetch f0, f1;
+    request_next(f0);
+    __builtin_amdgcn_sched_barrier(0);   // in this order: the first wait names exactly the first set's loads
+    request_next(f1);
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      // the first units come from the first four pairs, so that few later weights need new ones
+      float mr[SETS], mw[SETS];
+      EOQ_SFOR(s, SETS, mr[s] = 0.0f; mw[s] = 0.0f;);
+      EOQ_SFOR(k, 4,
+        const size_t t = (size_t)min(k, count - 1) * PAIR;
+        EOQ_SFOR(i, 2,
+          const uint32_t rho = *reinterpret_cast<const uint32_t*>(rho_p + t + 32 * i);
+          const float r0 = half_bits_to_float((uint16_t)(rho & 0xFFFFu)) * inv_sqrt_d; const float r1 = half_bits_to_float((uint16_t)(rho >> 16)) * inv_sqrt_d;
+          EOQ_SFOR(s, SETS,
+            const F2 a = *reinterpret_cast<const F2*>(w_p[s] + t + 32 * i);
+            const float w0 = head_live[s] ? fabsf(a.x) : 0.0f; const float w1 = head_live[s] ? fabsf(a.y) : 0.0f;
+            const float sr = fmaf(w0, fabsf(r0), w1 * fabsf(r1)); const float sm = w0 + w1;
+            mr[s] = (sr > mr[s] || !(sr == sr)) ? sr : mr[s];
+            mw[s] = (sm > mw[s] || !(sm == sm)) ? sm : mw[s];
+          );
+        );
+      );
+      choose_units(mr, mw);
     }
+#pragma unroll 1
+    for (int p = 1;; p += 2) {       // two exits: on every path back the younger requests are the other set's
+      work(f0, p == count);
+      if (p == count) break;
+      work(f1, p + 1 == count);
+      if (p + 1 == count) break;
+    }
+    drain_ring(std::integral_constant<int, 4>{});
+    flush_rot();
   }
-  // The codebook term: the two token groups of a wave meet in registers (lane ^ 32: both get the same sum), the four
-  // waves through LDS, added in wave order.  The low-rank term: the two lane halves through LDS.  Then the partial sums
-  // of this run are written: [rot | lin][h][c].
-  __syncthreads();   // the staging memory is free
-#pragma unroll
-  for (int h = 0; h < GH; ++h)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) rot[h][e] += __shfl_xor(rot[h][e], 32, 64);
-  if ((tid & 32) == 0) {
-#pragma unroll
-    for (int h = 0; h < GH; ++h)
-      *reinterpret_cast<float4*>(fold4_s + ((tid >> 6) * GH + h) * D + 4 * cg) = make_float4(rot[h][0], rot[h][1], rot[h][2], rot[h][3]);
-  }
-  if (th == 1) {
-#pragma unroll
-    for (int h = 0; h < GH; ++h) fold_s[h * D + c] = lin[h];
-  }
+  // ---- the four waves meet, in wave order ----
+  __builtin_amdgcn_wave_barrier();
+  float* lin_m = reinterpret_cast<float*>(mine);
+  EOQ_SFOR(h, GH, *reinterpret_cast<float2*>(lin_m + h * D + c2) = make_float2(lin[h][0], lin[h][1]););
   __syncthreads();
-  if (th == 0) {
-    float* dst = partial + ((sg * gridDim.x + blockIdx.x) * 2 * MAXG) * D;
-#pragma unroll
-    for (int h = 0; h < MAXG; ++h) {   // heads past GH are written as zeros: the finishing kernel sums all eight
-      float rsum = 0.0f, lsum = 0.0f;
-      if (h < GH) {
-        const int hh = h < GH ? h : 0;
-        rsum = ((fold4_s[(0 * GH + hh) * D + c] + fold4_s[(1 * GH + hh) * D + c]) + fold4_s[(2 * GH + hh) * D + c]) + fold4_s[(3 * GH + hh) * D + c];
-        lsum = lin[hh] + fold_s[hh * D + c];
-      }
-      dst[h * D + c] = rsum;
-      dst[(MAXG + h) * D + c] = lsum;
-    }
+  float* dst = partial + ((sg * gridDim.x + blockIdx.x) * 2 * MAXG + h0) * D;
+  for (int e = tid; e < GH * D; e += THREADS) {
+    float rs[4];
+    float ls[4];
+    EOQ_SFOR(w, 4,
+      ls[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES)[e];
+      rs[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES + S::BASE_BYTES + S::BS_BYTES)[e];
+    );
+    dst[e] = ((rs[0] + rs[1]) + rs[2]) + rs[3];
+    dst[MAXG * D + e] = ((ls[0] + ls[1]) + ls[2]) + ls[3];
   }
 }
 
 // out[s][h][j] = sum_c Pi[c][j] a_h[c] + lin_h[j], the runs added in order.  One workgroup per (sequence, KV head,
 // query head of the group): lane (j, half) sums the rotated-domain partials (half 0) or the low-rank partials (half 1)
-// of the runs, one load per run with sixteen in flight; the rotation back and the tail are split between the halves
-// (coordinates 64 half .. 64 half + 63, tail tokens of parity half) and met through LDS in a fixed order.
-// With tail_len > 0 the uncompressed binary16 tail values are added: + sum_t weights[.., tail_offset + t] tail[t].
+// of the runs, one load per run with sixteen in flight; the rotation back is split between the halves (coordinates
+// 64 half .. 64 half + 63).  With tail_len > 0 the uncompressed binary16 tail values are added, + sum_t weights[..,
+// tail_offset + t] tail[t]: sixteen lanes share a token (16 bytes each), sixteen tokens at a time, the sixteen sums per
+// coordinate met through LDS in order.  (One lane per coordinate and every second token, as before, is a chain of
+// tail_len / 2 loads: 16 us at 389 tokens.)
 __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_heads, int group, int runs,
                                                                     const float* __restrict__ pi,
                                                                     const float* __restrict__ partial,
@@ -276,6 +592,7 @@ __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_hea
                                                                     int64_t tail_capacity, int tail_len) {
   __shared__ float a_s[D];
   __shared__ float meet_s[D];
+  __shared__ __align__(16) float tail_s[16 * D];
   const int tid = threadIdx.x;
   const int j = tid & (D - 1), half = tid >> 7;
   const size_t sg = blockIdx.x;
@@ -289,96 +606,165 @@ __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_hea
     for (int rn = 0; rn < runs; ++rn) sum += src[(size_t)rn * 2 * MAXG * D];
   }
   if (half == 0) a_s[j] = sum;
+  if (tail_len > 0) {
+    const float* wrow = weights + (sq * n_q_heads + kv * group + h) * (size_t)weight_stride + tail_offset;
+    const int l16 = tid & 15, ts = tid >> 4;
+    const uint16_t* trow = tail + sg * (size_t)tail_capacity * D + 8 * l16;
+    float t8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int t = ts; t < tail_len; t += 16) {
+      float x[8];
+      load8(trow, EOQ_F16, (size_t)t * D, x);
+      const float w = wrow[t];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t8[e] = fmaf(w, x[e], t8[e]);
+    }
+    *reinterpret_cast<float4*>(tail_s + ts * D + 8 * l16) = make_float4(t8[0], t8[1], t8[2], t8[3]);
+    *reinterpret_cast<float4*>(tail_s + ts * D + 8 * l16 + 4) = make_float4(t8[4], t8[5], t8[6], t8[7]);
+  }
   __syncthreads();
   float acc = (half == 1) ? sum : 0.0f;   // half 1 starts from the low-rank term
 #pragma unroll 16
   for (int cc = 64 * half; cc < 64 * half + 64; ++cc) acc = fmaf(pi[cc * D + j], a_s[cc], acc);
   if (tail_len > 0) {
-    const float* wrow = weights + (sq * n_q_heads + kv * group + h) * (size_t)weight_stride + tail_offset;
-#pragma unroll 8
-    for (int t = half; t < tail_len; t += 2)
-      acc = fmaf(wrow[t], half_bits_to_float(tail[(sg * (size_t)tail_capacity + t) * D + j]), acc);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) acc += tail_s[(8 * half + s) * D + j];
   }
   if (half == 1) meet_s[j] = acc;
   __syncthreads();
   if (half == 0) out[(sq * n_q_heads + kv * group + h) * D + j] = acc + meet_s[j];
 }
 
-// Row-wise softmax in place (the attention weights of Sec. 2.1): one workgroup per row, three passes; 16-byte
-// accesses when the row allows them (VEC), several of them in flight per lane.
-template <bool VEC>
-__global__ __launch_bounds__(THREADS) void eoq_softmax_kernel(float* __restrict__ x, int64_t len, int64_t stride) {
-  __shared__ float red[THREADS / 64];
-  __shared__ float bcast;
-  float* row = x + blockIdx.x * (size_t)stride;
+// Row-wise softmax in place (the attention weights of Sec. 2.1), one workgroup of NT lanes per row.  The row passes
+// through registers once: up to 4 NV elements per lane are loaded (all loads in flight), their maximum is met, they are
+// exponentiated and summed, met again, scaled and stored -- one read and one write of the row instead of three reads and
+// two writes (512 rows of 65536: 97 us before).  What a row has beyond 4 NV NT elements stays in memory and is read and
+// written in the three passes of the plain algorithm.  Four consecutive elements per access wherever the row starts:
+// accesses sit on 16-byte boundaries of the buffer, and the one at either end of a row that also covers elements of
+// another row (or none) goes element by element.
+template <int NT, int NV>
+__global__ __launch_bounds__(NT) void eoq_softmax_kernel(float* __restrict__ x, int64_t len, int64_t stride) {
+  __shared__ float red[NT / 64];
+  const size_t first = blockIdx.x * (size_t)stride;
+  const int head = (int)(first & 3);              // elements between the 16-byte boundary and the row
+  float* row = x + (first - head);                // elements head .. end - 1 of this pointer are the row
+  const int64_t end = head + len;
+  const int64_t items = (end + 3) >> 2;
+  const int n_reg = (int)(items < NV * NT ? items : NV * NT);      // accesses of the register part
+  // accesses e_first .. e_last - 1 cover nothing but the row
+  const int e_first = head ? 1 : 0;
+  const int64_t e_last = end >> 2;
   const int tid = threadIdx.x;
-  constexpr int W = VEC ? 4 : 1;
-  const int64_t items = len / W;   // VEC: len is a multiple of 4
+  auto meet = [&](float v, bool maximum) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) {
+      const float o = __shfl_xor(v, s, 64);
+      v = maximum ? fmaxf(v, o) : v + o;
+    }
+    if constexpr (NT > 64) {
+      __syncthreads();
+      if ((tid & 63) == 0) red[tid >> 6] = v;
+      __syncthreads();
+      v = red[0];
+#pragma unroll
+      for (int w = 1; w < NT / 64; ++w) v = maximum ? fmaxf(v, red[w]) : v + red[w];
+    }
+    return v;
+  };
+  auto load = [&](auto e) __attribute__((always_inline)) {
+    float4 v = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (e >= e_first && e < e_last) {
+      v = reinterpret_cast<const float4*>(row)[e];
+    } else {
+      const int64_t b = 4 * (int64_t)e;
+      if (b >= head && b < end) v.x = row[b];
+      if (b + 1 >= head && b + 1 < end) v.y = row[b + 1];
+      if (b + 2 >= head && b + 2 < end) v.z = row[b + 2];
+      if (b + 3 >= head && b + 3 < end) v.w = row[b + 3];
+    }
+    return v;
+  };
+  auto store = [&](auto e, const float4& v) __attribute__((always_inline)) {
+    if (e >= e_first && e < e_last) {
+      reinterpret_cast<float4*>(row)[e] = v;
+    } else {
+      const int64_t b = 4 * (int64_t)e;
+      if (b >= head && b < end) row[b] = v.x;
+      if (b + 1 >= head && b + 1 < end) row[b + 1] = v.y;
+      if (b + 2 >= head && b + 2 < end) row[b + 2] = v.z;
+      if (b + 3 >= head && b + 3 < end) row[b + 3] = v.w;
+    }
+  };
+  float4 v[NV];
   float m = -INFINITY;
-#pragma unroll 4
-  for (int64_t e = tid; e < items; e += THREADS) {
-    if constexpr (VEC) {
-      const float4 v = reinterpret_cast<const float4*>(row)[e];
-      m = fmaxf(fmaxf(m, fmaxf(v.x, v.y)), fmaxf(v.z, v.w));
-    } else {
-      m = fmaxf(m, row[e]);
-    }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int e = tid + k * NT;
+    v[k] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (e < n_reg) v[k] = load(e);
   }
 #pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
-  if ((tid & 63) == 0) red[tid >> 6] = m;
-  __syncthreads();
-  if (tid == 0) bcast = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  m = bcast;
+  for (int k = 0; k < NV; ++k) m = fmaxf(fmaxf(m, fmaxf(v[k].x, v[k].y)), fmaxf(v[k].z, v[k].w));
+#pragma unroll 4
+  for (int64_t e = tid + (int64_t)NV * NT; e < items; e += NT) {
+    const float4 o = load(e);
+    m = fmaxf(fmaxf(m, fmaxf(o.x, o.y)), fmaxf(o.z, o.w));
+  }
+  m = meet(m, true);
   float sum = 0.0f;
-#pragma unroll 4
-  for (int64_t e = tid; e < items; e += THREADS) {
-    if constexpr (VEC) {
-      float4 v = reinterpret_cast<const float4*>(row)[e];
-      v.x = expf(v.x - m);
-      v.y = expf(v.y - m);
-      v.z = expf(v.z - m);
-      v.w = expf(v.w - m);
-      reinterpret_cast<float4*>(row)[e] = v;
-      sum += (v.x + v.y) + (v.z + v.w);
-    } else {
-      const float v = expf(row[e] - m);
-      row[e] = v;
-      sum += v;
+  // elements that are not the row's are -inf and contribute exp(-inf) = 0 (a row of -inf alone is NaN, as it was)
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    if (tid + k * NT < n_reg) {
+      v[k].x = expf(v[k].x - m);
+      v[k].y = expf(v[k].y - m);
+      v[k].z = expf(v[k].z - m);
+      v[k].w = expf(v[k].w - m);
+      sum += (v[k].x + v[k].y) + (v[k].z + v[k].w);
     }
   }
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s, 64);
-  __syncthreads();
-  if ((tid & 63) == 0) red[tid >> 6] = sum;
-  __syncthreads();
-  if (tid == 0) bcast = (red[0] + red[1]) + (red[2] + red[3]);
-  __syncthreads();
-  const float inv = 1.0f / bcast;
 #pragma unroll 4
-  for (int64_t e = tid; e < items; e += THREADS) {
-    if constexpr (VEC) {
-      float4 v = reinterpret_cast<const float4*>(row)[e];
-      v.x *= inv;
-      v.y *= inv;
-      v.z *= inv;
-      v.w *= inv;
-      reinterpret_cast<float4*>(row)[e] = v;
-    } else {
-      row[e] *= inv;
-    }
+  for (int64_t e = tid + (int64_t)NV * NT; e < items; e += NT) {
+    float4 o = load(e);
+    o.x = expf(o.x - m);
+    o.y = expf(o.y - m);
+    o.z = expf(o.z - m);
+    o.w = expf(o.w - m);
+    store(e, o);
+    sum += (o.x + o.y) + (o.z + o.w);
+  }
+  sum = meet(sum, false);
+  const float inv = 1.0f / sum;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int e = tid + k * NT;
+    v[k].x *= inv;
+    v[k].y *= inv;
+    v[k].z *= inv;
+    v[k].w *= inv;
+    if (e < n_reg) store(e, v[k]);
+  }
+#pragma unroll 4
+  for (int64_t e = tid + (int64_t)NV * NT; e < items; e += NT) {
+    float4 o = load(e);
+    o.x *= inv;
+    o.y *= inv;
+    o.z *= inv;
+    o.w *= inv;
+    store(e, o);
   }
 }
 
 }  // namespace
 
-int64_t eoq_attend_runs(int64_t sg_total, int64_t blocks_per_head, int* run_out) {
-  // blocks per workgroup: up to 16, shorter when that leaves fewer than ~8 workgroups per compute unit
-  int64_t run = (sg_total * blocks_per_head) / 2048;
-  run = run < 1 ? 1 : (run > 16 ? 16 : run);
-  *run_out = (int)run;
-  return (blocks_per_head + run - 1) / run;
+int64_t eoq_attend_runs(int64_t sg_total, int64_t blocks_per_head, int n, int* pairs_per_wave) {
+  // 2048 waves are what the chip holds (two per SIMD): one round of them, so no last round runs half empty; at most
+  // 96 pairs (6144 tokens) per wave, where a second round costs little
+  const int64_t pairs = blocks_per_head * (n / PAIR);
+  int64_t ppw = (sg_total * pairs + 2047) / 2048;
+  ppw = ppw < 1 ? 1 : (ppw > 96 ? 96 : ppw);
+  *pairs_per_wave = (int)ppw;
+  return (pairs + 4 * ppw - 1) / (4 * ppw);
 }
 
 hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_seq, int n_kv_heads,
@@ -396,26 +782,23 @@ hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_se
     if (L.ev) (void)hipEventRecord(L.ev[9], L.stream);
     return hipGetLastError();
   }
-  int run = 1;
-  const int64_t runs = eoq_attend_runs(sg_total, blocks_per_head, &run);
+  int ppw = 1;
+  // up to 2 bits a wave takes all (up to eight) heads of the group; with byte terms the 32 operand rows hold four heads,
+  // and a group of more is two sets of workgroups (the runs, at most as many as the workspace was sized for, are then
+  // twice as long)
+  const unsigned z = (L.bits >= 3 && group > 4) ? 2u : 1u;
+  const int64_t runs = eoq_attend_runs(sg_total * z, blocks_per_head, L.n, &ppw);
   if (sg_total > 65535 || runs > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)runs, (unsigned)sg_total), block(THREADS);
-#define EOQ_ATTEND(BITS)                                                                                              \
-  do {                                                                                                                \
-    if (group <= 4)                                                                                                   \
-      hipLaunchKernelGGL((eoq_attend_partial_kernel<BITS, 4>), grid, block, 0, L.stream, L.n, L.r_max, n_kv_heads,    \
-                         group, blocks_per_head, block_capacity, weight_stride, run, L.tab, values.codes,             \
-                         values.norms, values.rank, values.lfac, values.rfac, weights, partial);                      \
-    else                                                                                                              \
-      hipLaunchKernelGGL((eoq_attend_partial_kernel<BITS, 8>), grid, block, 0, L.stream, L.n, L.r_max, n_kv_heads,    \
-                         group, blocks_per_head, block_capacity, weight_stride, run, L.tab, values.codes,             \
-                         values.norms, values.rank, values.lfac, values.rfac, weights, partial);                      \
-  } while (0)
+  const dim3 block(THREADS);
+#define EOQ_ATTEND(BITS, GH, Z)                                                                                        \
+  hipLaunchKernelGGL((eoq_attend_partial_kernel<BITS, GH>), dim3((unsigned)runs, (unsigned)sg_total, Z), block, 0,     \
+                     L.stream, L.n, L.r_max, n_kv_heads, group, blocks_per_head, block_capacity, weight_stride, ppw,   \
+                     L.tab, values.codes, values.norms, values.rank, values.lfac, values.rfac, weights, partial)
   switch (L.bits) {
-    case 1: EOQ_ATTEND(1); break;
-    case 2: EOQ_ATTEND(2); break;
-    case 3: EOQ_ATTEND(3); break;
-    default: EOQ_ATTEND(4); break;
+    case 1: if (group <= 4) EOQ_ATTEND(1, 4, 1); else EOQ_ATTEND(1, 8, 1); break;
+    case 2: if (group <= 4) EOQ_ATTEND(2, 4, 1); else EOQ_ATTEND(2, 8, 1); break;
+    case 3: EOQ_ATTEND(3, 4, z); break;
+    default: EOQ_ATTEND(4, 4, z); break;
   }
 #undef EOQ_ATTEND
   hipError_t e = hipGetLastError();
@@ -428,10 +811,16 @@ hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_se
 
 hipError_t eoq_launch_softmax(const EoqLaunch& L, float* x, int64_t rows, int64_t len, int64_t stride) {
   if (L.ev) (void)hipEventRecord(L.ev[10], L.stream);
-  if (((len | stride) & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0)
-    hipLaunchKernelGGL(eoq_softmax_kernel<true>, dim3((unsigned)rows), dim3(THREADS), 0, L.stream, x, len, stride);
-  else
-    hipLaunchKernelGGL(eoq_softmax_kernel<false>, dim3((unsigned)rows), dim3(THREADS), 0, L.stream, x, len, stride);
+  // as many lanes as it takes to hold the row in registers (64 elements per lane are what 1024 lanes have room for);
+  // rows of up to 4096 with few elements per lane: the latency of a lane's chain is what counts there
+  const int64_t span = len + 3;
+#define EOQ_SOFTMAX(NT, NV) hipLaunchKernelGGL((eoq_softmax_kernel<NT, NV>), dim3((unsigned)rows), dim3(NT), 0, L.stream, x, len, stride)
+  if (span <= 1024) EOQ_SOFTMAX(256, 1);
+  else if (span <= 4096) EOQ_SOFTMAX(256, 4);
+  else if (span <= 16384) EOQ_SOFTMAX(1024, 4);
+  else if (span <= 32768) EOQ_SOFTMAX(1024, 8);
+  else EOQ_SOFTMAX(1024, 16);
+#undef EOQ_SOFTMAX
   if (L.ev) (void)hipEventRecord(L.ev[11], L.stream);
   return hipGetLastError();
 }

@@ -527,8 +527,8 @@ eoq_status eoq_scores_stream(eoq_ctx* ctx, eoq_packed keys, int64_t n_seq, int n
 
 size_t eoq_attend_workspace_bytes(const eoq_ctx* ctx, int64_t n_seq, int n_kv_heads, int64_t blocks_per_head) {
   if (!ctx || n_seq <= 0 || n_kv_heads <= 0 || blocks_per_head <= 0) return 0;
-  int run = 1;
-  const int64_t runs = eoq_attend_runs(n_seq * n_kv_heads, blocks_per_head, &run);
+  int ppw = 1;
+  const int64_t runs = eoq_attend_runs(n_seq * n_kv_heads, blocks_per_head, ctx->n, &ppw);
   return (size_t)(n_seq * n_kv_heads) * (size_t)runs * 16 * EOQ_D * sizeof(float);
 }
 

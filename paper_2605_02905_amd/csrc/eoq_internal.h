@@ -102,7 +102,7 @@ hipError_t eoq_launch_scores(const EoqLaunch& L, eoq_packed keys, int64_t n_seq,
                              int64_t tail_capacity = 0, int tail_len = 0);
 
 // attention output on compressed values: number of partial-sum runs per (sequence, KV head) and the launches
-int64_t eoq_attend_runs(int64_t sg_total, int64_t blocks_per_head, int* run_out);
+int64_t eoq_attend_runs(int64_t sg_total, int64_t blocks_per_head, int n, int* pairs_per_wave);
 hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_seq, int n_kv_heads,
                              int64_t blocks_per_head, int64_t block_capacity, const float* weights,
                              int64_t weight_stride, int n_q_heads, float* out, float* partial,

@@ -888,6 +888,56 @@ def test_attention_output_of_oracle_records(n, bits, n_seq, n_kv, group, cap, fi
     assert not bool(empty.any())
 
 
+@pytest.mark.parametrize("length,pad", [(1, 0), (3, 2), (1021, 0), (1025, 3), (4093, 4), (16385, 1), (32766, 0), (65533, 2), (65537, 7), (70001, 0)])
+def test_softmax_row_lengths_and_alignments(length, pad):
+    """Rows around the lengths at which the row stops fitting the registers of a workgroup size, at strides that put
+    them at every offset from a 16-byte boundary."""
+    gen = torch.Generator().manual_seed(length)
+    s = (torch.randn(5, length + pad, generator=gen) * 4.0).to(DEV)
+    ref = s.clone()
+    eoq.Context(n=128, bits=2).eoq_softmax(s, length)
+    torch.cuda.synchronize()
+    want = oracle.softmax_rows(ref[:, :length].double().cpu().numpy())
+    assert np.max(np.abs(s[:, :length].double().cpu().numpy() - want) / want) <= 2e-5
+    assert torch.equal(s[:, length:], ref[:, length:])
+
+
+@pytest.mark.parametrize("n,bits,group,filled,tail_len", [(128, 1, 7, 5, 0), (256, 2, 5, 9, 77), (128, 2, 3, 70, 127), (512, 3, 6, 3, 389),
+                                                          (128, 4, 7, 33, 1), (1024, 4, 4, 2, 0)])
+def test_attention_output_weights_of_any_size(n, bits, group, filled, tail_len):
+    """Weights that are no softmax: signs, zeros, a magnitude that grows by 2^60 along the row (the fixed-point unit has
+    to follow), an odd row stride; ranks above 16; tails.  One head with a NaN weight leaves the others alone."""
+    n_kv, cap, r_max = 2, filled + 1, 32
+    ctx = eoq.Context(n=n, bits=bits, r_max=r_max)
+    spec = synth.BlockSpec("vals", n=n, n_tensors=n_kv, blocks_per_tensor=cap, rank_lo=0, rank_hi=24)
+    blocks, _ = synth.make_blocks(spec, seed=77 + n + bits, device=DEV)
+    store, _ = ctx.eoq_compress(blocks)
+    x = ctx.eoq_decompress(store).double().cpu().view(n_kv, cap * n, 128)[:, :filled * n]
+    gen = torch.Generator().manual_seed(bits)
+    tail = torch.randn(1, n_kv, n, 128, generator=gen).to(torch.float16)
+    T = filled * n + tail_len
+    w = torch.randn(1, n_kv * group, T + (5 if T % 2 == 0 else 4), generator=gen)
+    grow = torch.exp2(torch.linspace(-40, 20, T).round())
+    w[0, 0, :T] *= grow
+    w[0, 1, : T // 2] = 0.0
+    w[0, 2, :T] *= grow.flip(0)
+    ref = torch.cat([x, tail[0, :, :tail_len].double()], dim=1)
+    want = torch.stack([w[0, h, :T].double() @ ref[h // group] for h in range(n_kv * group)]).numpy()
+    # decompression rounds to binary16 and rotates with a binary16 table: the bar is that error's, per head
+    norm = np.stack([(w[0, h, :T].double().square() @ ref[h // group].square().sum(1)).sqrt().item() for h in range(n_kv * group)])
+    out = ctx.eoq_attend_stream(store, w.to(DEV), n_kv, cap, filled, tail.to(DEV), tail_len)
+    torch.cuda.synchronize()
+    got = out[0].double().cpu().numpy()
+    assert np.all(np.max(np.abs(got - want), axis=1) <= 1e-3 * norm)
+    bad = w.clone()
+    bad[0, group, T // 3] = float("nan")
+    out2 = ctx.eoq_attend_stream(store, bad.to(DEV), n_kv, cap, filled, tail.to(DEV), tail_len)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(out2[0, group]).all())
+    keep = [h for h in range(n_kv * group) if h != group]
+    assert np.all(np.max(np.abs(out2[0, keep].double().cpu().numpy() - want[keep]), axis=1) <= 1e-3 * norm[keep])
+
+
 def test_decode_step_scores_softmax_attend_in_the_bench_launch_configuration():
     """Config 2 at full size as one decode step: keys = the K tensors, values = the V tensors of the compressed batch
     (8 KV heads x 64 blocks of 512 tokens), 32 query heads: eoq_scores -> eoq_softmax -> eoq_attend in the launch shapes
