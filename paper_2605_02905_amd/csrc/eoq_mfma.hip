@@ -10,10 +10,10 @@
 // A[row = l%32][k = 8*(l/32) .. +7] and B[k = 8*(l/32) .. +7][col = l%32]; it receives
 // D[row = 8*(v/4) + 4*(l/32) + v%4][col = l%32] in accumulator register v = 0..15.
 //
-// Layout of the work: the rotation is the stationary operand.  In the encoder and the qjl kernel wave w of a workgroup
-// keeps the 32 columns j = 32w .. 32w+31 of Pi (binary16 hi + lo parts, B operand) in registers for the whole block; the
-// tokens stream through LDS in tiles of 32 (A operand), each tile prepared by one wave and consumed by all four.  In the
-// decoder every wave keeps the whole of Pi^T (binary16 rounding, A operand) and works on tiles of its own.
+// Layout of the work: the rotation is the stationary operand.  In the encoder wave w of a workgroup keeps the 32 columns
+// j = 32w .. 32w+31 of Pi (binary16 hi + lo parts, B operand) in registers for the whole block; the tokens stream
+// through LDS in tiles of 32 (A operand), each tile prepared by one wave and consumed by all four.  In the decoder and the
+// qjl kernel every wave keeps the whole of Pi^T (binary16 rounding, A operand) and works on tiles of its own.
 #include "eoq_device.h"
 #include "eoq_internal.h"
 
@@ -25,7 +25,6 @@ constexpr int D = EOQ_D;
 constexpr int THREADS = 256;
 constexpr int CHUNK = 128;          // tokens per pass of a workgroup: one tile of 32 per wave
 constexpr int ZLD = D + 8;          // row stride (halfs) of the token tiles in LDS: 272 B, conflict-free b128 reads
-constexpr int CLD = EOQ_RMAX_CAP + 8;
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
@@ -164,52 +163,6 @@ __device__ __forceinline__ H8 centroids_of(const uint32_t (&byte)[BITS], const u
   return out;
 }
 
-// ---------------------------------------------------------------------------------------------
-// Record fetches of the workgroup-per-block kernels (TQ_prod side information below).
-// ---------------------------------------------------------------------------------------------
-// What one thread requests of a chunk of 128 tokens: lane (l32, hf) of wave w unpacks half of token 32 w + l32;
-// thread tid also carries 8 tokens of row (tid + 256 u) / 16 of the left factors, u = 0, 1.
-template <int BITS>
-struct DecodeFetch {
-  uint4 pl[BITS];  // the token's bit-planes
-  uint4 cf[2];     // left factors C[i][8 seg .. 8 seg + 7], (i, seg) = ((tid + 256 u) / 16, tid % 16), if i < r
-  uint16_t rho;    // the token's stored norm
-  int r;           // rank of the block the chunk belongs to
-};
-template <int BITS>
-__device__ __forceinline__ void decode_fetch(DecodeFetch<BITS>& f, int64_t blk, int t0, int n, int r, int r_max, int tid, int tl,
-                                             const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms,
-                                             const uint16_t* __restrict__ lfac) {
-  constexpr int ROWB = BITS * D / 8;
-  const size_t tok = (size_t)blk * n + t0 + tl;
-  f.r = r;
-#pragma unroll
-  for (int p = 0; p < BITS; ++p) f.pl[p] = *reinterpret_cast<const uint4*>(codes + tok * ROWB + p * 16);
-  f.rho = norms[tok];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int i = (tid + THREADS * u) >> 4, seg = tid & 15;
-    f.cf[u] = (i < r) ? *reinterpret_cast<const uint4*>(lfac + ((size_t)blk * r_max + i) * n + t0 + 8 * seg)
-                      : make_uint4(0u, 0u, 0u, 0u);
-  }
-}
-// right factors of a block as B operand of the low-rank product: V[i][jcol], i = 16 k2 + 8 hf + e.  The sixteen
-// two-byte loads land in registers of their own and are packed by pack_v once they are needed, so that issuing
-// them waits for nothing.
-__device__ __forceinline__ void decode_fetch_v(uint32_t (&raw)[16], int64_t blk, int r, int r_max, int jcol, int hf,
-                                               const uint16_t* __restrict__ rfac) {
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int i = 16 * (q >> 3) + 8 * hf + (q & 7);
-    raw[q] = (i < r) ? (uint32_t)rfac[((size_t)blk * r_max + i) * D + jcol] : 0u;
-  }
-}
-__device__ __forceinline__ void pack_v(H8 (&Bv)[2], const uint32_t (&raw)[16]) {
-#pragma unroll
-  for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) Bv[k2].w[w] = raw[8 * k2 + 2 * w] | (raw[8 * k2 + 2 * w + 1] << 16);
-}
 // Rank of block blk as a vector load (zero past the end of the array): a scalar load would share its counter with
 // the LDS traffic and be waited for at the next LDS wait, a vector load is waited for where its value is read.
 __device__ __forceinline__ int rank_request(__amdgpu_buffer_rsrc_t ranks, int64_t blk) {
@@ -511,215 +464,270 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// TQ_prod side information (Alg. 1 lines "TQ_prod"): one workgroup per block.  The reconstruction of the record is
-// formed as in the decoder, tile by tile in float32 accumulators (centroids and rotation as binary16 hi + lo here:
-// the residual is a small difference), r_x = S - x_hat goes to LDS as binary16 hi + lo, its norm is taken there, and
-// one more product with Phi (binary16 by definition, stationary in registers like the rotation) gives Phi r_x, of
-// which only the signs are kept, packed like one more bit-plane.
+// TQ_prod side information (Alg. 1 lines "TQ_prod").  As in the decoder every wave is a worker of its own on tiles of 32
+// tokens (a contiguous range of the batch's tiles each), the lane that owns a token unpacks it and the products come out
+// transposed.  Centroids and rotation enter as binary16 hi + lo (three matrix instructions per operand: r_x = S - x_hat
+// is a small difference); r_x forms in the accumulators from the token's own row, its norm is a sum over the lane and
+// its partner, and its hi + lo parts are packed from the accumulators straight into the operand of the product with Phi
+// (binary16 by definition), whose contraction index is permuted to the order the accumulators have.  The sign bits
+// of the result are assembled inside the lane.  Pi^T hi sits in registers, Pi^T lo and Phi in LDS in operand order, shared by
+// the eight waves of the workgroup (one per compute unit, two waves per SIMD).
+// Bound by the matrix cores: 160 instructions per tile, 32 cycles each (about 45 at the clock such a stretch leaves), of
+// a wave that has no registers to read operands far ahead: every phase left out of it takes twice its matrix
+// instructions' time with it.  262144 tokens of 2 bits: 52 us.  The workgroup-per-block version this replaces exchanged
+// centroids and residuals through LDS with a barrier per 64 tokens at one wave per SIMD: 100 us.
 // ---------------------------------------------------------------------------------------------
+constexpr int QWAVES = 8;
+constexpr int SLD = 64 + 8;   // row stride (halfs) of the staged half tile
 template <int BITS>
-__global__ __launch_bounds__(THREADS, 1) void eoq_qjl_kernel(
-    const uint16_t* __restrict__ blocks, int n, int r_max, const uint16_t* __restrict__ pih,
+__global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
+    const uint16_t* __restrict__ blocks, int n, int r_max, int64_t tiles, int64_t per_wave, const uint16_t* __restrict__ pih,
     const uint16_t* __restrict__ phih, const float* __restrict__ tab, const uint8_t* __restrict__ codes,
     const uint16_t* __restrict__ norms, const int32_t* __restrict__ rank_in, const uint16_t* __restrict__ lfac,
     const uint16_t* __restrict__ rfac, uint8_t* __restrict__ qsigns, uint16_t* __restrict__ qnorms) {
-  __shared__ __align__(16) uint16_t Z[CHUNK * ZLD];     // centroid values (hi) of the chunk, [token][coordinate]
-  __shared__ __align__(16) uint16_t Zl[CHUNK * ZLD];    // their low parts
-  __shared__ __align__(16) uint16_t Ct[CHUNK * CLD];    // low-rank coefficients, [token][component]
-  __shared__ __align__(16) float rho_s[CHUNK];          // rho / sqrt(d)
-  __shared__ __align__(16) uint4 mask_tab[256];
-  // residual tiles of 64 tokens (two tiles of 32), hi and lo, double-buffered: while the products with Phi read one
-  // pair the next two tiles are written into the other, so one barrier per 64 tokens is enough
-  __shared__ __align__(16) uint16_t Eh[2][64 * ZLD];
-  __shared__ __align__(16) uint16_t El[2][64 * ZLD];
+  __shared__ __align__(16) uint4 Plo[4 * 8 * 64];            // Pi^T lo, [column block][instruction][lane]
+  __shared__ __align__(16) uint4 Fop[4 * 8 * 64];            // Phi, the same, contraction order of the accumulators
+  __shared__ __align__(16) uint16_t Vt[QWAVES * D * 16];     // per wave: right factors 0 .. 15 of the block, [column][component]
+  __shared__ __align__(16) uint16_t St[QWAVES * 32 * SLD];   // per wave: half the columns of a tile of S, [token][column]
+  __shared__ __align__(16) uint16_t Cs[QWAVES * 16 * CTLD];  // per wave: coefficient rows of a tile
+  __shared__ __align__(16) uint4 mask_tab[256];              // BITS = 4: plane byte -> halfword masks; BITS <= 3: nibble tables, hi then lo
+  __shared__ __align__(16) uint2 sign_tab[BITS == 3 ? 16 : 1];
+  uint2* cen_hi = reinterpret_cast<uint2*>(mask_tab);
+  uint2* cen_lo = cen_hi + 256;
+  constexpr int ROWB = BITS * D / 8;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
-  const int jcol = 32 * wave + l32;
-  const int tl = 32 * wave + l32;
-  const size_t blk = blockIdx.x;
+  set_fp16_overflow_clamp();   // parts of r_x saturate by the conversion itself
 
-  build_mask_table(mask_tab, tid);
-  for (int e = tid; e < CHUNK * CLD / 8; e += THREADS) *reinterpret_cast<uint4*>(&Ct[e * 8]) = make_uint4(0u, 0u, 0u, 0u);
+  if constexpr (BITS == 4) {
+    build_mask_table(mask_tab, tid);
+  } else if (tid < 256) {
+    // entry (nibble of plane / magnitude bit 0 | nibble of 1 << 4) -> centroids (BITS <= 2) or their magnitudes (BITS = 3)
+    const int n0 = tid & 15, n1 = tid >> 4;
+    uint16_t h[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int two = ((n0 >> e) & 1) | ((BITS >= 2) ? (((n1 >> e) & 1) << 1) : 0);
+      split_half(tab[(BITS == 3 ? 4 : 0) + two], h[e], l[e]);
+    }
+    cen_hi[tid] = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+    cen_lo[tid] = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
+    if (BITS == 3 && tid < 16)   // sign bits of four halfwords: set where the sign plane is clear
+      sign_tab[tid] = make_uint2(((tid & 1) ? 0u : 0x8000u) | ((tid & 2) ? 0u : 0x80000000u), ((tid & 4) ? 0u : 0x8000u) | ((tid & 8) ? 0u : 0x80000000u));
+  }
   Mags<BITS> mg;
-  mg.load(tab);
+  if constexpr (BITS == 4) mg.load(tab);
   const uint16_t* pit_hi = pih + 2 * D * D;
   const uint16_t* pit_lo = pih + 3 * D * D;
-  // stationary operands: columns of Pi^T (hi + lo) and rows of Phi (binary16 as it is) of this lane
-  H8 Bhi[8], Blo[8], Fhi[8];
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
-    Bhi[kk].u = *reinterpret_cast<const uint4*>(pit_hi + jcol * D + 16 * kk + 8 * hf);
-    Blo[kk].u = *reinterpret_cast<const uint4*>(pit_lo + jcol * D + 16 * kk + 8 * hf);
-    Fhi[kk].u = *reinterpret_cast<const uint4*>(phih + jcol * D + 16 * kk + 8 * hf);
+  for (int k = 0; k < 4 * 8 / QWAVES; ++k) {
+    const int cb = k * QWAVES / 8, kk = wave;   // this wave's share of the operands in LDS
+    Plo[(cb * 8 + kk) * 64 + lane] = *reinterpret_cast<const uint4*>(pit_lo + (32 * cb + l32) * D + 64 * hf + 8 * kk);
+    const uint16_t* frow = phih + (32 * cb + l32) * D + 16 * kk + 4 * hf;
+    const uint2 fa = *reinterpret_cast<const uint2*>(frow), fb = *reinterpret_cast<const uint2*>(frow + 8);
+    Fop[(cb * 8 + kk) * 64 + lane] = make_uint4(fa.x, fa.y, fb.x, fb.y);
   }
-  const float inv_sqrt_d = 1.0f / sqrtf((float)D);
-  DecodeFetch<BITS> cur;
-  H8 Bv[2];
-  const int r = min(max(rank_in[blk], 0), r_max);
-  {
-    uint32_t vraw[16];
-    decode_fetch_v(vraw, blk, r, r_max, jcol, hf, rfac);
-    pack_v(Bv, vraw);
-  }
-  int eb = 0;   // residual buffer of the current pair of tiles
+  __syncthreads();   // the only one: from here on the waves do not meet again
 
-  for (int t0 = 0; t0 < n; t0 += CHUNK) {
-    decode_fetch<BITS>(cur, blk, t0, n, r, r_max, tid, tl, codes, norms, lfac);
-    // the block's own entries S[row][jcol] of the first pair of tiles
-    uint16_t sv[2][16];
+  const int64_t first = ((int64_t)blockIdx.x * QWAVES + wave) * per_wave;
+  const int64_t last = min(first + per_wave, tiles);
+  if (first >= last) return;
+  H8 Ap[4][8];
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2) {
-      const uint16_t* srow = blocks + (blk * (size_t)n + t0 + 32 * h2) * D + jcol;
+  for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sv[h2][v] = srow[(size_t)(8 * (v >> 2) + 4 * hf + (v & 3)) * D];
+    for (int kk = 0; kk < 8; ++kk)
+      Ap[cb][kk].u = *reinterpret_cast<const uint4*>(pit_hi + (32 * cb + l32) * D + 64 * hf + 8 * kk);
+  const float inv_sqrt_d = 1.0f / sqrtf((float)D);
+
+  const int tpb = n / 32;
+  const uint32_t vo_code = (uint32_t)(l32 * ROWB + 8 * hf);
+  const uint32_t vo_cf = (uint32_t)(((lane >> 2) * n + (lane & 3) * 8) * 2);
+  const uint32_t vo_row = (uint32_t)((lane >> 4) * (D * 2) + (lane & 15) * 16);
+  uint16_t* vt = Vt + wave * (D * 16);
+  uint16_t* st = St + wave * (32 * SLD);
+  uint16_t* cs = Cs + wave * (16 * CTLD);
+
+  TileFetch<BITS> cur;
+  auto request = [&](int64_t blk, int r, int t0) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t cb = buffer_of(codes + (size_t)blk * n * ROWB, (size_t)n * ROWB);
+#pragma unroll
+    for (int p = 0; p < BITS; ++p) cur.pl[p] = __builtin_amdgcn_raw_buffer_load_b64(cb, vo_code + 16 * p, t0 * ROWB, 0);
+    cur.rho = norms[(size_t)blk * n + t0 + l32];
+    cur.cf = __builtin_amdgcn_raw_buffer_load_b128(buffer_of(lfac + (size_t)blk * r_max * n, (size_t)r * n * 2), vo_cf, t0 * 2, 0);
+  };
+  auto v_operand = [&](int cb) __attribute__((always_inline)) {   // V[8 hf + e][32 cb + l32] as staged
+    H8 x;
+    x.u = *reinterpret_cast<const uint4*>(vt + (32 * cb + l32) * 16 + 8 * hf);
+    return x;
+  };
+  auto c_operand = [&]() __attribute__((always_inline)) {         // -C[token l32][8 hf + e] of the rows staged in cs
+    H8 x;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t a = cs[(8 * hf + 2 * w) * CTLD + l32], b = cs[(8 * hf + 2 * w + 1) * CTLD + l32];
+      x.w[w] = (a | (b << 16)) ^ 0x80008000u;
     }
-    __syncthreads();  // previous chunk consumed; orders the mask table and the cleared Ct before first use
+    return x;
+  };
+  auto stage_v = [&](__amdgpu_buffer_rsrc_t vbuf, int k2) __attribute__((always_inline)) {   // rows 16 k2 .. + 15 into vt
+    u32x4 vrow[4];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      uint32_t byte[BITS];
+    for (int k = 0; k < 4; ++k) vrow[k] = __builtin_amdgcn_raw_buffer_load_b128(vbuf, vo_row + (16 * k2 + 4 * k) * (D * 2), 0, 0);
 #pragma unroll
-      for (int p = 0; p < BITS; ++p) {
-        const uint32_t wsel = (kk < 2) ? cur.pl[p].x : (kk < 4) ? cur.pl[p].y : (kk < 6) ? cur.pl[p].z : cur.pl[p].w;
-        byte[p] = (wsel >> (16 * (kk & 1) + 8 * hf)) & 0xFFu;
-      }
-      H8 clo;
-      const H8 c = centroids_of<BITS, true>(byte, mask_tab, mg, &clo);
-      *reinterpret_cast<uint4*>(&Z[tl * ZLD + 16 * kk + 8 * hf]) = c.u;
-      *reinterpret_cast<uint4*>(&Zl[tl * ZLD + 16 * kk + 8 * hf]) = clo.u;
+    for (int k = 0; k < 4; ++k) {
+      uint16_t* dst = vt + (lane & 15) * 8 * 16 + 4 * k + (lane >> 4);   // column 8 (L % 16) + e, component 4 k + L / 16
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dst[16 * e] = (uint16_t)(vrow[k][e >> 1] >> (16 * (e & 1)));
     }
-    if (hf == 0) rho_s[tl] = half_bits_to_float(cur.rho) * inv_sqrt_d;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = (tid + THREADS * u) >> 4, seg = tid & 15;
-      if (i < r) {
-        H8 c;
-        c.u = cur.cf[u];
-#pragma unroll
-        for (int x = 0; x < 8; ++x) Ct[(8 * seg + x) * CLD + i] = c.s[x];
-      }
-    }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  int64_t blk = first / tpb;
+  int ti = (int)(first - blk * tpb);
+  int r = rank_value(rank_in[blk], r_max);
+  request(blk, r, 32 * ti);
+  bool fresh = true;   // the block's right factors are not staged yet
 #pragma unroll 1
-    for (int tau = 0; tau < CHUNK / 32; tau += 2) {
-      uint16_t svn[2][16];
-      if (tau + 2 < CHUNK / 32) {   // the next pair's entries of S, requested before this pair's products
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) {
-          const uint16_t* srow = blocks + (blk * (size_t)n + t0 + 32 * (tau + 2 + h2)) * D + jcol;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) svn[h2][v] = srow[(size_t)(8 * (v >> 2) + 4 * hf + (v & 3)) * D];
-        }
-      }
-      // ---- x_hat of tokens 32 tau .. 32 tau + 63, columns 32 wave .. 32 wave + 31: two independent chains ----
-      float16v acc[2];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.0f;
-      const int arow = 32 * tau + l32;
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        H8 a0, a1, b0, b1;
-        a0.u = *reinterpret_cast<const uint4*>(&Z[arow * ZLD + 16 * kk + 8 * hf]);
-        b0.u = *reinterpret_cast<const uint4*>(&Z[(arow + 32) * ZLD + 16 * kk + 8 * hf]);
-        a1.u = *reinterpret_cast<const uint4*>(&Zl[arow * ZLD + 16 * kk + 8 * hf]);
-        b1.u = *reinterpret_cast<const uint4*>(&Zl[(arow + 32) * ZLD + 16 * kk + 8 * hf]);
-        acc[0] = mfma16(a0, Bhi[kk], acc[0]);
-        acc[1] = mfma16(b0, Bhi[kk], acc[1]);
-        acc[0] = mfma16(a0, Blo[kk], acc[0]);
-        acc[1] = mfma16(b0, Blo[kk], acc[1]);
-        acc[0] = mfma16(a1, Bhi[kk], acc[0]);
-        acc[1] = mfma16(b1, Bhi[kk], acc[1]);
-      }
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 s = *reinterpret_cast<const float4*>(&rho_s[32 * (tau + h2) + 8 * q + 4 * hf]);
-          acc[h2][4 * q + 0] *= s.x;
-          acc[h2][4 * q + 1] *= s.y;
-          acc[h2][4 * q + 2] *= s.z;
-          acc[h2][4 * q + 3] *= s.w;
-        }
-      if (r > 0) {
-#pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2) {
-          if (16 * k2 < r) {
-            H8 a0, b0;
-            a0.u = *reinterpret_cast<const uint4*>(&Ct[arow * CLD + 16 * k2 + 8 * hf]);
-            b0.u = *reinterpret_cast<const uint4*>(&Ct[(arow + 32) * CLD + 16 * k2 + 8 * hf]);
-            acc[0] = mfma16(a0, Bv[k2], acc[0]);
-            acc[1] = mfma16(b0, Bv[k2], acc[1]);
-          }
-        }
-      }
-      // ---- r_x = S - x_hat into the pair's buffer, hi + lo ----
-      uint16_t* eh = Eh[eb];
-      uint16_t* el = El[eb];
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = 32 * h2 + 8 * (v >> 2) + 4 * hf + (v & 3);
-          const float e = half_bits_to_float(sv[h2][v]) - acc[h2][v];
-          uint16_t hi, lo;
-          split_half(e, hi, lo);
-          eh[row * ZLD + jcol] = hi;
-          el[row * ZLD + jcol] = lo;
-        }
-      __syncthreads();  // the pair is complete; the other buffer was last read before the previous barrier
-      // ---- norms: 4 lanes per token, 32 columns each ----
-      {
-        const int row = tid >> 2, seg = tid & 3;
-        float ss = 0.0f;
-#pragma unroll
-        for (int h4 = 0; h4 < 4; ++h4) {
-          H8 a, b;
-          a.u = *reinterpret_cast<const uint4*>(&eh[row * ZLD + 32 * seg + 8 * h4]);
-          b.u = *reinterpret_cast<const uint4*>(&el[row * ZLD + 32 * seg + 8 * h4]);
-#pragma unroll
-          for (int x = 0; x < 8; ++x) {
-            const float e = half_bits_to_float(a.s[x]) + half_bits_to_float(b.s[x]);
-            ss = fmaf(e, e, ss);
-          }
-        }
-        ss += dpp_mov<0xB1>(ss);
-        ss += dpp_mov<0x4E>(ss);
-        if (seg == 0) qnorms[blk * (size_t)n + t0 + 32 * tau + row] = float_to_half_bits(sqrtf(ss));
-      }
-      // ---- Phi r_x for outputs i = 32 wave + l32 of both tiles, signs only ----
-      float16v pr[2];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) pr[0][v] = pr[1][v] = 0.0f;
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        H8 a0, a1, b0, b1;
-        a0.u = *reinterpret_cast<const uint4*>(&eh[l32 * ZLD + 16 * kk + 8 * hf]);
-        b0.u = *reinterpret_cast<const uint4*>(&eh[(l32 + 32) * ZLD + 16 * kk + 8 * hf]);
-        a1.u = *reinterpret_cast<const uint4*>(&el[l32 * ZLD + 16 * kk + 8 * hf]);
-        b1.u = *reinterpret_cast<const uint4*>(&el[(l32 + 32) * ZLD + 16 * kk + 8 * hf]);
-        pr[0] = mfma16(a0, Fhi[kk], pr[0]);
-        pr[1] = mfma16(b0, Fhi[kk], pr[1]);
-        pr[0] = mfma16(a1, Fhi[kk], pr[0]);
-        pr[1] = mfma16(b1, Fhi[kk], pr[1]);
-      }
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) {
-        uint32_t outw = 0u;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const unsigned long long m = __ballot(pr[h2][v] >= 0.0f);
-          const int row_lo = 8 * (v >> 2) + (v & 3);   // token of the low word; the high word is row_lo + 4
-          outw = (lane == row_lo) ? (uint32_t)m : ((lane == row_lo + 4) ? (uint32_t)(m >> 32) : outw);
-        }
-        if (lane < 32)
-          *reinterpret_cast<uint32_t*>(qsigns + (blk * (size_t)n + t0 + 32 * (tau + h2) + lane) * (D / 8) + 4 * wave) = outw;
-      }
-      eb ^= 1;
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sv[h2][v] = svn[h2][v];
+  for (int64_t tile = first; tile < last; ++tile) {
+    const int t0 = 32 * ti;
+    const __amdgpu_buffer_rsrc_t vbuf = buffer_of(rfac + (size_t)blk * r_max * D, (size_t)r * D * 2);
+    if (fresh && r > 0) stage_v(vbuf, 0);
+    fresh = false;
+    const float rs = half_bits_to_float((uint16_t)cur.rho) * inv_sqrt_d;
+    if (r > 0) {   // uniform
+      *reinterpret_cast<u32x4*>(cs + (lane >> 2) * CTLD + (lane & 3) * 8) = cur.cf;
+      __builtin_amdgcn_wave_barrier();
     }
+    // nibble words of the lane's 64 coordinates (BITS <= 3): byte kk of word set [kk / 4] is instruction kk
+    uint32_t even[2], odd[2], seven[2], sodd[2];
+    if constexpr (BITS <= 3) {
+#pragma unroll
+      for (int wq = 0; wq < 2; ++wq) {
+        uint32_t a, b;
+        if constexpr (BITS == 1) {
+          a = cur.pl[0][wq];
+          b = 0u;
+        } else if constexpr (BITS == 2) {
+          a = cur.pl[0][wq];
+          b = cur.pl[1][wq];
+        } else {
+          a = ~(cur.pl[0][wq] ^ cur.pl[2][wq]);
+          b = ~(cur.pl[1][wq] ^ cur.pl[2][wq]);
+          seven[wq] = cur.pl[2][wq] & 0x0F0F0F0Fu;
+          sodd[wq] = (cur.pl[2][wq] >> 4) & 0x0F0F0F0Fu;
+        }
+        even[wq] = bfi(0x0F0F0F0Fu, a, b << 4);
+        odd[wq] = bfi(0x0F0F0F0Fu, a >> 4, b);
+      }
+    }
+    float16v acc[4];
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[cb][v] = 0.0f;
+    // the tile of S: row 8 i + L / 8, columns 64 h + 8 (L % 8) .. + 7, a 128-byte line per eight lanes
+    const uint16_t* srow = blocks + ((size_t)blk * n + t0 + (lane >> 3)) * D + 8 * (lane & 7);
+    u32x4 sv[2][4];
+    EOQ_SFOR(h, 2, EOQ_SFOR(i, 4, sv[h][i] = *reinterpret_cast<const u32x4*>(srow + 8 * i * D + 64 * h);););
+    EOQ_SFOR(kk, 8,
+      H8 zh;
+      H8 zl;
+      if constexpr (BITS <= 3) {
+        const uint32_t ie = (even[kk >> 2] >> (8 * (kk & 3))) & 0xFFu; const uint32_t io = (odd[kk >> 2] >> (8 * (kk & 3))) & 0xFFu;
+        const uint2 a = cen_hi[ie]; const uint2 b = cen_hi[io]; const uint2 c = cen_lo[ie]; const uint2 d = cen_lo[io];
+        zh.u = make_uint4(a.x, a.y, b.x, b.y);
+        zl.u = make_uint4(c.x, c.y, d.x, d.y);
+        if constexpr (BITS == 3) {
+          const uint2 sa = sign_tab[(seven[kk >> 2] >> (8 * (kk & 3))) & 0xFFu]; const uint2 sb = sign_tab[(sodd[kk >> 2] >> (8 * (kk & 3))) & 0xFFu];
+          zh.u = make_uint4(zh.u.x ^ sa.x, zh.u.y ^ sa.y, zh.u.z ^ sb.x, zh.u.w ^ sb.y);
+          zl.u = make_uint4(zl.u.x ^ sa.x, zl.u.y ^ sa.y, zl.u.z ^ sb.x, zl.u.w ^ sb.y);
+        }
+      } else {
+        uint32_t byte[BITS];
+        EOQ_SFOR(p, BITS, byte[p] = (cur.pl[p][kk >> 2] >> (8 * (kk & 3))) & 0xFFu;);
+        zh = centroids_of<BITS, true>(byte, mask_tab, mg, &zl);
+      }
+      EOQ_SFOR(cb, 4, acc[cb] = mfma16(Ap[cb][kk], zh, acc[cb]););
+      EOQ_SFOR(cb, 4, acc[cb] = mfma16(Ap[cb][kk], zl, acc[cb]););
+      EOQ_SFOR(cb, 4,
+        H8 lo;
+        lo.u = Plo[(cb * 8 + kk) * 64 + lane];
+        acc[cb] = mfma16(lo, zh, acc[cb]);
+      );
+    );
+    // ---- r_x = S - x_hat: S goes through LDS, half the columns at a time, into the lanes that own the tokens; register v
+    // of column block cb is column 32 cb + 8 (v / 4) + 4 hf + v % 4 ----
+    EOQ_SFOR(h, 2,
+      EOQ_SFOR(i, 4, *reinterpret_cast<u32x4*>(st + (8 * i + (lane >> 3)) * SLD + 8 * (lane & 7)) = sv[h][i];);
+      __builtin_amdgcn_wave_barrier();
+      EOQ_SFOR(c, 2, EOQ_SFOR(q, 4,
+        constexpr int cb = 2 * h + c;
+        const u32x2 w = *reinterpret_cast<const u32x2*>(st + l32 * SLD + 32 * c + 8 * q + 4 * hf);
+        EOQ_SFOR(e, 4,
+          acc[cb][4 * q + e] = fmaf(acc[cb][4 * q + e], -rs, half_bits_to_float((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu))));
+        );
+      ););
+      __builtin_amdgcn_wave_barrier();
+    );
+    if (r > 0) {
+      const H8 cop = c_operand();
+      EOQ_SFOR(cb, 4, acc[cb] = mfma16(v_operand(cb), cop, acc[cb]););
+      if (r > 16) {   // components 16 .. 31 (rare): nothing of them is kept, the first ones are staged again for the next tile
+        fresh = true;
+        const __amdgpu_buffer_rsrc_t lbuf = buffer_of(lfac + (size_t)blk * r_max * n, (size_t)r * n * 2);
+        const u32x4 c2 = __builtin_amdgcn_raw_buffer_load_b128(lbuf, vo_cf + (uint32_t)(16 * n * 2), t0 * 2, 0);
+        __builtin_amdgcn_wave_barrier();
+        *reinterpret_cast<u32x4*>(cs + (lane >> 2) * CTLD + (lane & 3) * 8) = c2;
+        stage_v(vbuf, 1);
+        const H8 cop2 = c_operand();
+        EOQ_SFOR(cb, 4, acc[cb] = mfma16(v_operand(cb), cop2, acc[cb]););
+      }
+      __builtin_amdgcn_wave_barrier();   // the tile's LDS is rewritten by the next one
+    }
+    float ss = 0.0f;
+    EOQ_SFOR(cb, 4, EOQ_SFOR(v, 16, ss = fmaf(acc[cb][v], acc[cb][v], ss);););
+    ss += __shfl_xor(ss, 32, 64);
+    if (hf == 0) qnorms[(size_t)blk * n + t0 + l32] = float_to_half_bits(sqrtf(ss));
+    H8 rh[8], rl[8];   // instruction 2 cb + s: columns 32 cb + 16 s + {0, 8} + 4 hf + 0 .. 3
+    EOQ_SFOR(st, 8, EOQ_SFOR(w, 4,
+      constexpr int cb = st >> 1; constexpr int v = 8 * (st & 1) + 2 * w;
+      const float a = acc[cb][v]; const float b = acc[cb][v + 1];
+      const uint32_t h = pack_half2(a, b);
+      rh[st].w[w] = h;
+      rl[st].w[w] = pack_half2(a - half_bits_to_float((uint16_t)(h & 0xFFFFu)), b - half_bits_to_float((uint16_t)(h >> 16)));
+    ););
+    // ---- the next tile's record bytes travel during the product with Phi ----
+    const size_t row = (size_t)blk * n + t0 + l32;
+    if (tile + 1 < last) {   // uniform
+      if (++ti == tpb) {
+        ti = 0;
+        ++blk;
+        r = rank_value(rank_in[blk], r_max);
+        fresh = true;
+      }
+      request(blk, r, 32 * ti);
+    }
+    // ---- signs of Phi r_x: register v of block ib is output 32 ib + 8 (v / 4) + 4 hf + v % 4 ----
+    uint32_t word[4];
+    EOQ_SFOR(ib, 4,
+      float16v pr;
+      EOQ_SFOR(v, 16, pr[v] = 0.0f;);
+      EOQ_SFOR(st, 8,
+        H8 f;
+        f.u = Fop[(ib * 8 + st) * 64 + lane];
+        pr = mfma16(f, rh[st], pr);
+        pr = mfma16(f, rl[st], pr);
+      );
+      uint32_t m = 0u;   // bit v: sign bit of register v
+      EOQ_SFOR(k, 16, m = __builtin_amdgcn_alignbit(m, __float_as_uint(pr[15 - k]), 31););
+      m = (m | (m << 8)) & 0x00FF00FFu;
+      m = ((m | (m << 4)) & 0x0F0F0F0Fu) ^ 0x0F0F0F0Fu;      // a set bit stands for >= 0
+      m <<= 4 * hf;
+      word[ib] = m | (uint32_t)__shfl_xor((int)m, 32, 64);
+    );
+    *reinterpret_cast<u32x2*>(qsigns + row * (D / 8) + 8 * hf) = hf ? (u32x2){word[2], word[3]} : (u32x2){word[0], word[1]};
   }
 }
 
@@ -1021,10 +1029,13 @@ hipError_t eoq_launch_decode(const EoqLaunch& L, eoq_packed in, int64_t B, void*
 }
 
 hipError_t eoq_launch_qjl(const EoqLaunch& L, const void* blocks_fp16, int64_t B, eoq_packed rec, eoq_qjl out) {
-  const dim3 grid((unsigned)B), block(THREADS);
+  // one workgroup per compute unit, every wave a contiguous range of tiles
+  const int64_t tiles = B * (L.n / 32);
+  const int64_t per_wave = (tiles + 256 * QWAVES - 1) / (256 * QWAVES);
+  const dim3 grid((unsigned)((tiles + per_wave * QWAVES - 1) / (per_wave * QWAVES))), block(64 * QWAVES);
   const uint16_t* src = static_cast<const uint16_t*>(blocks_fp16);
 #define EOQ_QJL(BITS)                                                                                              \
-  hipLaunchKernelGGL(eoq_qjl_kernel<BITS>, grid, block, 0, L.stream, src, L.n, L.r_max, L.pih, L.phih, L.tab,      \
+  hipLaunchKernelGGL(eoq_qjl_kernel<BITS>, grid, block, 0, L.stream, src, L.n, L.r_max, tiles, per_wave, L.pih, L.phih, L.tab, \
                      rec.codes, rec.norms, rec.rank, rec.lfac, rec.rfac, out.signs, out.norms)
   switch (L.bits) {
     case 1: EOQ_QJL(1); break;
