@@ -11,141 +11,147 @@ using namespace eoqdev;
 constexpr int D = EOQ_D;
 
 // ---------------------------------------------------------------------------
-// encode kernel: 64 rows of one block per workgroup.
+// encode kernel for float32 blocks: 64 rows of one block per workgroup, float32 arithmetic throughout.
+//   rows in LDS -> C = S W^T rounded to the stored binary16 -> R = S - C V^T, its norm and u in registers -> u in LDS
+//   -> z = u Pi^T with v_mfma_f32_32x32x2_f32, wave w the coordinates 32 w .. 32 w + 31 with its columns of Pi in 64
+//   registers -> comparison masks = packed bit-planes.
+// Operands of v_mfma_f32_32x32x2_f32 (wave64): lane l supplies A[row = l%32][k = l/32] and B[k = l/32][col = l%32] and
+// receives D[row = 8*(v/4) + 4*(l/32) + v%4][col = l%32] in register v.  The contraction index is permuted so that a lane's
+// entries of four consecutive instructions are four consecutive floats.
+// Float32 products run at twice the vector rate on the matrix cores, and the rotation no longer takes 64 KB of LDS and
+// twelve LDS reads per 32 multiply-adds, which left one workgroup per compute unit: 125 blocks of 512 rows 119 -> 39 us.
 // ---------------------------------------------------------------------------
 constexpr int ENC_ROWS = 64;
 constexpr int ENC_THREADS = 256;
-constexpr int LDS_X = D + 1;
+constexpr int LDS_X = D + 4;                 // row stride in floats: 16-byte reads of 32 rows hit every bank alike
+constexpr int LDS_C = EOQ_RMAX_CAP + 1;
+typedef float float16v __attribute__((ext_vector_type(16)));
 
-__global__ __launch_bounds__(ENC_THREADS) void eoq_encode_kernel(
-    const void* __restrict__ blocks, EoqBlockMap map, int64_t b0, int dtype, int n, int bits, int r_max,
-    const float* __restrict__ pit,
+template <int BITS>
+__global__ __launch_bounds__(ENC_THREADS, 2) void eoq_encode_kernel(
+    const float* __restrict__ blocks, EoqBlockMap map, int64_t b0, int n, int r_max, const float* __restrict__ pi,
     const float* __restrict__ tab, const float* __restrict__ wfac, const int32_t* __restrict__ rank_in,
     const uint16_t* __restrict__ rfac, uint16_t* __restrict__ lfac, uint16_t* __restrict__ norms,
     uint8_t* __restrict__ codes) {
-  __shared__ float X[ENC_ROWS * LDS_X];            // rows of S, then R, then sqrt(d) u
-  __shared__ float PT[D * D];                      // Pi^T: PT[j*D + c] = Pi[c][j]
-  __shared__ float Wl[EOQ_RMAX_CAP * D];           // V diag(phi/sigma), later reused for the code bytes
-  __shared__ float Vl[EOQ_RMAX_CAP * D];           // stored binary16 right factors as float
-  __shared__ float Cl[ENC_ROWS * (EOQ_RMAX_CAP + 1)];
-  __shared__ float rho_s[ENC_ROWS];
+  __shared__ __align__(16) float X[ENC_ROWS * LDS_X];      // rows of S, then sqrt(d) u
+  __shared__ __align__(16) float Wl[EOQ_RMAX_CAP * D];     // V diag(phi/sigma)
+  __shared__ float Cl[ENC_ROWS * LDS_C];
+  constexpr int ROWB = BITS * D / 8;
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, hf = lane >> 5;
   const size_t blk = (size_t)b0 + blockIdx.y;
   const size_t slot = map.slot(blk);
   const int row0 = blockIdx.x * ENC_ROWS;
   const int r = rank_in[slot];
 
-  // stage the strip, the rotation and the factors
-  for (int g = tid; g < ENC_ROWS * D / 8; g += ENC_THREADS) {
-    const int e = g * 8;
-    float v[8];
-    const int t = e >> 7, j = e & (D - 1);
-    load8(blocks, dtype, map.in_base(blk) + (size_t)(row0 + t) * (size_t)map.token_stride + j, v);
+  // rows and factors; then the wave's columns of the rotation, which are needed last
+  {
+    const float* src = blocks + map.in_base(blk) + (size_t)(row0 + (tid >> 5)) * (size_t)map.token_stride + 4 * (tid & 31);
+    float4 x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) X[t * LDS_X + j + i] = v[i];
+    for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const float4*>(src + (size_t)(8 * k) * (size_t)map.token_stride);
+    for (int e = tid; e < r * (D / 4); e += ENC_THREADS)
+      reinterpret_cast<float4*>(Wl)[e] = reinterpret_cast<const float4*>(wfac + blk * r_max * D)[e];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) *reinterpret_cast<float4*>(X + (8 * k + (tid >> 5)) * LDS_X + 4 * (tid & 31)) = x[k];
   }
-  for (int e = tid; e < D * D / 4; e += ENC_THREADS)
-    reinterpret_cast<float4*>(PT)[e] = reinterpret_cast<const float4*>(pit)[e];
-  for (int e = tid; e < r * D; e += ENC_THREADS) {
-    Wl[e] = wfac[blk * r_max * D + e];
-    Vl[e] = half_bits_to_float(rfac[slot * r_max * D + e]);
-  }
+  float4 P[16];
+#pragma unroll
+  for (int m = 0; m < 16; ++m) P[m] = *reinterpret_cast<const float4*>(pi + (32 * wave + l32) * D + 8 * m + 4 * hf);
+  Bounds<BITS> bnd;
+  bnd.load(tab + 16);
   __syncthreads();
 
   // C = S W^T (= U diag(phi)), rounded to the stored binary16 (Alg. 2 Return, Alg. 3 Store)
-  {
-    const int t = tid & (ENC_ROWS - 1);
-    for (int i = tid >> 6; i < r; i += ENC_THREADS / ENC_ROWS) {
-      float acc = 0.0f;
-      for (int j = 0; j < D; ++j) acc = fmaf(X[t * LDS_X + j], Wl[i * D + j], acc);
-      const uint16_t hb = float_to_half_bits(acc);
-      lfac[(slot * r_max + i) * (size_t)n + row0 + t] = hb;
-      Cl[t * (EOQ_RMAX_CAP + 1) + i] = half_bits_to_float(hb);
+  for (int i = wave; i < r; i += 4) {
+    float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll 4
+    for (int j = 0; j < D; j += 4) {
+      const float4 x = *reinterpret_cast<const float4*>(X + lane * LDS_X + j), w = *reinterpret_cast<const float4*>(Wl + i * D + j);
+      s0 = fmaf(x.x, w.x, s0);
+      s1 = fmaf(x.y, w.y, s1);
+      s0 = fmaf(x.z, w.z, s0);
+      s1 = fmaf(x.w, w.w, s1);
     }
+    const uint16_t hb = float_to_half_bits(s0 + s1);
+    lfac[(slot * r_max + i) * (size_t)n + row0 + lane] = hb;
+    Cl[lane * LDS_C + i] = half_bits_to_float(hb);
   }
   __syncthreads();
 
-  const int tr = tid >> 5, tc = tid & 31;  // rows tr*8 .. tr*8+7, columns tc + 32*m
-  // R = S - C V^T (Alg. 3; the whole block when r = 0)
-  if (r > 0) {
+  // R = S - C V^T (Alg. 3; the whole block when r = 0), rho_t = |R_t|, sqrt(d) u_t = sqrt(d) R_t / rho_t (Alg. 1 line 3):
+  // a half wave takes eight rows, a lane the columns 4 l32 .. + 3 of them
+  {
+    const int tr = tid >> 5;
+    float4 x[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) x[a] = *reinterpret_cast<const float4*>(X + (8 * tr + a) * LDS_X + 4 * l32);
+    const uint16_t* vrow = rfac + slot * r_max * D + 4 * l32;
+#pragma unroll 2
+    for (int i = 0; i < r; ++i) {
+      const uint2 h = *reinterpret_cast<const uint2*>(vrow + i * D);
+      const float v0 = half_bits_to_float((uint16_t)(h.x & 0xFFFFu)), v1 = half_bits_to_float((uint16_t)(h.x >> 16));
+      const float v2 = half_bits_to_float((uint16_t)(h.y & 0xFFFFu)), v3 = half_bits_to_float((uint16_t)(h.y >> 16));
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        const float c = Cl[(8 * tr + a) * LDS_C + i];
+        x[a].x = fmaf(-c, v0, x[a].x);
+        x[a].y = fmaf(-c, v1, x[a].y);
+        x[a].z = fmaf(-c, v2, x[a].z);
+        x[a].w = fmaf(-c, v3, x[a].w);
+      }
+    }
+#pragma unroll
     for (int a = 0; a < 8; ++a) {
-      const int t = tr * 8 + a;
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int i = 0; i < r; ++i) {
-        const float c = Cl[t * (EOQ_RMAX_CAP + 1) + i];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) acc[m] = fmaf(c, Vl[i * D + tc + 32 * m], acc[m]);
-      }
-#pragma unroll
-      for (int m = 0; m < 4; ++m) X[t * LDS_X + tc + 32 * m] -= acc[m];
+      float ss = fmaf(x[a].x, x[a].x, fmaf(x[a].y, x[a].y, fmaf(x[a].z, x[a].z, x[a].w * x[a].w)));
+      ss += dpp_mov<0xB1>(ss);
+      ss += dpp_mov<0x4E>(ss);
+      ss += dpp_mov<0x141>(ss);
+      ss += dpp_mov<0x140>(ss);
+      ss += __shfl_xor(ss, 16, 64);
+      const float rho = sqrtf(ss);
+      const float sc = (rho > 0.0f) ? sqrtf((float)D) / rho : 0.0f;
+      if (l32 == 0) norms[slot * (size_t)n + row0 + 8 * tr + a] = float_to_half_bits(rho);
+      *reinterpret_cast<float4*>(X + (8 * tr + a) * LDS_X + 4 * l32) = make_float4(x[a].x * sc, x[a].y * sc, x[a].z * sc, x[a].w * sc);
     }
   }
   __syncthreads();
 
-  // rho_t = |R_t|, u = R_t / rho_t (Alg. 1 line 3); rows are rescaled to sqrt(d) u
-  {
-    const int t = tid >> 2, q = tid & 3;
-    float ss = 0.0f;
-    for (int m = 0; m < D / 4; ++m) {
-      const float x = X[t * LDS_X + q + 4 * m];
-      ss = fmaf(x, x, ss);
+  // z = Pi u (Alg. 1 line 4) and index of the nearest centroid (line 5): two tiles of 32 rows
+  float16v acc[2];
+  EOQ_SFOR(t, 2, EOQ_SFOR(v, 16, acc[t][v] = 0.0f;););
+  EOQ_SFOR(m, 16,
+    const float4 u0 = *reinterpret_cast<const float4*>(X + l32 * LDS_X + 8 * m + 4 * hf);
+    const float4 u1 = *reinterpret_cast<const float4*>(X + (32 + l32) * LDS_X + 8 * m + 4 * hf);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.x, P[m].x, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.x, P[m].x, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.y, P[m].y, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.y, P[m].y, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.z, P[m].z, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.z, P[m].z, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.w, P[m].w, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.w, P[m].w, acc[1], 0, 0, 0);
+  );
+  // every comparison mask holds one bit-plane of coordinates 32 w .. 32 w + 31 for the rows 8 q + e (low word) and
+  // 8 q + 4 + e (high word)
+  EOQ_SFOR(t, 2,
+    uint32_t outw[BITS];
+    EOQ_SFOR(p, BITS, outw[p] = 0u;);
+    EOQ_SFOR(v, 16,
+      unsigned long long m[BITS];
+      bnd.masks(acc[t][v], m);
+      constexpr int row_lo = 8 * (v >> 2) + (v & 3);
+      EOQ_SFOR(p, BITS,
+        outw[p] = write_lane<row_lo>(outw[p], (uint32_t)m[p]);
+        outw[p] = write_lane<row_lo + 4>(outw[p], (uint32_t)(m[p] >> 32));
+      );
+    );
+    if (lane < 32) {
+      uint8_t* dst = codes + (slot * (size_t)n + row0 + 32 * t + lane) * ROWB + 4 * wave;
+      EOQ_SFOR(p, BITS, *reinterpret_cast<uint32_t*>(dst + 16 * p) = outw[p];);
     }
-    ss = quad_sum(ss);
-    const float rho = sqrtf(ss);
-    const float sc = (rho > 0.0f) ? sqrtf((float)D) / rho : 0.0f;
-    for (int m = 0; m < D / 4; ++m) X[t * LDS_X + q + 4 * m] *= sc;
-    if (q == 0) norms[slot * (size_t)n + row0 + t] = float_to_half_bits(rho);
-  }
-  __syncthreads();
-
-  // z = Pi u (Alg. 1 line 4) and index of the nearest centroid (line 5)
-  uint8_t* code_s = reinterpret_cast<uint8_t*>(Wl);  // [64][128] bytes
-  {
-    float acc[8][4];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) acc[a][m] = 0.0f;
-    for (int j = 0; j < D; ++j) {
-      float p[4], u[8];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) p[m] = PT[j * D + tc + 32 * m];
-#pragma unroll
-      for (int a = 0; a < 8; ++a) u[a] = X[(tr * 8 + a) * LDS_X + j];
-#pragma unroll
-      for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) acc[a][m] = fmaf(u[a], p[m], acc[a][m]);
-    }
-    const int nb = (1 << bits) - 1;
-    float bnd[15];
-#pragma unroll
-    for (int i = 0; i < 15; ++i) bnd[i] = tab[16 + i];  // +inf beyond the last boundary
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        int code = 0;
-#pragma unroll
-        for (int i = 0; i < 15; ++i) code += (i < nb && bnd[i] <= acc[a][m]) ? 1 : 0;
-        code_s[(tr * 8 + a) * D + tc + 32 * m] = (uint8_t)code;
-      }
-  }
-  __syncthreads();
-
-  // bit-plane packing: lane handles 32 coordinates of one row
-  {
-    const int t = tid >> 2, q = tid & 3;
-    uint32_t plane[4] = {0u, 0u, 0u, 0u};
-    for (int j = 0; j < 32; ++j) {
-      const uint32_t c = code_s[t * D + q * 32 + j];
-#pragma unroll
-      for (int p = 0; p < 4; ++p) plane[p] |= ((c >> p) & 1u) << j;
-    }
-    uint32_t* dst = reinterpret_cast<uint32_t*>(codes + (slot * (size_t)n + row0 + t) * (size_t)(bits * D / 8));
-    for (int p = 0; p < bits; ++p) dst[p * 4 + q] = plane[p];
-  }
+  );
 }
 
 }  // namespace
@@ -164,9 +170,17 @@ hipError_t eoq_launch_encode(const EoqLaunch& L, const void* blocks, int dtype, 
   // gridDim.y is limited to 65535: split long batches
   for (int64_t b0 = 0; b0 < B; b0 += 32768) {
     const int64_t nb = (B - b0 < 32768) ? B - b0 : 32768;
-    hipLaunchKernelGGL(eoq_encode_kernel, dim3(L.n / ENC_ROWS, (unsigned)nb), dim3(ENC_THREADS), 0, L.stream, blocks,
-                       L.map, b0, dtype, L.n, L.bits, L.r_max, L.pit, L.tab, wfac, out.rank, out.rfac, out.lfac,
-                       out.norms, out.codes);
+#define EOQ_ENCODE(BITS)                                                                                               \
+  hipLaunchKernelGGL(eoq_encode_kernel<BITS>, dim3(L.n / ENC_ROWS, (unsigned)nb), dim3(ENC_THREADS), 0, L.stream,     \
+                     static_cast<const float*>(blocks), L.map, b0, L.n, L.r_max, L.pi, L.tab, wfac, out.rank,          \
+                     out.rfac, out.lfac, out.norms, out.codes)
+    switch (L.bits) {
+      case 1: EOQ_ENCODE(1); break;
+      case 2: EOQ_ENCODE(2); break;
+      case 3: EOQ_ENCODE(3); break;
+      default: EOQ_ENCODE(4); break;
+    }
+#undef EOQ_ENCODE
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -159,4 +159,50 @@ __device__ __forceinline__ uint32_t write_lane(uint32_t old, uint32_t val) {
   return eoq_llvm_writelane(val, LANE, old);
 }
 
+// Decision boundaries of the codebook as separate values, not an array or a vector: the compiler turns a select between
+// two elements into an element at a selected index (scratch memory for an array, a chain of sixteen selects for a
+// register vector).
+template <int BITS>
+struct Bounds {
+  float b0, b1, b2, b3, b4, b5, b6, b7, b8, b9, b10, b11, b12, b13, b14;
+  __device__ __forceinline__ void load(const float* __restrict__ bnd) {
+    constexpr int N = (1 << BITS) - 1;
+    b0 = bnd[0];
+    b1 = 1 < N ? bnd[1] : 0.0f; b2 = 2 < N ? bnd[2] : 0.0f;
+    b3 = 3 < N ? bnd[3] : 0.0f; b4 = 4 < N ? bnd[4] : 0.0f; b5 = 5 < N ? bnd[5] : 0.0f; b6 = 6 < N ? bnd[6] : 0.0f;
+    b7 = 7 < N ? bnd[7] : 0.0f; b8 = 8 < N ? bnd[8] : 0.0f; b9 = 9 < N ? bnd[9] : 0.0f; b10 = 10 < N ? bnd[10] : 0.0f;
+    b11 = 11 < N ? bnd[11] : 0.0f; b12 = 12 < N ? bnd[12] : 0.0f; b13 = 13 < N ? bnd[13] : 0.0f; b14 = 14 < N ? bnd[14] : 0.0f;
+  }
+  // index = number of boundaries <= z, found from the top bit down; m[p] is bit p of the lanes' indices.  The candidates
+  // of the later levels are selected by the earlier decisions as soon as those are known, so the last comparison waits
+  // for one select only.
+  __device__ __forceinline__ void masks(float z, unsigned long long (&m)[BITS]) const {
+    if constexpr (BITS == 1) {
+      m[0] = __ballot(z >= b0);
+    } else if constexpr (BITS == 2) {
+      const bool t1 = z >= b1;
+      m[1] = __ballot(t1);
+      m[0] = __ballot(z >= (t1 ? b2 : b0));
+    } else if constexpr (BITS == 3) {
+      const bool t2 = z >= b3;
+      m[2] = __ballot(t2);
+      const float lo0 = t2 ? b4 : b0, lo1 = t2 ? b6 : b2;
+      const bool t1 = z >= (t2 ? b5 : b1);
+      m[1] = __ballot(t1);
+      m[0] = __ballot(z >= (t1 ? lo1 : lo0));
+    } else {
+      const bool t3 = z >= b7;
+      m[3] = __ballot(t3);
+      const float q0 = t3 ? b8 : b0, q1 = t3 ? b10 : b2, q2 = t3 ? b12 : b4, q3 = t3 ? b14 : b6;
+      const float h0 = t3 ? b9 : b1, h1 = t3 ? b13 : b5;
+      const bool t2 = z >= (t3 ? b11 : b3);
+      m[2] = __ballot(t2);
+      const float lo0 = t2 ? q2 : q0, lo1 = t2 ? q3 : q1;
+      const bool t1 = z >= (t2 ? h1 : h0);
+      m[1] = __ballot(t1);
+      m[0] = __ballot(z >= (t1 ? lo1 : lo0));
+    }
+  }
+};
+
 }  // namespace eoqdev

@@ -796,13 +796,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
       if constexpr (ROT_LO) Blo[kk].u = *reinterpret_cast<const uint4*>(pih + D * D + c * D + 16 * kk + 8 * hf);
     }
   }
-  // the decision boundaries as separate values, not an array or a vector: the compiler turns a select between two
-  // elements into an element at a selected index (scratch memory for an array, a chain of sixteen selects for a
-  // register vector)
-#define EOQ_BND(i) const float bnd##i = ((i) < (1 << BITS) - 1) ? tab[16 + (i)] : 0.0f
-  EOQ_BND(0); EOQ_BND(1); EOQ_BND(2); EOQ_BND(3); EOQ_BND(4); EOQ_BND(5); EOQ_BND(6); EOQ_BND(7);
-  EOQ_BND(8); EOQ_BND(9); EOQ_BND(10); EOQ_BND(11); EOQ_BND(12); EOQ_BND(13); EOQ_BND(14);
-#undef EOQ_BND
+  Bounds<BITS> bnd;
+  bnd.load(tab + 16);
 
   // factors of the block: W = V diag(phi/sigma) split into hi + lo, and V16^T.  Only the rows below the rank
   // rounded up to a multiple of 8 are ever multiplied with something that is not forced to zero (see Cneg)
@@ -949,33 +944,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
       EOQ_SFOR(v, 16,
         const float z = acc[v];
         unsigned long long m[BITS];
-        if constexpr (BITS == 1) {
-          m[0] = __ballot(z >= bnd0);
-        } else if constexpr (BITS == 2) {
-          const bool b1 = z >= bnd1;
-          m[1] = __ballot(b1);
-          m[0] = __ballot(z >= (b1 ? bnd2 : bnd0));
-        } else if constexpr (BITS == 3) {
-          // the candidates of the later levels are selected by the earlier decisions as soon as those are known, so
-          // the last comparison waits for one select only
-          const bool b2 = z >= bnd3;
-          m[2] = __ballot(b2);
-          const float lo0 = b2 ? bnd4 : bnd0, lo1 = b2 ? bnd6 : bnd2;
-          const bool b1 = z >= (b2 ? bnd5 : bnd1);
-          m[1] = __ballot(b1);
-          m[0] = __ballot(z >= (b1 ? lo1 : lo0));
-        } else {
-          const bool b3 = z >= bnd7;
-          m[3] = __ballot(b3);
-          const float q0 = b3 ? bnd8 : bnd0, q1 = b3 ? bnd10 : bnd2, q2 = b3 ? bnd12 : bnd4, q3 = b3 ? bnd14 : bnd6;
-          const float h0 = b3 ? bnd9 : bnd1, h1 = b3 ? bnd13 : bnd5;
-          const bool b2 = z >= (b3 ? bnd11 : bnd3);
-          m[2] = __ballot(b2);
-          const float lo0 = b2 ? q2 : q0, lo1 = b2 ? q3 : q1;
-          const bool b1 = z >= (b2 ? h1 : h0);
-          m[1] = __ballot(b1);
-          m[0] = __ballot(z >= (b1 ? lo1 : lo0));
-        }
+        bnd.masks(z, m);
         constexpr int row_lo = 8 * (v >> 2) + (v & 3);   // token of the low word; the high word is row_lo + 4
         EOQ_SFOR(p, BITS,
           outw[p] = write_lane<row_lo>(outw[p], (uint32_t)m[p]);
