@@ -347,11 +347,10 @@ eoq_status compress_impl(eoq_ctx* ctx, const void* blocks, eoq_dtype dtype, int6
   double* lam = static_cast<double*>(workspace);
   char* ws = static_cast<char*>(workspace);
   float* wfac = reinterpret_cast<float*>(ws + eoq_ws_lam_bytes(B));
-  int* fb_count = reinterpret_cast<int*>(ws + eoq_ws_lam_bytes(B) + eoq_ws_wfac_bytes(B, ctx->r_max));
-  int* fb_list = fb_count + 4;
-  const uintptr_t tri_at = reinterpret_cast<uintptr_t>(reinterpret_cast<char*>(fb_count) + eoq_ws_list_bytes(B));
+  int* marks = reinterpret_cast<int*>(ws + eoq_ws_lam_bytes(B) + eoq_ws_wfac_bytes(B, ctx->r_max)) + 4;
+  const uintptr_t tri_at = reinterpret_cast<uintptr_t>(reinterpret_cast<char*>(marks - 4) + eoq_ws_list_bytes(B));
   double* tri = reinterpret_cast<double*>((tri_at + 63) & ~(uintptr_t)63);
-  hipError_t e = eoq_launch_spectral(L, blocks, (int)dtype, B, lam, wfac, fb_count, fb_list, tri, out);
+  hipError_t e = eoq_launch_spectral(L, blocks, (int)dtype, B, lam, wfac, marks, tri, out);
   if (fq) {
     if (L.ev && e == hipSuccess) (void)hipEventRecord(L.ev[2], L.stream);  // the factor stage counts as encode time
     if (e == hipSuccess) e = eoq_launch_factor_quant(L, blocks, B, wfac, out, *fq, ctx->gauss16);

@@ -163,11 +163,11 @@ constexpr int LDA = D + 1;  // padded column stride of the LDS-resident matrix
 constexpr int MAX_SWEEPS = 30;
 constexpr double JACOBI_TOL = 5e-14;  // a pair is orthogonal when |<a_p,a_q>| <= tol |a_p||a_q|
 
-// With `list` non-null the workgroups walk the block numbers list[0 .. *count) (grid-stride); otherwise
-// workgroup b handles block b.
+// With `marks` non-null the workgroups share the batch (a contiguous range each) and solve the blocks whose mark is set;
+// otherwise workgroup b handles block b.
 __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
     const void* __restrict__ blocks, EoqBlockMap map, int dtype, int n, int k, double rank_thr, int r_max, int loss, int64_t B,
-    const int* __restrict__ list, const int* __restrict__ count, double* __restrict__ lam_out,
+    const int* __restrict__ marks, double* __restrict__ lam_out,
     float* __restrict__ wfac, int32_t* __restrict__ rank_out, float* __restrict__ phi_out,
     float* __restrict__ sigma_out, uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
   __shared__ double A[D * LDA];            // column s of the working matrix at A[s*LDA ...]
@@ -180,9 +180,15 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
   __shared__ unsigned flag_s;
 
   const int tid = threadIdx.x;
-  const int64_t total = list ? (int64_t)*count : B;
-  for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-    const size_t blk = list ? (size_t)list[item] : (size_t)item;
+  const int64_t share = (B + gridDim.x - 1) / gridDim.x;
+  const int64_t first = blockIdx.x * share, last = (first + share < B) ? first + share : B;
+  for (int64_t item = first; item < last; ++item) {
+    if (marks && ((item - first) & (THREADS - 1)) == 0) {   // uniform; the usual case: nothing marked in the next 256
+      while (item < last && !__syncthreads_or(item + tid < last ? marks[item + tid] : 0)) item += THREADS;
+      if (item >= last) break;
+    }
+    if (marks && !marks[item]) continue;
+    const size_t blk = (size_t)item;
     const size_t slot = map.slot(blk);
     __syncthreads();
     if (tid == 0) flag_s = 0u;
@@ -998,7 +1004,7 @@ __device__ __forceinline__ void reflector_product(int q, const float* refl, doub
 
 __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     const void* __restrict__ blocks, EoqBlockMap map, int dtype, int n, int k_pilot, double rank_thr, int r_max, int loss,
-    int* __restrict__ fb_list, int* __restrict__ fb_count, double* __restrict__ lam_out, float* __restrict__ wfac,
+    int* __restrict__ marks, double* __restrict__ lam_out, float* __restrict__ wfac,
     double* __restrict__ tri, int32_t* __restrict__ rank_out, float* __restrict__ phi_out, float* __restrict__ sigma_out,
     uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
   // one pool, used in turn by the Gram stage (byte planes / float strip), the reduction (reflectors) and the
@@ -1261,8 +1267,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     if (lam_s[i] - lam_s[i + 1] <= CLUSTER_TOL * lam_s[0]) repeated = true;
   if (repeated) {
     if (tid == 0) {
-      const int fb_slot = atomicAdd(fb_count, 1);
-      fb_list[fb_slot] = (int)blk;
+      marks[blk] = 1;
       rank_out[slot] = r;
       flags_out[slot] = flag_s;
     }
@@ -1378,13 +1383,10 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     }
   }
   if (tid == 0) {
+    marks[blk] = 0;
     rank_out[slot] = r;
     flags_out[slot] = flag_s;
   }
-}
-
-__global__ void eoq_zero_counter_kernel(int* counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
 }
 
 }  // namespace
@@ -1393,20 +1395,19 @@ __global__ void eoq_zero_counter_kernel(int* counter) {
 // launcher
 // ---------------------------------------------------------------------------------------------
 hipError_t eoq_launch_spectral(const EoqLaunch& L, const void* blocks, int dtype, int64_t B, double* lam,
-                               float* wfac, int* fb_count, int* fb_list, double* tri, eoq_packed out) {
+                               float* wfac, int* marks, double* tri, eoq_packed out) {
   if (L.ev) (void)hipEventRecord(L.ev[0], L.stream);
   if (L.solver == 1) {
     hipLaunchKernelGGL(eoq_spectral_jacobi_kernel, dim3((unsigned)B), dim3(THREADS), 0, L.stream, blocks, L.map, dtype, L.n,
-                       L.k, L.rank_thr, L.r_max, L.loss, B, (const int*)nullptr, (const int*)nullptr, lam, wfac, out.rank,
+                       L.k, L.rank_thr, L.r_max, L.loss, B, (const int*)nullptr, lam, wfac, out.rank,
                        out.phi, out.sigma, out.rfac, out.flags);
   } else {
-    hipLaunchKernelGGL(eoq_zero_counter_kernel, dim3(1), dim3(64), 0, L.stream, fb_count);
     hipLaunchKernelGGL(eoq_spectral_tridiag_kernel, dim3((unsigned)B), dim3(THREADS), 0, L.stream, blocks, L.map, dtype, L.n,
-                       L.k, L.rank_thr, L.r_max, L.loss, fb_list, fb_count, lam, wfac, tri, out.rank, out.phi, out.sigma, out.rfac,
+                       L.k, L.rank_thr, L.r_max, L.loss, marks, lam, wfac, tri, out.rank, out.phi, out.sigma, out.rfac,
                        out.flags);
     const unsigned grid = (unsigned)((B < 256) ? B : 256);
     hipLaunchKernelGGL(eoq_spectral_jacobi_kernel, dim3(grid), dim3(THREADS), 0, L.stream, blocks, L.map, dtype, L.n, L.k,
-                       L.rank_thr, L.r_max, L.loss, B, (const int*)fb_list, (const int*)fb_count, lam, wfac, out.rank, out.phi,
+                       L.rank_thr, L.r_max, L.loss, B, (const int*)marks, lam, wfac, out.rank, out.phi,
                        out.sigma, out.rfac, out.flags);
   }
   if (L.ev) (void)hipEventRecord(L.ev[1], L.stream);
