@@ -1102,13 +1102,28 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       de[tid] = t;
       tri_blk[tid] = t;
     }
-    __threadfence();
+    // The stores are in the L2 of this XCD once they are acknowledged, and that is where a miss of the scalar cache is
+    // served from: waiting for them is enough.  (A fence at device scope also writes back what the whole L2 holds
+    // modified: 35 K of a block's 475 K cycles with every compute unit at it.)
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     __syncthreads();
     // the copy in global memory, addressed through the scalar unit; the address passes through an opaque
     // register move placed after the barrier so that none of these loads can be scheduled before the stores
     unsigned long long tri_addr = reinterpret_cast<unsigned long long>(tri_blk);
     asm volatile("" : "+s"(tri_addr) : : "memory");
     sc_double* sde = reinterpret_cast<sc_double*>(tri_addr);
+    {
+      // one word of every line first, all of them in flight together: the count below requests its operands two groups
+      // ahead only and would otherwise wait for 32 misses of the scalar cache one after the other (35 K of a block's 475 K
+      // cycles with every compute unit at it)
+      typedef __attribute__((address_space(4))) const int sc_int;
+      sc_int* line = reinterpret_cast<sc_int*>(tri_addr);
+      int touch[2 * D * 8 / 64];
+#pragma unroll
+      for (int q = 0; q < 2 * D * 8 / 64; ++q) touch[q] = line[16 * q];
+#pragma unroll
+      for (int q = 0; q < 2 * D * 8 / 64; ++q) asm volatile("" : : "s"(touch[q]));
+    }
     const int j = tid >> 1, sub = tid & 1;
     double lo = -0x1.0p-40, hi = 1.0 + 0x1.0p-40;   // G is positive semi-definite; Gershgorin bounds the top by 1
     // What is known about the two ends: the count there (c_lo <= j < c_hi always: every update below follows the
