@@ -309,8 +309,8 @@ constexpr int XPAD = 17;  // row stride of a 16 x 16 exchange plane: transposed 
 constexpr int PAIR_A[28] = {0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 2, 2, 2, 2, 2, 3, 3, 3, 3, 4, 4, 4, 5, 5, 6};
 constexpr int PAIR_B[28] = {1, 2, 3, 4, 5, 6, 7, 2, 3, 4, 5, 6, 7, 3, 4, 5, 6, 7, 4, 5, 6, 7, 5, 6, 7, 6, 7, 7};
 
-// packed reflector storage: reflector k has entries i = k+1 .. 127
-__device__ __forceinline__ int refl_off(int k) { return k * (D - 1) - (k * (k - 1)) / 2; }
+// packed reflector storage: reflector k has entries i = k+1 .. 127 (24-bit products: full rate)
+__device__ __forceinline__ int refl_off(int k) { return (int)(__umul24(k, D - 1) - (__umul24(k, k - 1) >> 1)); }
 constexpr int REFL_LEN = (D - 1) * D / 2;  // 8128
 constexpr int GRID_POINTS = 256;           // first localisation: one Sturm count per lane on a grid (cubically spaced)
 constexpr int MULTISECT_ITERS = 17;        // then two lanes per eigenvalue down to the width of 17 trisections of a uniform
@@ -320,15 +320,18 @@ constexpr int REFINE_COUNT = 32;           // at most this many eigenvalues go o
 constexpr int REFINE_KEEP = 48;            // brackets of the largest eigenvalues kept for that second phase
 static_assert(REFINE_COUNT * 8 == THREADS && REFINE_COUNT >= EOQ_RMAX_CAP && 2 * REFINE_KEEP <= D, "second phase layout");
 constexpr int EV_BATCH = 8;                // eigenvectors per twisted-factorisation pass
-// Twisted-factorisation scratch: per eigenvector of a batch two arrays of D pairs, F then Bk.  The arrays are D + 1
-// pairs apart: lanes that walk different arrays in step (one per array, same row) then fall into different banks;
-// at a stride of D pairs = 2048 bytes all sixteen would hit the same ones.
+// Twisted-factorisation scratch: per eigenvector of a batch two arrays of D doubles, F then Bk.  The arrays are D + 1
+// doubles apart: lanes that walk different arrays in step (one per array, same row) then fall into different banks;
+// at a stride of D doubles = 1024 bytes all sixteen would hit the same ones.
 constexpr int TW_STRIDE = D + 1;
-constexpr int U1_BYTES = EV_BATCH * 2 * TW_STRIDE * 16;  // 33 KB; also the Gram strip (16 KB)
+constexpr int TW_BYTES = EV_BATCH * 2 * TW_STRIDE * 8;   // 16.1 KB; also the exchange of the back-transformation
+constexpr int WY_BYTES = (D / 16) * 256 * 8;             // 16 KB: the triangular factor of every sixteen reflectors
+constexpr int U1_BYTES = TW_BYTES + WY_BYTES;            // also the Gram strip (16 KB)
+static_assert(TW_BYTES >= 2 * 4 * 256 * 8 && TW_BYTES >= (32 * 33 + 30 * 32) * 8 && U1_BYTES >= GRAM_STRIP * D * 4 && EV_BATCH <= 16, "u1 layout");
 constexpr double CLUSTER_TOL = 1e-10;      // relative gap below which retained eigenvalues count as repeated
 constexpr int REFL_SLACK = 16;             // floats in front of the reflectors (masked reads may reach them)
 constexpr int REFL_BYTES = (REFL_LEN + REFL_SLACK) * 4;   // 32576 (a multiple of 16)
-constexpr int POOL_BYTES = REFL_BYTES + U1_BYTES;
+constexpr int POOL_BYTES = REFL_BYTES + U1_BYTES > 65536 ? REFL_BYTES + U1_BYTES : 65536;   // the Gram planes fill 64 KB
 
 // G = S^T S in the cyclic layout.  Only the sub-tiles a <= b are accumulated (36 of 64 products per block row);
 // the others are mirrored from the lane that holds the transposed position, through LDS.
@@ -885,121 +888,126 @@ __device__ __forceinline__ int sturm_count(sc_double* de, double x, double* val 
   return cnt;
 }
 
-// Back-transformation through the reflectors 16 SG .. 16 SG + 15, four at a time, of the vector whose entries
-// i = l + 16 m this lane holds in y[m].  All sixteen reflectors vanish on the entries m < SG, are full on m > SG, and
-// reflector k starts inside m = SG (entries l > k % 16); so only that one entry needs a mask and the dead ones are
-// skipped.  `refl` has 16 floats of slack in front, which the masked reads of the first reflectors may touch.
-template <int SG>
-__device__ __forceinline__ void backtransform_stage(double (&y)[8], const float* refl, const double* betaT,
-                                                    const double* cW, int l) {
+// Back-transformation.  The sixteen reflectors k = 16 SG + i multiply to H_16SG .. H_16SG+15 = I - V T V^T, V = (v_16SG ..
+// v_16SG+15), T upper triangular with T_jj = beta_j and T_0..j-1,j = -beta_j T_0..j-1,0..j-1 (V^T v_j), so y <- y - V (T (V^T y))
+// for a batch of vectors y is a chain of products for v_mfma_f64_16x16x4_f64.  Its operands (wave64): lane l = 16 g + c
+// supplies A[row = c][k = g] and B[k = g][col = c] and receives D[row = 4 v + g][col = c] in register v: a result register v
+// is the B operand of the k-step that takes the rows 4 v .. 4 v + 3, nothing changes lanes.
+typedef double double4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ double4v mfma64(double a, double b, double4v c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// position of T_ik in the 16 x 16 array of a block: the sixteen lanes of an operand read touch different banks
+__device__ __forceinline__ int wy_pos(int i, int k) { return 16 * i + (k ^ i); }
+
+// The factors T of the reflector blocks sg0 and sg1 into their places of `wy` (256 doubles per block), by one wave: V^T V on
+// the matrix cores (an entry of V is A and B operand alike), then lane 16 q + i < 32 forms row i of block q.
+__device__ __forceinline__ void wy_factors(int sg0, int sg1, const float* refl, const double* betaT, double* wy, int lane) {
+  const int c = lane & 15, g = lane >> 4;
 #pragma unroll 1
-  for (int bl = 3; bl >= 0; --bl) {
-    const int bb = 4 * SG + bl;
-    double u[4][8], dt[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int k = 4 * bb + 3 - a;                           // k / 16 == SG
-      const float* rp = refl + refl_off(k) - (k + 1) + l;     // entry i at rp[i - l]
-      const bool head = (l > (k & 15)) && (SG < 7 || k < D - 2);  // reflectors 126, 127 do not exist
-      double acc = 0.0;
-#pragma unroll
-      for (int m = SG; m < 8; ++m) {
-        const float raw = rp[16 * m];
-        u[a][m] = (m == SG) ? (head ? (double)raw : 0.0) : (double)raw;
-        acc = fma(u[a][m], y[m], acc);
-      }
-      dt[a] = acc;
+  for (int q = 0; q < 2; ++q) {
+    const int sg = q ? sg1 : sg0, k = 16 * sg + c;
+    const float* rp = refl + refl_off(k) - (k + 1) + 16 * sg + g;   // entry 16 sg + g + i of reflector k at rp[i]
+    double4v w = {0.0, 0.0, 0.0, 0.0};
+    EOQ_SFOR(v, 4,
+      const double x = (4 * v + g > c && k < D - 2) ? (double)rp[4 * v] : 0.0;
+      w = mfma64(x, x, w);
+    );
+    for (int t = sg + 1; t < D / 16; ++t) {   // uniform
+      rp += 16;
+      EOQ_SFOR(v, 4,
+        const double x = (double)rp[4 * v];
+        w = mfma64(x, x, w);
+      );
     }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) dt[a] = row16_sum_uniform(dt[a]);
-    const double* c = cW + bb * 6;
-    const double f1 = betaT[4 * bb + 3] * dt[0];
-    const double f2 = betaT[4 * bb + 2] * fma(-c[0], f1, dt[1]);
-    const double f3 = betaT[4 * bb + 1] * fma(-c[2], f2, fma(-c[1], f1, dt[2]));
-    const double f4 = betaT[4 * bb] * fma(-c[5], f3, fma(-c[4], f2, fma(-c[3], f1, dt[3])));
-#pragma unroll
-    for (int m = SG; m < 8; ++m)
-      y[m] = fma(-f4, u[3][m], fma(-f3, u[2][m], fma(-f2, u[1][m], fma(-f1, u[0][m], y[m]))));
+    EOQ_SFOR(v, 4, wy[256 * sg + 16 * (4 * v + g) + c] = w[v];);
+  }
+  __builtin_amdgcn_wave_barrier();   // one wave: its LDS operations complete in order
+  if (lane < 32) {
+    const int sg = g ? sg1 : sg0;
+    double* W = wy + 256 * sg;
+    double row[16];
+    EOQ_SFOR(j, 16,
+      double sum = 0.0;
+      EOQ_SFOR(m, j, sum = fma(row[m], W[16 * m + j], sum););
+      const double beta = betaT[16 * sg + j];
+      row[j] = (j == c) ? beta : -beta * sum;   // columns left of the diagonal: sum is zero
+      if constexpr ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // not all 120 operands in registers at once
+    );
+    __builtin_amdgcn_wave_barrier();
+    EOQ_SFOR(j, 16, W[wy_pos(c, j)] = row[j];);
   }
 }
 
-// Minors of T - mu I by the three-term recurrence, from the top (UP = false: p_i, stored with p_{i-1}) or from the
-// bottom (UP = true: q_i, stored with q_{i+1}); de[i] = (d_i, e_{i-1}^2), de[D] = 0.  Eight steps per group, then
-// both running values are rescaled by a power of two (the ratios of consecutive minors are what is used).
+// Minors of T - mu I by the three-term recurrence, from the top (UP = false: p_i) or from the bottom (UP = true: q_i); the
+// operands d_i, e_{i-1}^2 come through the scalar cache, a group of four steps ahead.  After every eight steps both running
+// values are rescaled by a power of two, so that the last one lies in [1/2, 1): the first ratio p_i / p_{i-1} of the next
+// eight is to be taken with the mantissa of the stored p_{i-1}.
 template <bool UP>
-__device__ __forceinline__ void minors_sweep(const double2* de, double mu, double2* out) {
+__device__ __forceinline__ void minors_sweep(sc_double* de, double mu, double* out) {
   double pm = 0.0, p = 1.0;
-#pragma unroll 2
-  for (int s0 = 0; s0 < D; s0 += 8) {
-    double dmu[8], e2[8];
+  double d0[4], e0[4], d1[4], e1[4];
+  auto fetch = [&](int s0, double (&d)[4], double (&e)[4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
+    for (int s = 0; s < 4; ++s) {
       const int i = UP ? D - 1 - (s0 + s) : s0 + s;
-      dmu[s] = de[i].x - mu;
-      e2[s] = de[i + (UP ? 1 : 0)].y;  // e_{i-1}^2 going down, e_i^2 going up
+      d[s] = de[2 * i];
+      e[s] = de[UP ? 2 * min(i + 1, D - 1) + 1 : 2 * i + 1];   // e_{i-1}^2 going down, e_i^2 going up (times zero at the start)
     }
+  };
+  auto steps = [&](int s0, const double (&d)[4], const double (&e)[4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
+    for (int s = 0; s < 4; ++s) {
       const int i = UP ? D - 1 - (s0 + s) : s0 + s;
-      const double pn = fma(dmu[s], p, -(e2[s] * pm));
-      out[i] = make_double2(pn, p);
+      const double pn = fma(d[s] - mu, p, -(e[s] * pm));
+      out[i] = pn;
       pm = p;
       p = pn;
     }
-    const int e = __builtin_amdgcn_frexp_exp(p);
-    p = ldexp(p, -e);
-    pm = ldexp(pm, -e);
+  };
+  fetch(0, d0, e0);
+#pragma unroll 1
+  for (int s0 = 0; s0 < D; s0 += 8) {
+    fetch(s0 + 4, d1, e1);
+    steps(s0, d0, e0);
+    fetch(min(s0 + 8, D - 4), d0, e0);
+    steps(s0 + 4, d1, e1);
+    const int ex = __builtin_amdgcn_frexp_exp(p);
+    p = ldexp(p, -ex);
+    pm = ldexp(pm, -ex);
   }
 }
 
 // Entries of the twisted-factorisation vector on one side of the twist index rt (z_rt = 1): z_i = -mult_i z_{i+1}
-// for i < rt (UP = false, multipliers e_i / D+_i in M[i].x) or z_i = -mult_i z_{i-1} for i > rt (UP = true,
-// e_{i-1} / D-_i); z_i goes to F[i].y, the sum of their squares to *ssq_out.  Whole groups of eight rows first
+// for i < rt (UP = false, multipliers e_i / D+_i in M[i]) or z_i = -mult_i z_{i-1} for i > rt (UP = true,
+// e_{i-1} / D-_i); z_i goes to F[i], the sum of their squares to *ssq_out.  Whole groups of eight rows first
 // (constant offsets from one moving base, nothing conditional), then the rest row by row.
 template <bool UP>
-__device__ __forceinline__ void twisted_chain(double2* F, const double2* M, int rt, double* ssq_out) {
+__device__ __forceinline__ void twisted_chain(double* F, const double* M, int rt, double* ssq_out) {
   const int count = UP ? D - 1 - rt : rt;
   double z = 1.0, ssq = 0.0;
-  if (!UP) F[rt].y = 1.0;
+  if (!UP) F[rt] = 1.0;
   int s0 = 0;
 #pragma unroll 1
   for (; s0 + 8 <= count; s0 += 8) {
     const int i0 = UP ? rt + s0 + 1 : rt - s0 - 8;   // lowest row of the group
     double mlt[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) mlt[s] = M[i0 + (UP ? s : 7 - s)].x;
+    for (int s = 0; s < 8; ++s) mlt[s] = M[i0 + (UP ? s : 7 - s)];
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       z = -mlt[s] * z;
-      F[i0 + (UP ? s : 7 - s)].y = z;
+      F[i0 + (UP ? s : 7 - s)] = z;
       ssq = fma(z, z, ssq);
     }
   }
 #pragma unroll 1
   for (; s0 < count; ++s0) {
     const int i = UP ? rt + s0 + 1 : rt - s0 - 1;
-    z = -M[i].x * z;
-    F[i].y = z;
+    z = -M[i] * z;
+    F[i] = z;
     ssq = fma(z, z, ssq);
   }
   *ssq_out = ssq;
-}
-
-// Inner product number q of the reflectors of group q / 6 = {4b, .., 4b+3}, in the order the back-transformation applies
-// them (u_1 = v_{4b+3} .. u_4 = v_{4b}): c21 c31 c32 c41 c42 c43; one product per lane, over the rows where both
-// reflectors live (i > kb; what lies outside a reflector is arbitrary)
-__device__ __forceinline__ void reflector_product(int q, const float* refl, double* cW) {
-  const int bb = q / 6, pr = q - 6 * bb;
-  const int a = (pr == 0) ? 2 : ((pr < 3) ? 3 : 4), b2 = (pr == 0) ? 1 : ((pr < 3) ? pr : pr - 2);
-  const int ka = 4 * bb + 4 - a, kb = 4 * bb + 4 - b2;  // ka < kb
-  const float* pa = refl + refl_off(ka) - (ka + 1);      // entry i of reflector ka at pa[i]
-  const float* pb = refl + refl_off(kb) - (kb + 1);
-  double acc = 0.0;
-  if (kb < D - 2) {
-#pragma unroll 4
-    for (int i = kb + 1; i < D; ++i) acc = fma((double)pa[i], (double)pb[i], acc);
-  }
-  cW[q] = acc;
 }
 
 __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
@@ -1012,12 +1020,11 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
   __shared__ __align__(16) unsigned char pool[POOL_BYTES];
   float* refl = reinterpret_cast<float*>(pool) + REFL_SLACK;
   unsigned char* u1 = pool + REFL_BYTES;
+  double* wy = reinterpret_cast<double*>(u1 + TW_BYTES);   // triangular factors of the back-transformation
   __shared__ __align__(16) double vbuf[2][D];
   __shared__ __align__(16) double pbuf[8 * PB_LD];
   __shared__ __align__(16) double2 de[D + 1];  // (d_i, e_{i-1}^2) of the scaled tridiagonal matrix; de[D] = 0
   __shared__ double dT[D], eT[D], betaT[D];
-  __shared__ double cW[(D / 4) * 6];  // inner products of the reflectors inside each group of four
-  __shared__ double norm_s[EV_BATCH];
   __shared__ double chain_s[EV_BATCH][2];  // sums of squares of the two halves of each vector
   __shared__ int twist_s[EV_BATCH];
   __shared__ double lam_s[D], atoms[D];
@@ -1063,10 +1070,10 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       if (ly == 6 && lx == 6) dT[D - 2] = T[15];
       if (ly == 7 && lx == 6) eT[D - 2] = T[15];
       if (ly == 7 && lx == 7) dT[D - 1] = T[15];
-    } else if (tid - 64 < 144) {
-      // meanwhile the other waves form the inner products of the reflectors 0 .. 95 (groups 0 .. 23), whose float
-      // copies are complete
-      reflector_product(tid - 64, refl, cW);
+    } else {
+      // meanwhile the other waves form the triangular factors of the reflectors 0 .. 95, whose float copies are complete
+      // (two blocks of sixteen each, one of many rows and one of few)
+      wy_factors(wave - 1, 6 - wave, refl, betaT, wy, lane);
     }
     __syncthreads();
     // float copies of the last 30 reflectors (local entries c > kq of step kq), by everybody
@@ -1077,11 +1084,9 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     }
   }
   __syncthreads();
-  // the inner products of the reflectors 96 .. 127 (the others were formed beside the one-wave tail): by the last wave,
-  // while the first scales the tridiagonal matrix
-  if (tid >= THREADS - 48) reflector_product(144 + tid - (THREADS - 48), refl, cW);
 
   // ---- eigenvalues of T by Sturm-count multisection: lane pair j brackets the j-th smallest ----
+  sc_double* sde;   // the scaled tridiagonal matrix, for scalar loads
   {
     // power-of-two scaling (exact) so that every |d_i| + |e_{i-1}| + |e_i| <= 1
     if (wave == 0) {
@@ -1111,7 +1116,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     // register move placed after the barrier so that none of these loads can be scheduled before the stores
     unsigned long long tri_addr = reinterpret_cast<unsigned long long>(tri_blk);
     asm volatile("" : "+s"(tri_addr) : : "memory");
-    sc_double* sde = reinterpret_cast<sc_double*>(tri_addr);
+    sde = reinterpret_cast<sc_double*>(tri_addr);
     {
       // one word of every line first, all of them in flight together: the count below requests its operands two groups
       // ahead only and would otherwise wait for 32 misses of the scalar cache one after the other (35 K of a block's 475 K
@@ -1296,18 +1301,27 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
   // every division happens afterwards, all rows in parallel.  The twist index minimises
   // |gamma_i| = |D+_i + D-_i - (d_i - mu)|; z_twist = 1, z_i = -(e_i / D+_i) z_{i+1} above it and
   // z_i = -(e_{i-1} / D-_i) z_{i-1} below it.
-  double2* tw = reinterpret_cast<double2*>(u1);  // per eigenvector of a batch: F[128] (top-down) then Bk[128] (bottom-up)
+  double* tw = reinterpret_cast<double*>(u1);  // per eigenvector of a batch: F[128] (top-down) then Bk[128] (bottom-up)
   const double sc = tscale_s;
 #pragma unroll 1
   for (int b0 = 0; b0 < r; b0 += EV_BATCH) {
+    // the lane number passes through an opaque move: what depends on it is computed inside the loop (hoisted out of it,
+    // a hundred addresses went to scratch memory)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     __syncthreads();
     // (1) minors: wave 0 runs the top-down recurrences, wave 1 the bottom-up ones, one lane per eigenvector (the
-    // direction is then the same for a whole wave: constant offsets, no selects); F[i] = (p_i, p_{i-1}),
-    // Bk[i] = (q_i, q_{i+1})
-    if (wave < 2 && lane < EV_BATCH && b0 + lane < r) {
-      const double mu = lam_s[b0 + lane] * sc;
-      if (wave == 0) minors_sweep<false>(de, mu, tw + (lane * 2) * TW_STRIDE);
-      else minors_sweep<true>(de, mu, tw + (lane * 2 + 1) * TW_STRIDE);
+    // direction is then the same for a whole wave: constant offsets, no selects); F[i] = p_i, Bk[i] = q_i.  Meanwhile
+    // another wave forms the triangular factors of the last two blocks of reflectors.
+    if (wave < 2) {
+      if (lane < EV_BATCH && b0 + lane < r) {
+        const double mu = lam_s[b0 + lane] * sc;
+        if (wave == 0) minors_sweep<false>(sde, mu, tw + (lane * 2) * TW_STRIDE);
+        else minors_sweep<true>(sde, mu, tw + (lane * 2 + 1) * TW_STRIDE);
+      }
+    } else if (b0 == 0 && wave == 2) {
+      wy_factors(6, 7, refl, betaT, wy, lane);
     }
     __syncthreads();
     // (2) pivots, multipliers and twist index: rows i = l + LG m of eigenvector tid / LG, with LG = 64 lanes per
@@ -1319,24 +1333,36 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
         const int ev = tid / LG, l = tid % LG;
         if (ev < EV_BATCH && b0 + ev < r) {
           const double mu = lam_s[b0 + ev] * sc;
-          double2* F = tw + ev * 2 * TW_STRIDE;
-          double2* Bk = F + TW_STRIDE;
+          double* F = tw + ev * 2 * TW_STRIDE;
+          double* Bk = F + TW_STRIDE;
           const double piv = 0x1.0p-100;  // smallest pivot magnitude (the matrix is scaled to norm <= 1)
           double best = INFINITY;
+          // p_i, p_{i-1}, q_i, q_{i+1} of all rows first: the multipliers take their places
+          double fx[D / LG], fy[D / LG], bx[D / LG], by[D / LG];
 #pragma unroll
           for (int m = 0; m < D / LG; ++m) {
             const int i = l + LG * m;
-            const double2 f = F[i], bq = Bk[i];
-            const double fn = (fabs(f.x) < piv * fabs(f.y)) ? copysign(piv * fabs(f.y), f.x) : f.x;
-            const double bn = (fabs(bq.x) < piv * fabs(bq.y)) ? copysign(piv * fabs(bq.y), bq.x) : bq.x;
-            double g = fabs(fma(fn, newton_rcp(f.y), fma(bn, newton_rcp(bq.y), -(de[i].x - mu))));
+            fx[m] = F[i];
+            bx[m] = Bk[i];
+            const double fl = (i > 0) ? F[max(i - 1, 0)] : 1.0, bh = (i < D - 1) ? Bk[min(i + 1, D - 1)] : 1.0;
+            // the running value was rescaled in front of every group of eight
+            fy[m] = ((i & 7) == 0 && i > 0) ? __builtin_amdgcn_frexp_mant(fl) : fl;
+            by[m] = ((i & 7) == 7 && i < D - 1) ? __builtin_amdgcn_frexp_mant(bh) : bh;
+          }
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int m = 0; m < D / LG; ++m) {
+            const int i = l + LG * m;
+            const double fn = (fabs(fx[m]) < piv * fabs(fy[m])) ? copysign(piv * fabs(fy[m]), fx[m]) : fx[m];
+            const double bn = (fabs(bx[m]) < piv * fabs(by[m])) ? copysign(piv * fabs(by[m]), bx[m]) : bx[m];
+            double g = fabs(fma(fn, newton_rcp(fy[m]), fma(bn, newton_rcp(by[m]), -(de[i].x - mu))));
             if (!(g == g)) g = INFINITY;
-            double lmul = (i < D - 1) ? eT[i] * sc * f.y * newton_rcp(fn) : 0.0;   // e_i / D+_i
-            double umul = (i > 0) ? eT[i - 1] * sc * bq.y * newton_rcp(bn) : 0.0;  // e_{i-1} / D-_i
+            double lmul = (i < D - 1) ? eT[i] * sc * fy[m] * newton_rcp(fn) : 0.0;   // e_i / D+_i
+            double umul = (i > 0) ? eT[i - 1] * sc * by[m] * newton_rcp(bn) : 0.0;  // e_{i-1} / D-_i
             if (!isfinite(lmul)) lmul = 0.0;
             if (!isfinite(umul)) umul = 0.0;
-            F[i].x = lmul;
-            Bk[i].x = umul;
+            F[i] = lmul;
+            Bk[i] = umul;
             // the row index rides in the low mantissa bits: the minimum of the keys carries its own position
             const double key = __hiloint2double(__double2hiint(g), (__double2loint(g) & ~127) | i);
             best = fmin(best, key);
@@ -1356,44 +1382,76 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       else pivots(std::integral_constant<int, 16>{});
     }
     __syncthreads();
-    // (3) the vector itself, upwards (wave 0) and downwards (wave 1) from the twist index; z_i goes to F[i].y
+    // (3) the vector itself, upwards (wave 0) and downwards (wave 1) from the twist index; z_i goes to F[i]
     if (wave < 2 && lane < EV_BATCH && b0 + lane < r) {
-      double2* F = tw + lane * 2 * TW_STRIDE;
+      double* F = tw + lane * 2 * TW_STRIDE;
       const int rt = twist_s[lane];
       if (wave == 0) twisted_chain<false>(F, F, rt, &chain_s[lane][0]);
       else twisted_chain<true>(F, F + TW_STRIDE, rt, &chain_s[lane][1]);
     }
     __syncthreads();
-    if (tid < EV_BATCH && b0 + tid < r) {
-      const double ssq = 1.0 + chain_s[tid][0] + chain_s[tid][1];
-      norm_s[tid] = ssq;
-      if (!(ssq > 0.0) || !isfinite(ssq)) atomicOr(&flag_s, EOQ_FLAG_NO_CONVERGE);
-    }
-    __syncthreads();
-    // (4) back-transformation v = H_0 H_1 ... H_125 z, four reflectors at a time: 16 lanes per eigenvector, 8
-    // entries (i = l + 16 m) each.  With u_1 .. u_4 = v_{4b+3} .. v_{4b} (order of application), d_a = u_a^T y and
-    // c_ab = u_a^T u_b (prepared once per block), the four coefficients follow from a triangular recurrence and
-    // y <- y - sum_a f_a u_a.
-    if (tid < 16 * EV_BATCH) {
-      const int ev = tid >> 4, l = tid & 15;
-      const bool live = (b0 + ev < r);
-      const double2* F = tw + ev * 2 * TW_STRIDE;
-      double y[8];
+    // (4) back-transformation, sixteen reflectors at a time and all vectors of the batch at once: wave w holds the rows 16 t ..
+    // 16 t + 15 of t = w and w + 4, vector c in column c.  Per block of reflectors every wave forms V^T y over its rows,
+    // the four meet through LDS (two buffers in turn, one barrier), and every wave multiplies by T and updates its rows.
+    {
+      const int c = lane & 15, g = lane >> 4;
+      const bool live = c < EV_BATCH && b0 + c < r;
+      double4v Y[2];
       {
-        const double ssq = live ? norm_s[ev] : 1.0;
-        const double inv = (ssq > 0.0 && isfinite(ssq)) ? 1.0 / sqrt(ssq) : 0.0;
-#pragma unroll
-        for (int m = 0; m < 8; ++m) y[m] = live ? F[l + 16 * m].y * inv : 0.0;
+        const double ssq = live ? 1.0 + chain_s[c & (EV_BATCH - 1)][0] + chain_s[c & (EV_BATCH - 1)][1] : 1.0;
+        const bool good = ssq > 0.0 && isfinite(ssq);
+        if (!good && wave == 0 && g == 0) atomicOr(&flag_s, EOQ_FLAG_NO_CONVERGE);
+        const double inv = good ? 1.0 / sqrt(ssq) : 0.0;
+        const double* F = tw + (live ? c : 0) * 2 * TW_STRIDE;
+        EOQ_SFOR(tt, 2, EOQ_SFOR(v, 4, Y[tt][v] = live ? F[16 * (wave + 4 * tt) + 4 * v + g] * inv : 0.0;););
       }
-      EOQ_SFOR(sgr, 8, backtransform_stage<7 - sgr>(y, refl, betaT, cW, l););
+      __syncthreads();   // the scratch of the vectors becomes the exchange
+      double* xb = tw;
+#pragma unroll 1
+      for (int sg = D / 16 - 1; sg >= 0; --sg) {
+        double4v d = {0.0, 0.0, 0.0, 0.0};
+        double vt[2][4];   // entries for the update, read ahead of the barrier
+        // row view: reflector 16 sg + c, entries 4 v + g of a tile; column view: reflectors 16 sg + 4 v + g, entry c
+        const int kr = 16 * sg + c, kc = 16 * sg + g;
+        const float* pr = refl + refl_off(kr) - (kr + 1) + g;
+        const float* pc[4];
+        EOQ_SFOR(v, 4, pc[v] = refl + refl_off(kc + 4 * v) - (kc + 4 * v + 1) + c;);
+        EOQ_SFOR(tt, 2,
+          const int t = wave + 4 * tt;
+          if (t > sg) {   // uniform: the reflectors are full here
+            EOQ_SFOR(v, 4, d = mfma64((double)pr[16 * t + 4 * v], Y[tt][v], d););
+            EOQ_SFOR(v, 4, vt[tt][v] = -(double)pc[v][16 * t];);
+          } else if (t == sg) {   // and start inside this tile; above it they vanish
+            EOQ_SFOR(v, 4, d = mfma64((4 * v + g > c && kr < D - 2) ? (double)pr[16 * t + 4 * v] : 0.0, Y[tt][v], d););
+            EOQ_SFOR(v, 4, vt[tt][v] = (c > 4 * v + g && kc + 4 * v < D - 2) ? -(double)pc[v][16 * t] : 0.0;);
+          });
+        double* x = xb + (sg & 1) * 1024;
+        EOQ_SFOR(v, 4, x[wave * 256 + 64 * v + lane] = d[v];);
+        double tm[4];
+        EOQ_SFOR(v, 4, tm[v] = wy[sg * 256 + wy_pos(c, 4 * v + g)];);
+        __syncthreads();
+        double4v f = {0.0, 0.0, 0.0, 0.0};
+        EOQ_SFOR(v, 4,
+          const double sum = (x[64 * v + lane] + x[256 + 64 * v + lane]) + (x[512 + 64 * v + lane] + x[768 + 64 * v + lane]);
+          f = mfma64(tm[v], sum, f);
+        );
+        EOQ_SFOR(tt, 2,
+          if (wave + 4 * tt >= sg) {
+            EOQ_SFOR(v, 4, Y[tt] = mfma64(vt[tt][v], f[v], Y[tt]););
+          });
+      }
+      __syncthreads();
+      // through LDS into rows: [vector][row]
       if (live) {
-        const double s = scale_s[b0 + ev];
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const int i = l + 16 * m;
-          rfac[(slot * r_max + b0 + ev) * D + i] = double_to_half_bits(y[m]);
-          wfac[(blk * r_max + b0 + ev) * D + i] = (float)(y[m] * s);
-        }
+        EOQ_SFOR(tt, 2, EOQ_SFOR(v, 4, xb[c * TW_STRIDE + 16 * (wave + 4 * tt) + 4 * v + g] = Y[tt][v];););
+      }
+      __syncthreads();
+      const int nv = min(r - b0, EV_BATCH);
+      for (int e = tid; e < nv * D; e += THREADS) {
+        const int ev = e >> 7, i = e & (D - 1);
+        const double y = xb[ev * TW_STRIDE + i];
+        rfac[(slot * r_max + b0 + ev) * D + i] = double_to_half_bits(y);
+        wfac[(blk * r_max + b0 + ev) * D + i] = (float)(y * scale_s[b0 + ev]);
       }
     }
   }
