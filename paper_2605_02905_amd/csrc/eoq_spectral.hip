@@ -300,15 +300,7 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
 // A[a * 8 + b] = G[ty + 16 a][tx + 16 b].  Rows and columns are dealt round-robin, so the trailing submatrix
 // of the reduction stays spread over all lanes while it shrinks: during steps 16 s .. 16 s + 15 every lane's
 // live part is the sub-tile a, b >= s.  The 16 lanes of one DPP row share ty.
-constexpr int GRAM_STRIP = 32;  // block rows staged per pass
-// Position of column j in a staged row: the 8 columns {c + 16 m} that one lane needs are split into two groups
-// of four consecutive floats, the groups of the 16 lanes side by side (16-byte reads without bank conflicts).
-__device__ __forceinline__ int stage_pos(int j) { return ((j >> 6) << 6) | ((j & 15) << 2) | ((j >> 4) & 3); }
 constexpr int XPAD = 17;  // row stride of a 16 x 16 exchange plane: transposed reads hit distinct banks
-// the 28 sub-tiles above the diagonal, in the order they are mirrored
-constexpr int PAIR_A[28] = {0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 2, 2, 2, 2, 2, 3, 3, 3, 3, 4, 4, 4, 5, 5, 6};
-constexpr int PAIR_B[28] = {1, 2, 3, 4, 5, 6, 7, 2, 3, 4, 5, 6, 7, 3, 4, 5, 6, 7, 4, 5, 6, 7, 5, 6, 7, 6, 7, 7};
-
 // packed reflector storage: reflector k has entries i = k+1 .. 127 (24-bit products: full rate)
 __device__ __forceinline__ int refl_off(int k) { return (int)(__umul24(k, D - 1) - (__umul24(k, k - 1) >> 1)); }
 constexpr int REFL_LEN = (D - 1) * D / 2;  // 8128
@@ -326,61 +318,12 @@ constexpr int EV_BATCH = 8;                // eigenvectors per twisted-factorisa
 constexpr int TW_STRIDE = D + 1;
 constexpr int TW_BYTES = EV_BATCH * 2 * TW_STRIDE * 8;   // 16.1 KB; also the exchange of the back-transformation
 constexpr int WY_BYTES = (D / 16) * 256 * 8;             // 16 KB: the triangular factor of every sixteen reflectors
-constexpr int U1_BYTES = TW_BYTES + WY_BYTES;            // also the Gram strip (16 KB)
-static_assert(TW_BYTES >= 2 * 4 * 256 * 8 && TW_BYTES >= (32 * 33 + 30 * 32) * 8 && U1_BYTES >= GRAM_STRIP * D * 4 && EV_BATCH <= 16, "u1 layout");
+constexpr int U1_BYTES = TW_BYTES + WY_BYTES; 
+static_assert(TW_BYTES >= 2 * 4 * 256 * 8 && TW_BYTES >= (32 * 33 + 30 * 32) * 8 && EV_BATCH <= 16, "u1 layout");
 constexpr double CLUSTER_TOL = 1e-10;      // relative gap below which retained eigenvalues count as repeated
 constexpr int REFL_SLACK = 16;             // floats in front of the reflectors (masked reads may reach them)
 constexpr int REFL_BYTES = (REFL_LEN + REFL_SLACK) * 4;   // 32576 (a multiple of 16)
 constexpr int POOL_BYTES = REFL_BYTES + U1_BYTES > 65536 ? REFL_BYTES + U1_BYTES : 65536;   // the Gram planes fill 64 KB
-
-// G = S^T S in the cyclic layout.  Only the sub-tiles a <= b are accumulated (36 of 64 products per block row);
-// the others are mirrored from the lane that holds the transposed position, through LDS.
-__device__ __forceinline__ void gram_cyclic(const void* __restrict__ blocks, int dtype, size_t base_elem, size_t tok, int n,
-                                            float* stage, int tid, double (&A)[64], unsigned* flag_s) {
-  const int ty = tid >> 4, tx = tid & 15;
-  EOQ_SFOR(i, 64, A[i] = 0.0;);
-  float nxt[2][8];
-  const int wrow = tid >> 4, wcol = (tid & 15) * 8;
-  load8(blocks, dtype, base_elem + (size_t)wrow * tok + wcol, nxt[0]);
-  load8(blocks, dtype, base_elem + (size_t)(16 + wrow) * tok + wcol, nxt[1]);
-#pragma unroll 1
-  for (int t0 = 0; t0 < n; t0 += GRAM_STRIP) {
-    __syncthreads();  // the previous strip has been consumed
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) stage[(g * 16 + wrow) * D + stage_pos(wcol + i)] = nxt[g][i];
-    __syncthreads();
-    if (t0 + GRAM_STRIP < n) {  // next strip on its way while this one is multiplied
-      const size_t e = base_elem + (size_t)(t0 + GRAM_STRIP + wrow) * tok + wcol;
-      load8(blocks, dtype, e, nxt[0]);
-      load8(blocks, dtype, e + 16 * tok, nxt[1]);
-    }
-#pragma unroll 2
-    for (int t = 0; t < GRAM_STRIP; ++t) {
-      const float4 a0 = *reinterpret_cast<const float4*>(stage + t * D + ty * 4);
-      const float4 a1 = *reinterpret_cast<const float4*>(stage + t * D + 64 + ty * 4);
-      const float4 b0 = *reinterpret_cast<const float4*>(stage + t * D + tx * 4);
-      const float4 b1 = *reinterpret_cast<const float4*>(stage + t * D + 64 + tx * 4);
-      const double a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-      const double b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-      EOQ_SFOR(e, 64, if constexpr ((e >> 3) <= (e & 7)) A[e] = fma(a[e >> 3], b[e & 7], A[e]););
-    }
-  }
-  {
-    bool bad = false;   // an Inf or NaN entry of the block reaches the diagonal of G
-    EOQ_SFOR(i, 8, bad |= !(fabs(A[i * 9]) < INFINITY););
-    if (bad) atomicOr(flag_s, EOQ_FLAG_NONFINITE);
-  }
-  // mirror: G[ty+16b][tx+16a] (a < b) is what lane (tx, ty) accumulated as its sub-tile (a, b)
-  double* X = reinterpret_cast<double*>(stage);
-  EOQ_SFOR(round, 4,
-    __syncthreads();
-    EOQ_SFOR(q, 7, X[q * 16 * XPAD + ty * XPAD + tx] = A[PAIR_A[round * 7 + q] * 8 + PAIR_B[round * 7 + q]];);
-    __syncthreads();
-    EOQ_SFOR(q, 7, A[PAIR_B[round * 7 + q] * 8 + PAIR_A[round * 7 + q]] = X[q * 16 * XPAD + tx * XPAD + ty];);
-  );
-}
 
 // ---------------------------------------------------------------------------------------------
 // Gram matrix of a binary16 block by exact integer arithmetic on the matrix cores.
@@ -392,9 +335,8 @@ __device__ __forceinline__ void gram_cyclic(const void* __restrict__ blocks, int
 // v_mfma_i32_16x16x64_i8, two instructions deep per plane pair (exact int32 sums over the 128 tokens); the sixteen
 // plane pairs go to seven accumulators, one per weight 2^(8 (p + q)).  The group result, scaled by
 // 2^(E_i + E_j - 58), is added to a double-precision accumulator: one conversion per 128 tokens.  Only the 36
-// tiles of 16 x 16 on and above the diagonal are computed, nine per wave.  Element (ty, tx) of tile (a, b) is entry
-// A[a * 8 + b] of lane (ty, tx) in the cyclic layout, so at the end the tiles only change lanes (through LDS), the
-// mirrored ones read transposed.
+// tiles of 16 x 16 on and above the diagonal are computed, nine per wave; at the end they change lanes through LDS
+// (tiles_to_lanes).
 // ---------------------------------------------------------------------------------------------
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
@@ -415,6 +357,75 @@ constexpr int UT_I[GI_TILES] = {0, 0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 2, 
 constexpr int UT_J[GI_TILES] = {0, 1, 2, 3, 4, 5, 6, 7, 1, 2, 3, 4, 5, 6, 7, 2, 3, 4, 5, 6, 7, 3, 4, 5, 6, 7, 4, 5, 6, 7, 5, 6, 7, 6, 7, 7};
 __device__ const int ut_i_dev[GI_TILES] = {0, 0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 2, 2, 2, 2, 2, 2, 3, 3, 3, 3, 3, 4, 4, 4, 4, 5, 5, 5, 6, 6, 7};
 __device__ const int ut_j_dev[GI_TILES] = {0, 1, 2, 3, 4, 5, 6, 7, 1, 2, 3, 4, 5, 6, 7, 2, 3, 4, 5, 6, 7, 3, 4, 5, 6, 7, 4, 5, 6, 7, 5, 6, 7, 6, 7, 7};
+
+// The 36 tiles, three rounds of twelve through LDS, into the cyclic layout: lane (ty, tx) takes element (ty, tx) of tile
+// (a, b) as A[a * 8 + b] and, for a < b, element (tx, ty) as A[b * 8 + a].  `get(s, v)` is this lane's entry number v of the
+// wave's tile wave + 4 s, in column lane % 16 and row `row(v)`.
+template <typename Get, typename Row>
+__device__ __forceinline__ void tiles_to_lanes(double* Tl, int tid, double (&A)[64], Get&& get, Row&& row) {
+  const int ty = tid >> 4, tx = tid & 15, wave = tid >> 6;
+  EOQ_SFOR(rd, 3,
+    __syncthreads();
+    EOQ_SFOR(s3, 3,
+      double* dst = Tl + (wave + 4 * s3) * 16 * XPAD;
+      EOQ_SFOR(v, 4, dst[row(v) * XPAD + tx] = get(std::integral_constant<int, 3 * rd + s3>{}, v_ic););
+    );
+    __syncthreads();
+    EOQ_SFOR(pp, 12,
+      constexpr int tile = 12 * rd + pp;
+      constexpr int a = UT_I[tile]; constexpr int b = UT_J[tile];
+      A[a * 8 + b] = Tl[pp * 16 * XPAD + ty * XPAD + tx];
+      if constexpr (a != b) A[b * 8 + a] = Tl[pp * 16 * XPAD + tx * XPAD + ty];
+    );
+  );
+}
+
+typedef double double4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ double4v mfma64(double a, double b, double4v c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// Gram matrix of a float32 block on the fp64 matrix cores (products of float32 numbers are exact in double): nine of the 36
+// tiles per wave.  Lane l = 16 g + c supplies S[t + g][16 I + c] as operand of tile row or column I of v_mfma_f64_16x16x4_f64,
+// straight from memory, sixteen tokens ahead; result register v is row 4 v + g, column c.  As vector multiply-adds out
+// of LDS a compress call of 125 blocks of 512 x 128 took 272 us, now 241.
+__device__ __forceinline__ void gram_f64(const float* __restrict__ src, size_t tok, int n, double* Tl, int tid, double (&A)[64],
+                                         unsigned* flag_s) {
+  const int lane = tid & 63, c = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double4v acc[9];
+  EOQ_SFOR(s, 9, EOQ_SFOR(v, 4, acc[s][v] = 0.0;););
+  const float* p = src + (size_t)g * tok + c;
+  float x[2][8], y[2][8];
+  auto fetch = [&](int t, float (&f)[2][8]) __attribute__((always_inline)) {   // tokens t + g and t + 4 + g
+    EOQ_SFOR(h, 2, EOQ_SFOR(I, 8, f[h][I] = p[(size_t)(t + 4 * h) * tok + 16 * I];););
+  };
+  auto products = [&](const float (&f)[2][8]) __attribute__((always_inline)) {
+    EOQ_SFOR(h, 2,
+      double o[8];
+      EOQ_SFOR(I, 8, o[I] = (double)f[h][I];);
+      // the wave's tiles wave, wave + 4, ..: four cases, so that every operand is a register known at compile time
+      auto tiles = [&](auto w_ic) __attribute__((always_inline)) {
+        constexpr int w = decltype(w_ic)::value;
+        EOQ_SFOR(s, 9, acc[s] = mfma64(o[UT_I[w + 4 * s]], o[UT_J[w + 4 * s]], acc[s]););
+      };
+      if (wave == 0) tiles(std::integral_constant<int, 0>{});
+      else if (wave == 1) tiles(std::integral_constant<int, 1>{});
+      else if (wave == 2) tiles(std::integral_constant<int, 2>{});
+      else tiles(std::integral_constant<int, 3>{});
+    );
+  };
+  fetch(0, x);
+#pragma unroll 1
+  for (int t = 0; t < n; t += 16) {
+    fetch(t + 8, y);
+    products(x);
+    fetch(min(t + 16, n - 8), x);
+    products(y);
+  }
+  bool bad = false;   // an Inf or NaN entry of the block reaches the diagonal of G, which the diagonal tiles hold
+  EOQ_SFOR(s, 9, EOQ_SFOR(v, 4, bad |= ut_i_dev[wave + 4 * s] == ut_j_dev[wave + 4 * s] && !(fabs(acc[s][v]) < INFINITY);););
+  if (bad) atomicOr(flag_s, EOQ_FLAG_NONFINITE);
+  tiles_to_lanes(Tl, tid, A, [&](auto s, auto v) { return acc[decltype(s)::value][decltype(v)::value]; }, [&](int v) { return 4 * v + g; });
+}
 
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
   const ushort2v r = __builtin_elementwise_max(*reinterpret_cast<ushort2v*>(&a), *reinterpret_cast<ushort2v*>(&b));
@@ -538,25 +549,8 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
   }
   // a column maximum with all exponent bits set: the integer conversion of that pass saturated, G is meaningless
   if (q == 0 && (((top & 0xFFFFu) >= 0x7C00u) || ((top >> 16) >= 0x7C00u))) atomicOr(flag_s, EOQ_FLAG_NONFINITE);
-  // ---- tiles change lanes: three rounds of twelve tiles through LDS; lane (ty, tx) takes element (ty, tx) of tile
-  // (a, b) as A[a * 8 + b] and, for a < b, element (tx, ty) as A[b * 8 + a] ----
-  double* Tl = reinterpret_cast<double*>(pool);
-  const int ty = tid >> 4, tx = tid & 15;
-  EOQ_SFOR(rd, 3,
-    __syncthreads();
-    EOQ_SFOR(s3, 3,
-      constexpr int s = 3 * rd + s3;
-      double* dst = Tl + (wave + 4 * s3) * 16 * XPAD;
-      EOQ_SFOR(v, 4, dst[(4 * kg + v) * XPAD + l16] = Gacc[s][v];);
-    );
-    __syncthreads();
-    EOQ_SFOR(pp, 12,
-      constexpr int tile = 12 * rd + pp;
-      constexpr int a = UT_I[tile]; constexpr int b = UT_J[tile];
-      A[a * 8 + b] = Tl[pp * 16 * XPAD + ty * XPAD + tx];
-      if constexpr (a != b) A[b * 8 + a] = Tl[pp * 16 * XPAD + tx * XPAD + ty];
-    );
-  );
+  tiles_to_lanes(reinterpret_cast<double*>(pool), tid, A, [&](auto s, auto v) { return Gacc[decltype(s)::value][decltype(v)::value]; },
+                 [&](int v) { return 4 * kg + v; });
 }
 
 // Sum over the 16 lanes of a DPP row of the values p[S .. 7] of every lane (the values below S are dead),
@@ -893,9 +887,6 @@ __device__ __forceinline__ int sturm_count(sc_double* de, double x, double* val 
 // for a batch of vectors y is a chain of products for v_mfma_f64_16x16x4_f64.  Its operands (wave64): lane l = 16 g + c
 // supplies A[row = c][k = g] and B[k = g][col = c] and receives D[row = 4 v + g][col = c] in register v: a result register v
 // is the B operand of the k-step that takes the rows 4 v .. 4 v + 3, nothing changes lanes.
-typedef double double4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ double4v mfma64(double a, double b, double4v c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-
 // position of T_ik in the 16 x 16 array of a block: the sixteen lanes of an operand read touch different banks
 __device__ __forceinline__ int wy_pos(int i, int k) { return 16 * i + (k ^ i); }
 
@@ -1048,7 +1039,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       gram_int8(static_cast<const uint16_t*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, pool,
                 reinterpret_cast<uint32_t*>(lam_s), reinterpret_cast<int*>(atoms), tid, A, &flag_s);
     else
-      gram_cyclic(blocks, dtype, map.in_base(blk), (size_t)map.token_stride, n, reinterpret_cast<float*>(u1), tid, A, &flag_s);
+      gram_f64(static_cast<const float*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, reinterpret_cast<double*>(pool), tid, A, &flag_s);
     __syncthreads();  // the pool changes hands
     EOQ_SFOR(s, 6, householder_stage<s>(A, tid, vbuf, pbuf, refl, dT, eT, betaT););
     if (wave == 1) stash_reflector(vbuf[1], 95, lane, refl);   // reflector 95: the stages stash one step behind
