@@ -1230,11 +1230,6 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       if (sub == 0 && i_desc < REFINE_KEEP) {
         atoms[2 * i_desc] = lo;
         atoms[2 * i_desc + 1] = hi;
-        // the place of the secant point inside the bracket, 1/2 where the values at the ends do not give one
-        const float fh = ldexpf(f_hi, min(max((ce_hi >> 8) - (ce_lo >> 8), -100), 100));
-        const float ratio = f_lo / (f_lo - fh);
-        const bool secant = ((ce_hi - ce_lo) & 0xFF) == 1 && f_lo * fh < 0.0f && ratio > 0.0f && ratio < 1.0f;
-        reinterpret_cast<float*>(&vbuf[1][0])[i_desc] = secant ? ratio : 0.5f;
       }
     }
     int rt;
@@ -1258,27 +1253,16 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       const int i_desc = !act ? 0 : (!wide ? jj : (jj <= rt ? jj : (jj == rt + 1 ? k_pilot : 2 * k_pilot)));
       const int jr = D - 1 - i_desc;
       double rlo = atoms[2 * i_desc], rhi = atoms[2 * i_desc + 1];
-      const float at = reinterpret_cast<const float*>(&vbuf[1][0])[i_desc];
       const int shift = (tid & 63) & ~(G - 1);
       const unsigned long long gmask = (lg == 6) ? ~0ull : ((1ull << G) - 1ull);
-      // One sweep usually does: in a bracket of 3e-11 with one eigenvalue, far from its neighbours by that measure, the
-      // determinant is a straight line to seven digits or more, so the first G points sit around its zero, the final
-      // width apart.  Where the eigenvalue is not among them, the sections of the interval that is left follow.
-      const double fine = (lg == 3) ? 0x1.0p-50 : ((lg == 4) ? 0x1.0p-51 : 0x1.0p-52);
-      const double mid = fma((double)at, rhi - rlo, rlo);
 #pragma unroll 1
-      for (int it = 0; it <= iters; ++it) {
-        const double w = (it == 0) ? fine : (rhi - rlo) * inv;
-        const double base = (it == 0) ? mid - (0.5 * (G + 1)) * fine : rlo;   // point s at base + (s + 1) w, inside the bracket
-        const double x = fmin(fmax(fma((double)(sg + 1), w, base), rlo), rhi);
-        const int c = sturm_count(sde, x);
+      for (int it = 0; it < iters; ++it) {
+        const double w = (rhi - rlo) * inv;
+        const int c = sturm_count(sde, fma((double)(sg + 1), w, rlo));
         const unsigned long long below = __ballot(c <= jr);   // points not above the eigenvalue: a prefix of the group
         const int mcount = __popcll((below >> shift) & gmask);
-        // the bounds move only where the points say so: a prefix of none or all leaves that end
-        const double up = fmin(fmax(fma((double)(mcount + 1), w, base), rlo), rhi), down = fmin(fmax(fma((double)mcount, w, base), rlo), rhi);
-        rhi = (mcount == G) ? rhi : up;
-        rlo = (mcount == 0) ? rlo : down;
-        if (__ballot(act && rhi - rlo > 2.0 * fine) == 0ull) break;   // wave-uniform
+        rhi = (mcount == G) ? rhi : fma((double)(mcount + 1), w, rlo);
+        rlo = fma((double)mcount, w, rlo);
       }
       if (act && sg == 0) lam_s[i_desc] = fmax(0.5 * (rlo + rhi), 0.0) / sc;
     }
