@@ -1230,6 +1230,9 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       if (sub == 0 && i_desc < REFINE_KEEP) {
         atoms[2 * i_desc] = lo;
         atoms[2 * i_desc + 1] = hi;
+        // the sign of det(T - x I) at the lower end as a value of its own; 0 where the sign does not tell the side
+        const bool single = ((ce_hi - ce_lo) & 0xFF) == 1 && f_lo * f_hi < 0.0f;
+        reinterpret_cast<float*>(&vbuf[1][0])[i_desc] = single ? copysignf(1.0f, f_lo) : 0.0f;
       }
     }
     int rt;
@@ -1253,13 +1256,24 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       const int i_desc = !act ? 0 : (!wide ? jj : (jj <= rt ? jj : (jj == rt + 1 ? k_pilot : 2 * k_pilot)));
       const int jr = D - 1 - i_desc;
       double rlo = atoms[2 * i_desc], rhi = atoms[2 * i_desc + 1];
+      const float side = reinterpret_cast<const float*>(&vbuf[1][0])[i_desc];
+      const bool by_sign = __ballot(act && side == 0.0f) == 0ull;   // wave-uniform; the signs alone, as in the rounds above
       const int shift = (tid & 63) & ~(G - 1);
       const unsigned long long gmask = (lg == 6) ? ~0ull : ((1ull << G) - 1ull);
 #pragma unroll 1
       for (int it = 0; it < iters; ++it) {
         const double w = (rhi - rlo) * inv;
-        const int c = sturm_count(sde, fma((double)(sg + 1), w, rlo));
-        const unsigned long long below = __ballot(c <= jr);   // points not above the eigenvalue: a prefix of the group
+        const double x = fma((double)(sg + 1), w, rlo);
+        bool not_above;
+        if (by_sign) {
+          double fv;
+          int fe;
+          (void)sturm_count<false>(sde, x, &fv, &fe);
+          not_above = (__double2hiint(fv) ^ __float_as_int(side)) >= 0;
+        } else {
+          not_above = sturm_count(sde, x) <= jr;
+        }
+        const unsigned long long below = __ballot(not_above);   // points not above the eigenvalue: a prefix of the group
         const int mcount = __popcll((below >> shift) & gmask);
         rhi = (mcount == G) ? rhi : fma((double)(mcount + 1), w, rlo);
         rlo = fma((double)mcount, w, rlo);
