@@ -468,13 +468,14 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
 // tokens (a contiguous range of the batch's tiles each), the lane that owns a token unpacks it and the products come out
 // transposed.  Centroids and rotation enter as binary16 hi + lo (three matrix instructions per operand: r_x = S - x_hat
 // is a small difference); r_x forms in the accumulators from the token's own row, its norm is a sum over the lane and
-// its partner, and its hi + lo parts are packed from the accumulators straight into the operand of the product with Phi
-// (binary16 by definition), whose contraction index is permuted to the order the accumulators have.  The sign bits
-// of the result are assembled inside the lane.  Pi^T hi sits in registers, Pi^T lo and Phi in LDS in operand order, shared by
+// its partner, and its hi + lo parts are packed from the accumulators into the operand of the product with Phi (binary16
+// by definition); four registers of eight change places with the partner lane, so that every sum over columns runs in
+// column order: a sign bit whose sum is within rounding of zero does not depend on the layout.  The sign bits of the
+// result are assembled inside the lane.  Pi^T hi sits in registers, Pi^T lo and Phi in LDS in operand order, shared by
 // the eight waves of the workgroup (one per compute unit, two waves per SIMD).
 // Bound by the matrix cores: 160 instructions per tile, 32 cycles each (about 45 at the clock such a stretch leaves), of
 // a wave that has no registers to read operands far ahead: every phase left out of it takes twice its matrix
-// instructions' time with it.  262144 tokens of 2 bits: 52 us.  The workgroup-per-block version this replaces exchanged
+// instructions' time with it.  262144 tokens of 2 bits: 53 us.  The workgroup-per-block version this replaces exchanged
 // centroids and residuals through LDS with a barrier per 64 tokens at one wave per SIMD: 100 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int QWAVES = 8;
@@ -486,7 +487,7 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
     const uint16_t* __restrict__ norms, const int32_t* __restrict__ rank_in, const uint16_t* __restrict__ lfac,
     const uint16_t* __restrict__ rfac, uint8_t* __restrict__ qsigns, uint16_t* __restrict__ qnorms) {
   __shared__ __align__(16) uint4 Plo[4 * 8 * 64];            // Pi^T lo, [column block][instruction][lane]
-  __shared__ __align__(16) uint4 Fop[4 * 8 * 64];            // Phi, the same, contraction order of the accumulators
+  __shared__ __align__(16) uint4 Fop[4 * 8 * 64];            // Phi, the same
   __shared__ __align__(16) uint16_t Vt[QWAVES * D * 16];     // per wave: right factors 0 .. 15 of the block, [column][component]
   __shared__ __align__(16) uint16_t St[QWAVES * 32 * SLD];   // per wave: half the columns of a tile of S, [token][column]
   __shared__ __align__(16) uint16_t Cs[QWAVES * 16 * CTLD];  // per wave: coefficient rows of a tile
@@ -523,10 +524,8 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
 #pragma unroll
   for (int k = 0; k < 4 * 8 / QWAVES; ++k) {
     const int cb = k * QWAVES / 8, kk = wave;   // this wave's share of the operands in LDS
-    Plo[(cb * 8 + kk) * 64 + lane] = *reinterpret_cast<const uint4*>(pit_lo + (32 * cb + l32) * D + 64 * hf + 8 * kk);
-    const uint16_t* frow = phih + (32 * cb + l32) * D + 16 * kk + 4 * hf;
-    const uint2 fa = *reinterpret_cast<const uint2*>(frow), fb = *reinterpret_cast<const uint2*>(frow + 8);
-    Fop[(cb * 8 + kk) * 64 + lane] = make_uint4(fa.x, fa.y, fb.x, fb.y);
+    Plo[(cb * 8 + kk) * 64 + lane] = *reinterpret_cast<const uint4*>(pit_lo + (32 * cb + l32) * D + 16 * kk + 8 * hf);
+    Fop[(cb * 8 + kk) * 64 + lane] = *reinterpret_cast<const uint4*>(phih + (32 * cb + l32) * D + 16 * kk + 8 * hf);
   }
   __syncthreads();   // the only one: from here on the waves do not meet again
 
@@ -538,7 +537,7 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk)
-      Ap[cb][kk].u = *reinterpret_cast<const uint4*>(pit_hi + (32 * cb + l32) * D + 64 * hf + 8 * kk);
+      Ap[cb][kk].u = *reinterpret_cast<const uint4*>(pit_hi + (32 * cb + l32) * D + 16 * kk + 8 * hf);
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
 
   const int tpb = n / 32;
@@ -562,12 +561,12 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
     x.u = *reinterpret_cast<const uint4*>(vt + (32 * cb + l32) * 16 + 8 * hf);
     return x;
   };
-  auto c_operand = [&]() __attribute__((always_inline)) {         // -C[token l32][8 hf + e] of the rows staged in cs
+  auto c_operand = [&]() __attribute__((always_inline)) {         // C[token l32][8 hf + e] of the rows staged in cs
     H8 x;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const uint32_t a = cs[(8 * hf + 2 * w) * CTLD + l32], b = cs[(8 * hf + 2 * w + 1) * CTLD + l32];
-      x.w[w] = (a | (b << 16)) ^ 0x80008000u;
+      x.w[w] = a | (b << 16);
     }
     return x;
   };
@@ -599,6 +598,13 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
     if (r > 0) {   // uniform
       *reinterpret_cast<u32x4*>(cs + (lane >> 2) * CTLD + (lane & 3) * 8) = cur.cf;
       __builtin_amdgcn_wave_barrier();
+    }
+    // byte 2 kk + hf of a plane belongs to instruction kk: the even bytes to the lane, the odd ones to its partner
+#pragma unroll
+    for (int p = 0; p < BITS; ++p) {
+      const uint32_t ev = __builtin_amdgcn_perm(cur.pl[p].y, cur.pl[p].x, 0x06040200u), od = __builtin_amdgcn_perm(cur.pl[p].y, cur.pl[p].x, 0x07050301u);
+      const u32x2 e = __builtin_amdgcn_permlane32_swap(ev, od, false, false);
+      cur.pl[p] = e;
     }
     // nibble words of the lane's 64 coordinates (BITS <= 3): byte kk of word set [kk / 4] is instruction kk
     uint32_t even[2], odd[2], seven[2], sodd[2];
@@ -650,27 +656,21 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
         zh = centroids_of<BITS, true>(byte, mask_tab, mg, &zl);
       }
       EOQ_SFOR(cb, 4, acc[cb] = mfma16(Ap[cb][kk], zh, acc[cb]););
-      EOQ_SFOR(cb, 4, acc[cb] = mfma16(Ap[cb][kk], zl, acc[cb]););
       EOQ_SFOR(cb, 4,
         H8 lo;
         lo.u = Plo[(cb * 8 + kk) * 64 + lane];
         acc[cb] = mfma16(lo, zh, acc[cb]);
       );
+      EOQ_SFOR(cb, 4, acc[cb] = mfma16(Ap[cb][kk], zl, acc[cb]););
     );
-    // ---- r_x = S - x_hat: S goes through LDS, half the columns at a time, into the lanes that own the tokens; register v
-    // of column block cb is column 32 cb + 8 (v / 4) + 4 hf + v % 4 ----
-    EOQ_SFOR(h, 2,
+    auto stage_s = [&](auto h_ic) __attribute__((always_inline)) {   // half of the tile's columns into LDS
+      constexpr int h = decltype(h_ic)::value;
       EOQ_SFOR(i, 4, *reinterpret_cast<u32x4*>(st + (8 * i + (lane >> 3)) * SLD + 8 * (lane & 7)) = sv[h][i];);
       __builtin_amdgcn_wave_barrier();
-      EOQ_SFOR(c, 2, EOQ_SFOR(q, 4,
-        constexpr int cb = 2 * h + c;
-        const u32x2 w = *reinterpret_cast<const u32x2*>(st + l32 * SLD + 32 * c + 8 * q + 4 * hf);
-        EOQ_SFOR(e, 4,
-          acc[cb][4 * q + e] = fmaf(acc[cb][4 * q + e], -rs, half_bits_to_float((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu))));
-        );
-      ););
-      __builtin_amdgcn_wave_barrier();
-    );
+    };
+    stage_s(std::integral_constant<int, 0>{});
+    __builtin_amdgcn_sched_barrier(0);   // sixteen registers free
+    EOQ_SFOR(cb, 4, EOQ_SFOR(v, 16, acc[cb][v] *= rs;););
     if (r > 0) {
       const H8 cop = c_operand();
       EOQ_SFOR(cb, 4, acc[cb] = mfma16(v_operand(cb), cop, acc[cb]););
@@ -686,17 +686,40 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
       }
       __builtin_amdgcn_wave_barrier();   // the tile's LDS is rewritten by the next one
     }
+    // ---- r_x = S - x_hat: S goes through LDS, half the columns at a time, into the lanes that own the tokens; register v
+    // of column block cb is column 32 cb + 8 (v / 4) + 4 hf + v % 4 ----
+    EOQ_SFOR(h, 2,
+      if constexpr (h == 1) stage_s(h_ic);
+      EOQ_SFOR(c, 2, EOQ_SFOR(q, 4,
+        constexpr int cb = 2 * h + c;
+        const u32x2 w = *reinterpret_cast<const u32x2*>(st + l32 * SLD + 32 * c + 8 * q + 4 * hf);
+        EOQ_SFOR(e, 4,
+          acc[cb][4 * q + e] = half_bits_to_float((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu))) - acc[cb][4 * q + e];
+        );
+      ););
+      __builtin_amdgcn_wave_barrier();
+    );
     float ss = 0.0f;
     EOQ_SFOR(cb, 4, EOQ_SFOR(v, 16, ss = fmaf(acc[cb][v], acc[cb][v], ss);););
     ss += __shfl_xor(ss, 32, 64);
     if (hf == 0) qnorms[(size_t)blk * n + t0 + l32] = float_to_half_bits(sqrtf(ss));
-    H8 rh[8], rl[8];   // instruction 2 cb + s: columns 32 cb + 16 s + {0, 8} + 4 hf + 0 .. 3
+    // instruction 2 cb + s: from columns 32 cb + 16 s + {0, 8} + 4 hf + 0 .. 3, as the accumulators have them, to columns
+    // 32 cb + 16 s + 8 hf + 0 .. 7, the order of the contraction
+    H8 rh[8], rl[8];
     EOQ_SFOR(st, 8, EOQ_SFOR(w, 4,
       constexpr int cb = st >> 1; constexpr int v = 8 * (st & 1) + 2 * w;
       const float a = acc[cb][v]; const float b = acc[cb][v + 1];
       const uint32_t h = pack_half2(a, b);
       rh[st].w[w] = h;
       rl[st].w[w] = pack_half2(a - half_bits_to_float((uint16_t)(h & 0xFFFFu)), b - half_bits_to_float((uint16_t)(h >> 16)));
+    ););
+    EOQ_SFOR(st, 8, EOQ_SFOR(w, 2,
+      const u32x2 h = __builtin_amdgcn_permlane32_swap(rh[st].w[w], rh[st].w[w + 2], false, false);
+      const u32x2 l = __builtin_amdgcn_permlane32_swap(rl[st].w[w], rl[st].w[w + 2], false, false);
+      rh[st].w[w] = h.x;
+      rh[st].w[w + 2] = h.y;
+      rl[st].w[w] = l.x;
+      rl[st].w[w + 2] = l.y;
     ););
     // ---- the next tile's record bytes travel during the product with Phi ----
     const size_t row = (size_t)blk * n + t0 + l32;
