@@ -531,20 +531,26 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       // the first units come from the first four pairs, so that few later weights need new ones
       float mr[SETS], mw[SETS];
       EOQ_SFOR(s, SETS, mr[s] = 0.0f; mw[s] = 0.0f;);
+      uint32_t rho[4][2];
+      F2 wv[4][SETS][2];
       EOQ_SFOR(k, 4,
         const size_t t = (size_t)min(k, count - 1) * PAIR;
         EOQ_SFOR(i, 2,
-          const uint32_t rho = *reinterpret_cast<const uint32_t*>(rho_p + t + 32 * i);
-          const float r0 = half_bits_to_float((uint16_t)(rho & 0xFFFFu)) * inv_sqrt_d; const float r1 = half_bits_to_float((uint16_t)(rho >> 16)) * inv_sqrt_d;
-          EOQ_SFOR(s, SETS,
-            const F2 a = *reinterpret_cast<const F2*>(w_p[s] + t + 32 * i);
-            const float w0 = head_live[s] ? fabsf(a.x) : 0.0f; const float w1 = head_live[s] ? fabsf(a.y) : 0.0f;
-            const float sr = fmaf(w0, fabsf(r0), w1 * fabsf(r1)); const float sm = w0 + w1;
-            mr[s] = (sr > mr[s] || !(sr == sr)) ? sr : mr[s];
-            mw[s] = (sm > mw[s] || !(sm == sm)) ? sm : mw[s];
-          );
+          rho[k][i] = *reinterpret_cast<const uint32_t*>(rho_p + t + 32 * i);
+          EOQ_SFOR(s, SETS, wv[k][s][i] = *reinterpret_cast<const F2*>(w_p[s] + t + 32 * i););
         );
       );
+      __builtin_amdgcn_sched_barrier(0);   // all of them in flight together
+      EOQ_SFOR(k, 4, EOQ_SFOR(i, 2,
+        const float r0 = half_bits_to_float((uint16_t)(rho[k][i] & 0xFFFFu)) * inv_sqrt_d; const float r1 = half_bits_to_float((uint16_t)(rho[k][i] >> 16)) * inv_sqrt_d;
+        EOQ_SFOR(s, SETS,
+          const F2 a = wv[k][s][i];
+          const float w0 = head_live[s] ? fabsf(a.x) : 0.0f; const float w1 = head_live[s] ? fabsf(a.y) : 0.0f;
+          const float sr = fmaf(w0, fabsf(r0), w1 * fabsf(r1)); const float sm = w0 + w1;
+          mr[s] = (sr > mr[s] || !(sr == sr)) ? sr : mr[s];
+          mw[s] = (sm > mw[s] || !(sm == sm)) ? sm : mw[s];
+        );
+      ););
       choose_units(mr, mw);
     }
 #pragma unroll 1

@@ -53,62 +53,69 @@ __device__ __forceinline__ float4v mfma32(const H8& a, const H8& b, float4v c) {
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
 // out[h][c] = sum_j table[c][j] q[h][j] for the heads of one group (rows above the group are zero), the table given as
-// binary16 hi + lo parts [c][j]: the query side of the rotation (<q, Pi^T z> = <Pi q, z>) and of the projection Phi q.
-// q is binary16, so every product is exact; v_mfma_f32_16x16x32_f16, 16 matrix instructions and 20 sixteen-byte loads
-// per wave, all in flight together.  `out` is LDS, [SC_MAXG][D]; the caller synchronises.
-__device__ __forceinline__ void rotate_query(const uint16_t* __restrict__ tab_hi, const uint16_t* __restrict__ tab_lo,
-                                             const uint16_t* __restrict__ qg, int group, float* out, int wave, int l16,
-                                             int g) {
-  H8 a[4];
+// binary16 hi + lo parts [c][j] (LO = false: it is binary16 to begin with): the query side of the rotation (<q, Pi^T z> =
+// <Pi q, z>) and of the projection Phi q.  q is binary16, so every product is exact; v_mfma_f32_16x16x32_f16, A operand
+// `a` = q: lane (l16, g) holds q[l16][32 ks + 8 g .. + 7].  The loads are a step of their own so that they are in flight
+// together.  `out` is LDS, [SC_MAXG][D]; the caller synchronises.
+template <bool LO>
+struct TableRows {
+  H8 hi[2][4], lo[2][LO ? 4 : 1];
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ tab_hi, const uint16_t* __restrict__ tab_lo, int wave, int l16, int g) {
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-    a[ks].u = (l16 < group) ? *reinterpret_cast<const uint4*>(qg + l16 * D + 32 * ks + 8 * g) : make_uint4(0u, 0u, 0u, 0u);
+    for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-  for (int tt = 0; tt < 2; ++tt) {
-    const int c = 16 * (2 * wave + tt) + l16;
-    float4v acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      H8 bh, bl;
-      bh.u = *reinterpret_cast<const uint4*>(tab_hi + c * D + 32 * ks + 8 * g);
-      acc = mfma32(a[ks], bh, acc);
-      if (tab_lo) {   // uniform: a table that is binary16 to begin with has no low part
-        bl.u = *reinterpret_cast<const uint4*>(tab_lo + c * D + 32 * ks + 8 * g);
-        acc = mfma32(a[ks], bl, acc);
+      for (int ks = 0; ks < 4; ++ks) {
+        const int at = (16 * (2 * wave + tt) + l16) * D + 32 * ks + 8 * g;
+        hi[tt][ks].u = *reinterpret_cast<const uint4*>(tab_hi + at);
+        if constexpr (LO) lo[tt][ks].u = *reinterpret_cast<const uint4*>(tab_lo + at);
       }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (4 * g + v < SC_MAXG) out[(4 * g + v) * D + c] = acc[v];
   }
-}
+  __device__ __forceinline__ void rotate(const H8 (&a)[4], float* out, int wave, int l16, int g) const {
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt) {
+      const int c = 16 * (2 * wave + tt) + l16;
+      float4v acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        acc = mfma32(a[ks], hi[tt][ks], acc);
+        if constexpr (LO) acc = mfma32(a[ks], lo[tt][ks], acc);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (4 * g + v < SC_MAXG) out[(4 * g + v) * D + c] = acc[v];
+    }
+  }
+};
 
 // Rows of `rows` ([SC_MAXG][D] float, LDS), each multiplied by the NT coefficients coef[0 .. NT-1], to 32-bit fixed
 // point: per row the unit is 2^(E - 29) with E the exponent of the largest |coef| |entry| of the row, so |integer| <=
 // 2^30; the integer is cut into four balanced signed bytes (the bytes of I + 0x80808080 with the top bit of each flipped)
-// and byte plane p of row h goes to dig[(4 h + p) * NT * D + ...] with the NT terms of four consecutive coordinates side
+// and byte plane p of row h goes to dig[(4 h + p) * dig_stride(NT) + ...] with the NT terms of four consecutive coordinates side
 // by side: byte ((c / 4) * NT + term) * 4 + c % 4 -- the order of k in the matrix instructions.  unit[h] = value of one
-// integer unit (0 for a row that is zero, below 2^-87 or not finite).  All 256 lanes; barriers inside, the last one
-// after the planes are written.
+// integer unit (0 for a row that is zero, below 2^-87 or not finite).  All 256 lanes, 32 per row; the caller synchronises.
+// 16 bytes more than the row has: the lanes of an operand read, a row each, meet all banks (a multiple of 256 bytes put
+// them all on the same four: 8.5 of 55 thousand cycles of a workgroup at 4 bits)
+constexpr int dig_stride(int terms) { return terms * D + 16; }
 template <int NT>
-__device__ __forceinline__ void fixed_point_rows(const float* rows, const float (&coef)[NT], unsigned char* dig, unsigned* max_s,
-                                                 float* unit, int tid) {
-  if (tid < SC_MAXG) max_s[tid] = 0u;
-  __syncthreads();
+__device__ __forceinline__ void fixed_point_rows(const float* rows, const float (&coef)[NT], unsigned char* dig, float* unit,
+                                                 int tid) {
   const int h = tid >> 5, c0 = 4 * (tid & 31);
   float cmax = 0.0f;
 #pragma unroll
   for (int t = 0; t < NT; ++t) cmax = fmaxf(cmax, fabsf(coef[t]));
   float v[4];
-  unsigned m = 0u;
+  int m = 0;   // bits of the largest magnitude
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     v[e] = rows[h * D + c0 + e];
-    m = max(m, (unsigned)__float_as_uint(fabsf(v[e]) * cmax));
+    m = max(m, __float_as_int(fabsf(v[e]) * cmax));
   }
-  atomicMax(&max_s[h], m);
-  __syncthreads();
-  const int eb = (int)(max_s[h] >> 23);   // biased exponent of the row maximum
+  m = max(m, dpp_mov<0xB1>(m));
+  m = max(m, dpp_mov<0x4E>(m));
+  m = max(m, dpp_mov<0x141>(m));
+  m = max(m, dpp_mov<0x140>(m));
+  m = max(m, __shfl_xor(m, 16, 64));
+  const int eb = m >> 23;   // biased exponent of the row maximum
   const bool live = eb >= 40 && eb < 255;
   const double up = live ? (double)__uint_as_float((unsigned)(283 - eb) << 23) : 0.0;   // 2^(29 - (eb - 127))
 #pragma unroll
@@ -122,10 +129,9 @@ __device__ __forceinline__ void fixed_point_rows(const float* rows, const float 
     uint32_t pl[4];
     transpose_bytes(dg[0], dg[1], dg[2], dg[3], pl);
 #pragma unroll
-    for (int p = 0; p < 4; ++p) *reinterpret_cast<uint32_t*>(dig + (size_t)(4 * h + p) * NT * D + ((c0 >> 2) * NT + t) * 4) = pl[p];
+    for (int p = 0; p < 4; ++p) *reinterpret_cast<uint32_t*>(dig + (4 * h + p) * dig_stride(NT) + ((c0 >> 2) * NT + t) * 4) = pl[p];
   }
   if ((tid & 31) == 0) unit[h] = live ? __uint_as_float((unsigned)(eb - 29) << 23) : 0.0f;
-  __syncthreads();
 }
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -199,22 +205,20 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     int64_t tail_capacity, int tail_len) {
   constexpr int TYPES = 1 << (BITS - 1);
   constexpr int NMM = 4 * TYPES;   // matrix instructions per tile: 64 coordinates x TYPES bytes per lane, 16 at a time
-  constexpr int WH = 2 * NQ;       // heads the run's w table holds
-  // One pool, used in turn: during the set-up the query (float), its rotation, and the byte planes of coef[M] Pi q
-  // ([head][plane][k]) and of Phi q; in the tile loop the four waves' coefficient tiles.  The barrier behind the w
-  // table separates the two uses.
-  constexpr int SETUP_BYTES = 2 * SC_MAXG * D * 4 + SC_MAXG * 4 * TYPES * D + (QJL ? SC_MAXG * 4 * D : 0);
-  constexpr int CS_BYTES = 4 * 2 * 16 * CTLD * 2;            // the four waves' coefficient tiles
-  constexpr int LOOP_BYTES = CS_BYTES + SC_RUN_MAX * 32 * 16;   // and the run's low-rank operands
-  __shared__ __align__(16) unsigned char pool[SETUP_BYTES > LOOP_BYTES ? SETUP_BYTES : LOOP_BYTES];
-  float* qraw = reinterpret_cast<float*>(pool);
-  float* qrot = qraw + SC_MAXG * D;
-  unsigned char* qdig = pool + 2 * SC_MAXG * D * 4;
-  unsigned char* pdig = qdig + SC_MAXG * 4 * TYPES * D;
-  __shared__ __align__(16) float wbuf[SC_RUN_MAX * EOQ_RMAX_CAP * WH];   // [block of the run][component][head]: <v_i, q_h>/sqrt(d)
-  __shared__ int rank_s[SC_RUN_MAX];
+  // One pool, used in turn: during the set-up the rotated query and the byte planes of coef[M] Pi q ([head][plane][k])
+  // and of Phi q; in the tile loop the four waves' coefficient tiles.
+  constexpr int ROT_BYTES = SC_MAXG * D * 4 * (QJL ? 2 : 1);
+  constexpr int SETUP_BYTES = ROT_BYTES + SC_MAXG * 4 * dig_stride(TYPES) + (QJL ? SC_MAXG * 4 * dig_stride(1) : 0);
+  constexpr int CS_BYTES = 4 * 2 * 16 * CTLD * 2;
+  __shared__ __align__(16) unsigned char pool[SETUP_BYTES > CS_BYTES ? SETUP_BYTES : CS_BYTES];
+  float* qrot = reinterpret_cast<float*>(pool);
+  float* prot = qrot + SC_MAXG * D;
+  unsigned char* qdig = pool + ROT_BYTES;
+  unsigned char* pdig = qdig + SC_MAXG * 4 * dig_stride(TYPES);
+  // A operands of the low-rank product, components 16 k2 .. + 15 of every block of the run: entry (16 f + 2 h + part) of a
+  // block are components 8 f .. + 7 of head h, part 0 binary16(w), part 1 what that rounding lost
+  __shared__ __align__(16) uint4 wop[2][SC_RUN_MAX * 32];
   __shared__ __align__(16) uint2 nib_tab[256];
-  __shared__ unsigned max_s[SC_MAXG];
   __shared__ float qunit[SC_MAXG], punit[SC_MAXG];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave: scalar
@@ -229,10 +233,27 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
   if ((int)blockIdx.x >= runs) {   // a workgroup of the tail
     tail_scores(tail + sg * (size_t)tail_capacity * D, TAIL_TOK * ((int)blockIdx.x - runs), tail_len, q + q0, group,
-                scores + (sq * n_q_heads + kv * group) * T + (size_t)blocks_per_head * n, T, qraw, tid);
+                scores + (sq * n_q_heads + kv * group) * T + (size_t)blocks_per_head * n, T, qrot, tid);
     return;
   }
 
+  const int64_t jb0 = (int64_t)blockIdx.x * run;
+  const int nblk = (int)(min(jb0 + run, blocks_per_head) - jb0);
+  const int tpb = n / 32;
+  const int NT = nblk * tpb;
+  const size_t blk0 = sg * (size_t)block_capacity + jb0;   // the store holds block_capacity slots per head
+
+  // ---- set-up.  It is paid once per workgroup and is latency: everything that depends on nothing is requested first
+  // (ranks, query, tables), then the first tile and the right factors of the wave's share of the blocks, which travel while
+  // the rotated query is cut into bytes.  (One table row after the other behind a branch, and the products with the
+  // right factors as a loop of loads and sums over lanes, took 65 of 213 thousand cycles of a workgroup at 16 blocks of 512.)
+  int rk_all = rank_in[blk0 + min(lane & 15, nblk - 1)];   // ranks of the run's blocks, one per lane
+  H8 aq[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    aq[ks].u = (l16 < group) ? *reinterpret_cast<const uint4*>(q + q0 + l16 * D + 32 * ks + 8 * g) : make_uint4(0u, 0u, 0u, 0u);
+  TableRows<true> pi_rows;
+  pi_rows.load(pih, pih + D * D, wave, l16, g);
   {
     const int tn = tid & 15, xn = tid >> 4;
     uint32_t sd = 0u, td = 0u;
@@ -244,8 +265,6 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     }
     nib_tab[tid] = make_uint2(sd, td);
   }
-  for (int e = tid; e < SC_MAXG * D; e += THREADS) qraw[e] = (e < group * D) ? half_bits_to_float(q[q0 + e]) : 0.0f;
-  __syncthreads();
   // coefficients of the multilinear form of the magnitudes: level number sum_p m_p 2^p is centroid L/2 + level of the
   // ascending N(0,1) table; coef[M] = sum over subsets S of M of (-1)^(|M| - |S|) centroid[L/2 + S]
   float coef[TYPES];
@@ -257,87 +276,6 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
       if ((S & M) == S) c += ((__builtin_popcount(M ^ S) & 1) ? -1.0f : 1.0f) * tab[TYPES + S];
     coef[M] = c;
   }
-  // q' = Pi q (the rotation moved to the query side: <q, Pi^T z> = <Pi q, z>), then the byte planes of coef[M] q'
-  rotate_query(pih, pih + D * D, q + q0, group, qrot, wave, l16, g);
-  __syncthreads();
-  fixed_point_rows<TYPES>(qrot, coef, qdig, max_s, qunit, tid);
-  if constexpr (QJL) {
-    rotate_query(phih, nullptr, q + q0, group, qrot, wave, l16, g);
-    __syncthreads();
-    const float one[1] = {1.0f};
-    fixed_point_rows<1>(qrot, one, pdig, max_s, punit, tid);
-  }
-  // A operands: row l32 = byte plane l32 % 4 of head 2 (l32 / 8) + (l32 / 4) % 2; instruction i covers the 16 bytes of k
-  // from 16 i of lane half hf's 64 coordinates (64 TYPES bytes: per nibble of four coordinates the TYPES terms).  Kq / Kp:
-  // what one integer unit of head 2 qq + hf is worth in the logit.
-  const int arow = 4 * (2 * (l32 >> 3) + ((l32 >> 2) & 1)) + (l32 & 3);   // row of the byte planes: 4 head + plane
-  v4i Aq[NMM], Ap[QJL ? 4 : 1];
-  float Kq[NQ], Kp[QJL ? NQ : 1];
-  const float qjl_scale = sqrtf(1.5707963267948966f) / (float)D;
-#pragma unroll
-  for (int i = 0; i < NMM; ++i) Aq[i] = *reinterpret_cast<const v4i*>(qdig + ((size_t)arow * D + 64 * hf) * TYPES + 16 * i);
-#pragma unroll
-  for (int qq = 0; qq < NQ; ++qq) Kq[qq] = qunit[2 * qq + hf] * (1.0f / (float)D);   // z_hat = centroid / sqrt(d), logit = <q, x_hat> / sqrt(d)
-  if constexpr (QJL) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) Ap[i] = *reinterpret_cast<const v4i*>(pdig + arow * D + 64 * hf + 16 * i);
-#pragma unroll
-    for (int qq = 0; qq < NQ; ++qq) Kp[qq] = punit[2 * qq + hf] * (qjl_scale * inv_sqrt_d);
-  }
-
-  const int64_t jb0 = (int64_t)blockIdx.x * run;
-  const int nblk = (int)(min(jb0 + run, blocks_per_head) - jb0);
-  const int tpb = n / 32;
-  const int NT = nblk * tpb;
-  const size_t blk0 = sg * (size_t)block_capacity + jb0;   // the store holds block_capacity slots per head
-
-  // w[b][i][h] = <v_i, q_h>/sqrt(d) of every block of the run, up front (the low-rank term is <C_t, w_h>): all loads of
-  // the set-up are in flight together and the tile loop below has no barrier.  16 lanes per (component, head): one
-  // 16-byte load of eight entries of v_i each, then a sum over the DPP row.
-  if (tid < nblk) rank_s[tid] = min(max(rank_in[blk0 + tid], 0), r_max);   // records may come from storage: never index past r_max rows
-  __syncthreads();
-  int rtop = 0;
-  for (int b = 0; b < nblk; ++b) rtop = max(rtop, rank_s[b]);
-  for (int e0 = 0; e0 < nblk * rtop * (WH * 16); e0 += THREADS) {   // uniform trip count: whole rows reduce together
-    const int e = e0 + tid;
-    const int seg = e & 15, h = (e >> 4) & (WH - 1);
-    const int bi = e / (WH * 16), b = bi / rtop, i = bi - b * rtop;
-    const int rb = rank_s[min(b, nblk - 1)];
-    float acc = 0.0f;
-    if (b < nblk && i < rb) {
-      float v[8];
-      load8(rfac, EOQ_F16, ((blk0 + b) * r_max + i) * (size_t)D + 8 * seg, v);
-#pragma unroll
-      for (int x = 0; x < 8; ++x) acc = fmaf(v[x], qraw[h * D + 8 * seg + x], acc);
-    }
-    acc += dpp_mov<0xB1>(acc);
-    acc += dpp_mov<0x4E>(acc);
-    acc += dpp_mov<0x141>(acc);
-    acc += dpp_mov<0x140>(acc);
-    if (seg == 0 && b < nblk && i < rb) wbuf[(b * EOQ_RMAX_CAP + i) * WH + h] = acc * inv_sqrt_d;
-  }
-  __syncthreads();
-  // A operands of the low-rank product, components 0 .. 15, for every block of the run: row 8 qq + 4 f of the matrix
-  // instruction holds binary16(w) of head 2 qq + f, the row after it what that rounding lost, the other two rows are
-  // zero and not stored.  Entry (b, ci): lane half ci / 16 (components 8 hf + e), row group (ci / 2) % 8, part ci % 2.
-  uint4* wop = reinterpret_cast<uint4*>(pool + CS_BYTES);
-  for (int e = tid; e < nblk * 32; e += THREADS) {
-    const int b = e >> 5, ci = e & 31;
-    const int ohf = ci >> 4, l4 = (ci >> 1) & 7, part = ci & 1;
-    const int h = 2 * (l4 >> 1) + (l4 & 1), rb = rank_s[b];
-    H8 x;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int i = 8 * ohf + k;
-      const float w = (i < rb && h < WH) ? wbuf[(b * EOQ_RMAX_CAP + i) * WH + (h & (WH - 1))] : 0.0f;
-      const uint16_t hi = float_to_half_bits(w);
-      x.s[k] = part == 0 ? hi : float_to_half_bits(w - half_bits_to_float(hi));
-    }
-    wop[e] = x.u;
-  }
-  __syncthreads();
-  if (wave >= NT) return;
-
   // Buffer addressing: a resource descriptor in scalar registers, a scalar byte offset that moves from tile to tile and
   // a per-lane 32-bit offset that never changes -- no vector arithmetic per load.  The coefficients get a descriptor per
   // block that ends behind row rank - 1, and the range check covers the per-lane part of the offset, which holds the
@@ -367,7 +305,7 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   const __amdgpu_buffer_rsrc_t bgam = buffer_of(qnorms0, QJL ? (size_t)nblk * n * 2 : 0);
   const __amdgpu_buffer_rsrc_t bout = buffer_of(scores0 + (size_t)jb0 * n, ((size_t)group * T - (size_t)jb0 * n) * 4);
   const __amdgpu_buffer_rsrc_t bnone = buffer_of(scores0, 0);
-  const int rk_all = rank_s[min(lane, nblk - 1)];
+  rk_all = min(max(rk_all, 0), r_max);   // records may come from storage: never index past r_max rows
   auto rank_of = [&](int b) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(rk_all, b); };
   auto coef_buffer = [&](int b) __attribute__((always_inline)) {
     return buffer_of(lfac + (blk0 + b) * (size_t)r_max * n, (size_t)rank_of(b) * n * 2);
@@ -384,18 +322,10 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     }
   };
   // A operand of the low-rank product for block b of the run, components 16 k2 + 8 hf + e: row 8 qq + 4 f of the matrix
-  // instruction holds binary16(w) of head 2 qq + f, the row after it what that rounding lost, the other two rows zero
+  // instruction holds binary16(w) of head 2 qq + f, the row after it what that rounding lost, the other two rows are zero
   auto w_operand = [&](int b, int k2) __attribute__((always_inline)) {
-    const int h = 2 * (l32 >> 3) + ((l32 >> 2) & 1), part = l32 & 3;
-    const int rb = rank_of(b);
     H8 x;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i = 16 * k2 + 8 * hf + e;
-      const float w = (i < rb && h < WH && part < 2) ? wbuf[(b * EOQ_RMAX_CAP + i) * WH + (h & (WH - 1))] : 0.0f;
-      const uint16_t hi = float_to_half_bits(w);
-      x.s[e] = part == 0 ? hi : float_to_half_bits(w - half_bits_to_float(hi));
-    }
+    x.u = ((l32 & 3) < 2) ? wop[k2][b * 32 + 16 * hf + 2 * (l32 >> 2) + (l32 & 1)] : make_uint4(0u, 0u, 0u, 0u);
     return x;
   };
   // C[token l32][16 k2 + 8 hf + e] of the rows staged in the wave's coefficient tile: the B operand of that product
@@ -409,12 +339,101 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     return x;
   };
 
+  // the first tile's record bytes
+  TileFetch<BITS, QJL> f0, f1;
+  const int count = (NT - wave + 3) / 4;        // tiles of this wave: wave, wave + 4, ... (a block has four or more)
+  const int tok_last = 32 * (wave + 4 * (count - 1));
+  int tok_r = 32 * wave, b_r = 0, end_r = n;                  // next tile to request: first token, block, end of the block
+  __amdgpu_buffer_rsrc_t cfd = coef_buffer(0);
+#define EOQ_SC_REQUEST(F)                    \
+  if (tok_r >= end_r) {                      \
+    ++b_r;                                   \
+    end_r += n;                              \
+    cfd = coef_buffer(b_r);                  \
+  }                                          \
+  request(F, tok_r, b_r, cfd);               \
+  tok_r = min(tok_r + 128, tok_last);
+  // q' = Pi q (the rotation moved to the query side: <q, Pi^T z> = <Pi q, z>), and Phi q
+  pi_rows.rotate(aq, qrot, wave, l16, g);
+  if constexpr (QJL) {
+    TableRows<false> phi_rows;
+    phi_rows.load(phih, nullptr, wave, l16, g);
+    phi_rows.rotate(aq, prot, wave, l16, g);
+  }
+  EOQ_SC_REQUEST(f0)
+  // w[i][h] = <v_i, q_h> / sqrt(d) of the run's blocks (the low-rank term is <C_t, w_h>): the same matrix product with the
+  // right factors as table, block b by wave b % 4, rows at and above the rank zero by the descriptor; component 16 k2 + l16
+  constexpr int VB = SC_RUN_MAX / 4;
+  H8 vrow[VB][4];
+  auto load_v = [&](H8 (&v)[4], int b, int k2) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t vb = buffer_of(rfac + (blk0 + b) * (size_t)r_max * D, (size_t)rank_of(b) * D * 2);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(vb, (uint32_t)(((16 * k2 + l16) * D + 32 * ks + 8 * g) * 2), 0, 0);
+      v[ks].u = make_uint4(x[0], x[1], x[2], x[3]);
+    }
+  };
+  auto put_w = [&](const H8 (&v)[4], int b, int k2) __attribute__((always_inline)) {
+    float4v acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = mfma32(aq[ks], v[ks], acc);
+    uint16_t* dst = reinterpret_cast<uint16_t*>(&wop[k2][b * 32 + 16 * (l16 >> 3)]) + (l16 & 7);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int h = 4 * g + e;
+      if (h < SC_MAXG) {
+        const float w = acc[e] * inv_sqrt_d;
+        const uint16_t hi = float_to_half_bits(w);
+        dst[16 * h] = hi;
+        dst[16 * h + 8] = float_to_half_bits(w - half_bits_to_float(hi));
+      }
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < VB; ++k)
+    if (4 * k + wave < nblk) load_v(vrow[k], 4 * k + wave, 0);   // uniform
+  __syncthreads();   // qrot (and prot) written
+  fixed_point_rows<TYPES>(qrot, coef, qdig, qunit, tid);
+  if constexpr (QJL) {
+    const float one[1] = {1.0f};
+    fixed_point_rows<1>(prot, one, pdig, punit, tid);
+  }
+#pragma unroll
+  for (int k = 0; k < VB; ++k)
+    if (4 * k + wave < nblk) {
+      put_w(vrow[k], 4 * k + wave, 0);
+      if (rank_of(4 * k + wave) > 16) {   // rare
+        load_v(vrow[k], 4 * k + wave, 1);
+        put_w(vrow[k], 4 * k + wave, 1);
+      }
+    }
+  __syncthreads();   // byte planes and low-rank operands written
+  // A operands: row l32 = byte plane l32 % 4 of head 2 (l32 / 8) + (l32 / 4) % 2; instruction i covers the 16 bytes of k
+  // from 16 i of lane half hf's 64 coordinates (64 TYPES bytes: per nibble of four coordinates the TYPES terms).  Kq / Kp:
+  // what one integer unit of head 2 qq + hf is worth in the logit.
+  const int arow = 4 * (2 * (l32 >> 3) + ((l32 >> 2) & 1)) + (l32 & 3);   // row of the byte planes: 4 head + plane
+  v4i Aq[NMM], Ap[QJL ? 4 : 1];
+  float Kq[NQ], Kp[QJL ? NQ : 1];
+  const float qjl_scale = sqrtf(1.5707963267948966f) / (float)D;
+#pragma unroll
+  for (int i = 0; i < NMM; ++i) Aq[i] = *reinterpret_cast<const v4i*>(qdig + arow * dig_stride(TYPES) + 64 * TYPES * hf + 16 * i);
+#pragma unroll
+  for (int qq = 0; qq < NQ; ++qq) Kq[qq] = qunit[2 * qq + hf] * (1.0f / (float)D);   // z_hat = centroid / sqrt(d), logit = <q, x_hat> / sqrt(d)
+  if constexpr (QJL) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Ap[i] = *reinterpret_cast<const v4i*>(pdig + arow * dig_stride(1) + 64 * hf + 16 * i);
+#pragma unroll
+    for (int qq = 0; qq < NQ; ++qq) Kp[qq] = punit[2 * qq + hf] * (qjl_scale * inv_sqrt_d);
+  }
+
+  __syncthreads();   // the pool changes hands
+
   int wb = -1;   // block of the run whose w operand the wave holds
   H8 Aw;
   Aw.u = make_uint4(0u, 0u, 0u, 0u);
   auto work = [&](TileFetch<BITS, QJL>& cur, int tok, int b, int r, bool valid) __attribute__((always_inline)) {
     if (b != wb) {   // uniform
-      Aw.u = ((l32 & 3) < 2) ? wop[b * 32 + 16 * hf + 2 * (l32 >> 2) + (l32 & 1)] : make_uint4(0u, 0u, 0u, 0u);
+      Aw = w_operand(b, 0);
       wb = b;
     }
     // ---- the integer term: the lane's 64 coordinates, byte kk of every plane at a time ----
@@ -529,20 +548,7 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   // Two register sets in turn: the next tile is on its way while this one is worked on.  The loop body has no branch
   // around a memory instruction (a wait can then name exactly the loads it needs): behind the wave's last tile a
   // request fetches that tile once more and a pass stores nothing.
-  TileFetch<BITS, QJL> f0, f1;
-  const int count = (NT - wave + 3) / 4;        // tiles of this wave: wave, wave + 4, ...
-  const int tok_last = 32 * (wave + 4 * (count - 1));
-  int tok_r = 32 * wave, b_r = 0, end_r = n;                  // next tile to request: first token, block, end of the block
   int tok_w = 32 * wave, b_w = 0, end_w = n, r_w = rank_of(0), nwk = 0;   // next tile to work on
-  __amdgpu_buffer_rsrc_t cfd = coef_buffer(0);
-#define EOQ_SC_REQUEST(F)                    \
-  if (tok_r >= end_r) {                      \
-    ++b_r;                                   \
-    end_r += n;                              \
-    cfd = coef_buffer(b_r);                  \
-  }                                          \
-  request(F, tok_r, b_r, cfd);               \
-  tok_r = min(tok_r + 128, tok_last);
 #define EOQ_SC_WORK(F)                       \
   if (tok_w >= end_w) {                      \
     ++b_w;                                   \
@@ -552,7 +558,6 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   work(F, tok_w, b_w, r_w, nwk < count);     \
   tok_w = min(tok_w + 128, tok_last);        \
   ++nwk;
-  EOQ_SC_REQUEST(f0)
   for (int it = 0; it < (count + 1) / 2; ++it) {
     EOQ_SC_REQUEST(f1)
     EOQ_SC_WORK(f0)
@@ -571,12 +576,17 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   if (block_capacity <= 0) block_capacity = blocks_per_head;
   if (score_stride <= 0) score_stride = blocks_per_head * L.n;
   if (L.ev) (void)hipEventRecord(L.ev[6], L.stream);
-  // blocks per workgroup: the query set-up is paid once per workgroup, so runs are as long as they can be (16) while the
-  // grid still has a workgroup for each of the 4 x 256 places on the chip
-  int64_t run = (sg_total * blocks_per_head + 1023) / 1024;
+  const int64_t tail_groups = (tail_len + TAIL_TOK - 1) / TAIL_TOK;
+  // blocks per workgroup: the set-up is paid once per workgroup, so runs are as long as they can be (16) while the grid
+  // still has a workgroup for each place on the chip (256 compute units times what registers allow; a workgroup of the tail
+  // is short, four of them count as one).  A second, partly filled round of workgroups costs a set-up and a run, more
+  // than runs that are one block longer: 612 blocks of 512, 4 bits, 51 us in two rounds, 34 in one.
+  const int64_t places = 256 * (qjl ? (L.bits <= 2 ? 3 : (L.bits == 3 ? 2 : 1)) : (L.bits <= 2 ? 4 : (L.bits == 3 ? 3 : 2)));
+  const int64_t tail_places = sg_total * tail_groups / 4;
+  const int64_t room = places - (tail_places < places / 2 ? tail_places : places / 2);
+  int64_t run = (sg_total * blocks_per_head + room - 1) / room;
   run = run < 1 ? 1 : (run > SC_RUN_MAX ? SC_RUN_MAX : run);
   const int64_t runs = (blocks_per_head + run - 1) / run;
-  const int64_t tail_groups = (tail_len + TAIL_TOK - 1) / TAIL_TOK;
   if (sg_total > 65535 || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(runs + tail_groups), (unsigned)sg_total), block(THREADS);
   const uint16_t* q = static_cast<const uint16_t*>(q_fp16);
