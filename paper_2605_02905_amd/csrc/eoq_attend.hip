@@ -581,13 +581,14 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
   }
 }
 
-// out[s][h][j] = sum_c Pi[c][j] a_h[c] + lin_h[j], the runs added in order.  One workgroup per (sequence, KV head,
-// query head of the group): lane (j, half) sums the rotated-domain partials (half 0) or the low-rank partials (half 1)
-// of the runs, one load per run with sixteen in flight; the rotation back is split between the halves (coordinates
-// 64 half .. 64 half + 63).  With tail_len > 0 the uncompressed binary16 tail values are added, + sum_t weights[..,
-// tail_offset + t] tail[t]: sixteen lanes share a token (16 bytes each), sixteen tokens at a time, the sixteen sums per
-// coordinate met through LDS in order.  (One lane per coordinate and every second token, as before, is a chain of
-// tail_len / 2 loads: 16 us at 389 tokens.)
+// out[s][h][j] = sum_c Pi[c][j] a_h[c] + lin_h[j].  One workgroup per (sequence, KV head, query head of the group), all of
+// it latency: the lane's part of Pi (rows 16 rg .. + 15 of four columns) is requested first and travels while the partials
+// of the runs are summed (a run's 128 rotated-domain and 128 low-rank sums are 64 loads of 16 bytes, one per lane of a
+// wave; wave w takes the runs w, w + 4, ..); everything then meets through LDS in a fixed order.  (Pi requested when the sums
+// were there, one element per load: 6.4 us for 32 heads of 12 runs, now 4.8.)  With tail_len > 0 the uncompressed
+// binary16 tail values are added, + sum_t weights[.., tail_offset + t] tail[t]: sixteen lanes share a token (16 bytes
+// each), sixteen tokens at a time.  (One lane per coordinate and every second token was a chain of tail_len / 2 loads:
+// 16 us at 389 tokens.)
 __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_heads, int group, int runs,
                                                                     const float* __restrict__ pi,
                                                                     const float* __restrict__ partial,
@@ -596,28 +597,32 @@ __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_hea
                                                                     int64_t weight_stride, int64_t tail_offset,
                                                                     const uint16_t* __restrict__ tail,
                                                                     int64_t tail_capacity, int tail_len) {
-  __shared__ float a_s[D];
-  __shared__ float meet_s[D];
+  __shared__ __align__(16) float part_s[4 * 2 * D];   // [wave][rotated domain, low-rank][coordinate]
+  __shared__ __align__(16) float rot_s[8 * D];        // [row group of Pi][coordinate]
   __shared__ __align__(16) float tail_s[16 * D];
-  const int tid = threadIdx.x;
-  const int j = tid & (D - 1), half = tid >> 7;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j4 = tid & 31, rg = tid >> 5;
   const size_t sg = blockIdx.x;
   const int h = blockIdx.y;
   const size_t sq = sg / n_kv_heads, kv = sg % n_kv_heads;
   const int n_q_heads = n_kv_heads * group;
-  float sum = 0.0f;
+  float4v pv[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) pv[i] = *reinterpret_cast<const float4v*>(pi + (16 * rg + i) * D + 4 * j4);
+  __builtin_amdgcn_sched_barrier(0);   // on their way before anything else
   {
-    const float* src = partial + (sg * runs * 2 * MAXG + (size_t)(half * MAXG + h)) * D + j;
-#pragma unroll 16
-    for (int rn = 0; rn < runs; ++rn) sum += src[(size_t)rn * 2 * MAXG * D];
+    float4v sum = {0.f, 0.f, 0.f, 0.f};
+    const float* src = partial + (sg * runs * 2 * MAXG + (size_t)((lane >> 5) * MAXG + h)) * D + 4 * j4;
+#pragma unroll 8
+    for (int rn = wave; rn < runs; rn += 4) sum += *reinterpret_cast<const float4v*>(src + (size_t)rn * 2 * MAXG * D);
+    *reinterpret_cast<float4v*>(part_s + wave * 2 * D + 4 * lane) = sum;
   }
-  if (half == 0) a_s[j] = sum;
   if (tail_len > 0) {
     const float* wrow = weights + (sq * n_q_heads + kv * group + h) * (size_t)weight_stride + tail_offset;
     const int l16 = tid & 15, ts = tid >> 4;
     const uint16_t* trow = tail + sg * (size_t)tail_capacity * D + 8 * l16;
     float t8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
+#pragma unroll 8
     for (int t = ts; t < tail_len; t += 16) {
       float x[8];
       load8(trow, EOQ_F16, (size_t)t * D, x);
@@ -629,16 +634,31 @@ __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_hea
     *reinterpret_cast<float4*>(tail_s + ts * D + 8 * l16 + 4) = make_float4(t8[4], t8[5], t8[6], t8[7]);
   }
   __syncthreads();
-  float acc = (half == 1) ? sum : 0.0f;   // half 1 starts from the low-rank term
-#pragma unroll 16
-  for (int cc = 64 * half; cc < 64 * half + 64; ++cc) acc = fmaf(pi[cc * D + j], a_s[cc], acc);
-  if (tail_len > 0) {
+  float4v acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < 8; ++s) acc += tail_s[(8 * half + s) * D + j];
+  for (int i4 = 0; i4 < 4; ++i4) {
+    const float* a = part_s + 16 * rg + 4 * i4;
+    const float4v a4 = (*reinterpret_cast<const float4v*>(a) + *reinterpret_cast<const float4v*>(a + 2 * D)) +
+                       (*reinterpret_cast<const float4v*>(a + 4 * D) + *reinterpret_cast<const float4v*>(a + 6 * D));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(pv[4 * i4 + i][e], a4[i], acc[e]);
   }
-  if (half == 1) meet_s[j] = acc;
+  *reinterpret_cast<float4v*>(rot_s + rg * D + 4 * j4) = acc;
   __syncthreads();
-  if (half == 0) out[(sq * n_q_heads + kv * group + h) * D + j] = acc + meet_s[j];
+  if (tid < D) {
+    float v = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v += rot_s[k * D + tid];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v += part_s[w * 2 * D + D + tid];
+    if (tail_len > 0) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v += tail_s[k * D + tid];
+    }
+    out[(sq * n_q_heads + kv * group + h) * D + tid] = v;
+  }
 }
 
 // Row-wise softmax in place (the attention weights of Sec. 2.1), one workgroup of NT lanes per row.  The row passes
