@@ -145,8 +145,8 @@ class Packed:
     flags: torch.Tensor   # int32  [B]
 
     def c_struct(self) -> _Packed:
-        return _Packed(*(t.data_ptr() for t in (self.codes, self.norms, self.rank, self.phi, self.sigma,
-                                                 self.lfac, self.rfac, self.flags)))
+        return _Packed(self.codes.data_ptr(), self.norms.data_ptr(), self.rank.data_ptr(), self.phi.data_ptr(),
+                       self.sigma.data_ptr(), self.lfac.data_ptr(), self.rfac.data_ptr(), self.flags.data_ptr())
 
     @staticmethod
     def empty(B: int, n: int, d: int, bits: int, r_max: int, device) -> "Packed":
@@ -174,7 +174,7 @@ class FactorCodes:
     phi16: torch.Tensor   # float16 [B, r_max]
 
     def c_struct(self) -> _FactorCodes:
-        return _FactorCodes(*(t.data_ptr() for t in (self.lcodes, self.rcodes, self.fbook, self.phi16)))
+        return _FactorCodes(self.lcodes.data_ptr(), self.rcodes.data_ptr(), self.fbook.data_ptr(), self.phi16.data_ptr())
 
     @staticmethod
     def empty(B: int, n: int, d: int, r_max: int, device) -> "FactorCodes":
@@ -203,8 +203,14 @@ class Qjl:
                    torch.empty(B, n, dtype=torch.float16, device=device))
 
 
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
 def _stream_ptr(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    """The device's current stream, without a Stream object around it: 0.2 instead of 2.1 us, three times in a decode
+    step of 27 us."""
+    index = device.index
+    return torch.cuda.current_stream(device).cuda_stream if index is None else _raw_stream(index)
 
 
 class Context:
@@ -347,18 +353,19 @@ class Context:
         dimension (blocks_filled * n + tail_len when `out` is not given)."""
         assert q.is_cuda and q.is_contiguous() and q.dtype == torch.float16
         n_seq, n_q_heads, _ = q.shape
-        assert keys.rank.shape[0] >= n_seq * n_kv_heads * block_capacity
+        assert keys.rank.size(0) >= n_seq * n_kv_heads * block_capacity
         tail_cap = 0
         if tail is not None:
             assert tail.is_cuda and tail.is_contiguous() and tail.dtype == torch.float16
-            assert tail.shape[0] == n_seq and tail.shape[1] == n_kv_heads and tail.shape[3] == self.d
-            tail_cap = tail.shape[2]
+            t_seq, t_heads, tail_cap, t_d = tail.shape
+            assert t_seq == n_seq and t_heads == n_kv_heads and t_d == self.d
         if out is None:
             out = torch.empty(n_seq, n_q_heads, blocks_filled * self.n + tail_len, dtype=torch.float32, device=q.device)
-        assert out.is_contiguous() and out.shape[:2] == (n_seq, n_q_heads)
+        o_seq, o_heads, stride = out.shape
+        assert out.is_contiguous() and o_seq == n_seq and o_heads == n_q_heads
         self._check(lib().eoq_scores_stream(self._h, keys.c_struct(), n_seq, n_kv_heads, block_capacity, blocks_filled,
                                             tail.data_ptr() if tail is not None else None, tail_cap, tail_len,
-                                            q.data_ptr(), n_q_heads, out.data_ptr(), out.shape[2],
+                                            q.data_ptr(), n_q_heads, out.data_ptr(), stride,
                                             _stream_ptr(q.device)))
         return out
 
@@ -389,7 +396,7 @@ class Context:
         """In-place softmax over the first `length` entries (default: all) of every row of a contiguous float32
         device tensor [..., row_stride]."""
         assert scores.is_cuda and scores.is_contiguous() and scores.dtype == torch.float32
-        stride = scores.shape[-1]
+        stride = scores.size(-1)
         rows = scores.numel() // stride if stride else 0
         self._check(lib().eoq_softmax(self._h, scores.data_ptr(), rows, stride if length is None else length, stride,
                                       _stream_ptr(scores.device)))
@@ -408,7 +415,7 @@ class Context:
             block_capacity = values.rank.shape[0] // (n_seq * n_kv_heads)
         if blocks_filled is None:
             blocks_filled = block_capacity
-        assert values.rank.shape[0] >= n_seq * n_kv_heads * block_capacity
+        assert values.rank.size(0) >= n_seq * n_kv_heads * block_capacity
         if out is None:
             out = torch.empty(n_seq, n_q_heads, self.d, dtype=torch.float32, device=weights.device)
         need = self.eoq_attend_workspace_bytes(n_seq, n_kv_heads, blocks_filled)
@@ -425,12 +432,12 @@ class Context:
         """eoq_attend plus the float16 tail values [n_seq, n_kv_heads, tail_capacity, d] (weights behind the blocks')."""
         assert weights.is_cuda and weights.is_contiguous() and weights.dtype == torch.float32
         n_seq, n_q_heads, stride = weights.shape
-        assert values.rank.shape[0] >= n_seq * n_kv_heads * block_capacity
+        assert values.rank.size(0) >= n_seq * n_kv_heads * block_capacity
         tail_cap = 0
         if tail is not None:
             assert tail.is_cuda and tail.is_contiguous() and tail.dtype == torch.float16
-            assert tail.shape[0] == n_seq and tail.shape[1] == n_kv_heads and tail.shape[3] == self.d
-            tail_cap = tail.shape[2]
+            t_seq, t_heads, tail_cap, t_d = tail.shape
+            assert t_seq == n_seq and t_heads == n_kv_heads and t_d == self.d
         if out is None:
             out = torch.empty(n_seq, n_q_heads, self.d, dtype=torch.float32, device=weights.device)
         if workspace is None:
