@@ -220,31 +220,28 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
   // output saturates like every other binary16 quantity of the record, without a clamp per element
   set_fp16_overflow_clamp();
 
-  if constexpr (BITS <= 2) build_centroid_table<BITS>(cen_tab, tab, tid);
-  else if constexpr (BITS == 3) build_magnitude_table3(cen_tab, tab, tid);
-  else build_mask_table(mask_tab, tid);
-  Mags<BITS> mg;
-  if constexpr (BITS == 4) mg.load(tab);
-  __syncthreads();   // the only one: from here on the waves do not meet again
-
   const int tiles_per_unit = (n / 32) >> parts_log2;
   const int part_mask = (1 << parts_log2) - 1;
   const int64_t U = B << parts_log2;
   const int64_t GW = (int64_t)gridDim.x * 4;
   int64_t u = (int64_t)blockIdx.x * 4 + wave;
-  if (u >= U) return;
+  const bool idle = u >= U;   // a wave of the last workgroup without a unit: it helps with the set-up
+  if (idle) u = U - 1;
 
-  // stationary operand: rows j = 32 cb + l32 of Pi^T rounded to binary16, contraction slots in the permuted order
+  // ---- set-up: two waits.  First the ranks, Pi^T (by rows, the whole workgroup) and the first tile's codes; then what
+  // needs the rank, which travels while Pi^T goes through LDS into operand order.  (Every wave reading its operand from
+  // memory, 64 rows per instruction, and four waits in a row: 18.7 us for 371 blocks of 128 at 4 bits, now MEASURED.) ----
+  const __amdgpu_buffer_rsrc_t ranks = buffer_of(rank_in, (size_t)B * 4);
+  int64_t blk = u >> parts_log2;
+  int part = (int)u & part_mask;
+  const int rk_first = rank_request(ranks, blk);
+  int rk_next = rank_request(ranks, min((u + GW) >> parts_log2, B - 1));   // behind the last unit: not used
   const uint16_t* pit_hi = pih + 2 * D * D;
-  H8 Ap[4][8];
+  u32x4 prow[8];   // row 16 k + tid / 16
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      Ap[cb][kk].u = *reinterpret_cast<const uint4*>(pit_hi + (32 * cb + l32) * D + 64 * hf + 8 * kk);
+  for (int k = 0; k < 8; ++k) prow[k] = *reinterpret_cast<const u32x4*>(pit_hi + (16 * k + (tid >> 4)) * D + 8 * (tid & 15));
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
 
-  const __amdgpu_buffer_rsrc_t ranks = buffer_of(rank_in, (size_t)B * 4);
   // per-lane parts of the offsets (they never change)
   const uint32_t vo_code = (uint32_t)(l32 * ROWB + 8 * hf);
   const uint32_t vo_norm = (uint32_t)(2 * l32);
@@ -265,10 +262,13 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
 #pragma unroll
     for (int p = 0; p < BITS; ++p) f.pl[p] = __builtin_amdgcn_raw_buffer_load_b64(s.codes, vo_code + 16 * p, t0 * ROWB, 0);
     f.rho = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(s.norms, vo_norm, t0 * 2, 0);
+  };
+  auto request_cf = [&](TileFetch<BITS>& f, const TileSource& s, int t0) __attribute__((always_inline)) {
     f.cf = __builtin_amdgcn_raw_buffer_load_b128(s.lfac, vo_cf, t0 * 2, 0);
   };
   // V[8 hf + e + 16 k2][32 cb + l32], e = 0 .. 7, of the rows staged in the wave's LDS tile: an A operand of the low-rank product
-  auto v_operand = [&](int cb) __attribute__((always_inline)) {
+  auto v_operand = [&](int cb, int lane) __attribute__((always_inline)) {
+    const int l32 = lane & 31, hf = lane >> 5;
     H8 x;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -288,42 +288,77 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
     return x;
   };
 
-  // state of the unit being worked on and of the one after it
-  int64_t blk = u >> parts_log2;
-  int part = (int)u & part_mask;
-  int r = rank_value(rank_request(ranks, blk), r_max);
-  int rk_next = rank_request(ranks, min((u + GW) >> parts_log2, B - 1));   // behind the last unit: not used
-  TileSource src = source_of(blk, r, true);
   TileFetch<BITS> cur, nxt;
+  TileSource src = source_of(blk, 0, true);
   request(cur, src, 32 * part * tiles_per_unit);
+  if constexpr (BITS <= 2) build_centroid_table<BITS>(cen_tab, tab, tid);
+  else if constexpr (BITS == 3) build_magnitude_table3(cen_tab, tab, tid);
+  else build_mask_table(mask_tab, tid);
+  Mags<BITS> mg;
+  if constexpr (BITS == 4) mg.load(tab);
+  int r = rank_value(rk_first, r_max);
+  src = source_of(blk, r, true);
+  request_cf(cur, src, 32 * part * tiles_per_unit);
+  // rows of a block's right factors travel as 16-byte pieces (rows at and above the rank read zero), change lanes through
+  // the wave's LDS tile and are read back one binary16 at a time in operand order; rows 16 .. 31 (blocks of rank > 16,
+  // rare) are kept in LDS as finished operands
+  auto request_v = [&](u32x4 (&vrow)[4], int k2) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t vbuf = buffer_of(rfac + (size_t)blk * r_max * D, (size_t)r * D * 2);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) vrow[k] = __builtin_amdgcn_raw_buffer_load_b128(vbuf, vo_row + (16 * k2 + 4 * k) * (D * 2), 0, 0);
+  };
+  auto stage_v = [&](const u32x4 (&vrow)[4], int lane) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) *reinterpret_cast<u32x4*>(ot + (4 * k + (lane >> 4)) * ZLD + (lane & 15) * 8) = vrow[k];
+    __builtin_amdgcn_wave_barrier();
+  };
+  u32x4 vfirst[4];
+  request_v(vfirst, 0);
+  // stationary operand: rows j = 32 cb + l32 of Pi^T rounded to binary16, contraction slots in the permuted order; the
+  // rows pass through the output tiles' memory
+#pragma unroll
+  for (int k = 0; k < 8; ++k) *reinterpret_cast<u32x4*>(Ot + (16 * k + (tid >> 4)) * ZLD + 8 * (tid & 15)) = prow[k];
+  __syncthreads();
+  H8 Ap[4][8];
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) Ap[cb][kk].u = *reinterpret_cast<const uint4*>(Ot + (32 * cb + l32) * ZLD + 64 * hf + 8 * kk);
+  __syncthreads();   // from here on the waves do not meet again
+  __builtin_amdgcn_sched_barrier(0);
+  if (idle) return;
   H8 Bv[4];   // right factors of the unit's block as A operand of the low-rank product: V[8 hf + e][32 cb + l32]
-  __amdgpu_buffer_rsrc_t obuf = buffer_of(out, 0);
+  __amdgpu_buffer_rsrc_t obuf = buffer_of(out + (size_t)blk * n * D, (size_t)n * D * 2);
   int ti = 0;
+  bool fresh = r > 16;   // the right factors are still to be fetched
+  if (!fresh) {
+    stage_v(vfirst, lane);
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) Bv[cb] = v_operand(cb, lane);
+    __builtin_amdgcn_wave_barrier();
+  }
   // nothing of the set-up is left in flight: inside the loop a wait then only ever covers what the loop itself
   // requested, and never the stores of the tile before
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
   for (;;) {
-    if (ti == 0) {
-      // rows of the block's right factors travel as 16-byte pieces (rows at and above the rank read zero), change
-      // lanes through the wave's LDS tile and are read back one binary16 at a time in operand order; rows 16 .. 31
-      // (blocks of rank > 16, rare) are kept in LDS as finished operands
-      const __amdgpu_buffer_rsrc_t vbuf = buffer_of(rfac + (size_t)blk * r_max * D, (size_t)r * D * 2);
-      for (int k2 = (r > 16) ? 1 : 0; k2 >= 0; --k2) {   // uniform
+    if (fresh) {
+      fresh = false;
+      int at = lane;
+      asm volatile("" : "+v"(at));   // opaque: the addresses are computed here, not kept across the loop in scratch memory
+      if (r > 16) {   // uniform
         u32x4 vrow[4];
+        request_v(vrow, 1);
+        stage_v(vrow, at);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) vrow[k] = __builtin_amdgcn_raw_buffer_load_b128(vbuf, vo_row + (16 * k2 + 4 * k) * (D * 2), 0, 0);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) *reinterpret_cast<u32x4*>(ot + (4 * k + (lane >> 4)) * ZLD + (lane & 15) * 8) = vrow[k];
-        __builtin_amdgcn_wave_barrier();
-        if (k2 == 1) {
-#pragma unroll
-          for (int cb = 0; cb < 4; ++cb) v2[cb * 64 + lane] = v_operand(cb).u;
-        } else {
-#pragma unroll
-          for (int cb = 0; cb < 4; ++cb) Bv[cb] = v_operand(cb);
-        }
+        for (int cb = 0; cb < 4; ++cb) v2[cb * 64 + at] = v_operand(cb, at).u;
         __builtin_amdgcn_wave_barrier();
       }
+      u32x4 vrow[4];
+      request_v(vrow, 0);
+      stage_v(vrow, at);
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) Bv[cb] = v_operand(cb, at);
+      __builtin_amdgcn_wave_barrier();
       obuf = buffer_of(out + (size_t)blk * n * D, (size_t)n * D * 2);
     }
     const int t0 = 32 * (part * tiles_per_unit + ti);
@@ -342,6 +377,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
       t_n = 32 * part_n * tiles_per_unit;
     }
     request(nxt, src, t_n);
+    request_cf(nxt, src, t_n);
 
     // ---- this tile ----
     const float rs = half_bits_to_float((uint16_t)cur.rho) * inv_sqrt_d;
@@ -457,6 +493,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
       part = part_n;
       r = r_n;
       ti = 0;
+      fresh = true;
     } else {
       ++ti;
     }
