@@ -79,28 +79,6 @@ __device__ __forceinline__ void build_centroid_table(uint2* tab4, const float* _
   }
 }
 
-// Tables for codes of 3 bits: entry (nibble of m_0 | nibble of m_1 << 4) -> the binary16 magnitudes of four coordinates
-// (m_p = magnitude bit p of the code: plane p where the sign plane is set, its complement where it is clear; level
-// m_0 + 2 m_1 is centroid L/2 + level of the ascending table), and behind them 16 entries (nibble of the sign plane) ->
-// the sign bits of the four halfwords (set where the plane bit is clear: negative).
-__device__ __forceinline__ void build_magnitude_table3(uint2* tab4, const float* __restrict__ cent, int tid) {
-  if (tid < 256) {
-    const int n0 = tid & 15, n1 = tid >> 4;
-    uint16_t h[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) h[e] = float_to_half_bits(cent[4 + (((n0 >> e) & 1) | (((n1 >> e) & 1) << 1))]);
-    tab4[tid] = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-    if (tid < 16) {
-      uint32_t lo = 0u, hi = 0u;
-      if (!(tid & 1)) lo |= 0x8000u;
-      if (!(tid & 2)) lo |= 0x80000000u;
-      if (!(tid & 4)) hi |= 0x8000u;
-      if (!(tid & 8)) hi |= 0x80000000u;
-      tab4[256 + tid] = make_uint2(lo, hi);
-    }
-  }
-}
-
 // Centroid magnitudes of the symmetric codebook as duplicated binary16 pairs: mag[m] = (h << 16) | h with
 // h = binary16(centroid[L/2 + m]), m = 0 .. L/2-1.
 template <int BITS>
@@ -206,11 +184,11 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
     int n, int r_max, int64_t B, int parts_log2, const uint16_t* __restrict__ pih, const float* __restrict__ tab,
     const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms, const int32_t* __restrict__ rank_in,
     const uint16_t* __restrict__ lfac, const uint16_t* __restrict__ rfac, uint16_t* __restrict__ out) {
-  __shared__ __align__(16) uint4 mask_tab[256];            // BITS = 4: plane byte -> halfword masks; BITS <= 3: the nibble tables
+  __shared__ __align__(16) uint2 cen_tab[BITS <= 2 ? 256 : 128];   // BITS <= 2: centroids by two nibbles; else 256 pairs of centroids by two codes
   __shared__ __align__(16) uint16_t Ot[4 * 32 * ZLD];      // per wave: one output tile, [token][column]
   __shared__ __align__(16) uint16_t Cs[4 * 2 * 16 * CTLD]; // per wave: coefficient rows 0..15 and 16..31 of a tile
   __shared__ __align__(16) uint4 V2[4 * 4 * 64];           // per wave: operands of components 16..31 (blocks of rank > 16)
-  uint2* cen_tab = reinterpret_cast<uint2*>(mask_tab);
+  uint32_t* pair_tab = reinterpret_cast<uint32_t*>(cen_tab);
   constexpr int ROWB = BITS * D / 8;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -230,7 +208,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
 
   // ---- set-up: two waits.  First the ranks, Pi^T (by rows, the whole workgroup) and the first tile's codes; then what
   // needs the rank, which travels while Pi^T goes through LDS into operand order.  (Every wave reading its operand from
-  // memory, 64 rows per instruction, and four waits in a row: 18.7 us for 371 blocks of 128 at 4 bits, now MEASURED.) ----
+  // memory, 64 rows per instruction, and four waits in a row: 18.7 us for 371 blocks of 128 at 4 bits, then 14.6.) ----
   const __amdgpu_buffer_rsrc_t ranks = buffer_of(rank_in, (size_t)B * 4);
   int64_t blk = u >> parts_log2;
   int part = (int)u & part_mask;
@@ -292,10 +270,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
   TileSource src = source_of(blk, 0, true);
   request(cur, src, 32 * part * tiles_per_unit);
   if constexpr (BITS <= 2) build_centroid_table<BITS>(cen_tab, tab, tid);
-  else if constexpr (BITS == 3) build_magnitude_table3(cen_tab, tab, tid);
-  else build_mask_table(mask_tab, tid);
-  Mags<BITS> mg;
-  if constexpr (BITS == 4) mg.load(tab);
+  else pair_tab[tid] = (uint32_t)float_to_half_bits(tab[tid & ((1 << BITS) - 1)]) | ((uint32_t)float_to_half_bits(tab[(tid >> 4) & ((1 << BITS) - 1)]) << 16);
   int r = rank_value(rk_first, r_max);
   src = source_of(blk, r, true);
   request_cf(cur, src, 32 * part * tiles_per_unit);
@@ -317,15 +292,24 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
   // stationary operand: rows j = 32 cb + l32 of Pi^T rounded to binary16, contraction slots in the permuted order; the
   // rows pass through the output tiles' memory
 #pragma unroll
-  for (int k = 0; k < 8; ++k) *reinterpret_cast<u32x4*>(Ot + (16 * k + (tid >> 4)) * ZLD + 8 * (tid & 15)) = prow[k];
+  for (int k = 0; k < 8; ++k) {
+    if constexpr (BITS > 2) {   // slots 2 k, 2 k + 1 are coordinates k, k + 4 of an instruction's eight
+      const u32x4 x = prow[k];
+      prow[k] = (u32x4){__builtin_amdgcn_perm(x[2], x[0], 0x05040100u), __builtin_amdgcn_perm(x[2], x[0], 0x07060302u),
+                        __builtin_amdgcn_perm(x[3], x[1], 0x05040100u), __builtin_amdgcn_perm(x[3], x[1], 0x07060302u)};
+    }
+    *reinterpret_cast<u32x4*>(Ot + (16 * k + (tid >> 4)) * ZLD + 8 * (tid & 15)) = prow[k];
+  }
   __syncthreads();
   H8 Ap[4][8];
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) Ap[cb][kk].u = *reinterpret_cast<const uint4*>(Ot + (32 * cb + l32) * ZLD + 64 * hf + 8 * kk);
+    for (int kk = 0; kk < 8; ++kk) {
+      Ap[cb][kk].u = *reinterpret_cast<const uint4*>(Ot + (32 * cb + l32) * ZLD + 64 * hf + 8 * kk);
+      asm volatile("" : "+v"(Ap[cb][kk].h));   // in registers before the barrier: the reads were sunk behind it into the branch
+    }
   __syncthreads();   // from here on the waves do not meet again
-  __builtin_amdgcn_sched_barrier(0);
   if (idle) return;
   H8 Bv[4];   // right factors of the unit's block as A operand of the low-rank product: V[8 hf + e][32 cb + l32]
   __amdgpu_buffer_rsrc_t obuf = buffer_of(out + (size_t)blk * n * D, (size_t)n * D * 2);
@@ -388,91 +372,78 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
       __builtin_amdgcn_wave_barrier();
       Cop = c_operand(0);
     }
-    // nibble words of the lane's 64 coordinates (BITS <= 3): byte kk of word set [kk / 4] is instruction kk
-    uint32_t even[2], odd[2], seven[2], sodd[2];
-    if constexpr (BITS <= 3) {
+    // BITS <= 2: nibble words of the lane's 64 coordinates, byte kk of word set [kk / 4] is instruction kk.  BITS >= 3: the
+    // bits of a code side by side, nib[wq][k] holds the codes of coordinates 32 wq + 4 i + k as nibble i: a byte of it names
+    // two centroids that one table read brings (masks for all levels of the codebook and a select per level were 16 times
+    // the instructions of a tile: 3000 blocks of 512 at 4 bits 226 us, now 110)
+    uint32_t even[2], odd[2], nib[2][BITS > 2 ? 4 : 1];
 #pragma unroll
-      for (int wq = 0; wq < 2; ++wq) {
-        uint32_t a, b;
-        if constexpr (BITS == 1) {
-          a = cur.pl[0][wq];
-          b = 0u;
-        } else if constexpr (BITS == 2) {
-          a = cur.pl[0][wq];
-          b = cur.pl[1][wq];
-        } else {
-          // magnitude bit p of a code: plane p where the sign plane is set, its complement where it is clear
-          a = ~(cur.pl[0][wq] ^ cur.pl[2][wq]);
-          b = ~(cur.pl[1][wq] ^ cur.pl[2][wq]);
-          seven[wq] = cur.pl[2][wq] & 0x0F0F0F0Fu;
-          sodd[wq] = (cur.pl[2][wq] >> 4) & 0x0F0F0F0Fu;
-        }
+    for (int wq = 0; wq < 2; ++wq) {
+      if constexpr (BITS <= 2) {
+        const uint32_t a = cur.pl[0][wq], b = BITS == 2 ? cur.pl[BITS - 1][wq] : 0u;
         even[wq] = bfi(0x0F0F0F0Fu, a, b << 4);   // byte j: low nibbles of byte j of the two planes
         odd[wq] = bfi(0x0F0F0F0Fu, a >> 4, b);    // byte j: high nibbles
+      } else {
+        EOQ_SFOR(k, 4,
+          auto to = [&](int p) __attribute__((always_inline)) { return p >= k ? cur.pl[p][wq] << (p - k) : cur.pl[p][wq] >> (k - p); };
+          uint32_t x = bfi(0x22222222u, to(1), bfi(0x11111111u, to(0), to(2)));
+          if constexpr (BITS == 4) x = bfi(0x88888888u, to(BITS - 1), x);
+          else x &= 0x77777777u;
+          nib[wq][k] = x;
+        );
       }
     }
     auto operand = [&](auto kk_ic) __attribute__((always_inline)) {
       constexpr int kk = decltype(kk_ic)::value;
       H8 z;
-      if constexpr (BITS <= 3) {
+      if constexpr (BITS <= 2) {
         const uint2 lo4 = cen_tab[(even[kk >> 2] >> (8 * (kk & 3))) & 0xFFu], hi4 = cen_tab[(odd[kk >> 2] >> (8 * (kk & 3))) & 0xFFu];
         z.u = make_uint4(lo4.x, lo4.y, hi4.x, hi4.y);
-        if constexpr (BITS == 3) {
-          const uint2 ls = cen_tab[256 + ((seven[kk >> 2] >> (8 * (kk & 3))) & 0xFFu)];
-          const uint2 hs = cen_tab[256 + ((sodd[kk >> 2] >> (8 * (kk & 3))) & 0xFFu)];
-          z.u = make_uint4(lo4.x | ls.x, lo4.y | ls.y, hi4.x | hs.x, hi4.y | hs.y);
-        }
       } else {
-        uint32_t byte[BITS];
-#pragma unroll
-        for (int p = 0; p < BITS; ++p) byte[p] = (cur.pl[p][kk >> 2] >> (8 * (kk & 3))) & 0xFFu;
-        z = centroids_of<BITS>(byte, mask_tab, mg);
+        EOQ_SFOR(k, 4, z.w[k] = pair_tab[(nib[kk >> 2][k] >> (8 * (kk & 3))) & 0xFFu];);
       }
       return z;
     };
-    // all four column blocks at once (every unpacked operand feeds four matrix instructions); at 4 bits, where the
-    // unpacking itself needs more registers, one at a time in four passes
-    constexpr int NCB = (BITS == 4) ? 1 : 4;
+    // all four column blocks at once: every unpacked operand feeds four matrix instructions
+    {
+      float16v acc[4];
 #pragma unroll
-    for (int pass = 0; pass < 4 / NCB; ++pass) {
-      float16v acc[NCB];
-#pragma unroll
-      for (int c = 0; c < NCB; ++c)
+      for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[c][v] = 0.0f;
       EOQ_SFOR(kk, 8,
         const H8 z = operand(std::integral_constant<int, kk>{});
-        EOQ_SFOR(c, NCB, acc[c] = mfma16(Ap[NCB * pass + c][kk], z, acc[c]););
+        EOQ_SFOR(c, 4, acc[c] = mfma16(Ap[c][kk], z, acc[c]););
       );
 #pragma unroll
-      for (int c = 0; c < NCB; ++c)
+      for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[c][v] *= rs;
       if (r > 0) {   // uniform
-        EOQ_SFOR(c, NCB, acc[c] = mfma16(Bv[NCB * pass + c], Cop, acc[c]););
+        EOQ_SFOR(c, 4, acc[c] = mfma16(Bv[c], Cop, acc[c]););
         if (r > 16) {
           // components 16 .. 31: their coefficient rows of this tile are fetched here, nothing of them is kept
-          if (pass == 0) {
+          {
             const __amdgpu_buffer_rsrc_t lbuf = buffer_of(lfac + (size_t)blk * r_max * n, (size_t)r * n * 2);
             const u32x4 c2 = __builtin_amdgcn_raw_buffer_load_b128(lbuf, vo_cf + (uint32_t)(16 * n * 2), t0 * 2, 0);
             *reinterpret_cast<u32x4*>(cs + (16 + (lane >> 2)) * CTLD + (lane & 3) * 8) = c2;
             __builtin_amdgcn_wave_barrier();
           }
           const H8 c2op = c_operand(1);
-          EOQ_SFOR(c, NCB,
+          EOQ_SFOR(c, 4,
             H8 va;
-            va.u = v2[(NCB * pass + c) * 64 + lane];
+            va.u = v2[(c) * 64 + lane];
             acc[c] = mfma16(va, c2op, acc[c]);
           );
         }
       }
       // register v of column block cb is column 32 cb + 8 (v / 4) + 4 hf + v % 4 of the lane's token
 #pragma unroll
-      for (int c = 0; c < NCB; ++c)
+      for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const uint2 pk = make_uint2(pack_half2(acc[c][4 * q], acc[c][4 * q + 1]), pack_half2(acc[c][4 * q + 2], acc[c][4 * q + 3]));
-          *reinterpret_cast<uint2*>(ot + l32 * ZLD + 32 * (NCB * pass + c) + 8 * q + 4 * hf) = pk;
+          *reinterpret_cast<uint2*>(ot + l32 * ZLD + 32 * (c) + 8 * q + 4 * hf) = pk;
         }
     }
     // the tile leaves by rows: lane L stores 16 bytes of row 4 ps + L / 16 (one wave's LDS operations complete in order)
@@ -1036,10 +1007,11 @@ hipError_t eoq_launch_decode(const EoqLaunch& L, eoq_packed in, int64_t B, void*
     return hipGetLastError();
   }
   // Every wave is a worker; two workgroups of four per compute unit (2048 waves).  A unit of work is a whole block
-  // when that leaves every wave at least two of them, otherwise a half or a quarter of a block's 32-token tiles.
+  // when that leaves every wave at least two of them, otherwise a half or a quarter of a block's 32-token tiles, and
+  // less than that, down to one tile, while there are waves without a unit (16 blocks of 1024: 14.7 us with quarters).
   const int tiles = L.n / 32;
   int parts_log2 = 0;
-  while (parts_log2 < 2 && (B << parts_log2) < 4096 && tiles % (2 << parts_log2) == 0) ++parts_log2;
+  while ((B << parts_log2) < (parts_log2 < 2 ? 4096 : 2048) && tiles % (2 << parts_log2) == 0) ++parts_log2;
   const int64_t units = B << parts_log2;
   const dim3 grid((unsigned)(units < 2048 ? (units + 3) / 4 : 512)), block(THREADS);
   uint16_t* out = static_cast<uint16_t*>(out_fp16);
