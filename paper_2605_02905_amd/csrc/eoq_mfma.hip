@@ -29,9 +29,12 @@ constexpr int ZLD = D + 8;          // row stride (halfs) of the token tiles in 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 union H8 {
   half8 h;
   uint4 u;
+  u32x4 v;
   uint32_t w[4];
   uint16_t s[8];
 };
@@ -49,16 +52,6 @@ __device__ __forceinline__ float16v mfma16(const H8& a, const H8& b, float16v c)
 __device__ __forceinline__ void split_half(float v, uint16_t& hi, uint16_t& lo) {
   hi = float_to_half_bits(v);
   lo = float_to_half_bits(v - half_bits_to_float(hi));
-}
-
-// Mask table: entry m (a byte of one bit-plane) -> 8 halfwords, halfword e = 0xFFFF if bit e of m is set.
-__device__ __forceinline__ void build_mask_table(uint4* tab, int tid) {
-  if (tid < 256) {
-    H8 x;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x.s[e] = ((tid >> e) & 1) ? 0xFFFFu : 0u;
-    tab[tid] = x.u;
-  }
 }
 
 // Direct table for codes of 1 or 2 bits: entry (nibble of plane 0 | nibble of plane 1 << 4) -> the binary16 centroids of
@@ -79,66 +72,20 @@ __device__ __forceinline__ void build_centroid_table(uint2* tab4, const float* _
   }
 }
 
-// Centroid magnitudes of the symmetric codebook as duplicated binary16 pairs: mag[m] = (h << 16) | h with
-// h = binary16(centroid[L/2 + m]), m = 0 .. L/2-1.
-template <int BITS>
-struct Mags {
-  uint32_t m[(1 << BITS) / 2];   // binary16(centroid), duplicated in both halves
-  uint32_t lo[(1 << BITS) / 2];  // binary16(centroid - hi): the part the first rounding lost (signed)
-  __device__ __forceinline__ void load(const float* __restrict__ tab) {
-#pragma unroll
-    for (int i = 0; i < (1 << BITS) / 2; ++i) {
-      const float c = tab[(1 << BITS) / 2 + i];
-      const uint32_t h = float_to_half_bits(c);
-      m[i] = (h << 16) | h;
-      const uint32_t l = float_to_half_bits(c - half_bits_to_float((uint16_t)h));
-      lo[i] = (l << 16) | l;
-    }
-  }
-};
-
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
-// 8 code indices (one byte of each bit-plane) -> 8 binary16 centroid values.
-// Index = sum_p bit_p 2^p; the codebook is symmetric: the top bit is the sign (set = positive) and the lower
-// bits count the magnitude outwards from zero (inverted for the negative half).
-template <int BITS, bool WITH_LO = false>
-__device__ __forceinline__ H8 centroids_of(const uint32_t (&byte)[BITS], const uint4* mask_tab, const Mags<BITS>& mg,
-                                           H8* out_lo = nullptr) {
-  H8 M[BITS];
-#pragma unroll
-  for (int p = 0; p < BITS; ++p) M[p].u = mask_tab[byte[p]];
-  H8 out;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const uint32_t top = M[BITS - 1].w[w];
-    uint32_t mag, mlo = 0;
-    if constexpr (BITS == 1) {
-      mag = mg.m[0];
-      if constexpr (WITH_LO) mlo = mg.lo[0];
-    } else if constexpr (BITS == 2) {
-      const uint32_t s0 = ~(M[0].w[w] ^ top);
-      mag = bfi(s0, mg.m[1], mg.m[0]);
-      if constexpr (WITH_LO) mlo = bfi(s0, mg.lo[1], mg.lo[0]);
-    } else if constexpr (BITS == 3) {
-      const uint32_t s0 = ~(M[0].w[w] ^ top), s1 = ~(M[1].w[w] ^ top);
-      mag = bfi(s1, bfi(s0, mg.m[3], mg.m[2]), bfi(s0, mg.m[1], mg.m[0]));
-      if constexpr (WITH_LO) mlo = bfi(s1, bfi(s0, mg.lo[3], mg.lo[2]), bfi(s0, mg.lo[1], mg.lo[0]));
-    } else {
-      const uint32_t s0 = ~(M[0].w[w] ^ top), s1 = ~(M[1].w[w] ^ top), s2 = ~(M[2].w[w] ^ top);
-      const uint32_t lo = bfi(s1, bfi(s0, mg.m[3], mg.m[2]), bfi(s0, mg.m[1], mg.m[0]));
-      const uint32_t hi = bfi(s1, bfi(s0, mg.m[7], mg.m[6]), bfi(s0, mg.m[5], mg.m[4]));
-      mag = bfi(s2, hi, lo);
-      if constexpr (WITH_LO) {
-        const uint32_t llo = bfi(s1, bfi(s0, mg.lo[3], mg.lo[2]), bfi(s0, mg.lo[1], mg.lo[0]));
-        const uint32_t lhi = bfi(s1, bfi(s0, mg.lo[7], mg.lo[6]), bfi(s0, mg.lo[5], mg.lo[4]));
-        mlo = bfi(s2, lhi, llo);
-      }
-    }
-    out.w[w] = bfi(0x7FFF7FFFu, mag, ~top);
-    if constexpr (WITH_LO) out_lo->w[w] = mlo ^ (~top & 0x80008000u);   // negative centroid: flip the sign
-  }
-  return out;
+// Codes of 3 and 4 bits: the bits of a code side by side.  Nibble i of the result is the code of coordinate 4 i + k of the 32
+// that the plane words hold; a byte of it names two centroids, coordinates k and k + 4 of eight, which one table read
+// brings.  The contraction slots are permuted to that order, 0 4 1 5 2 6 3 7 (pair_order on the other operand).
+template <int BITS>
+__device__ __forceinline__ uint32_t code_nibbles(const u32x2 (&pl)[BITS], int wq, int k) {
+  auto to = [&](int p) __attribute__((always_inline)) { return p >= k ? pl[p][wq] << (p - k) : pl[p][wq] >> (k - p); };
+  const uint32_t x = bfi(0x22222222u, to(1), bfi(0x11111111u, to(0), to(2)));
+  return BITS == 4 ? bfi(0x88888888u, to(BITS - 1), x) : (x & 0x77777777u);
+}
+__device__ __forceinline__ u32x4 pair_order(const u32x4& x) {
+  return (u32x4){__builtin_amdgcn_perm(x[2], x[0], 0x05040100u), __builtin_amdgcn_perm(x[2], x[0], 0x07060302u),
+                 __builtin_amdgcn_perm(x[3], x[1], 0x05040100u), __builtin_amdgcn_perm(x[3], x[1], 0x07060302u)};
 }
 
 // Rank of block blk as a vector load (zero past the end of the array): a scalar load would share its counter with
@@ -161,8 +108,6 @@ __device__ __forceinline__ int rank_value(int raw, int r_max) {
 // The contraction index is permuted so that lane half hf owns coordinates 64 hf .. 64 hf + 63 (8 consecutive bytes
 // of every bit-plane): slot e of instruction kk is coordinate 64 hf + 8 kk + e on both operands.
 // ---------------------------------------------------------------------------------------------
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // What a lane requests of a tile: lane (l32, hf) owns token l32 of the tile.
 template <int BITS>
@@ -293,11 +238,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
   // rows pass through the output tiles' memory
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    if constexpr (BITS > 2) {   // slots 2 k, 2 k + 1 are coordinates k, k + 4 of an instruction's eight
-      const u32x4 x = prow[k];
-      prow[k] = (u32x4){__builtin_amdgcn_perm(x[2], x[0], 0x05040100u), __builtin_amdgcn_perm(x[2], x[0], 0x07060302u),
-                        __builtin_amdgcn_perm(x[3], x[1], 0x05040100u), __builtin_amdgcn_perm(x[3], x[1], 0x07060302u)};
-    }
+    if constexpr (BITS > 2) prow[k] = pair_order(prow[k]);
     *reinterpret_cast<u32x4*>(Ot + (16 * k + (tid >> 4)) * ZLD + 8 * (tid & 15)) = prow[k];
   }
   __syncthreads();
@@ -372,10 +313,9 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
       __builtin_amdgcn_wave_barrier();
       Cop = c_operand(0);
     }
-    // BITS <= 2: nibble words of the lane's 64 coordinates, byte kk of word set [kk / 4] is instruction kk.  BITS >= 3: the
-    // bits of a code side by side, nib[wq][k] holds the codes of coordinates 32 wq + 4 i + k as nibble i: a byte of it names
-    // two centroids that one table read brings (masks for all levels of the codebook and a select per level were 16 times
-    // the instructions of a tile: 3000 blocks of 512 at 4 bits 226 us, now 110)
+    // nibble words of the lane's 64 coordinates, byte kk % 4 of word set [kk / 4] is instruction kk (BITS >= 3: masks for all
+    // levels of the codebook and a select per level were 16 times the instructions: 3000 blocks of 512 at 4 bits 226 us,
+    // now 110)
     uint32_t even[2], odd[2], nib[2][BITS > 2 ? 4 : 1];
 #pragma unroll
     for (int wq = 0; wq < 2; ++wq) {
@@ -384,13 +324,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
         even[wq] = bfi(0x0F0F0F0Fu, a, b << 4);   // byte j: low nibbles of byte j of the two planes
         odd[wq] = bfi(0x0F0F0F0Fu, a >> 4, b);    // byte j: high nibbles
       } else {
-        EOQ_SFOR(k, 4,
-          auto to = [&](int p) __attribute__((always_inline)) { return p >= k ? cur.pl[p][wq] << (p - k) : cur.pl[p][wq] >> (k - p); };
-          uint32_t x = bfi(0x22222222u, to(1), bfi(0x11111111u, to(0), to(2)));
-          if constexpr (BITS == 4) x = bfi(0x88888888u, to(BITS - 1), x);
-          else x &= 0x77777777u;
-          nib[wq][k] = x;
-        );
+        EOQ_SFOR(k, 4, nib[wq][k] = code_nibbles<BITS>(cur.pl, wq, k););
       }
     }
     auto operand = [&](auto kk_ic) __attribute__((always_inline)) {
@@ -499,9 +433,8 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
   __shared__ __align__(16) uint16_t Vt[QWAVES * D * 16];     // per wave: right factors 0 .. 15 of the block, [column][component]
   __shared__ __align__(16) uint16_t St[QWAVES * 32 * SLD];   // per wave: half the columns of a tile of S, [token][column]
   __shared__ __align__(16) uint16_t Cs[QWAVES * 16 * CTLD];  // per wave: coefficient rows of a tile
-  __shared__ __align__(16) uint4 mask_tab[256];              // BITS = 4: plane byte -> halfword masks; BITS <= 3: nibble tables, hi then lo
-  __shared__ __align__(16) uint2 sign_tab[BITS == 3 ? 16 : 1];
-  uint2* cen_hi = reinterpret_cast<uint2*>(mask_tab);
+  // BITS <= 2: binary16 parts of four centroids by two nibbles, hi then lo; else the parts of two centroids by two codes, (hi, lo)
+  __shared__ __align__(16) uint2 cen_hi[BITS <= 2 ? 512 : 256];
   uint2* cen_lo = cen_hi + 256;
   constexpr int ROWB = BITS * D / 8;
 
@@ -509,30 +442,30 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
   const int l32 = lane & 31, hf = lane >> 5;
   set_fp16_overflow_clamp();   // parts of r_x saturate by the conversion itself
 
-  if constexpr (BITS == 4) {
-    build_mask_table(mask_tab, tid);
-  } else if (tid < 256) {
-    // entry (nibble of plane / magnitude bit 0 | nibble of 1 << 4) -> centroids (BITS <= 2) or their magnitudes (BITS = 3)
+  if (tid < 256) {
     const int n0 = tid & 15, n1 = tid >> 4;
-    uint16_t h[4], l[4];
+    if constexpr (BITS <= 2) {   // entry (nibble of plane 0 | nibble of plane 1 << 4)
+      uint16_t h[4], l[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int two = ((n0 >> e) & 1) | ((BITS >= 2) ? (((n1 >> e) & 1) << 1) : 0);
-      split_half(tab[(BITS == 3 ? 4 : 0) + two], h[e], l[e]);
+      for (int e = 0; e < 4; ++e) split_half(tab[((n0 >> e) & 1) | (BITS == 2 ? ((n1 >> e) & 1) << 1 : 0)], h[e], l[e]);
+      cen_hi[tid] = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+      cen_lo[tid] = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
+    } else {
+      uint16_t h[2], l[2];
+      split_half(tab[n0 & ((1 << BITS) - 1)], h[0], l[0]);
+      split_half(tab[n1 & ((1 << BITS) - 1)], h[1], l[1]);
+      cen_hi[tid] = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)l[0] | ((uint32_t)l[1] << 16));
     }
-    cen_hi[tid] = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-    cen_lo[tid] = make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
-    if (BITS == 3 && tid < 16)   // sign bits of four halfwords: set where the sign plane is clear
-      sign_tab[tid] = make_uint2(((tid & 1) ? 0u : 0x8000u) | ((tid & 2) ? 0u : 0x80000000u), ((tid & 4) ? 0u : 0x8000u) | ((tid & 8) ? 0u : 0x80000000u));
   }
-  Mags<BITS> mg;
-  if constexpr (BITS == 4) mg.load(tab);
   const uint16_t* pit_hi = pih + 2 * D * D;
   const uint16_t* pit_lo = pih + 3 * D * D;
 #pragma unroll
   for (int k = 0; k < 4 * 8 / QWAVES; ++k) {
     const int cb = k * QWAVES / 8, kk = wave;   // this wave's share of the operands in LDS
-    Plo[(cb * 8 + kk) * 64 + lane] = *reinterpret_cast<const uint4*>(pit_lo + (32 * cb + l32) * D + 16 * kk + 8 * hf);
+    H8 lo;
+    lo.v = *reinterpret_cast<const u32x4*>(pit_lo + (32 * cb + l32) * D + 16 * kk + 8 * hf);
+    if constexpr (BITS > 2) lo.v = pair_order(lo.v);
+    Plo[(cb * 8 + kk) * 64 + lane] = lo.u;
     Fop[(cb * 8 + kk) * 64 + lane] = *reinterpret_cast<const uint4*>(phih + (32 * cb + l32) * D + 16 * kk + 8 * hf);
   }
   __syncthreads();   // the only one: from here on the waves do not meet again
@@ -545,7 +478,10 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk)
-      Ap[cb][kk].u = *reinterpret_cast<const uint4*>(pit_hi + (32 * cb + l32) * D + 16 * kk + 8 * hf);
+    {
+      Ap[cb][kk].v = *reinterpret_cast<const u32x4*>(pit_hi + (32 * cb + l32) * D + 16 * kk + 8 * hf);
+      if constexpr (BITS > 2) Ap[cb][kk].v = pair_order(Ap[cb][kk].v);
+    }
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
 
   const int tpb = n / 32;
@@ -614,26 +550,16 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
       const u32x2 e = __builtin_amdgcn_permlane32_swap(ev, od, false, false);
       cur.pl[p] = e;
     }
-    // nibble words of the lane's 64 coordinates (BITS <= 3): byte kk of word set [kk / 4] is instruction kk
-    uint32_t even[2], odd[2], seven[2], sodd[2];
-    if constexpr (BITS <= 3) {
+    // nibble words of the lane's 64 coordinates: byte kk % 4 of word set [kk / 4] is instruction kk
+    uint32_t even[2], odd[2], nib[2][BITS > 2 ? 4 : 1];
 #pragma unroll
-      for (int wq = 0; wq < 2; ++wq) {
-        uint32_t a, b;
-        if constexpr (BITS == 1) {
-          a = cur.pl[0][wq];
-          b = 0u;
-        } else if constexpr (BITS == 2) {
-          a = cur.pl[0][wq];
-          b = cur.pl[1][wq];
-        } else {
-          a = ~(cur.pl[0][wq] ^ cur.pl[2][wq]);
-          b = ~(cur.pl[1][wq] ^ cur.pl[2][wq]);
-          seven[wq] = cur.pl[2][wq] & 0x0F0F0F0Fu;
-          sodd[wq] = (cur.pl[2][wq] >> 4) & 0x0F0F0F0Fu;
-        }
+    for (int wq = 0; wq < 2; ++wq) {
+      if constexpr (BITS <= 2) {
+        const uint32_t a = cur.pl[0][wq], b = BITS == 2 ? cur.pl[BITS - 1][wq] : 0u;
         even[wq] = bfi(0x0F0F0F0Fu, a, b << 4);
         odd[wq] = bfi(0x0F0F0F0Fu, a >> 4, b);
+      } else {
+        EOQ_SFOR(k, 4, nib[wq][k] = code_nibbles<BITS>(cur.pl, wq, k););
       }
     }
     float16v acc[4];
@@ -648,20 +574,17 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
     EOQ_SFOR(kk, 8,
       H8 zh;
       H8 zl;
-      if constexpr (BITS <= 3) {
+      if constexpr (BITS <= 2) {
         const uint32_t ie = (even[kk >> 2] >> (8 * (kk & 3))) & 0xFFu; const uint32_t io = (odd[kk >> 2] >> (8 * (kk & 3))) & 0xFFu;
         const uint2 a = cen_hi[ie]; const uint2 b = cen_hi[io]; const uint2 c = cen_lo[ie]; const uint2 d = cen_lo[io];
         zh.u = make_uint4(a.x, a.y, b.x, b.y);
         zl.u = make_uint4(c.x, c.y, d.x, d.y);
-        if constexpr (BITS == 3) {
-          const uint2 sa = sign_tab[(seven[kk >> 2] >> (8 * (kk & 3))) & 0xFFu]; const uint2 sb = sign_tab[(sodd[kk >> 2] >> (8 * (kk & 3))) & 0xFFu];
-          zh.u = make_uint4(zh.u.x ^ sa.x, zh.u.y ^ sa.y, zh.u.z ^ sb.x, zh.u.w ^ sb.y);
-          zl.u = make_uint4(zl.u.x ^ sa.x, zl.u.y ^ sa.y, zl.u.z ^ sb.x, zl.u.w ^ sb.y);
-        }
       } else {
-        uint32_t byte[BITS];
-        EOQ_SFOR(p, BITS, byte[p] = (cur.pl[p][kk >> 2] >> (8 * (kk & 3))) & 0xFFu;);
-        zh = centroids_of<BITS, true>(byte, mask_tab, mg, &zl);
+        EOQ_SFOR(k, 4,
+          const uint2 c = cen_hi[(nib[kk >> 2][k] >> (8 * (kk & 3))) & 0xFFu];
+          zh.w[k] = c.x;
+          zl.w[k] = c.y;
+        );
       }
       EOQ_SFOR(cb, 4, acc[cb] = mfma16(Ap[cb][kk], zh, acc[cb]););
       EOQ_SFOR(cb, 4,
