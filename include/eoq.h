@@ -301,7 +301,9 @@ eoq_status eoq_softmax(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, i
  *                  j*n + t of a row weighs token t of block j.  weight_stride >= blocks_filled*n.
  *   out            DEVICE, [n_seq][n_q_heads][d] float32, overwritten.
  *   workspace      DEVICE, >= eoq_attend_workspace_bytes(ctx, n_seq, n_kv_heads, blocks_filled) bytes (partial sums;
- *                  they are added in a fixed order: the result does not depend on scheduling).
+ *                  they are added in a fixed order: the result does not depend on scheduling).  The size grows with each
+ *                  argument: a workspace of the size for a full store serves every smaller fill, and fewer sequences
+ *                  or heads, too.
  * Supported group sizes as eoq_scores.  blocks_filled = 0 writes zeros.
  */
 size_t     eoq_attend_workspace_bytes(const eoq_ctx* ctx, int64_t n_seq, int n_kv_heads, int64_t blocks_per_head);

@@ -793,6 +793,16 @@ int64_t eoq_attend_runs(int64_t sg_total, int64_t blocks_per_head, int n, int* p
   return (pairs + 4 * ppw - 1) / (4 * ppw);
 }
 
+int64_t eoq_attend_most_runs(int64_t sg_total, int64_t blocks_per_head, int n) {
+  // The runs of a head are shorter the fuller the store is, so their number steps up AND down with the fill.  With one pair
+  // per wave there are ceil(pairs / 4) of them; while a wave has up to 96 pairs, sg pairs <= 2048 ppw, hence at most
+  // ceil(512 / sg), together less than 512 + sg; beyond that ceil(pairs / 384).  Each bound grows with both arguments.
+  const int64_t pairs = blocks_per_head * (n / PAIR);
+  const int64_t one = sg_total * ((pairs + 3) / 4), round = 511 + sg_total, full = sg_total * ((pairs + 383) / 384);
+  const int64_t few = one < round ? one : round;
+  return few > full ? few : full;
+}
+
 hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_seq, int n_kv_heads,
                              int64_t blocks_per_head, int64_t block_capacity, const float* weights,
                              int64_t weight_stride, int n_q_heads, float* out, float* partial, const void* tail_fp16,

@@ -526,9 +526,7 @@ eoq_status eoq_scores_stream(eoq_ctx* ctx, eoq_packed keys, int64_t n_seq, int n
 
 size_t eoq_attend_workspace_bytes(const eoq_ctx* ctx, int64_t n_seq, int n_kv_heads, int64_t blocks_per_head) {
   if (!ctx || n_seq <= 0 || n_kv_heads <= 0 || blocks_per_head <= 0) return 0;
-  int ppw = 1;
-  const int64_t runs = eoq_attend_runs(n_seq * n_kv_heads, blocks_per_head, ctx->n, &ppw);
-  return (size_t)(n_seq * n_kv_heads) * (size_t)runs * 16 * EOQ_D * sizeof(float);
+  return (size_t)eoq_attend_most_runs(n_seq * n_kv_heads, blocks_per_head, ctx->n) * eoq_attend_run_bytes();
 }
 
 eoq_status eoq_softmax(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, int64_t row_stride, void* hip_stream) {
@@ -571,7 +569,10 @@ static eoq_status attend_impl(eoq_ctx* ctx, eoq_packed values, int64_t n_seq, in
   if (blocks_filled > 0) {
     if (eoq_status st = check_packed(ctx, values)) return st;
     if (!workspace || !aligned16(workspace)) return fail(ctx, EOQ_ERR_ARG, "null or misaligned workspace");
-    if (workspace_bytes < eoq_attend_workspace_bytes(ctx, n_seq, n_kv_heads, blocks_filled))
+    // what this fill needs, which may be less than eoq_attend_workspace_bytes: that is good for smaller fills as well
+    int ppw = 1;
+    const int64_t runs = eoq_attend_runs(n_seq * n_kv_heads, blocks_filled, ctx->n, &ppw);
+    if (workspace_bytes < (size_t)(n_seq * n_kv_heads * runs) * eoq_attend_run_bytes())
       return fail(ctx, EOQ_ERR_WORKSPACE, "workspace too small");
   }
   if (n_seq * n_kv_heads * block_capacity > (int64_t)1 << 24)

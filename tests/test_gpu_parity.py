@@ -1002,6 +1002,22 @@ def test_attend_argument_errors():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("bits,group", [(2, 4), (4, 7)])
+def test_one_attention_workspace_serves_every_fill(bits, group):
+    """A workspace sized at the store's capacity takes every fill up to it (the runs get longer, and fewer, as the store
+    fills), with the results of a workspace of the fill's own size."""
+    n, n_kv, cap = 128, 8, 130
+    ctx = eoq.Context(n=n, bits=bits)
+    spec = synth.BlockSpec("vals", n=n, n_tensors=n_kv, blocks_per_tensor=cap, rank_lo=0, rank_hi=6)
+    store, _ = ctx.eoq_compress(synth.make_blocks(spec, seed=41, device=DEV)[0])
+    w = torch.rand(1, n_kv * group, cap * n, generator=torch.Generator().manual_seed(8)).to(DEV)
+    one = torch.empty(ctx.eoq_attend_workspace_bytes(1, n_kv, cap), dtype=torch.uint8, device=DEV)
+    for filled in range(cap + 1):
+        out = ctx.eoq_attend(store, w, n_kv, cap, filled, workspace=one)
+        if filled % 13 == 0:
+            assert torch.equal(out, ctx.eoq_attend(store, w, n_kv, cap, filled)), filled
+
+
 # ---------------------------------------------------------------------------------------------------------------
 # TQ_prod: the 1-bit QJL correction (Alg. 1 lines "TQ_prod", Eq. (qjl)) on stored records
 # ---------------------------------------------------------------------------------------------------------------

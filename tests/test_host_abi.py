@@ -79,6 +79,18 @@ def test_workspace_size_and_host_only_context(lib):
         assert b"HIP device" in lib.eoq_last_error(ctx._h)
 
 
+@pytest.mark.parametrize("n,kv", [(128, 8), (512, 8), (128, 1), (1024, 3)])
+def test_attention_workspace_grows_with_the_fill(lib, n, kv):
+    """A serving loop allocates once, at the store's capacity: no smaller fill, batch or head count may ask for more."""
+    ctx = eoq.Context(n=n, bits=2)
+    for seqs in (1, 3, 16):
+        sizes = [ctx.eoq_attend_workspace_bytes(seqs, kv, b) for b in range(0, 1200)]
+        assert sizes[0] == 0 and all(a <= b for a, b in zip(sizes, sizes[1:]))
+    for blocks in (1, 7, 60, 400, 5000):
+        sizes = [ctx.eoq_attend_workspace_bytes(s, kv, blocks) for s in range(1, 600)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 def test_projection_table_matches_the_oracle_stream():
     """Phi of TQ_prod: the library's own generator (seed rot_seed + 1) against the oracle's, as binary16 tables."""
     ctx = eoq.Context(n=128, bits=2, rot_seed=77)
