@@ -1,0 +1,39 @@
+"""CPU-only checks of the compiler's listing of the kernels: orders that the hardware does not keep by itself."""
+import os
+import re
+import subprocess
+
+import pytest
+
+import __graft_entry__ as g
+
+
+def _kernel_lines(source, kernel, tmp_path):
+    """Instructions of one kernel, in listing order."""
+    out = os.path.join(str(tmp_path), source + ".s")
+    flags = [f for f in g.HIP_FLAGS if f not in ("-shared", "-fPIC")]
+    res = subprocess.run([g.HIPCC, *flags, "-I" + os.path.join(g.ROOT, "include"), "-I" + g.CSRC, "--offload-device-only", "-S",
+                          os.path.join(g.CSRC, source), "-o", out], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    lines = [l.split(";")[0].strip() for l in open(out)]
+    first = next(i for i, l in enumerate(lines) if re.match(r"_Z\w*" + kernel + r"\w*:", l))
+    last = next(i for i in range(first, len(lines)) if lines[i].startswith("s_endpgm"))
+    return [l for l in lines[first:last] if l]
+
+
+@pytest.mark.skipif(not os.path.exists(g.HIPCC), reason="no compiler")
+def test_tridiagonal_matrix_is_acknowledged_before_the_scalar_cache_reads_it(tmp_path):
+    """The scalar cache is not coherent with vector stores: between the stores of a block's tridiagonal matrix and the
+    barrier in front of its first scalar load the kernel waits until every store has been acknowledged."""
+    lines = _kernel_lines("eoq_spectral.hip", "eoq_spectral_tridiag_kernel", tmp_path)
+    # the 32 touches, one per 64-byte line of the 2 KB
+    load = next(i for i, l in enumerate(lines) if l.startswith("s_load_dword ") and l.endswith(", 0x7c0"))
+    base = lines[load].split(",")[1].strip()
+    first = next(i for i, l in enumerate(lines) if l.startswith("s_load_dword ") and l.endswith(f", {base}, 0x0"))
+    store = max(i for i in range(first) if lines[i].startswith("global_store_dwordx4"))
+    assert lines[store].endswith(base)
+    barrier = next(i for i in range(store, first) if lines[i] == "s_barrier")
+    waits = [i for i in range(store, barrier) if lines[i].startswith("s_waitcnt") and "vmcnt(0)" in lines[i]]
+    assert waits and not any("store" in l for l in lines[waits[0]:barrier])
+    # and nothing reads the matrix through the scalar cache before
+    assert not any(l.startswith("s_load") and f", {base}," in l for l in lines[store:barrier])
