@@ -161,10 +161,16 @@ __device__ int rank_and_shrink(const double* lam_s, double* atoms, double* scale
 // =============================================================================================
 constexpr int LDA = D + 1;  // padded column stride of the LDS-resident matrix
 constexpr int MAX_SWEEPS = 30;
+// Workgroups that share a batch when most of it is not theirs.  Blocks that need this solver come side by side (a head-tensor
+// that has repeated singular values has them in neighbouring blocks) or at a fixed distance (the first block of every
+// head-tensor), and one takes many times what the other solver takes, so the blocks are dealt out at a stride that has no
+// factor in common with such a distance: the largest prime below the 256 compute units.  (256 neighbours of 32768 blocks
+// of 512 x 128: compress 15.3 ms; as contiguous shares 65.6, two workgroups had them all.  Without any: 14.4 either way.)
+constexpr unsigned SHARERS = 251;
 constexpr double JACOBI_TOL = 5e-14;  // a pair is orthogonal when |<a_p,a_q>| <= tol |a_p||a_q|
 
-// With `marks` non-null the workgroups share the batch (a contiguous range each) and solve the blocks whose mark is set;
-// otherwise workgroup b handles block b.
+// With `marks` non-null the workgroups share the batch and solve the blocks whose mark is set; otherwise workgroup b
+// handles block b.
 __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
     const void* __restrict__ blocks, EoqBlockMap map, int dtype, int n, int k, double rank_thr, int r_max, int loss, int64_t B,
     const int* __restrict__ marks, double* __restrict__ lam_out,
@@ -180,12 +186,12 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
   __shared__ unsigned flag_s;
 
   const int tid = threadIdx.x;
-  const int64_t share = (B + gridDim.x - 1) / gridDim.x;
-  const int64_t first = blockIdx.x * share, last = (first + share < B) ? first + share : B;
-  for (int64_t item = first; item < last; ++item) {
-    if (marks && ((item - first) & (THREADS - 1)) == 0) {   // uniform; the usual case: nothing marked in the next 256
-      while (item < last && !__syncthreads_or(item + tid < last ? marks[item + tid] : 0)) item += THREADS;
-      if (item >= last) break;
+  // blocks blockIdx.x, blockIdx.x + gridDim.x, ..: see SHARERS (B <= 2^24)
+  const unsigned step = gridDim.x, total = (unsigned)B;
+  for (unsigned item = blockIdx.x, i = 0; item < total; item += step, ++i) {
+    if (marks && (i & (THREADS - 1)) == 0) {   // uniform; the usual case: nothing marked in the next 256 of them
+      while (item < total && !__syncthreads_or(item + tid * step < total ? marks[item + tid * step] : 0)) item += THREADS * step;
+      if (item >= total) break;
     }
     if (marks && !marks[item]) continue;
     const size_t blk = (size_t)item;
@@ -1485,7 +1491,7 @@ hipError_t eoq_launch_spectral(const EoqLaunch& L, const void* blocks, int dtype
     hipLaunchKernelGGL(eoq_spectral_tridiag_kernel, dim3((unsigned)B), dim3(THREADS), 0, L.stream, blocks, L.map, dtype, L.n,
                        L.k, L.rank_thr, L.r_max, L.loss, marks, lam, wfac, tri, out.rank, out.phi, out.sigma, out.rfac,
                        out.flags);
-    const unsigned grid = (unsigned)((B < 256) ? B : 256);
+    const unsigned grid = (unsigned)((B < SHARERS) ? B : SHARERS);
     hipLaunchKernelGGL(eoq_spectral_jacobi_kernel, dim3(grid), dim3(THREADS), 0, L.stream, blocks, L.map, dtype, L.n, L.k,
                        L.rank_thr, L.r_max, L.loss, B, (const int*)marks, lam, wfac, out.rank, out.phi,
                        out.sigma, out.rfac, out.flags);

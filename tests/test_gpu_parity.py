@@ -310,6 +310,67 @@ def test_repeated_singular_values_go_to_the_jacobi_solver():
                                                              rec.lfac, rec.rfac, rec.flags))), lam[1:], recs[1:], 2)
 
 
+def _bank_with_repeated_values(n):
+    """Eight blocks, the first two with two exactly equal leading singular values (they go to the Jacobi solver)."""
+    spec = synth.BlockSpec("bank", n=n, n_tensors=1, blocks_per_tensor=8, rank_lo=1, rank_hi=6)
+    bank = synth.make_blocks(spec, seed=19, device=DEV)[0].clone()
+    for b, (lo, hi) in enumerate(((0, 1), (5, 90))):
+        bank[b] = 0.0
+        bank[b, : n // 2, lo] = 100.0
+        bank[b, n // 2:, hi] = 100.0
+    return bank
+
+
+def test_hand_over_to_the_jacobi_solver_in_large_batches():
+    """Marked blocks at the ends of every workgroup's share and of its looks at 256 marks, in a batch where a share is more
+    than one look: every record and spectrum equal, bit for bit, to that of the same block in a batch of eight."""
+    n, sharers = 128, 251
+    B = 256 * sharers + 300
+    ctx = eoq.Context(n=n, bits=2, r_max=8)
+    bank = _bank_with_repeated_values(n)
+    ref, ws = ctx.eoq_compress(bank)
+    ref_lam = ctx.spectrum(ws, 8).clone()
+    assert ((ref.flags >> 8) & 0xFF > 0).tolist() == [True] * 2 + [False] * 6
+    idx = torch.arange(B, device=DEV) % 6 + 2
+    edge = 256 * sharers
+    marked = [0, 1, 250, 251, 255, 256, 257, 30000, 30001, 30251, edge - 252, edge - 251, edge - 1, edge, edge + 1, edge + 250, edge + 251, B - 1]
+    idx[torch.as_tensor(marked, device=DEV)] = torch.arange(len(marked), device=DEV) % 2
+    rec, ws = ctx.eoq_compress(bank[idx])
+    torch.cuda.synchronize()
+    assert int(((rec.flags >> 8) & 0xFF > 0).sum()) == len(marked)
+    for f in _FIELDS:
+        assert torch.equal(getattr(rec, f).view(torch.uint8), getattr(ref, f)[idx].view(torch.uint8)), f
+    assert torch.equal(ctx.spectrum(ws, B), ref_lam[idx])
+
+
+@pytest.mark.parametrize("distance", [1, 16, 20])
+def test_hand_over_to_the_jacobi_solver_uses_the_whole_chip(distance):
+    """200 marked blocks, side by side or at a fixed distance, take about as long as one: there are more workgroups than
+    that.  (With sixteen to a workgroup the call takes more than three times as long as with one.)"""
+    n, B = 128, 4096
+    ctx = eoq.Context(n=n, bits=2, r_max=8)
+    bank = _bank_with_repeated_values(n)
+
+    def time_ms(where):
+        idx = torch.arange(B, device=DEV) % 6 + 2
+        idx[where] = 0
+        x = bank[idx]
+        rec, ws = ctx.eoq_compress(x)
+        best = math.inf
+        for _ in range(3):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            ctx.eoq_compress(x, rec, ws)
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1))
+        return best
+
+    one = time_ms(torch.as_tensor([7], device=DEV))
+    many = time_ms(7 + distance * torch.arange(200, device=DEV))
+    assert many < 3.0 * one, (one, many)
+
+
 @pytest.mark.parametrize("bits,rank_lo,rank_hi,n", [(2, 2, 8, 512), (3, 2, 8, 512), (1, 1, 6, 256), (4, 2, 8, 256),
                                                      (2, 17, 24, 512), (3, 9, 20, 128), (2, 1, 12, 1024)])
 def test_decompress_of_oracle_records_elementwise(bits, rank_lo, rank_hi, n):
