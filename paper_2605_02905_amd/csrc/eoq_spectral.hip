@@ -1105,11 +1105,12 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       tri_blk[tid] = t;
     }
     // The stores are in the L2 of this XCD once they are acknowledged, and that is where a miss of the scalar cache is
-    // served from: waiting for them is enough.  The wait is an opaque statement that touches memory, so the compiler can
-    // move neither the stores behind it nor the loads below in front of it; a barrier alone orders a workgroup's vector
-    // accesses and need not wait for stores.  (A fence at device scope also writes back what the whole L2 holds modified:
-    // 35 K of a block's 475 K cycles with every compute unit at it.)
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    // served from: waiting for them is enough.  (A fence at device scope also writes back what the whole L2 holds
+    // modified: 35 K of a block's 475 K cycles with every compute unit at it.)  The opaque statement in front
+    // keeps the stores above the wait, the one behind the barrier the loads below it; the barrier by itself orders a
+    // workgroup's vector accesses and does not wait for stores.
+    asm volatile("" : : : "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     __syncthreads();
     // the copy in global memory, addressed through the scalar unit; the address passes through an opaque
     // register move placed after the barrier so that none of these loads can be scheduled before the stores
