@@ -3,6 +3,8 @@ tables as the oracle, and rejects bad arguments without a GPU."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -77,6 +79,17 @@ def test_workspace_size_and_host_only_context(lib):
         st = lib.eoq_decompress(ctx._h, eoq._Packed(), 1, None, None)
         assert st == eoq.EOQ_ERR_HIP
         assert b"HIP device" in lib.eoq_last_error(ctx._h)
+
+
+def test_binding_imports_and_serves_tables_on_a_pytorch_without_gpus(lib):
+    """Tables and sizes need no device, and a PyTorch built without one lacks its private stream lookup."""
+    code = ("import torch\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_2605_02905_amd import eoq\n"
+            "ctx = eoq.Context(n=128, bits=2)\n"
+            "assert ctx.eoq_codebook()[0].shape == (4,) and ctx.eoq_workspace_bytes(1) > 0\n")
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
 
 
 @pytest.mark.parametrize("n,kv", [(128, 8), (512, 8), (128, 1), (1024, 3)])
