@@ -155,6 +155,7 @@ EoqLaunch make_launch(const eoq_ctx* ctx, void* stream) {
   L.ev = ctx->profile ? ctx->ev : nullptr;
   L.solver = ctx->solver;
   L.loss = ctx->loss;
+  std::memcpy(L.score_places, ctx->score_places, sizeof(L.score_places));
   L.map = eoq_dense_map(ctx->n);
   return L;
 }
@@ -228,6 +229,12 @@ eoq_status eoq_create(eoq_ctx** out, int n, int d, int bits, uint64_t rot_seed, 
     if (e == hipSuccess) g_scratch_ptr[ctx->device] = p;
   }
   if (e == hipSuccess) e = eoq_factor_quant_prepare();
+  for (int corrected = 0; corrected < 2; ++corrected)
+    for (int wide = 0; wide < 2; ++wide) {
+      const int places = e == hipSuccess ? eoq_scores_places(bits, corrected, wide ? 8 : 4) : 0;
+      ctx->score_places[corrected][wide] = places;
+      if (e == hipSuccess && places <= 0) e = hipErrorInvalidDeviceFunction;
+    }
   const size_t mat_bytes = (size_t)d * d * sizeof(float);
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->d_pi, mat_bytes);
   if (e == hipSuccess) e = hipMalloc((void**)&ctx->d_pit, mat_bytes);

@@ -568,6 +568,12 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
 #undef EOQ_SC_WORK
 }
 
+template <int BITS>
+const void* scores_kernel(bool qjl, bool wide) {
+  if (qjl) return wide ? (const void*)eoq_scores_i8_kernel<BITS, true, 4> : (const void*)eoq_scores_i8_kernel<BITS, true, 2>;
+  return wide ? (const void*)eoq_scores_i8_kernel<BITS, false, 4> : (const void*)eoq_scores_i8_kernel<BITS, false, 2>;
+}
+
 hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl* qjl, int64_t n_seq, int n_kv_heads,
                               int64_t blocks_per_head, const void* q_fp16, int n_q_heads, float* scores,
                               int64_t block_capacity, int64_t score_stride, const void* tail_fp16,
@@ -578,10 +584,11 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   if (L.ev) (void)hipEventRecord(L.ev[6], L.stream);
   const int64_t tail_groups = (tail_len + TAIL_TOK - 1) / TAIL_TOK;
   // blocks per workgroup: the set-up is paid once per workgroup, so runs are as long as they can be (16) while the grid
-  // still has a workgroup for each place on the chip (256 compute units times what registers allow; a workgroup of the tail
-  // is short, four of them count as one).  A second, partly filled round of workgroups costs a set-up and a run, more
-  // than runs that are one block longer: 612 blocks of 512, 4 bits, 51 us in two rounds, 34 in one.
-  const int64_t places = 256 * (qjl ? (L.bits <= 2 ? 3 : (L.bits == 3 ? 2 : 1)) : (L.bits <= 2 ? 4 : (L.bits == 3 ? 3 : 2)));
+  // still has a workgroup for each place on the chip (what eoq_scores_places found for the kernel that is launched).  A
+  // workgroup of the tail is short, four of them count as one.  A second, partly filled round of workgroups costs a set-up
+  // and a run, more than runs that are one block longer: 612 blocks of 512, 4 bits, 51 us in two rounds, 34 in one.
+  const int group = n_q_heads / n_kv_heads;
+  const int64_t places = L.score_places[qjl ? 1 : 0][group <= 4 ? 0 : 1];
   const int64_t tail_places = sg_total * tail_groups / 4;
   const int64_t room = places - (tail_places < places / 2 ? tail_places : places / 2);
   int64_t run = (sg_total * blocks_per_head + room - 1) / room;
@@ -590,7 +597,6 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   if (sg_total > 65535 || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(runs + tail_groups), (unsigned)sg_total), block(THREADS);
   const uint16_t* q = static_cast<const uint16_t*>(q_fp16);
-  const int group = n_q_heads / n_kv_heads;
 #define EOQ_SCORES_ARGS                                                                                              \
   grid, block, 0, L.stream, L.n, L.r_max, n_kv_heads, group, blocks_per_head, block_capacity, score_stride, (int)run, \
       L.pih, L.tab, keys.codes, keys.norms, keys.rank, keys.lfac, keys.rfac, q, scores
@@ -624,6 +630,19 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
 }
 
 }  // namespace
+
+// Workgroups of the kernel for `bits` that the current device holds at a time, by the compiled kernel's own registers and LDS
+// (a table of numbers beside the kernels was wrong at 4 bits with the correction, one per unit where two fit: 2048 blocks of
+// 512 for groups of three 57 us, now 49; 512 blocks for groups of four 21 either way).
+extern "C" int eoq_scores_places(int bits, int corrected, int group) {
+  const bool qjl = corrected != 0, wide = group > 4;
+  const void* f = bits == 1 ? scores_kernel<1>(qjl, wide) : (bits == 2 ? scores_kernel<2>(qjl, wide) : (bits == 3 ? scores_kernel<3>(qjl, wide) : scores_kernel<4>(qjl, wide)));
+  int device = 0, units = 0, per_unit = 0;
+  if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_unit, f, THREADS, 0) != hipSuccess)
+    return 0;
+  return units * per_unit;
+}
 
 hipError_t eoq_launch_scores(const EoqLaunch& L, eoq_packed keys, int64_t n_seq, int n_kv_heads,
                              int64_t blocks_per_head, const void* q_fp16, int n_q_heads, float* scores,

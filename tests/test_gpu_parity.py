@@ -1156,6 +1156,31 @@ def test_scores_prod_of_oracle_records(bits, group, n):
     assert np.max(np.abs(sp - s0)) > 1e-3                               # the correction is there
 
 
+def test_scores_grid_follows_the_compiled_kernels(tmp_path):
+    """The number of workgroups that the grid rule counts with is what the registers and LDS of each compiled kernel allow
+    on a compute unit: 512 registers per lane and SIMD in steps of 8, four SIMDs, 160 KB."""
+    import __graft_entry__ as g
+    import os
+    import re
+    import subprocess
+    flags = [f for f in g.HIP_FLAGS if f not in ("-shared", "-fPIC")]
+    res = subprocess.run([g.HIPCC, *flags, "-I" + os.path.join(g.ROOT, "include"), "-I" + g.CSRC, "--offload-device-only", "-c",
+                          "-Rpass-analysis=kernel-resource-usage", os.path.join(g.CSRC, "eoq_scores.hip"), "-o", str(tmp_path / "o")],
+                         capture_output=True, text=True)
+    assert res.returncode == 0
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    seen = 0
+    for part in res.stderr.split("Function Name: ")[1:]:
+        m = re.search(r"eoq_scores_i8_kernelILi(\d)ELb(\d)ELi(\d)E", part.split()[0])
+        num = lambda what: int(re.search(re.escape(what) + r": (\d+)", part).group(1))
+        regs = -(-num("VGPRs") // 4) * 4 + num("AGPRs")       # the accumulation registers start at a multiple of 4
+        fit = min(512 // (-(-regs // 8) * 8), (160 << 10) // num("LDS Size [bytes/block]"))
+        bits, corrected, heads = (int(x) for x in m.groups())
+        assert eoq.lib().eoq_scores_places(bits, corrected, 2 * heads) == units * fit, (bits, corrected, heads, fit)
+        seen += 1
+    assert seen == 16
+
+
 def test_tq_prod_end_to_end_in_the_bench_launch_configuration():
     """Config 6 (4096 blocks of 128 x 128) through eoq_compress -> eoq_qjl_encode -> eoq_scores_prod in single launches;
     a strided sample of blocks is followed through the oracle on the stored records, and over the whole key set the
