@@ -227,3 +227,23 @@ def packed_to_records(rec, idx, bits: int):
             rec_np(rec.lfac[b, :k]).astype(np.float64), rec_np(rec.rfac[b, :k]).astype(np.float64),
             oracle.unpack_codes(rec_np(rec.codes[b]), bits, d), rec_np(rec.norms[b]).astype(np.float64)))
     return out
+
+
+def reconstruct64(rec, bits: int):
+    """What a device record (eoq.Packed) stands for, [B, n, d] in float64 on its device: rho/sqrt(d) centroid[codes] Pi +
+    C V, from the oracle's tables."""
+    import torch
+    dev = rec.codes.device
+    B, n = rec.norms.shape
+    d = rec.rfac.shape[2]
+    Pi, cb = oracle_tables(bits, d)
+    Pi, cent = torch.as_tensor(Pi, device=dev), torch.as_tensor(cb.centroids_f32.astype(np.float64), device=dev)
+    live = torch.arange(rec.lfac.shape[1], device=dev)[None, :] < rec.rank[:, None]
+    out = torch.empty(B, n, d, dtype=torch.float64, device=dev)
+    for b in range(B):
+        planes = (rec.codes[b].view(n, bits, d // 8)[..., None] >> torch.arange(8, dtype=torch.uint8, device=dev)) & 1
+        idx = (planes.reshape(n, bits, d).long() << torch.arange(bits, device=dev)[None, :, None]).sum(1)
+        scale = rec.norms[b].view(torch.float16).double() / math.sqrt(d)
+        k = live[b]
+        out[b] = scale[:, None] * (cent[idx] @ Pi) + rec.lfac[b][k].double().T.contiguous() @ rec.rfac[b][k].double()
+    return out

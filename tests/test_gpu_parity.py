@@ -963,17 +963,26 @@ def test_softmax_row_lengths_and_alignments(length, pad):
     assert torch.equal(s[:, length:], ref[:, length:])
 
 
+# Attention output against the record in float64, in units of (sum_t w_t^2 |x_hat_t|^2)^(1/2).  Per coordinate the roundings
+# are: w rho / sqrt(d), three of 2^-24 relative per token; float32 sums over waves, runs and the 128 terms of the rotation,
+# some ten roundings of the size of the sum or of a random share of it; the result itself.  Together a few 2^-24 of the
+# coordinate, whose root mean square is 128^(-1/2) of the unit; the bar is five times four of them, for the largest of all
+# coordinates.
+ATTEND_TOL = 5 * 4 * 2.0 ** -24 / 128 ** 0.5
+
+
 @pytest.mark.parametrize("n,bits,group,filled,tail_len", [(128, 1, 7, 5, 0), (256, 2, 5, 9, 77), (128, 2, 3, 70, 127), (512, 3, 6, 3, 389),
                                                           (128, 4, 7, 33, 1), (1024, 4, 4, 2, 0)])
 def test_attention_output_weights_of_any_size(n, bits, group, filled, tail_len):
-    """Weights that are no softmax: signs, zeros, a magnitude that grows by 2^60 along the row (the fixed-point unit has
-    to follow), an odd row stride; ranks above 16; tails.  One head with a NaN weight leaves the others alone."""
+    """Weights that are no softmax: signs, zeros, a magnitude that grows by 2^60 along the row (every wave has a
+    fixed-point unit of its own), an odd row stride; ranks above 16; tails.  One head with a NaN weight leaves the others
+    alone.  The reference is the record in float64; the bar is ATTEND_TOL's."""
     n_kv, cap, r_max = 2, filled + 1, 32
     ctx = eoq.Context(n=n, bits=bits, r_max=r_max)
     spec = synth.BlockSpec("vals", n=n, n_tensors=n_kv, blocks_per_tensor=cap, rank_lo=0, rank_hi=24)
     blocks, _ = synth.make_blocks(spec, seed=77 + n + bits, device=DEV)
     store, _ = ctx.eoq_compress(blocks)
-    x = ctx.eoq_decompress(store).double().cpu().view(n_kv, cap * n, 128)[:, :filled * n]
+    x = U.reconstruct64(store, bits).cpu().view(n_kv, cap * n, 128)[:, :filled * n]
     gen = torch.Generator().manual_seed(bits)
     tail = torch.randn(1, n_kv, n, 128, generator=gen).to(torch.float16)
     T = filled * n + tail_len
@@ -984,19 +993,68 @@ def test_attention_output_weights_of_any_size(n, bits, group, filled, tail_len):
     w[0, 2, :T] *= grow.flip(0)
     ref = torch.cat([x, tail[0, :, :tail_len].double()], dim=1)
     want = torch.stack([w[0, h, :T].double() @ ref[h // group] for h in range(n_kv * group)]).numpy()
-    # decompression rounds to binary16 and rotates with a binary16 table: the bar is that error's, per head
     norm = np.stack([(w[0, h, :T].double().square() @ ref[h // group].square().sum(1)).sqrt().item() for h in range(n_kv * group)])
     out = ctx.eoq_attend_stream(store, w.to(DEV), n_kv, cap, filled, tail.to(DEV), tail_len)
     torch.cuda.synchronize()
     got = out[0].double().cpu().numpy()
-    assert np.all(np.max(np.abs(got - want), axis=1) <= 1e-3 * norm)
+    U.log_stats(f"attend_any_size_b{bits}_g{group}_n{n}", dict(err=float(np.max(np.max(np.abs(got - want), axis=1) / (ATTEND_TOL * norm)))))
+    assert np.all(np.max(np.abs(got - want), axis=1) <= ATTEND_TOL * norm)
     bad = w.clone()
     bad[0, group, T // 3] = float("nan")
     out2 = ctx.eoq_attend_stream(store, bad.to(DEV), n_kv, cap, filled, tail.to(DEV), tail_len)
     torch.cuda.synchronize()
     assert bool(torch.isnan(out2[0, group]).all())
     keep = [h for h in range(n_kv * group) if h != group]
-    assert np.all(np.max(np.abs(out2[0, keep].double().cpu().numpy() - want[keep]), axis=1) <= 1e-3 * norm[keep])
+    assert np.all(np.max(np.abs(out2[0, keep].double().cpu().numpy() - want[keep]), axis=1) <= ATTEND_TOL * norm[keep])
+
+
+@pytest.mark.parametrize("bits,group,n", [(1, 4, 128), (1, 7, 512), (2, 4, 512), (2, 8, 1024), (3, 4, 128), (3, 6, 512), (4, 4, 1024), (4, 7, 128)])
+def test_attention_output_follows_weights_that_outgrow_their_unit(bits, group, n):
+    """Weights that grow by 2^8 and by 2^8 again inside the tokens of a wave (seven pairs of 32-token tiles; the first four
+    choose the unit): the sums so far are put away and a new unit is chosen, for the codebook and the low-rank term.  A NaN
+    in the middle of a wave stays in its head.  The bar sees the lowest byte of a weight: a reference whose weights lose it
+    is further away than that."""
+    n_kv, ppw = 2, 7
+    T = 401408                                             # per KV head: 2 x 6272 pairs on 2048 waves, seven each
+    filled, r_max = T // n, 8
+    B = n_kv * filled
+    gen = torch.Generator(device=DEV).manual_seed(bits + n)
+    rand = lambda *shape: torch.rand(*shape, generator=gen, device=DEV)
+    rec = eoq.Packed(torch.randint(0, 256, (B, n, 16 * bits), generator=gen, device=DEV, dtype=torch.uint8), (rand(B, n) * 0.4 + 0.8).half(),
+                     torch.randint(0, r_max + 1, (B,), generator=gen, device=DEV, dtype=torch.int32), rand(B, r_max), rand(B, r_max),
+                     (0.1 * (rand(B, r_max, n) - 0.5)).half(), (0.2 * (rand(B, r_max, 128) - 0.5)).half(),
+                     torch.zeros(B, dtype=torch.int32, device=DEV))
+    pair = torch.arange(T, device=DEV) // 64
+    step = torch.exp2(8.0 * ((pair % ppw) - 4).clamp(0, 2))   # pairs 0 .. 4 of a wave: 1, then 2^8, 2^16
+    step[: T // 2] = 1.0                                      # half of the waves keep their unit
+    w = (rand(1, n_kv * group, T) * 0.5 + 0.5) * torch.where(rand(1, n_kv * group, T) < 0.5, -1.0, 1.0)
+    w[0, 1::2] *= step
+    ctx = eoq.Context(n=n, bits=bits, r_max=r_max)
+    out = ctx.eoq_attend(rec, w, n_kv)[0].double()
+    x = U.reconstruct64(rec, bits).view(n_kv, T, 128)
+    rho = rec.norms.double().view(n_kv, T)
+    stats = dict(err=0.0, err_cut=math.inf)                   # in units of the bar
+    wants, norms = [], []
+    for h in range(n_kv * group):
+        xh, wh = x[h // group], w[0, h].double()
+        want = wh @ xh
+        norm = (wh.square() @ xh.square().sum(1)).sqrt()
+        wants.append(want)
+        norms.append(norm)
+        stats["err"] = max(stats["err"], float((out[h] - want).abs().max() / (ATTEND_TOL * norm)))
+        # 28 bits for the largest sum of four magnitudes of a wave, less a byte
+        wr = (wh * rho[h // group]).view(-1, ppw * 64)
+        unit = torch.exp2(torch.floor(torch.log2(2.0 * wr.abs().amax(1, keepdim=True))) - 20)
+        cut = (torch.round(wr / unit) * unit).view(-1) / rho[h // group]
+        if h % 2 == 0:
+            stats["err_cut"] = min(stats["err_cut"], float((cut @ xh - want).abs().max() / (ATTEND_TOL * norm)))
+    U.log_stats(f"attend_units_b{bits}_g{group}_n{n}", stats)
+    assert stats["err"] <= 1.0 < stats["err_cut"], stats
+    w[0, group, 64 * (5 * ppw + 5) + 3] = float("nan")
+    bad = ctx.eoq_attend(rec, w, n_kv)[0].double()
+    assert bool(torch.isnan(bad[group]).all())
+    for h in range(n_kv * group):                             # the others: their sums are put away at other places
+        assert h == group or float((bad[h] - wants[h]).abs().max()) <= ATTEND_TOL * float(norms[h]), h
 
 
 def test_decode_step_scores_softmax_attend_in_the_bench_launch_configuration():
