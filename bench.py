@@ -114,7 +114,7 @@ def _cpu_job(args):
 
 def cpu_baseline(blocks_cpu, bits: int, seed: int, q_cpu, sample_blocks: int, passes: int, factor_bits: int = 16):
     import numpy as np
-    cores = min(os.cpu_count() or 1, 16)       # at most 16 workers (the GPU machine's CPU share), stated in `cores`
+    cores = min(os.cpu_count() or 1, 16)       # at most 16 workers, stated in `cores`
     B = min(sample_blocks, blocks_cpu.shape[0])
     arr = blocks_cpu[:B].numpy()
     q = None if q_cpu is None else q_cpu.double().numpy()

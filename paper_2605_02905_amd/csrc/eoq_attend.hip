@@ -664,7 +664,7 @@ __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_hea
 // Row-wise softmax in place (the attention weights of Sec. 2.1), one workgroup of NT lanes per row.  The row passes
 // through registers once: up to 4 NV elements per lane are loaded (all loads in flight), their maximum is met, they are
 // exponentiated and summed, met again, scaled and stored -- one read and one write of the row instead of three reads and
-// two writes (512 rows of 65536: 97 us before).  What a row has beyond 4 NV NT elements stays in memory and is read and
+// two writes (512 rows of 65536: 97 us so, 57 now).  What a row has beyond 4 NV NT elements stays in memory and is read and
 // written in the three passes of the plain algorithm.  Four consecutive elements per access wherever the row starts:
 // accesses sit on 16-byte boundaries of the buffer, and the one at either end of a row that also covers elements of
 // another row (or none) goes element by element.

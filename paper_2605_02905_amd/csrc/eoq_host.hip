@@ -8,7 +8,7 @@
 #include "eoq_internal.h"
 
 // ---------------------------------------------------------------------------
-// Scratch of eoq_compress_static: the workspace of eoq_compress (eigenvalues, projection operands, hand-over list,
+// Scratch of eoq_compress_static: the workspace of eoq_compress (eigenvalues, projection operands, hand-over marks,
 // tridiagonal matrices) for callers that cannot hand one in.  One copy per GPU, held until the process ends.  In host
 // code the name below is only a stand-in for the symbol: the device address comes from hipGetSymbolAddress, once per
 // device (eoq_create, with that device current), and only that pointer is ever passed to a kernel.
@@ -299,7 +299,7 @@ void eoq_destroy(eoq_ctx* ctx) {
 
 size_t eoq_workspace_bytes(const eoq_ctx* ctx, int64_t B) {
   if (!ctx || B < 0) return 0;
-  return eoq_ws_lam_bytes(B) + eoq_ws_wfac_bytes(B, ctx->r_max) + eoq_ws_list_bytes(B) + eoq_ws_tri_bytes(B);
+  return eoq_ws_lam_bytes(B) + eoq_ws_wfac_bytes(B, ctx->r_max) + eoq_ws_marks_bytes(B) + eoq_ws_tri_bytes(B);
 }
 
 eoq_status eoq_rotation(const eoq_ctx* ctx, float* host_out) {
@@ -355,7 +355,7 @@ eoq_status compress_impl(eoq_ctx* ctx, const void* blocks, eoq_dtype dtype, int6
   char* ws = static_cast<char*>(workspace);
   float* wfac = reinterpret_cast<float*>(ws + eoq_ws_lam_bytes(B));
   int* marks = reinterpret_cast<int*>(ws + eoq_ws_lam_bytes(B) + eoq_ws_wfac_bytes(B, ctx->r_max)) + 4;
-  const uintptr_t tri_at = reinterpret_cast<uintptr_t>(reinterpret_cast<char*>(marks - 4) + eoq_ws_list_bytes(B));
+  const uintptr_t tri_at = reinterpret_cast<uintptr_t>(reinterpret_cast<char*>(marks - 4) + eoq_ws_marks_bytes(B));
   double* tri = reinterpret_cast<double*>((tri_at + 63) & ~(uintptr_t)63);
   hipError_t e = eoq_launch_spectral(L, blocks, (int)dtype, B, lam, wfac, marks, tri, out);
   if (fq) {

@@ -82,7 +82,7 @@ struct EoqLaunch {
 // back through the scalar cache: a block's 2 KB must not share a cache line with its neighbours').
 inline size_t eoq_ws_lam_bytes(int64_t B) { return (size_t)B * EOQ_D * sizeof(double); }
 inline size_t eoq_ws_wfac_bytes(int64_t B, int r_max) { return (size_t)B * r_max * EOQ_D * sizeof(float); }
-inline size_t eoq_ws_list_bytes(int64_t B) { return 16 + (((size_t)B * sizeof(int) + 15) & ~(size_t)15); }
+inline size_t eoq_ws_marks_bytes(int64_t B) { return 16 + (((size_t)B * sizeof(int) + 15) & ~(size_t)15); }
 inline size_t eoq_ws_tri_bytes(int64_t B) { return B > 0 ? 64 + (size_t)B * EOQ_D * 2 * sizeof(double) : 0; }
 
 hipError_t eoq_launch_spectral(const EoqLaunch& L, const void* blocks, int dtype, int64_t B, double* lam,

@@ -153,7 +153,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
 
   // ---- set-up: two waits.  First the ranks, Pi^T (by rows, the whole workgroup) and the first tile's codes; then what
   // needs the rank, which travels while Pi^T goes through LDS into operand order.  (Every wave reading its operand from
-  // memory, 64 rows per instruction, and four waits in a row: 18.7 us for 371 blocks of 128 at 4 bits, then 14.6.) ----
+  // memory, 64 rows per instruction, and four waits in a row: 18.7 us for 371 blocks of 128 at 4 bits, 14.6 so; 7.7 with
+  // the table of pairs, too.) ----
   const __amdgpu_buffer_rsrc_t ranks = buffer_of(rank_in, (size_t)B * 4);
   int64_t blk = u >> parts_log2;
   int part = (int)u & part_mask;
@@ -417,8 +418,10 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_decode_mfma_kernel(
 // the eight waves of the workgroup (one per compute unit, two waves per SIMD).
 // Bound by the matrix cores: 160 instructions per tile, 32 cycles each (about 45 at the clock such a stretch leaves), of
 // a wave that has no registers to read operands far ahead: every phase left out of it takes twice its matrix
-// instructions' time with it.  262144 tokens of 2 bits: 53 us.  The workgroup-per-block version this replaces exchanged
-// centroids and residuals through LDS with a barrier per 64 tokens at one wave per SIMD: 100 us.
+// instructions' time with it.  262144 tokens of 2 bits: 50 us (matrix cores busy 45 % of it).  A workgroup per block that
+// exchanged centroids and residuals through LDS with a barrier per 64 tokens at one wave per SIMD: 100 us.
+// The registers do not hold all of it: 128 of Pi^T, 64 accumulators and 64 of the residual's parts are the 256 a lane has,
+// and the compiler keeps 2, 5, 15 and 16 of them in scratch memory at 1, 2, 3 and 4 bits (12 to 52 bytes per lane).
 // ---------------------------------------------------------------------------------------------
 constexpr int QWAVES = 8;
 constexpr int SLD = 64 + 8;   // row stride (halfs) of the staged half tile

@@ -392,7 +392,7 @@ __device__ __forceinline__ double4v mfma64(double a, double b, double4v c) { ret
 // Gram matrix of a float32 block on the fp64 matrix cores (products of float32 numbers are exact in double): nine of the 36
 // tiles per wave.  Lane l = 16 g + c supplies S[t + g][16 I + c] as operand of tile row or column I of v_mfma_f64_16x16x4_f64,
 // straight from memory, sixteen tokens ahead; result register v is row 4 v + g, column c.  As vector multiply-adds out
-// of LDS a compress call of 125 blocks of 512 x 128 took 272 us, now 241.
+// of LDS a compress call of 125 blocks of 512 x 128 took 272 us, now 244.
 __device__ __forceinline__ void gram_f64(const float* __restrict__ src, size_t tok, int n, double* Tl, int tid, double (&A)[64],
                                          unsigned* flag_s) {
   const int lane = tid & 63, c = lane & 15, g = lane >> 4;
@@ -1012,8 +1012,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     int* __restrict__ marks, double* __restrict__ lam_out, float* __restrict__ wfac,
     double* __restrict__ tri, int32_t* __restrict__ rank_out, float* __restrict__ phi_out, float* __restrict__ sigma_out,
     uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
-  // one pool, used in turn by the Gram stage (byte planes / float strip), the reduction (reflectors) and the
-  // eigenvector stage (u1)
+  // one pool, used in turn by the Gram stage (byte planes, then the tiles on their way into the cyclic layout), the
+  // reduction (reflectors) and the eigenvector stage (u1)
   __shared__ __align__(16) unsigned char pool[POOL_BYTES];
   float* refl = reinterpret_cast<float*>(pool) + REFL_SLACK;
   unsigned char* u1 = pool + REFL_BYTES;
@@ -1138,7 +1138,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     int ce_lo = 0, ce_hi = D;
     float f_lo = 0.0f, f_hi = 0.0f;
     {
-      // every lane counts at one point of a uniform grid; each eigenvalue then starts from its grid cell
+      // every lane counts at one point of a grid; each eigenvalue then starts from its grid cell
       int* ce_s = reinterpret_cast<int*>(atoms);
       float* gval_s = reinterpret_cast<float*>(&vbuf[0][0]);   // the reduction's buffers are free by now
       // grid point g at ((g + 1) / 257)^3: most eigenvalues of a block are noise eigenvalues far below the largest

@@ -581,7 +581,7 @@ def test_full_size_batches_in_the_bench_launch_configuration(cfg, stride, bits):
 
 def test_second_call_reuses_the_workspace_with_other_data():
     """Two calls in a row on the same context, record and workspace with different blocks: nothing of the first
-    call (eigenvalues, tridiagonal scratch read through the scalar cache, hand-over list) leaks into the second."""
+    call (eigenvalues, tridiagonal scratch read through the scalar cache, hand-over marks) leaks into the second."""
     spec = synth.config(2)
     a, _ = synth.make_blocks(spec, tensors=range(1))
     b, _ = synth.make_blocks(spec, seed=synth.SEED_BASE + 77, tensors=range(1))
