@@ -203,16 +203,18 @@ class Qjl:
                    torch.empty(B, n, dtype=torch.float16, device=device))
 
 
-_raw_stream = None   # torch's own lookup of a device's current stream, found on first use (a PyTorch without GPUs has none)
+def _raw_stream(index: int) -> int:
+    """Current stream of device number `index`.  The first call puts torch's own lookup in this function's place, or the
+    public one where torch has none (a PyTorch without GPUs): importing this module needs neither."""
+    global _raw_stream
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _raw_stream(index)
 
 
 def _stream_ptr(device) -> int:
     """The device's current stream, without a Stream object around it where torch offers that: 0.2 instead of 2.1 us,
     three times in a decode step of 22 us."""
-    global _raw_stream
-    if _raw_stream is None:
-        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
-            lambda index: torch.cuda.current_stream(index).cuda_stream)
     index = device.index
     return torch.cuda.current_stream(device).cuda_stream if index is None else _raw_stream(index)
 
