@@ -156,6 +156,8 @@ struct TileFetch {
 // kernel, 64 tokens each: a kernel of their own cost a launch, and with one workgroup per head 32 us at 12 heads and 389
 // tokens.
 constexpr int TAIL_TOK = 64;
+constexpr int SHORT_RUN = 6;   // see the launch
+constexpr int QUAD = 128;   // tokens of one tile of each of the four waves
 __device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, int t0, int tail_len,
                                             const uint16_t* __restrict__ q, int group, float* __restrict__ row, size_t T, float* qs,
                                             int tid) {
@@ -189,9 +191,9 @@ __device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, i
   }
 }
 
-// One workgroup per (sequence, KV head, run of blocks); every wave works on 32-token tiles of its own (tile u of the
-// run: tokens 32 (u % tpb) .. of block u / tpb; wave w takes the tiles w, w + 4, ...), the record bytes of the next
-// tile on their way while this one is worked on.  NQ = query heads a lane finishes per token (2 for groups up to 4).
+// One workgroup per (sequence, KV head, run of tokens); every wave works on 32-token tiles of its own (wave w takes the tiles
+// w, w + 4, ... of the run), the record bytes of the next tile on their way while this one is worked on.  A run is a number of
+// steps of 128 tokens, a tile for each wave, and may begin and end inside a block (see the rule at the launch).  NQ = query heads a lane finishes per token (2 for groups up to 4).
 // QJL: the logits get the correction of Eq. (qjl), |r_x| sqrt(pi/2)/d <Phi q, sign(Phi r_x)>, from one more bit plane
 // (the signs) and the stored residual norm; Phi q goes through the same fixed-point form as Pi q.
 template <int BITS, bool QJL, int NQ>
@@ -237,10 +239,15 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     return;
   }
 
-  const int64_t jb0 = (int64_t)blockIdx.x * run;
-  const int nblk = (int)(min(jb0 + run, blocks_per_head) - jb0);
-  const int tpb = n / 32;
-  const int NT = nblk * tpb;
+  // the run: `run` steps of QUAD tokens from step number blockIdx.x * run of the head, which is token tok0 of block jb0; the
+  // blocks it touches are numbers 0 .. nblk - 1 of the run (B n < 2^39: a step number fits 32 bits)
+  const uint32_t steps_per_block = (uint32_t)n / QUAD;
+  const uint32_t step0 = blockIdx.x * (uint32_t)run;
+  const int count = (int)min((uint32_t)run, (uint32_t)blocks_per_head * steps_per_block - step0);   // tiles of every wave
+  const uint32_t first_block = step0 / steps_per_block, in_block = step0 - first_block * steps_per_block;
+  const int64_t jb0 = first_block;
+  const int tok0 = QUAD * (int)in_block;
+  const int nblk = (int)((in_block + (uint32_t)count - 1) / steps_per_block) + 1;
   const size_t blk0 = sg * (size_t)block_capacity + jb0;   // the store holds block_capacity slots per head
 
   // ---- set-up.  It is paid once per workgroup and is latency: everything that depends on nothing is requested first
@@ -279,9 +286,7 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   // Buffer addressing: a resource descriptor in scalar registers, a scalar byte offset that moves from tile to tile and
   // a per-lane 32-bit offset that never changes -- no vector arithmetic per load.  The coefficients get a descriptor per
   // block that ends behind row rank - 1, and the range check covers the per-lane part of the offset, which holds the
-  // row: rows at and above the rank read zero.  A request or a store for a tile behind the wave's last one goes through
-  // descriptors of size zero (nothing is read or written), so every pass of the loop below issues the same memory
-  // instructions and a wait can name exactly the loads it needs.
+  // row: rows at and above the rank read zero.
   const uint8_t* codes0 = codes + blk0 * (size_t)n * ROWB;
   const uint16_t* norms0 = norms + blk0 * (size_t)n;
   const uint8_t* qsigns0 = QJL ? qsigns + blk0 * (size_t)n * (D / 8) : nullptr;
@@ -304,7 +309,6 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   const __amdgpu_buffer_rsrc_t bsigns = buffer_of(qsigns0, QJL ? (size_t)nblk * n * (D / 8) : 0);
   const __amdgpu_buffer_rsrc_t bgam = buffer_of(qnorms0, QJL ? (size_t)nblk * n * 2 : 0);
   const __amdgpu_buffer_rsrc_t bout = buffer_of(scores0 + (size_t)jb0 * n, ((size_t)group * T - (size_t)jb0 * n) * 4);
-  const __amdgpu_buffer_rsrc_t bnone = buffer_of(scores0, 0);
   rk_all = min(max(rk_all, 0), r_max);   // records may come from storage: never index past r_max rows
   auto rank_of = [&](int b) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(rk_all, b); };
   auto coef_buffer = [&](int b) __attribute__((always_inline)) {
@@ -341,9 +345,8 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
 
   // the first tile's record bytes
   TileFetch<BITS, QJL> f0, f1;
-  const int count = (NT - wave + 3) / 4;        // tiles of this wave: wave, wave + 4, ... (a block has four or more)
-  const int tok_last = 32 * (wave + 4 * (count - 1));
-  int tok_r = 32 * wave, b_r = 0, end_r = n;                  // next tile to request: first token, block, end of the block
+  const int tok_last = tok0 + 32 * wave + QUAD * (count - 1);
+  int tok_r = tok0 + 32 * wave, b_r = 0, end_r = n;           // next tile to request: first token, block, end of the block
   __amdgpu_buffer_rsrc_t cfd = coef_buffer(0);
 #define EOQ_SC_REQUEST(F)                    \
   if (tok_r >= end_r) {                      \
@@ -352,7 +355,7 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     cfd = coef_buffer(b_r);                  \
   }                                          \
   request(F, tok_r, b_r, cfd);               \
-  tok_r = min(tok_r + 128, tok_last);
+  tok_r = min(tok_r + QUAD, tok_last);
   // q' = Pi q (the rotation moved to the query side: <q, Pi^T z> = <Pi q, z>), and Phi q
   pi_rows.rotate(aq, qrot, wave, l16, g);
   if constexpr (QJL) {
@@ -431,7 +434,7 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   int wb = -1;   // block of the run whose w operand the wave holds
   H8 Aw;
   Aw.u = make_uint4(0u, 0u, 0u, 0u);
-  auto work = [&](TileFetch<BITS, QJL>& cur, int tok, int b, int r, bool valid) __attribute__((always_inline)) {
+  auto work = [&](TileFetch<BITS, QJL>& cur, int tok, int b, int r) __attribute__((always_inline)) {
     if (b != wb) {   // uniform
       Aw = w_operand(b, 0);
       wb = b;
@@ -534,35 +537,36 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
 #pragma unroll
       for (int qq = 0; qq < NQ; ++qq) res[qq] += lr[4 * qq] + lr[4 * qq + 1];
     }
-    // head 2 qq + hf of the group: lanes of a head that the group does not have aim behind the descriptor, and a pass
-    // behind the wave's last tile stores through the empty descriptor
-    const __amdgpu_buffer_rsrc_t bo = valid ? bout : bnone;
+    // head 2 qq + hf of the group: lanes of a head that the group does not have aim behind the descriptor
 #pragma unroll
     for (int qq = 0; qq < NQ; ++qq) {
       const bool live = 2 * qq + hf < group;
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(res[qq]), bo, live ? vo_out : 0xFFFFFFF0u,
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(res[qq]), bout, live ? vo_out : 0xFFFFFFF0u,
                                             (int)((2 * qq * T + tok) * 4), 0);
     }
   };
 
   // Two register sets in turn: the next tile is on its way while this one is worked on.  The loop body has no branch
   // around a memory instruction (a wait can then name exactly the loads it needs): behind the wave's last tile a
-  // request fetches that tile once more and a pass stores nothing.
-  int tok_w = 32 * wave, b_w = 0, end_w = n, r_w = rank_of(0), nwk = 0;   // next tile to work on
+  // request fetches that tile once more.  Two exits: on every path back the younger requests are the other set's.  (With a
+  // pass that stored nothing behind an odd number of tiles, runs of five steps took as long as runs of six.)
+  int tok_w = tok0 + 32 * wave, b_w = 0, end_w = n, r_w = rank_of(0);   // next tile to work on
 #define EOQ_SC_WORK(F)                       \
   if (tok_w >= end_w) {                      \
     ++b_w;                                   \
     end_w += n;                              \
     r_w = rank_of(b_w);                      \
   }                                          \
-  work(F, tok_w, b_w, r_w, nwk < count);     \
-  tok_w = min(tok_w + 128, tok_last);        \
-  ++nwk;
-  for (int it = 0; it < (count + 1) / 2; ++it) {
+  work(F, tok_w, b_w, r_w);                  \
+  tok_w += QUAD;
+#pragma unroll 1
+  for (int it = 1;; it += 2) {
     EOQ_SC_REQUEST(f1)
     EOQ_SC_WORK(f0)
+    if (it == count) break;
     EOQ_SC_REQUEST(f0)
     EOQ_SC_WORK(f1)
+    if (it + 1 == count) break;
   }
 #undef EOQ_SC_REQUEST
 #undef EOQ_SC_WORK
@@ -583,17 +587,33 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   if (score_stride <= 0) score_stride = blocks_per_head * L.n;
   if (L.ev) (void)hipEventRecord(L.ev[6], L.stream);
   const int64_t tail_groups = (tail_len + TAIL_TOK - 1) / TAIL_TOK;
-  // blocks per workgroup: the set-up is paid once per workgroup, so runs are as long as they can be (16) while the grid
-  // still has a workgroup for each place on the chip (what eoq_scores_places found for the kernel that is launched).  A
-  // workgroup of the tail is short, four of them count as one.  A second, partly filled round of workgroups costs a set-up
-  // and a run, more than runs that are one block longer: 612 blocks of 512, 4 bits, 51 us in two rounds, 34 in one.
+  // Tokens per workgroup, in steps of 128 (a tile for each of its waves).  The set-up is paid once per workgroup, so runs are
+  // as long as they can be, up to 16 blocks, while the grid still has a workgroup for each place on the chip (what
+  // eoq_scores_places found for the kernel that is launched), the tail's among them: a second, partly filled round of
+  // workgroups costs a set-up and a run.  Whole blocks would be too coarse a measure: 12 x 204 steps on 512 places at 4 bits
+  // 28 us with runs of two blocks (8 steps), 24 with 6; 16 x 400 on 768 at 3 bits 32 with 10, 29 with 9.  Where that would
+  // leave fewer than six steps to a run, the set-ups of the workgroups of a unit, one behind the other, take longer than
+  // their steps (2 bits, 2048 steps: 4 workgroups to a unit of 2 steps each 14.2 us, 2 of 4 10.8, 1 of 8 10.2): then fewer to a
+  // unit, down to one.
   const int group = n_q_heads / n_kv_heads;
   const int64_t places = L.score_places[qjl ? 1 : 0][group <= 4 ? 0 : 1];
-  const int64_t tail_places = sg_total * tail_groups / 4;
-  const int64_t room = places - (tail_places < places / 2 ? tail_places : places / 2);
-  int64_t run = (sg_total * blocks_per_head + room - 1) / room;
-  run = run < 1 ? 1 : (run > SC_RUN_MAX ? SC_RUN_MAX : run);
-  const int64_t runs = (blocks_per_head + run - 1) / run;
+  const int64_t spb = L.n / QUAD, steps = blocks_per_head * spb, most = SC_RUN_MAX * spb;
+  const int64_t tails = sg_total * tail_groups;
+  auto run_for = [&](int64_t grid) {   // the shortest run with which runs and tail have no more workgroups than that
+    const int64_t per_head = (grid - (tails < grid / 2 ? tails : grid / 2)) / sg_total;
+    const int64_t r = per_head < 1 ? most : (steps + per_head - 1) / per_head;
+    return r < 1 ? 1 : (r < most ? r : most);            // no block at all: the tail's workgroups only
+  };
+  int64_t run = run_for(places);
+  if (run < SHORT_RUN) {
+    // fewer workgroups, whole numbers of them to a unit
+    int64_t w = places / 256;
+    while (w > 1 && run_for(256 * w) < SHORT_RUN) --w;
+    run = run_for(256 * (w > 1 ? w : 1));
+  }
+  // a run that begins inside a block touches one block more
+  if (run % spb != 0 && run > most - spb + 1) run = most;
+  const int64_t runs = (steps + run - 1) / run;
   if (sg_total > 65535 || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(runs + tail_groups), (unsigned)sg_total), block(THREADS);
   const uint16_t* q = static_cast<const uint16_t*>(q_fp16);

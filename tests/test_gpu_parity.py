@@ -1214,6 +1214,31 @@ def test_scores_prod_of_oracle_records(bits, group, n):
     assert np.max(np.abs(sp - s0)) > 1e-3                               # the correction is there
 
 
+@pytest.mark.parametrize("bits,group,n,blocks,corrected", [(2, 4, 512, 1540, False), (2, 7, 1024, 801, False), (4, 4, 256, 1601, False),
+                                                            (3, 8, 512, 1163, False), (2, 3, 1024, 590, True), (1, 1, 256, 3091, True)])
+def test_scores_of_runs_that_begin_inside_a_block(bits, group, n, blocks, corrected):
+    """One head of so many blocks that the workgroups' runs are an odd number of 128-token steps, which begin and end inside
+    blocks: the logits of every block are the same, bit for bit, as with the block as a head of its own."""
+    ctx = eoq.Context(n=n, bits=bits)
+    spec = synth.BlockSpec("keys", n=n, n_tensors=1, blocks_per_tensor=blocks, rank_lo=0, rank_hi=20)
+    x, _ = synth.make_blocks(spec, seed=5 + bits, device=DEV)
+    rec, _ = ctx.eoq_compress(x)
+    q = synth.make_queries(1, group, device=DEV)
+    each = q.repeat(1, blocks, 1).contiguous()
+    if corrected:
+        qjl = eoq.Qjl.empty(blocks, n, 128, DEV)
+        ctx.eoq_qjl_encode(x, rec, qjl)
+        got = ctx.eoq_scores_prod(rec, qjl, q, 1)
+        want = ctx.eoq_scores_prod(rec, qjl, each, blocks)
+    else:
+        got = ctx.eoq_scores(rec, q, 1)
+        want = ctx.eoq_scores(rec, each, blocks)
+    torch.cuda.synchronize()
+    places = eoq.lib().eoq_scores_places(bits, int(corrected), group)
+    assert -(-blocks * (n // 128) // places) >= 6 and -(-blocks * (n // 128) // places) % (n // 128) != 0   # such runs they are
+    assert torch.equal(got.view(group, blocks, n), want.view(blocks, group, n).transpose(0, 1))
+
+
 def test_scores_grid_follows_the_compiled_kernels(tmp_path):
     """The number of workgroups that the grid rule counts with is what the registers and LDS of each compiled kernel allow
     on a compute unit: 512 registers per lane and SIMD in steps of 8, four SIMDs, 160 KB."""
