@@ -65,16 +65,26 @@ __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) {
 // multiply-adds per token and lane): per pair of tiles 333 vector, 47 LDS and 26 matrix instructions, which take 0.10 ms
 // by themselves, beside 0.49 GB from memory, which takes 0.11 ms by itself (4.5 TB/s): the two overlap in part only, at
 // the two waves per SIMD that the registers allow.
-template <int BITS, int GH>
+// With byte terms and more than four heads two sets of workgroups (z = 0, 1) share the heads, 4 z .. 4 z + 3 each.  HALF: each
+// of them takes all heads of the codebook term and half of its coordinates (tiles 2 z, 2 z + 1) instead, so that a code is
+// unpacked once; the low-rank term stays divided by heads.  780 instead of 1090 32-bit vector instructions per pair of tiles;
+// 313 K tokens, seven heads, 4 bits: 38 -> 35 us.  At 3 bits, where a code is two instructions a term instead of three, what
+// is saved there goes into cutting all weights twice (313 K tokens 28.5 -> 29.7 us), so it is left as it was.
+template <int BITS, int GH, bool HALF>
 struct AttendShape {
   static constexpr bool BYTES = BITS >= 3;                   // byte terms of the centroid
   static constexpr bool SPLIT = BITS == 2 && GH == 4;        // the two terms in the two halves of the operand rows
   static constexpr int TERMS = BYTES ? 4 : BITS;
   static constexpr int NQ = BYTES ? 4 : GH / 2;              // groups of four accumulator registers in use
   static constexpr int SETS = GH / 4;                        // groups of four heads of the low-rank product
+  static constexpr int WSETS = HALF ? 2 : SETS;              // groups of four heads of the codebook term
+  static constexpr int RH = HALF ? 8 : GH;                   // heads of the codebook term
+  static constexpr int JT = HALF ? 2 : 4;                    // coordinate tiles
+  static_assert(!HALF || (BYTES && GH == 4), "byte terms");
   static constexpr int SETS_OF_BYTES = BYTES || SPLIT ? 1 : TERMS;   // how often the weights are cut into bytes
   // weight bytes: [row][64 tokens] and, where operand rows are left out, a row of zeros
-  static constexpr int DIG_BYTES = BYTES || SPLIT ? 4 * 4 * PAIR + PAIR : TERMS * 32 * PAIR;
+  static constexpr int DIG_BYTES = BYTES || SPLIT ? (HALF ? 2 : 1) * 4 * 4 * PAIR + PAIR : TERMS * 32 * PAIR;
+  static constexpr int ZERO_ROW = HALF ? 32 : 16;            // that row
   static constexpr int PART_LD = 2 * PAIR + 16;              // bytes per row of binary16 parts
   static constexpr int PART_BYTES = SETS * 12 * PART_LD;
   static constexpr int STAGE_BYTES = DIG_BYTES + PART_BYTES;
@@ -85,20 +95,20 @@ struct AttendShape {
   static constexpr int RING_BYTES = SETS * EOQ_RMAX_CAP * 4 * 4;     // of one block
   static constexpr int BS_BYTES = PARTS3_BYTES + RING * RING_BYTES;
   static constexpr int BASE_BYTES = STAGE_BYTES > LIN_BYTES ? STAGE_BYTES : LIN_BYTES;
-  static constexpr int WAVE_BYTES = BASE_BYTES + BS_BYTES + GH * D * 4 + 64;
+  static constexpr int WAVE_BYTES = BASE_BYTES + BS_BYTES + RH * D * 4 + 64;
   static constexpr int NTAB = BITS <= 2 ? 2 : 3;
   static constexpr bool AHEAD = BITS == 1 || SPLIT;          // registers left to work ahead of a coordinate tile
 };
 
-template <int BITS, int GH>
+template <int BITS, int GH, bool HALF = false>
 __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     int n, int r_max, int n_kv_heads, int group, int64_t blocks_per_head, int64_t block_capacity, int64_t weight_stride,
     int ppw, const float* __restrict__ tab, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms,
     const int32_t* __restrict__ rank_in, const uint16_t* __restrict__ lfac, const uint16_t* __restrict__ rfac,
     const float* __restrict__ weights, float* __restrict__ partial) {
-  using S = AttendShape<BITS, GH>;
+  using S = AttendShape<BITS, GH, HALF>;
   constexpr bool BYTES = S::BYTES;
-  constexpr int TERMS = S::TERMS, NQ = S::NQ, SETS = S::SETS;
+  constexpr int TERMS = S::TERMS, NQ = S::NQ, SETS = S::SETS, WSETS = S::WSETS, RH = S::RH, JT = S::JT;
   constexpr int ROWB = BITS * D / 8;
   __shared__ __align__(16) unsigned char mem[4 * S::WAVE_BYTES];
   __shared__ __align__(16) uint32_t tab_s[S::NTAB * 256];   // code bytes of four coordinates by two nibbles, times 1, 4 (and 16)
@@ -108,7 +118,9 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
   const size_t sg = blockIdx.y;
   const size_t sq = sg / n_kv_heads, kv = sg % n_kv_heads;
   const int n_q_heads = n_kv_heads * group;
-  const int h0 = 4 * blockIdx.z;                             // first head of this workgroup (byte terms: four heads each)
+  const int z = HALF ? (int)blockIdx.z : 0;
+  const int h0 = 4 * (int)blockIdx.z;                        // first head (HALF: of the low-rank term)
+  const int r0 = HALF ? 0 : h0;                              // first head of the codebook term
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
 
   unsigned char* mine = mem + wave * S::WAVE_BYTES;
@@ -117,8 +129,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
   float* bs = reinterpret_cast<float*>(mine + S::BASE_BYTES);                 // [set][part][component][head]
   float* ring = bs + S::PARTS3_BYTES / 4;                                     // [block][set][component][head]
   float* rot = reinterpret_cast<float*>(mine + S::BASE_BYTES + S::BS_BYTES);  // [head][coordinate]
-  float* unit_s = rot + GH * D;                                               // value of one integer unit, per head
-  float* winv_s = unit_s + GH;                                                // 1 / scale of the binary16 parts, per head
+  float* unit_s = rot + RH * D;                                               // value of one integer unit, per head
+  float* winv_s = unit_s + RH;                                                // 1 / scale of the binary16 parts, per head
 
   {
     uint32_t v = 0u;
@@ -128,7 +140,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     for (int k = 0; k < S::NTAB; ++k) tab_s[k * 256 + tid] = v << (2 * k);
   }
   for (int e = lane; e < S::DIG_BYTES / 4; e += 64) reinterpret_cast<uint32_t*>(dig)[e] = 0u;
-  for (int e = lane; e < GH * D; e += 64) rot[e] = 0.0f;
+  for (int e = lane; e < RH * D; e += 64) rot[e] = 0.0f;
   __syncthreads();
 
   // operand tables: four codes to four bytes of term t, entry i for code i (low register: codes 0 .. 3)
@@ -179,16 +191,16 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     const int rk_all = min(max(rank_in[blk0 + min(lane, nblk - 1)], 0), r_max);
     auto rank_of = [&](int b) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(rk_all, b); };
     const size_t tok0 = sg * (size_t)block_capacity * n + (size_t)p_begin * PAIR;   // first token in the record arrays
-    const uint8_t* code_p = codes + (tok0 + l32) * ROWB + 8 * hf;
+    const uint8_t* code_p = codes + (tok0 + l32) * ROWB + 8 * hf + 4 * z;
     // a staging item: four tokens whose bytes sit side by side in an operand word (tokens tt, tt + 1 of either tile) and
     // one head; word u of a row is [m][half][4 bytes]: see the pack below
     const int u = l16;
     const int tt = 16 * (u >> 3) + 8 * ((u >> 1) & 1) + 4 * ((u >> 2) & 1) + 2 * (u & 1);
     const uint16_t* rho_p = norms + tok0 + tt;
-    const float* w_p[SETS];
-    bool head_live[SETS];
-    EOQ_SFOR(s, SETS,
-      const int h = h0 + 4 * s + kg;
+    const float* w_p[WSETS];
+    bool head_live[WSETS];
+    EOQ_SFOR(s, WSETS,
+      const int h = r0 + 4 * s + kg;
       head_live[s] = h < group;
       w_p[s] = weights + (sq * n_q_heads + kv * group + (head_live[s] ? h : 0)) * (size_t)weight_stride + (size_t)p_begin * PAIR + tt;
     );
@@ -198,8 +210,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     };
 
     struct Fetch {
-      u32x2 pl[2][BITS];       // the lane's 8 bytes of every bit-plane, tokens l32 of both tiles
-      float w[SETS][4];        // weights of the staging item: tokens tt, 32 + tt, tt + 1, 33 + tt
+      uint32_t pl[2][BITS][HALF ? 1 : 2];   // the lane's 8 bytes (HALF: 4) of every bit-plane, tokens l32 of both tiles
+      float w[WSETS][4];       // weights of the staging item: tokens tt, 32 + tt, tt + 1, 33 + tt
       uint32_t rho[2];         // norms of tokens tt, tt + 1 and 32 + tt, 33 + tt
       u32x4 cf[2];             // coefficients: component l16, tokens 8 kg .. + 7 of either tile; zero at and above the rank
     };
@@ -207,8 +219,16 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     auto request = [&](Fetch& f, int p, int b, int in_b) __attribute__((always_inline)) {   // pair p of the wave: pair in_b of block b
       const size_t t = (size_t)p * PAIR;
       EOQ_SFOR(i, 2, EOQ_SFOR(k, BITS,
-        f.pl[i][k] = *reinterpret_cast<const u32x2*>(code_p + (t + 32 * i) * ROWB + 16 * k);););
-      EOQ_SFOR(s, SETS,
+        const uint8_t* src = code_p + (t + 32 * i) * ROWB + 16 * k;
+        if constexpr (HALF) {
+          f.pl[i][k][0] = *reinterpret_cast<const uint32_t*>(src);
+        } else {
+          const u32x2 x = *reinterpret_cast<const u32x2*>(src);
+          f.pl[i][k][0] = x[0];
+          f.pl[i][k][1] = x[1];
+        }
+      ););
+      EOQ_SFOR(s, WSETS,
         const F2 a = *reinterpret_cast<const F2*>(w_p[s] + t); const F2 c = *reinterpret_cast<const F2*>(w_p[s] + t + 32);
         f.w[s][0] = a.x; f.w[s][1] = c.x; f.w[s][2] = a.y; f.w[s][3] = c.y;
       );
@@ -217,34 +237,38 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       EOQ_SFOR(i, 2, f.cf[i] = __builtin_amdgcn_raw_buffer_load_b128(cfd, vo_cf, (in_b * PAIR + 32 * i) * 2, 0););
     };
 
-    v16i acc[4];               // coordinates 64 (l32 / 16) + 16 j + l32 % 16
-    EOQ_SFOR(j, 4, EOQ_SFOR(v, 16, acc[j][v] = 0;););
+    constexpr int ASETS = HALF ? 2 : 1;
+    v16i acc[ASETS][JT];       // coordinates 64 (l32 / 16) + 16 (2 z + j) + l32 % 16
+    EOQ_SFOR(s, ASETS, EOQ_SFOR(j, JT, EOQ_SFOR(v, 16, acc[s][j][v] = 0;);););
     float4v lr[SETS][2];       // row 4 part + head, column = component l16 / 16 + l16
     EOQ_SFOR(s, SETS, EOQ_SFOR(k, 2, EOQ_SFOR(v, 4, lr[s][k][v] = 0.0f;);););
-    float inv[SETS], sw[SETS]; // units of the staging item's head: integers = w' inv, binary16 parts of w sw
-    EOQ_SFOR(s, SETS, inv[s] = INFINITY; sw[s] = INFINITY;);
+    float inv[WSETS], sw[SETS]; // units of the staging item's head: integers = w' inv, binary16 parts of w sw
+    EOQ_SFOR(s, WSETS, inv[s] = INFINITY;);
+    EOQ_SFOR(s, SETS, sw[s] = INFINITY;);
     bool any = false;
 
     auto flush_rot = [&]() __attribute__((always_inline)) {
-      EOQ_SFOR(j, 4,
-        const int c = 64 * (l32 >> 4) + 16 * j + l16;
+      EOQ_SFOR(s, ASETS, EOQ_SFOR(j, JT,
+        const int c = 64 * (l32 >> 4) + 16 * (2 * z + j) + l16;
+        auto joined = [&](auto first) __attribute__((always_inline)) {   // the four bytes from register `first` on
+          constexpr int v = decltype(first)::value;
+          return fma(fma(fma((double)acc[s][j][v + 3], 256.0, (double)acc[s][j][v + 2]), 256.0, (double)acc[s][j][v + 1]), 256.0, (double)acc[s][j][v]);
+        };
         EOQ_SFOR(q, NQ,
-          double v = fma(fma(fma((double)acc[j][4 * q + 3], 256.0, (double)acc[j][4 * q + 2]), 256.0, (double)acc[j][4 * q + 1]), 256.0,
-                         (double)acc[j][4 * q]);
+          double v = joined(std::integral_constant<int, 4 * q>{});
           if constexpr (BYTES) {
             if (hf) v *= 0x1.0p32;                           // planes 4 .. 7
             v += __shfl_xor(v, 32, 64);
-            if (!hf) rot[q * D + c] += (float)(v * (double)unit_s[q] * 0x1.0p-28);
+            if (!hf) rot[(4 * s + q) * D + c] += (float)(v * (double)unit_s[4 * s + q] * 0x1.0p-28);
           } else if constexpr (!S::SPLIT) {
             rot[(2 * q + hf) * D + c] += (float)(v * (double)unit_s[2 * q + hf]);
           } else {
-            const double v1 = fma(fma(fma((double)acc[j][8 + 4 * q + 3], 256.0, (double)acc[j][8 + 4 * q + 2]), 256.0, (double)acc[j][8 + 4 * q + 1]), 256.0,
-                                  (double)acc[j][8 + 4 * q]);
+            const double v1 = joined(std::integral_constant<int, 8 + 4 * q>{});
             rot[(2 * q + hf) * D + c] += (float)(fma(v, (double)coef[0], v1 * (double)coef[1]) * (double)unit_s[2 * q + hf]);
           }
         );
-        EOQ_SFOR(v, 16, acc[j][v] = 0;);
-      );
+        EOQ_SFOR(v, 16, acc[s][j][v] = 0;);
+      ););
     };
     // The low-rank sums of block b: parts joined, kept in LDS; the V rows of RING blocks are then read in one go (per
     // block their latency was 12 us of 160 on 8.4 M tokens).
@@ -306,22 +330,31 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
 
     // New units for the heads whose weights (sums of magnitudes tr, tw over four tokens each, with rho / without) do not
     // fit the ones they have.  The low-rank sums so far are brought to the new scale (a power of two).
-    auto choose_units = [&](const float (&mr)[SETS], const float (&mw)[SETS]) __attribute__((always_inline)) {
-      EOQ_SFOR(s, SETS,
-        float tr = mr[s]; float tw = mw[s];
+    auto choose_units = [&](const float (&mr)[WSETS], const float (&mw)[SETS]) __attribute__((always_inline)) {
+      auto largest = [&](float t) __attribute__((always_inline)) {   // over the sixteen lanes of a head
         EOQ_SFOR(x, 4,
           constexpr int ctrl = x == 0 ? 0xB1 : (x == 1 ? 0x4E : (x == 2 ? 0x141 : 0x140));
-          const float a = dpp_mov<ctrl>(tr); const float c = dpp_mov<ctrl>(tw);
-          tr = (a > tr || !(a == a)) ? a : tr;             // a NaN stays
-          tw = (c > tw || !(c == c)) ? c : tw;
+          const float a = dpp_mov<ctrl>(t);
+          t = (a > t || !(a == a)) ? a : t;                // a NaN stays
         );
-        const bool bad = !(tr < INFINITY) || !(tw < INFINITY);
+        return t;
+      };
+      EOQ_SFOR(s, WSETS,
+        const float tr = largest(mr[s]);
+        const bool bad = !(tr < INFINITY);
         const int er = min(max((int)(__float_as_uint(tr) >> 23) - 127, -90), 126);
-        const int ew = min(max((int)(__float_as_uint(tw) >> 23) - 127, -90), 126);
         if (bad || !(tr * inv[s] < 1.85f * 0x1.0p30f)) {
           inv[s] = bad ? 0.0f : __uint_as_float((uint32_t)(28 - er + 127) << 23);     // integers below 2^29
           if (l16 == 0) unit_s[4 * s + kg] = bad ? 0.0f : __uint_as_float((uint32_t)(er - 28 + 127) << 23);
         }
+        if (bad) {   // Inf or NaN among the weights: so is the head's output
+          EOQ_SFOR(i, 8, rot[(4 * s + kg) * D + 16 * i + l16] = NAN;);
+        }
+      );
+      EOQ_SFOR(s, SETS,
+        const float tw = largest(mw[s]);
+        const bool bad = !(tw < INFINITY);
+        const int ew = min(max((int)(__float_as_uint(tw) >> 23) - 127, -90), 126);
         float turn = 1.0f;
         if (bad || !(tw * sw[s] < 0x1.0p15f)) {
           const float fresh = bad ? 0.0f : __uint_as_float((uint32_t)(12 - ew + 127) << 23);      // parts below 2^13
@@ -334,8 +367,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
           const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(turn), 16 * v));
           EOQ_SFOR(k, 2, lr[s][k][v] *= f;);
         );
-        if (bad) {   // Inf or NaN among the weights: so is the head's output
-          EOQ_SFOR(i, 8, rot[(4 * s + kg) * D + 16 * i + l16] = NAN;);
+        if (bad) {   // the weights alone, without rho: theirs is the low-rank term, but the output is one
+          EOQ_SFOR(i, 8, rot[(h0 - r0 + 4 * s + kg) * D + 16 * i + l16] = NAN;);
         }
       );
       __builtin_amdgcn_wave_barrier();
@@ -357,19 +390,23 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       const int r = rank_of(b);
       const bool last_in_block = in_b + 1 == ppb;
       // ---- weights: do they fit the units?  (sums of four magnitudes: NaN and Inf fail the test) ----
-      float wr[SETS][4], mr[SETS], mw[SETS];
+      float wr[WSETS][4], wl[SETS][4], mr[WSETS], mw[SETS];   // with rho; as they are, for the low-rank term
       bool fits = true;
       {
         const float ra[2] = {half_bits_to_float((uint16_t)(f.rho[0] & 0xFFFFu)) * inv_sqrt_d, half_bits_to_float((uint16_t)(f.rho[0] >> 16)) * inv_sqrt_d};
         const float rb[2] = {half_bits_to_float((uint16_t)(f.rho[1] & 0xFFFFu)) * inv_sqrt_d, half_bits_to_float((uint16_t)(f.rho[1] >> 16)) * inv_sqrt_d};
-        EOQ_SFOR(s, SETS,
+        EOQ_SFOR(s, WSETS,
           EOQ_SFOR(e, 4,
             f.w[s][e] = head_live[s] ? f.w[s][e] : 0.0f;
             wr[s][e] = f.w[s][e] * ((e & 1) ? rb[e >> 1] : ra[e >> 1]);
           );
           mr[s] = (fabsf(wr[s][0]) + fabsf(wr[s][1])) + (fabsf(wr[s][2]) + fabsf(wr[s][3]));
-          mw[s] = (fabsf(f.w[s][0]) + fabsf(f.w[s][1])) + (fabsf(f.w[s][2]) + fabsf(f.w[s][3]));
-          fits = fits && mr[s] * inv[s] < 1.85f * 0x1.0p30f && mw[s] * sw[s] < 0x1.0p15f;
+          fits = fits && mr[s] * inv[s] < 1.85f * 0x1.0p30f;
+        );
+        EOQ_SFOR(s, SETS,
+          EOQ_SFOR(e, 4, wl[s][e] = (HALF && z) ? +f.w[WSETS - 1][e] : +f.w[s][e];);
+          mw[s] = (fabsf(wl[s][0]) + fabsf(wl[s][1])) + (fabsf(wl[s][2]) + fabsf(wl[s][3]));
+          fits = fits && mw[s] * sw[s] < 0x1.0p15f;
         );
       }
       if (__ballot(!fits) != 0ull) {   // wave-uniform, rare: new units
@@ -378,7 +415,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       }
       any = true;
       // ---- staging: weight bytes and binary16 parts ----
-      EOQ_SFOR(s, SETS,
+      EOQ_SFOR(s, WSETS,
         EOQ_SFOR(t, S::SETS_OF_BYTES,
           uint32_t dg[4];
           const float sc = (BYTES || S::SPLIT) ? inv[s] : coef[t] * inv[s];
@@ -387,9 +424,11 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
           transpose_bytes(dg[0], dg[1], dg[2], dg[3], pl);
           EOQ_SFOR(e, 4, *reinterpret_cast<uint32_t*>(dig + t * (32 * PAIR) + (4 * (4 * s + kg) + e) * PAIR + 4 * u) = pl[e];);
         );
+      );
+      EOQ_SFOR(s, SETS,
         if (r > 0) {
           float x[4];
-          EOQ_SFOR(e, 4, x[e] = f.w[s][e] * sw[s];);
+          EOQ_SFOR(e, 4, x[e] = wl[s][e] * sw[s];);
           EOQ_SFOR(part, 3,
             unsigned char* dst = parts + (s * 12 + 4 * part + kg) * S::PART_LD + 2 * tt;
             const uint32_t pa = pack_half2(x[0], x[2]); const uint32_t pb = pack_half2(x[1], x[3]);
@@ -405,24 +444,27 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
         }
       );
       __builtin_amdgcn_wave_barrier();   // one wave: its LDS operations complete in order
-      // ---- A operands: row l32, tokens [m][half] ----
-      v4i A[TERMS][2];
-      EOQ_SFOR(t, TERMS,
+      // ---- A operands: row l32 (of four heads from 4 set on), tokens [m][half] ----
+      auto weight_bytes = [&](auto set, auto t_ic, auto m_ic) __attribute__((always_inline)) {
+        constexpr int t = decltype(t_ic)::value;
         const unsigned char* src;
         if constexpr (BYTES) {
           const int e = (l32 & 7) - t;
-          src = dig + ((e >= 0 && e < 4) ? ((l32 >> 3) * 4 + e) * PAIR : 16 * PAIR);
+          src = dig + ((e >= 0 && e < 4) ? ((4 * decltype(set)::value + (l32 >> 3)) * 4 + e) * PAIR : S::ZERO_ROW * PAIR);
         } else if constexpr (S::SPLIT) {
-          src = dig + ((l32 >> 4) == t ? l16 : 16) * PAIR;
+          src = dig + ((l32 >> 4) == t ? l16 : S::ZERO_ROW) * PAIR;
         } else {
           src = dig + t * (32 * PAIR) + l32 * PAIR;
         }
-        EOQ_SFOR(m, 2, A[t][m] = *reinterpret_cast<const v4i*>(src + 32 * m + 16 * hf););
-      );
+        return *reinterpret_cast<const v4i*>(src + 32 * decltype(m_ic)::value + 16 * hf);
+      };
+      constexpr std::integral_constant<int, 0> set0{};
+      v4i A[TERMS][2];
+      if constexpr (!HALF) { EOQ_SFOR(t, TERMS, EOQ_SFOR(m, 2, A[t][m] = weight_bytes(set0, t_ic, m_ic););); }
       // ---- codes: bytes, transposed, translated, multiplied ----
       // even / odd: byte = (nibble of plane 0 | nibble of plane 1 << 4) of the low / high nibbles
-      uint32_t ev[2][2][BITS > 2 ? 2 : 1]; uint32_t od[2][2][BITS > 2 ? 2 : 1];
-      EOQ_SFOR(i, 2, EOQ_SFOR(w, 2, EOQ_SFOR(k, (BITS > 2 ? 2 : 1),
+      uint32_t ev[2][HALF ? 1 : 2][BITS > 2 ? 2 : 1]; uint32_t od[2][HALF ? 1 : 2][BITS > 2 ? 2 : 1];
+      EOQ_SFOR(i, 2, EOQ_SFOR(w, (HALF ? 1 : 2), EOQ_SFOR(k, (BITS > 2 ? 2 : 1),
         const uint32_t x = f.pl[i][2 * k][w];
         if constexpr (2 * k + 1 < BITS) {
           const uint32_t y = f.pl[i][2 * k + 1][w];
@@ -479,42 +521,71 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
         code_bytes(std::integral_constant<int, 1>{}, X[1]);
         cd[0] = transpose(X[0]);
       }
-      EOQ_SFOR(j, 4,
-        if constexpr (S::AHEAD) {
-          if constexpr (j + 2 < 4) code_bytes(std::integral_constant<int, j + 2>{}, X[j & 1]);
-          if constexpr (j + 1 < 4) cd[(j + 1) & 1] = transpose(X[(j + 1) & 1]);
-          __builtin_amdgcn_sched_barrier(0);
-        } else {
-          code_bytes(std::integral_constant<int, j>{}, X[j & 1]);
-          cd[j & 1] = transpose(X[j & 1]);
-        }
-        // register v: token 8 (v / 4) + 4 hf + v % 4 of the first tile in byte 0, of the second in byte 1
-        uint32_t pk[8];
-        EOQ_SFOR(v, 8, pk[v] = (uint32_t)cd[j & 1][2 * v] | ((uint32_t)cd[j & 1][2 * v + 1] << 16););
-        EOQ_SFOR(m, 2,
-          uint32_t sel[4]; uint32_t top[4];
+      // register v: token 8 (v / 4) + 4 hf + v % 4 of the first tile in byte 0, of the second in byte 1
+      auto pack = [&](const v16i& c, uint32_t (&pk)[8]) __attribute__((always_inline)) {
+        EOQ_SFOR(v, 8, pk[v] = (uint32_t)c[2 * v] | ((uint32_t)c[2 * v + 1] << 16););
+      };
+      // the operand bytes of tile j's tokens of half m, term by term
+      auto translate = [&](const uint32_t (&pk)[8], auto m_ic, auto&& use) __attribute__((always_inline)) {
+        constexpr int m = decltype(m_ic)::value;
+        uint32_t sel[4]; uint32_t top[4];
+        EOQ_SFOR(w, 4,
+          sel[w] = pk[4 * m + w];
+          if constexpr (BITS == 4) {
+            const uint32_t up = (sel[w] >> 3) & 0x01010101u;
+            top[w] = (up << 8) - up;                         // 255 in the bytes whose code is 8 or more
+            sel[w] &= 0x07070707u;
+          }
+        );
+        EOQ_SFOR(t, TERMS,
+          v4i Bt;
           EOQ_SFOR(w, 4,
-            sel[w] = pk[4 * m + w];
-            if constexpr (BITS == 4) {
-              const uint32_t up = (sel[w] >> 3) & 0x01010101u;
-              top[w] = (up << 8) - up;                       // 255 in the bytes whose code is 8 or more
-              sel[w] &= 0x07070707u;
-            }
+            const uint32_t lo = __builtin_amdgcn_perm(lut[t][1], lut[t][0], sel[w]);
+            if constexpr (BITS == 4)
+              Bt[w] = (int)bfi(top[w], __builtin_amdgcn_perm(lut[t][3], lut[t][2], sel[w]), lo);
+            else
+              Bt[w] = (int)lo;
           );
-          EOQ_SFOR(t, TERMS,
-            v4i Bt;
-            EOQ_SFOR(w, 4,
-              const uint32_t lo = __builtin_amdgcn_perm(lut[t][1], lut[t][0], sel[w]);
-              if constexpr (BITS == 4)
-                Bt[w] = (int)bfi(top[w], __builtin_amdgcn_perm(lut[t][3], lut[t][2], sel[w]), lo);
-              else
-                Bt[w] = (int)lo;
-            );
-            acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[t][m], Bt, acc[j], 0, 0, 0);
+          use(t_ic, Bt);
+        );
+      };
+      if constexpr (HALF) {
+        // both tiles first, then half by half: the weight bytes of one half for all heads are what the registers hold
+        uint32_t pk[JT][8];
+        EOQ_SFOR(j, JT,
+          code_bytes(j_ic, X[0]);
+          pack(transpose(X[0]), pk[j]);
+        );
+        EOQ_SFOR(m, 2,
+          EOQ_SFOR(s, 2, EOQ_SFOR(t, TERMS, A[t][s] = weight_bytes(s_ic, t_ic, m_ic);););
+          EOQ_SFOR(j, JT,
+            translate(pk[j], m_ic, [&](auto t_ic, const v4i& Bt) __attribute__((always_inline)) {
+              constexpr int t = decltype(t_ic)::value;
+              EOQ_SFOR(s, 2, acc[s][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[t][s], Bt, acc[s][j], 0, 0, 0););
+            });
           );
         );
-        if constexpr (S::AHEAD) __builtin_amdgcn_sched_barrier(0);
-      );
+      } else {
+        EOQ_SFOR(j, 4,
+          if constexpr (S::AHEAD) {
+            if constexpr (j + 2 < 4) code_bytes(std::integral_constant<int, j + 2>{}, X[j & 1]);
+            if constexpr (j + 1 < 4) cd[(j + 1) & 1] = transpose(X[(j + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+          } else {
+            code_bytes(j_ic, X[j & 1]);
+            cd[j & 1] = transpose(X[j & 1]);
+          }
+          uint32_t pk[8];
+          pack(cd[j & 1], pk);
+          EOQ_SFOR(m, 2,
+            translate(pk, m_ic, [&](auto t_ic, const v4i& Bt) __attribute__((always_inline)) {
+              constexpr int t = decltype(t_ic)::value;
+              acc[0][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[t][m], Bt, acc[0][j], 0, 0, 0);
+            });
+          );
+          if constexpr (S::AHEAD) __builtin_amdgcn_sched_barrier(0);
+        );
+      }
       if (last_in_block) {
         ++b;
         in_b = 0;
@@ -529,28 +600,29 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     __builtin_amdgcn_sched_barrier(0);
     {
       // the first units come from the first four pairs, so that few later weights need new ones
-      float mr[SETS], mw[SETS];
-      EOQ_SFOR(s, SETS, mr[s] = 0.0f; mw[s] = 0.0f;);
+      float mr[WSETS], mw[SETS], mw_all[WSETS];
+      EOQ_SFOR(s, WSETS, mr[s] = 0.0f; mw_all[s] = 0.0f;);
       uint32_t rho[4][2];
-      F2 wv[4][SETS][2];
+      F2 wv[4][WSETS][2];
       EOQ_SFOR(k, 4,
         const size_t t = (size_t)min(k, count - 1) * PAIR;
         EOQ_SFOR(i, 2,
           rho[k][i] = *reinterpret_cast<const uint32_t*>(rho_p + t + 32 * i);
-          EOQ_SFOR(s, SETS, wv[k][s][i] = *reinterpret_cast<const F2*>(w_p[s] + t + 32 * i););
+          EOQ_SFOR(s, WSETS, wv[k][s][i] = *reinterpret_cast<const F2*>(w_p[s] + t + 32 * i););
         );
       );
       __builtin_amdgcn_sched_barrier(0);   // all of them in flight together
       EOQ_SFOR(k, 4, EOQ_SFOR(i, 2,
         const float r0 = half_bits_to_float((uint16_t)(rho[k][i] & 0xFFFFu)) * inv_sqrt_d; const float r1 = half_bits_to_float((uint16_t)(rho[k][i] >> 16)) * inv_sqrt_d;
-        EOQ_SFOR(s, SETS,
+        EOQ_SFOR(s, WSETS,
           const F2 a = wv[k][s][i];
           const float w0 = head_live[s] ? fabsf(a.x) : 0.0f; const float w1 = head_live[s] ? fabsf(a.y) : 0.0f;
           const float sr = fmaf(w0, fabsf(r0), w1 * fabsf(r1)); const float sm = w0 + w1;
           mr[s] = (sr > mr[s] || !(sr == sr)) ? sr : mr[s];
-          mw[s] = (sm > mw[s] || !(sm == sm)) ? sm : mw[s];
+          mw_all[s] = (sm > mw_all[s] || !(sm == sm)) ? sm : mw_all[s];
         );
       ););
+      EOQ_SFOR(s, SETS, mw[s] = (HALF && z) ? +mw_all[WSETS - 1] : +mw_all[s];);
       choose_units(mr, mw);
     }
 #pragma unroll 1
@@ -568,16 +640,17 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
   float* lin_m = reinterpret_cast<float*>(mine);
   EOQ_SFOR(h, GH, *reinterpret_cast<float2*>(lin_m + h * D + c2) = make_float2(lin[h][0], lin[h][1]););
   __syncthreads();
-  float* dst = partial + ((sg * gridDim.x + blockIdx.x) * 2 * MAXG + h0) * D;
+  float* dst = partial + (sg * gridDim.x + blockIdx.x) * (size_t)(2 * MAXG * D);
   for (int e = tid; e < GH * D; e += THREADS) {
-    float rs[4];
     float ls[4];
-    EOQ_SFOR(w, 4,
-      ls[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES)[e];
-      rs[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES + S::BASE_BYTES + S::BS_BYTES)[e];
-    );
-    dst[e] = ((rs[0] + rs[1]) + rs[2]) + rs[3];
-    dst[MAXG * D + e] = ((ls[0] + ls[1]) + ls[2]) + ls[3];
+    EOQ_SFOR(w, 4, ls[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES)[e];);
+    dst[(MAXG + h0) * D + e] = ((ls[0] + ls[1]) + ls[2]) + ls[3];
+  }
+  for (int i = tid; i < (HALF ? RH * D / 2 : RH * D); i += THREADS) {
+    const int e = HALF ? ((i >> 5) << 6) + 32 * z + (i & 31) : i;   // HALF: coordinates 32 z .. + 31 of either 64
+    float rs[4];
+    EOQ_SFOR(w, 4, rs[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES + S::BASE_BYTES + S::BS_BYTES)[e];);
+    dst[r0 * D + e] = ((rs[0] + rs[1]) + rs[2]) + rs[3];
   }
 }
 
@@ -821,20 +894,20 @@ hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_se
   int ppw = 1;
   // up to 2 bits a wave takes all (up to eight) heads of the group; with byte terms the 32 operand rows hold four heads,
   // and a group of more is two sets of workgroups (the runs, at most as many as the workspace was sized for, are then
-  // twice as long)
+  // twice as long), at 4 bits with the coordinates divided between them: see AttendShape
   const unsigned z = (L.bits >= 3 && group > 4) ? 2u : 1u;
   const int64_t runs = eoq_attend_runs(sg_total * z, blocks_per_head, L.n, &ppw);
   if (sg_total > 65535 || runs > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 block(THREADS);
-#define EOQ_ATTEND(BITS, GH, Z)                                                                                        \
-  hipLaunchKernelGGL((eoq_attend_partial_kernel<BITS, GH>), dim3((unsigned)runs, (unsigned)sg_total, Z), block, 0,     \
+#define EOQ_ATTEND(BITS, GH, Z, ...)                                                                                   \
+  hipLaunchKernelGGL((eoq_attend_partial_kernel<BITS, GH, ##__VA_ARGS__>), dim3((unsigned)runs, (unsigned)sg_total, Z), block, 0,     \
                      L.stream, L.n, L.r_max, n_kv_heads, group, blocks_per_head, block_capacity, weight_stride, ppw,   \
                      L.tab, values.codes, values.norms, values.rank, values.lfac, values.rfac, weights, partial)
   switch (L.bits) {
     case 1: if (group <= 4) EOQ_ATTEND(1, 4, 1); else EOQ_ATTEND(1, 8, 1); break;
     case 2: if (group <= 4) EOQ_ATTEND(2, 4, 1); else EOQ_ATTEND(2, 8, 1); break;
     case 3: EOQ_ATTEND(3, 4, z); break;
-    default: EOQ_ATTEND(4, 4, z); break;
+    default: if (group <= 4) EOQ_ATTEND(4, 4, 1); else EOQ_ATTEND(4, 4, 2, true); break;
   }
 #undef EOQ_ATTEND
   hipError_t e = hipGetLastError();

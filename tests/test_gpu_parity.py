@@ -1008,6 +1008,36 @@ def test_attention_output_weights_of_any_size(n, bits, group, filled, tail_len):
     assert np.all(np.max(np.abs(out2[0, keep].double().cpu().numpy() - want[keep]), axis=1) <= ATTEND_TOL * norm[keep])
 
 
+@pytest.mark.parametrize("n,group,filled", [(128, 5, 1), (512, 8, 3), (1024, 6, 37), (256, 7, 90)])
+def test_attention_output_of_wide_groups_at_4_bits(n, group, filled):
+    """More than four heads per KV head at 4 bits: two workgroups share the coordinates of the codebook term and the heads of
+    the low-rank term; one token pair to a wave and several, blocks of every rank.  Reference as above.  The bar takes the
+    output's energy to be spread over the coordinates; where a low-rank term of one token holds most of the weight it sits in
+    few of them, and its own float32 sum and the addition to the codebook term round once each, 2^-24 of the coordinate.  A
+    head with an infinite weight leaves the others alone."""
+    n_kv = 2
+    ctx = eoq.Context(n=n, bits=4)
+    spec = synth.BlockSpec("vals", n=n, n_tensors=n_kv, blocks_per_tensor=filled, rank_lo=0, rank_hi=24)
+    blocks, _ = synth.make_blocks(spec, seed=177 + n, device=DEV)
+    store, _ = ctx.eoq_compress(blocks)
+    x = U.reconstruct64(store, 4).cpu().view(n_kv, filled * n, 128)
+    T = filled * n
+    w = torch.softmax(4.0 * torch.randn(1, n_kv * group, T, generator=torch.Generator().manual_seed(n)), dim=-1)
+    out = ctx.eoq_attend(store, w.to(DEV), n_kv)
+    bad = w.clone()
+    bad[0, group + 4, T // 2] = float("inf")
+    out2 = ctx.eoq_attend(store, bad.to(DEV), n_kv)
+    torch.cuda.synchronize()
+    for h in range(n_kv * group):
+        want = (w[0, h].double() @ x[h // group]).numpy()
+        norm = (w[0, h].double().square() @ x[h // group].square().sum(1)).sqrt().item()
+        bar = ATTEND_TOL * norm + 2.0 * 2.0**-24 * np.max(np.abs(want))
+        assert np.max(np.abs(out[0, h].double().cpu().numpy() - want)) <= bar, h
+    assert bool(torch.isnan(out2[0, group + 4]).all())
+    keep = [h for h in range(n_kv * group) if h != group + 4]
+    assert torch.equal(out2[0, keep], out[0, keep])
+
+
 @pytest.mark.parametrize("bits,group,n", [(1, 4, 128), (1, 7, 512), (2, 4, 512), (2, 8, 1024), (3, 4, 128), (3, 6, 512), (4, 4, 1024), (4, 7, 128)])
 def test_attention_output_follows_weights_that_outgrow_their_unit(bits, group, n):
     """Weights that grow by 2^8 and by 2^8 again inside the tokens of a wave (seven pairs of 32-token tiles; the first four
