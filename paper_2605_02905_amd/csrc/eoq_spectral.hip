@@ -343,6 +343,11 @@ constexpr int POOL_BYTES = REFL_BYTES + U1_BYTES > 65536 ? REFL_BYTES + U1_BYTES
 // 2^(E_i + E_j - 58), is added to a double-precision accumulator: one conversion per 128 tokens.  Only the 36
 // tiles of 16 x 16 on and above the diagonal are computed, nine per wave; at the end they change lanes through LDS
 // (tiles_to_lanes).
+//
+// Vector instructions (4.2 cycles each on a SIMD, about 1250 per wave and group) and matrix instructions (304 of 16.5 cycles)
+// bound it about alike; per group of 128 tokens it takes 5.0 us with one workgroup on a unit and 9.1 with two.  With a conversion
+// and a product per entry, and operands read for every tile in rows that share banks, 5.5 and 9.7.  (A tile summed between the
+// matrix instructions of the next takes 4.6 and 9.2, but 31 more registers, and whole calls were longer by 1 %.)
 // ---------------------------------------------------------------------------------------------
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
@@ -353,16 +358,18 @@ constexpr int GI_PLANE = D * GI_ROW;             // 16384
 constexpr int GI_NPLANE = 4;
 constexpr int GI_BYTES = GI_NPLANE * GI_PLANE;   // 64 KB: the four planes fill the pool
 static_assert(GI_BYTES <= POOL_BYTES && GI_PLANE % 16 == 0, "Gram planes inside the pool");
-// A row is exactly as wide as the banks, so the chunks of a row are stored permuted: chunk c of column col sits at
-// position c ^ col ^ (col >> 3) (low three bits).  The sixteen lanes that read chunk c of sixteen consecutive
-// columns (operand loads) and the sixteen loaders that write chunk c of columns 8 m + const both touch every
-// position twice, which is what a 16-byte access of sixteen lanes needs anyway.
-__device__ __forceinline__ int gi_chunk_off(int col, int c) { return ((c ^ col ^ (col >> 3)) & 7) << 4; }
-constexpr int GI_TILES = 36;                     // upper tiles, row-major: (0,0) .. (0,7), (1,1) .. (7,7)
-constexpr int UT_I[GI_TILES] = {0, 0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 2, 2, 2, 2, 2, 2, 3, 3, 3, 3, 3, 4, 4, 4, 4, 5, 5, 5, 6, 6, 7};
-constexpr int UT_J[GI_TILES] = {0, 1, 2, 3, 4, 5, 6, 7, 1, 2, 3, 4, 5, 6, 7, 2, 3, 4, 5, 6, 7, 3, 4, 5, 6, 7, 4, 5, 6, 7, 5, 6, 7, 6, 7, 7};
-__device__ const int ut_i_dev[GI_TILES] = {0, 0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 2, 2, 2, 2, 2, 2, 3, 3, 3, 3, 3, 4, 4, 4, 4, 5, 5, 5, 6, 6, 7};
-__device__ const int ut_j_dev[GI_TILES] = {0, 1, 2, 3, 4, 5, 6, 7, 1, 2, 3, 4, 5, 6, 7, 2, 3, 4, 5, 6, 7, 3, 4, 5, 6, 7, 4, 5, 6, 7, 5, 6, 7, 6, 7, 7};
+// The chunks of a row are stored permuted: chunk c of column col sits at position c ^ col ^ (col >> 3) (low three bits) of row
+// col ^ (col >> 3 & 1) of its plane.  The lanes that read a chunk of sixteen consecutive columns and those that write two
+// chunks of the columns 8 m + const then spread over all 64 banks: 4.9 cycles a 16-byte read of a wave, as for consecutive
+// addresses (8.1 with the rows in order).
+__device__ __forceinline__ int gi_place(int col, int c) { return (col ^ ((col >> 3) & 1)) * GI_ROW + (((c ^ col ^ (col >> 3)) & 7) << 4); }
+// The tiles (I, J) of wave w, number s: 0 .. 5 in column 4 + w, the rows 4 + w, the next (w + 1 modulo 4), 0 .. 3; 7 and 8 in
+// column w, the rows w and w + 1; 6 the row w + 2 in column w of the waves 0 and 1, four added to both for the others.  The
+// operands of a column stay in registers for all its tiles but number 6, and those on the diagonal take no others.
+constexpr int gi_tile_i(int w, int s) {
+  return s < 2 ? 4 + ((w + s) & 3) : (s < 6 ? s - 2 : (s == 6 ? (w < 2 ? 0 : 4) + ((w + 2) & 3) : ((w + s - 7) & 3)));
+}
+constexpr int gi_tile_j(int w, int s) { return s < 6 ? 4 + w : (s == 6 && w >= 2 ? 4 + w : w); }
 
 // The 36 tiles, three rounds of twelve through LDS, into the cyclic layout: lane (ty, tx) takes element (ty, tx) of tile
 // (a, b) as A[a * 8 + b] and, for a < b, element (tx, ty) as A[b * 8 + a].  `get(s, v)` is this lane's entry number v of the
@@ -379,7 +386,7 @@ __device__ __forceinline__ void tiles_to_lanes(double* Tl, int tid, double (&A)[
     __syncthreads();
     EOQ_SFOR(pp, 12,
       constexpr int tile = 12 * rd + pp;
-      constexpr int a = UT_I[tile]; constexpr int b = UT_J[tile];
+      constexpr int a = gi_tile_i(tile & 3, tile >> 2); constexpr int b = gi_tile_j(tile & 3, tile >> 2);
       A[a * 8 + b] = Tl[pp * 16 * XPAD + ty * XPAD + tx];
       if constexpr (a != b) A[b * 8 + a] = Tl[pp * 16 * XPAD + tx * XPAD + ty];
     );
@@ -411,7 +418,7 @@ __device__ __forceinline__ void gram_f64(const float* __restrict__ src, size_t t
       // the wave's tiles wave, wave + 4, ..: four cases, so that every operand is a register known at compile time
       auto tiles = [&](auto w_ic) __attribute__((always_inline)) {
         constexpr int w = decltype(w_ic)::value;
-        EOQ_SFOR(s, 9, acc[s] = mfma64(o[UT_I[w + 4 * s]], o[UT_J[w + 4 * s]], acc[s]););
+        EOQ_SFOR(s, 9, acc[s] = mfma64(o[gi_tile_i(w, s)], o[gi_tile_j(w, s)], acc[s]););
       };
       if (wave == 0) tiles(std::integral_constant<int, 0>{});
       else if (wave == 1) tiles(std::integral_constant<int, 1>{});
@@ -428,7 +435,7 @@ __device__ __forceinline__ void gram_f64(const float* __restrict__ src, size_t t
     products(y);
   }
   bool bad = false;   // an Inf or NaN entry of the block reaches the diagonal of G, which the diagonal tiles hold
-  EOQ_SFOR(s, 9, EOQ_SFOR(v, 4, bad |= ut_i_dev[wave + 4 * s] == ut_j_dev[wave + 4 * s] && !(fabs(acc[s][v]) < INFINITY);););
+  EOQ_SFOR(v, 4, bad |= !(fabs(acc[0][v]) < INFINITY) || !(fabs(acc[7][v]) < INFINITY););
   if (bad) atomicOr(flag_s, EOQ_FLAG_NONFINITE);
   tiles_to_lanes(Tl, tid, A, [&](auto s, auto v) { return acc[decltype(s)::value][decltype(v)::value]; }, [&](int v) { return 4 * v + g; });
 }
@@ -436,6 +443,17 @@ __device__ __forceinline__ void gram_f64(const float* __restrict__ src, size_t t
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
   const ushort2v r = __builtin_elementwise_max(*reinterpret_cast<ushort2v*>(&a), *reinterpret_cast<ushort2v*>(&b));
   return *reinterpret_cast<const uint32_t*>(&r);
+}
+// a binary16 number in either half of a word times a power of two, exact: the conversion rides on the multiply-add
+__device__ __forceinline__ float scale_low_half(uint32_t w, float s) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(s));
+  return r;
+}
+__device__ __forceinline__ float scale_high_half(uint32_t w, float s) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(s));
+  return r;
 }
 // cmax: 4 x 64 words (the waves' column maxima), cexp: 128 ints (exponent of the integer unit of each column); both
 // outside the pool, which the planes fill.  n is a multiple of 128.
@@ -447,6 +465,8 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
   double Gacc[9][4];  // tile number wave + 4 s, rows 4 kg + v, column l16
   EOQ_SFOR(s, 9, EOQ_SFOR(v, 4, Gacc[s][v] = 0.0;););
 
+  // gi_place of the loader's column 8 m, chunk q / 4 (bits 4 .. 6 and 7 .. 9 flipped by c for column 8 m + c), and of the operands
+  const int w_base = gi_place(8 * m, q >> 2) + 4 * (q & 3), r_base = gi_place(l16, kg);
   uint32_t top = 0u;  // largest |binary16 pattern| this lane has seen in its columns: 0x7C00 and above is Inf / NaN
   uint4 raw[8];
 #pragma unroll
@@ -482,11 +502,12 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
     }
     top = pk_max_u16(top, pk_max_u16(pk_max_u16(mx[0], mx[1]), pk_max_u16(mx[2], mx[3])));
     // ---- integers, byte planes ----
+    int ex[8];
     EOQ_SFOR(c, 8,
       const uint32_t hmax = (mx[c >> 1] >> (16 * (c & 1))) & 0xFFFFu;
       const int ef = max((int)(hmax >> 10), 1);               // biased exponent of the column maximum (subnormals: 1)
       const float scale = __int_as_float((171 - ef) << 23);   // 2^(29 - (ef - 15))
-      if (q == 0) cexp[8 * m + c] = ef - 44;                  // one integer unit = 2^(ef - 15 - 29)
+      ex[c] = ef - 44;                                        // one integer unit = 2^(ef - 15 - 29)
       // I = sum_k d_k 256^k with balanced digits d_k in [-128, 127]: adding 128 to every digit place makes them the
       // plain bytes of I + 0x80808080 (|I| < 2^30: no carry out of the top), and flipping the top bit of each byte
       // takes the 128 off again, as a two's-complement byte.  The four planes are those bytes.
@@ -495,39 +516,45 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
         EOQ_SFOR(it, 4,
           const uint4 rw = raw[4 * h + it];
           const uint32_t w = (c >> 1) == 0 ? rw.x : ((c >> 1) == 1 ? rw.y : ((c >> 1) == 2 ? rw.z : rw.w));
-          const uint16_t hb = (uint16_t)(w >> (16 * (c & 1)));
-          const int I = (int)(half_bits_to_float(hb) * scale);   // truncation towards zero
+          const int I = (int)((c & 1) ? scale_high_half(w, scale) : scale_low_half(w, scale));   // truncation towards zero
           dg[it] = ((uint32_t)I + 0x80808080u) ^ 0x80808080u;
         );
         uint32_t pl[4];
         transpose_bytes(dg[0], dg[1], dg[2], dg[3], pl);
-        unsigned char* dst = pool + (8 * m + c) * GI_ROW + gi_chunk_off(8 * m + c, 4 * h + (q >> 2)) + 4 * (q & 3);
+        unsigned char* dst = pool + (w_base ^ (c << 4) ^ (h << 6) ^ (c * GI_ROW));
         *reinterpret_cast<uint32_t*>(dst) = pl[0];
         *reinterpret_cast<uint32_t*>(dst + GI_PLANE) = pl[1];
         *reinterpret_cast<uint32_t*>(dst + 2 * GI_PLANE) = pl[2];
         *reinterpret_cast<uint32_t*>(dst + 3 * GI_PLANE) = pl[3];
       );
     );
+    if (q == 0) {
+      int4* to = reinterpret_cast<int4*>(cexp + 8 * m);
+      to[0] = make_int4(ex[0], ex[1], ex[2], ex[3]);
+      to[1] = make_int4(ex[4], ex[5], ex[6], ex[7]);
+    }
     if (t0 + GI_TOK < n) {  // next group on its way during the products
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         raw[i] = *reinterpret_cast<const uint4*>(src + (size_t)(t0 + GI_TOK + 64 * (i >> 2) + 4 * q + (i & 3)) * tok + 8 * m);
     }
     __syncthreads();
-    // ---- products, one tile at a time: lane supplies row / column l16 of the tile, tokens 64 h + 16 kg .. + 15 ----
-    EOQ_SFOR(s, 9,
-      const int tile = wave + 4 * s;
-      const int tI = ut_i_dev[tile]; const int tJ = ut_j_dev[tile];
-      v4i acc[7];  // acc[c]: plane pairs (p, q) with p + q = c, weight 2^(8 c)
+    // ---- products: lane supplies row / column l16 of the tile, tokens 64 h + 16 kg .. + 15 ----
+    auto operand = [&](int I, int h, int p) __attribute__((always_inline)) {   // gi_place of column 16 I + l16, chunk 4 h + kg
+      return *reinterpret_cast<const v4i*>(pool + (r_base ^ ((2 * I & 7) << 4) ^ (h << 6)) + 16 * GI_ROW * I + p * GI_PLANE);
+    };
+    v4i kept[2][4];
+    v4i acc[7];   // acc[c]: plane pairs (p, q) with p + q = c, weight 2^(8 c)
+    auto tile_product = [&](auto s_ic) __attribute__((always_inline)) {
+      constexpr int s = decltype(s_ic)::value;
+      const int tI = gi_tile_i(wave, s); const int tJ = gi_tile_j(wave, s);
+      if constexpr (s == 0 || s == 7) { EOQ_SFOR(h, 2, EOQ_SFOR(p, 4, kept[h][p] = operand(tJ, h, p););); }
       EOQ_SFOR(cc, 7, EOQ_SFOR(v, 4, acc[cc][v] = 0;););
-      const int ca = 16 * tI + l16, cb = 16 * tJ + l16;
       EOQ_SFOR(h, 2,
-        const unsigned char* pa = pool + ca * GI_ROW + gi_chunk_off(ca, 4 * h + kg);
-        const unsigned char* pb = pool + cb * GI_ROW + gi_chunk_off(cb, 4 * h + kg);
         v4i a[4]; v4i b[4];
-        EOQ_SFOR(pl, 4,
-          a[pl] = *reinterpret_cast<const v4i*>(pa + pl * GI_PLANE);
-          b[pl] = *reinterpret_cast<const v4i*>(pb + pl * GI_PLANE);
+        EOQ_SFOR(p, 4,
+          b[p] = s == 6 ? operand(tJ, h, p) : kept[h][p];
+          a[p] = s == 0 || s == 7 ? kept[h][p] : operand(tI, h, p);
         );
         // order: consecutive instructions hit different accumulators
         EOQ_SFOR(rot, 4,
@@ -537,6 +564,10 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
           );
         );
       );
+    };
+    auto tile_sum = [&](auto s_ic) __attribute__((always_inline)) {
+      constexpr int s = decltype(s_ic)::value;
+      const int tI = gi_tile_i(wave, s); const int tJ = gi_tile_j(wave, s);
       // into double precision with the exponents of rows 4 kg + v (tile I) and column l16 (tile J)
       const int ej = cexp[16 * tJ + l16];
       const int4 ei = *reinterpret_cast<const int4*>(cexp + 16 * tI + 4 * kg);
@@ -547,11 +578,13 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
       // 128 (2^14 + 2^14) = 2^22, |c_5| <= 2^21, and every c_even + 2^8 c_odd stays below 2^31 (the largest,
       // c_2 + 2^8 c_3, below 1.62e9).
       EOQ_SFOR(v, 4,
-        const int m01 = acc[0][v] + (acc[1][v] << 8), m23 = acc[2][v] + (acc[3][v] << 8), m45 = acc[4][v] + (acc[5][v] << 8);
+        const int m01 = acc[0][v] + (acc[1][v] << 8), m23 = acc[2][v] + (acc[3][v] << 8);
+        const int m45 = acc[4][v] + (acc[5][v] << 8);
         const double val = fma(fma(fma((double)acc[6][v], 65536.0, (double)m45), 65536.0, (double)m23), 65536.0, (double)m01);
         Gacc[s][v] += ldexp(val, eiv[v] + ej);
       );
-    );
+    };
+    EOQ_SFOR(s, 9, tile_product(s_ic); tile_sum(s_ic););
   }
   // a column maximum with all exponent bits set: the integer conversion of that pass saturated, G is meaningless
   if (q == 0 && (((top & 0xFFFFu) >= 0x7C00u) || ((top >> 16) >= 0x7C00u))) atomicOr(flag_s, EOQ_FLAG_NONFINITE);
