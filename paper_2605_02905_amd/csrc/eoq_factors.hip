@@ -12,29 +12,27 @@
 #include "eoq_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
 using namespace eoqdev;
 
 constexpr int D = EOQ_D;
-constexpr int THREADS = 256;
+constexpr int THREADS = 256;   // of the expansion
 constexpr int LEVELS = 8;
 constexpr int LLOYD_ITERS = 8;
+constexpr int KEEP = 16;   // entries of a matrix that a lane keeps in registers
 
 struct GaussLevels {
   double c[LEVELS];  // Lloyd-Max magnitudes of N(0,1) at 16 levels
 };
 
-__device__ __forceinline__ int cell_of(double a, const double (&b)[LEVELS - 1]) {
+__device__ __forceinline__ int code_of(float x, const float (&b)[LEVELS - 1]) {
   int k = 0;
 #pragma unroll
-  for (int q = 0; q < LEVELS - 1; ++q) k += (a >= b[q]) ? 1 : 0;  // a tie goes to the upper cell
-  return k;
-}
-
-__device__ __forceinline__ int code_of(double x, const double (&b)[LEVELS - 1]) {
-  return cell_of(fabs(x), b) | ((x >= 0.0) ? 8 : 0);
+  for (int q = 0; q < LEVELS - 1; ++q) k += (fabsf(x) >= b[q]) ? 1 : 0;  // a tie goes to the upper cell
+  return k | ((x >= 0.0f) ? 8 : 0);
 }
 
 __device__ __forceinline__ double swizzle_xor(double v, int mask) {
@@ -80,44 +78,45 @@ __device__ __forceinline__ double wave_reduce8(const double (&v)[8], int lane) {
 // number of the value wave_reduce8 leaves in lane l (l < 8)
 __device__ __forceinline__ int reduce8_slot(int l) { return 4 * (l & 1) + 2 * ((l >> 1) & 1) + ((l >> 2) & 1); }
 
-// Partial Lloyd statistics of |x[0 .. count)| for the boundaries b: sums of the entries at or above every boundary
-// (st[0..6]) and of all entries (st[7]) per lane; the counts at or above every boundary per WAVE (cnt, uniform).
-__device__ __forceinline__ void lloyd_scan(const float* x, int count, const double (&b)[LEVELS - 1], int tid,
-                                           double (&st)[8], int (&cnt)[LEVELS - 1]) {
+// The boundaries between the levels that the lanes k = lane % 8 hold, as float32 numbers rounded up: a float32 number is at or
+// above one of them exactly where it is at or above the midpoint itself.
+__device__ __forceinline__ void boundaries(double level, float (&b)[LEVELS - 1]) {
+  const double mid = 0.5 * (level + dpp_mov<0x101>(level));   // (row_shl:1: the next lane's)
+  float f = (float)mid;
+  if ((double)f < mid) f = __uint_as_float(__float_as_uint(f) + 1u);   // (magnitudes: positive)
 #pragma unroll
-  for (int k = 0; k < 8; ++k) st[k] = 0.0;
-#pragma unroll
-  for (int k = 0; k < LEVELS - 1; ++k) cnt[k] = 0;
-  for (int e0 = 0; e0 < count; e0 += THREADS) {   // uniform trip count: the ballots need every lane
-    const int e = e0 + tid;
-    const double a = (e < count) ? fabs((double)x[e]) : -1.0;
-#pragma unroll
-    for (int q = 0; q < LEVELS - 1; ++q) {
-      const bool ge = a >= b[q];
-      st[q] += ge ? a : 0.0;
-      cnt[q] += __popcll(__ballot(ge));
-    }
-    st[7] += (e < count) ? a : 0.0;
-  }
+  for (int k = 0; k < LEVELS - 1; ++k) b[k] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), k));
 }
 
-template <int RCAP>
-__global__ __launch_bounds__(THREADS) void eoq_factor_quant_kernel(
+// One wave has V (r D entries), UW waves have U (r n entries, n / 128 of them up to 1024 tokens: the same share each).  A wave
+// walks its entries, which stay in its registers, and adds up for itself; its eight levels are all else that it keeps.  With
+// four waves on both matrices each of them went through both sums and both moves of the levels, and those, not the entries,
+// were most of its instructions.  4096 blocks of 128 x 128 (ranks 1 .. 6) took 246 us and take 121, 1024 of 512 x 128 154 and
+// 150, 16 blocks of 128 x 128 41 and 33.  What is left is bound by the reads of the rows of S, one to a lane: five waves to a
+// SIMD instead of four read them from further away and take 158.
+template <int RCAP, int UW>
+__global__ __launch_bounds__(64 * (UW + 1), 4) void eoq_factor_quant_kernel(
     const uint16_t* __restrict__ blocks, EoqBlockMap map, int64_t B, int n, int r_max, GaussLevels g,
     const int32_t* __restrict__ rank_in,
     const float* __restrict__ phi, const float* __restrict__ sigma, const float* __restrict__ wfac,
     uint16_t* __restrict__ rfac, uint16_t* __restrict__ lfac, uint8_t* __restrict__ lcodes,
     uint8_t* __restrict__ rcodes, uint16_t* __restrict__ fbook, uint16_t* __restrict__ phi16) {
+  constexpr int THREADS = 64 * (UW + 1);
   extern __shared__ __align__(16) float dyn[];  // Vs[r][D] then Us[r][n]
-  __shared__ __align__(16) double red[2][4][16];   // [parity][wave][U: 8 sums, V: 8 sums]
-  __shared__ int redc[2][4][16];                   // [parity][wave][U: 7 counts, pad, V: 7 counts, pad]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ __align__(16) double red[2][UW + 1][8];   // [parity][wave]: sums at or above the boundaries, and of all
+  __shared__ int redc[2][UW + 1][8];                   // counts
+  __shared__ float book[UW + 1][LEVELS];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool is_v = wave == UW;
   // The workgroups walk the batch with the grid's stride.  The launch with the small table has one workgroup per block
   // and takes the blocks of rank 1 .. 8 (and clears the codebook of rank-0 blocks); the launch with the large table is
   // a few persistent workgroups that look for the rest (usually there are none: a grid of B would only spend its
   // time placing workgroups with a large LDS allocation that return at once).
   for (size_t wblk = blockIdx.x; wblk < (size_t)B; wblk += gridDim.x) {   // number in the batch: workspace and input
   __syncthreads();                           // LDS of the previous block has been consumed
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));              // (else every address that follows from it is kept over the blocks)
+  const int lane = tid & 63;
   const size_t blk = map.slot(wblk);         // record slot: everything that is stored
   const int r = rank_in[blk];
   if (RCAP == 8) {
@@ -175,151 +174,126 @@ __global__ __launch_bounds__(THREADS) void eoq_factor_quant_kernel(
   }
   __syncthreads();
 
-  // ---- Lloyd fits of the two codebooks, side by side (one barrier per round) ----
-  const int cu = r * n, cv = r * D;
-  double mu[LEVELS], mv[LEVELS];
+  // ---- Lloyd fits of the two codebooks, side by side (one barrier per round, none where each is one wave's) ----
+  const float* X = is_v ? Vs : Us;
+  const int count = r * (is_v ? D : n), first = is_v ? lane : 64 * wave + lane, step = is_v ? 64 : 64 * UW;
+  const int k = lane & 7;   // every eight lanes hold the levels and move them alike
   int par = 0;
+  auto meet = [&]() __attribute__((always_inline)) {
+    if constexpr (UW > 1) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();   // one wave: its LDS operations complete in order
+  };
+  auto total = [&](int v) __attribute__((always_inline)) {   // value number v over the waves of the matrix
+    double t = red[par][is_v ? UW : 0][v];
+#pragma unroll
+    for (int w = 1; w < UW; ++w) t += is_v ? 0.0 : red[par][w][v];
+    return t;
+  };
+  auto number = [&](int v) __attribute__((always_inline)) {
+    int t = redc[par][is_v ? UW : 0][v];
+#pragma unroll
+    for (int w = 1; w < UW; ++w) t += is_v ? 0 : redc[par][w][v];
+    return t;
+  };
+  // The first entries of the lane stay in registers (all of them where a wave has the 128 tokens of eight components).
+  const int trips = (count + step - 1) / step;
+  float x[KEEP];
+  auto entry = [&](int j) __attribute__((always_inline)) {   // magnitude; -1 behind the last
+    const int e = j * step + first;
+    return (e < count) ? fabsf(X[e]) : -1.0f;
+  };
+#pragma unroll
+  for (int j = 0; j < KEEP; ++j) x[j] = (j < trips) ? entry(j) : -1.0f;
+  double level, all;
   {
     double st[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int e = tid; e < cu; e += THREADS) {
-      const double a = (double)Us[e];
+    auto add = [&](float f) __attribute__((always_inline)) {
+      const double a = (double)fmaxf(f, 0.0f);
       st[0] = fma(a, a, st[0]);
-    }
-    for (int e = tid; e < cv; e += THREADS) {
-      const double a = (double)Vs[e];
-      st[4] = fma(a, a, st[4]);   // value 4 ends in lane 1, value 0 in lane 0
-    }
+      st[4] += a;                                      // (values 0 and 4 end in the lanes 0 and 1)
+    };
+#pragma unroll
+    for (int j = 0; j < KEEP; ++j)
+      if (j < trips) add(x[j]);
+    for (int j = KEEP; j < trips; ++j) add(entry(j));
     const double y = wave_reduce8(st, lane);
     if (lane < 2) red[par][wave][lane] = y;
-    __syncthreads();
-    const double su = (red[par][0][0] + red[par][1][0]) + (red[par][2][0] + red[par][3][0]);
-    const double sv = (red[par][0][1] + red[par][1][1]) + (red[par][2][1] + red[par][3][1]);
-    const double rms_u = sqrt(su / (double)cu), rms_v = sqrt(sv / (double)cv);
+    meet();
+    const double rms = sqrt(total(0) / (double)count);
+    all = total(1);
+    level = 0.0;
 #pragma unroll
-    for (int k = 0; k < LEVELS; ++k) {
-      mu[k] = g.c[k] * rms_u;
-      mv[k] = g.c[k] * rms_v;
-    }
+    for (int q = 0; q < LEVELS; ++q) level = (k == q) ? g.c[q] * rms : level;
     par ^= 1;
   }
+  float b[LEVELS - 1];
 #pragma unroll 1
   for (int it = 0; it < LLOYD_ITERS; ++it) {
-    double b[LEVELS - 1], st[8];
-    int cnt[LEVELS - 1];
+    // sums of the entries at or above every boundary per lane, the counts per wave
+    double st[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int cnt[LEVELS - 1] = {0, 0, 0, 0, 0, 0, 0};
+    boundaries(level, b);
+    auto add = [&](float f) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < LEVELS - 1; ++k) b[k] = 0.5 * (mu[k] + mu[k + 1]);
-    lloyd_scan(Us, cu, b, tid, st, cnt);
-    double y = wave_reduce8(st, lane);
+      for (int q = 0; q < LEVELS - 1; ++q) {
+        const bool ge = f >= b[q];
+        float a = ge ? f : 0.0f;
+        asm("" : "+v"(a));   // (else all conversions are kept over the rounds)
+        st[q] += (double)a;
+        cnt[q] += __popcll(__ballot(ge));
+      }
+    };
+#pragma unroll
+    for (int j = 0; j < KEEP; ++j)
+      if (j < trips) add(x[j]);
+    for (int j = KEEP; j < trips; ++j) add(entry(j));
+    const double y = wave_reduce8(st, lane);
     if (lane < 8) red[par][wave][reduce8_slot(lane)] = y;
-    if (lane == 0) {
+    int mine = 0;
 #pragma unroll
-      for (int k = 0; k < LEVELS - 1; ++k) redc[par][wave][k] = cnt[k];
-    }
-#pragma unroll
-    for (int k = 0; k < LEVELS - 1; ++k) b[k] = 0.5 * (mv[k] + mv[k + 1]);
-    lloyd_scan(Vs, cv, b, tid, st, cnt);
-    y = wave_reduce8(st, lane);
-    if (lane < 8) red[par][wave][8 + reduce8_slot(lane)] = y;
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < LEVELS - 1; ++k) redc[par][wave][8 + k] = cnt[k];
-    }
-    __syncthreads();
-    // Lane l < 16 of every wave moves one level: matrix f = l / 8, level k = l % 8 (the waves repeat the work and agree
-    // bit for bit, so no second barrier).  Cell sum = difference of two "at or above" sums, T[0] = all (value 7),
-    // T[j] = value j - 1, T[8] = 0; counts likewise.
-    {
-      const int f = (lane >> 3) & 1, k = lane & 7;
-      const int ia = 8 * f + ((k == 0) ? 7 : k - 1), ib = 8 * f + min(k, LEVELS - 2);
-      const double sa = (red[par][0][ia] + red[par][1][ia]) + (red[par][2][ia] + red[par][3][ia]);
-      double sb = (red[par][0][ib] + red[par][1][ib]) + (red[par][2][ib] + red[par][3][ib]);
-      const int ja = 8 * f + max(k - 1, 0);
-      int ca = (redc[par][0][ja] + redc[par][1][ja]) + (redc[par][2][ja] + redc[par][3][ja]);
-      int cb = (redc[par][0][ib] + redc[par][1][ib]) + (redc[par][2][ib] + redc[par][3][ib]);
-      if (k == 0) ca = f ? cv : cu;
-      if (k == LEVELS - 1) {
-        sb = 0.0;
-        cb = 0;
-      }
-      const int ck = ca - cb;
-      double mine = 0.0;   // this lane's level before the round
-#pragma unroll
-      for (int q = 0; q < LEVELS; ++q) mine = (k == q) ? (f ? mv[q] : mu[q]) : mine;
-      const double moved = (ck > 0) ? (sa - sb) / (double)ck : mine;   // an empty cell keeps its level
-#pragma unroll
-      for (int q = 0; q < LEVELS; ++q) {
-        mu[q] = readlane_f64(moved, q);
-        mv[q] = readlane_f64(moved, LEVELS + q);
-      }
-    }
+    for (int q = 0; q < LEVELS - 1; ++q) mine = (lane == q) ? cnt[q] : mine;
+    if (lane < LEVELS - 1) redc[par][wave][lane] = mine;
+    meet();
+    // Every lane moves level k (the waves of a matrix repeat the work and agree bit for bit, so no second barrier).  Cell
+    // sum = difference of two "at or above" sums, T[0] = all, T[j] = value j - 1, T[8] = 0; counts likewise.
+    const int ib = min(k, LEVELS - 2);
+    const double sa = (k == 0) ? all : total(max(k - 1, 0)), sb = (k == LEVELS - 1) ? 0.0 : total(ib);
+    const int ca = (k == 0) ? count : number(max(k - 1, 0)), cb = (k == LEVELS - 1) ? 0 : number(ib);
+    const int ck = ca - cb;
+    level = (ck > 0) ? (sa - sb) / (double)ck : level;   // an empty cell keeps its level
     par ^= 1;
   }
 
-  double m16[LEVELS];
-  uint16_t bits16[LEVELS];
-  double b[LEVELS - 1];
-  // ---- U ----
-#pragma unroll
-  for (int k = 0; k < LEVELS; ++k) {
-    bits16[k] = double_to_half_bits(mu[k]);
-    m16[k] = (double)half_bits_to_float(bits16[k]);
-  }
-  if (tid < LEVELS) {
-    uint16_t mine = 0;
-#pragma unroll
-    for (int k = 0; k < LEVELS; ++k) mine = (tid == k) ? bits16[k] : mine;
-    fbook[blk * 2 * LEVELS + tid] = mine;
-  }
-#pragma unroll
-  for (int k = 0; k < LEVELS - 1; ++k) b[k] = 0.5 * (m16[k] + m16[k + 1]);
-  for (int e = tid; e < r * (n / 2); e += THREADS) {  // two tokens per byte
-    const int i = e / (n / 2), t = 2 * (e - i * (n / 2));
-    const uint16_t ph16 = float_to_half_bits(phi[blk * r_max + i]);
-    const double p16 = (double)half_bits_to_float(ph16);
-    int code[2];
-    uint16_t outv[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const double x = (double)Us[(size_t)i * n + t + u];
-      code[u] = code_of(x, b);
-      double lev = 0.0;
-#pragma unroll
-      for (int k = 0; k < LEVELS; ++k) lev = ((code[u] & 7) == k) ? m16[k] : lev;
-      outv[u] = double_to_half_bits(((code[u] & 8) ? lev : -lev) * p16);
+  // ---- levels in binary16, codes and what they expand to ----
+  const uint16_t bits16 = double_to_half_bits(level);
+  const float m16 = half_bits_to_float(bits16);
+  if ((wave == 0 || is_v) && lane < LEVELS) fbook[blk * 2 * LEVELS + (is_v ? LEVELS : 0) + lane] = bits16;
+  if (lane < LEVELS) book[wave][lane] = m16;
+  boundaries((double)m16, b);
+  __builtin_amdgcn_wave_barrier();
+  if (!is_v) {
+    for (int i = 0; i < r; ++i) {
+      const uint16_t ph16 = float_to_half_bits(phi[blk * r_max + i]);
+      const double p16 = (double)half_bits_to_float(ph16);
+      if (tid == 0) phi16[blk * r_max + i] = ph16;
+      for (int t = first; t < n / 2; t += step) {   // two tokens per byte
+        const float2 x = *reinterpret_cast<const float2*>(Us + (size_t)i * n + 2 * t);
+        const int c0 = code_of(x.x, b), c1 = code_of(x.y, b);
+        const double l0 = (double)book[wave][c0 & 7], l1 = (double)book[wave][c1 & 7];
+        const uint32_t o0 = double_to_half_bits(((c0 & 8) ? l0 : -l0) * p16), o1 = double_to_half_bits(((c1 & 8) ? l1 : -l1) * p16);
+        *reinterpret_cast<uint32_t*>(lfac + (blk * r_max + i) * (size_t)n + 2 * t) = o0 | (o1 << 16);
+        lcodes[(blk * r_max + i) * (size_t)(n / 2) + t] = (uint8_t)(c0 | (c1 << 4));
+      }
     }
-    *reinterpret_cast<uint32_t*>(lfac + (blk * r_max + i) * (size_t)n + t) = (uint32_t)outv[0] | ((uint32_t)outv[1] << 16);
-    lcodes[(blk * r_max + i) * (size_t)(n / 2) + (t >> 1)] = (uint8_t)(code[0] | (code[1] << 4));
-    if (t == 0) phi16[blk * r_max + i] = ph16;
-  }
-  // ---- V ----
-#pragma unroll
-  for (int k = 0; k < LEVELS; ++k) {
-    bits16[k] = double_to_half_bits(mv[k]);
-    m16[k] = (double)half_bits_to_float(bits16[k]);
-  }
-  if (tid < LEVELS) {
-    uint16_t mine = 0;
-#pragma unroll
-    for (int k = 0; k < LEVELS; ++k) mine = (tid == k) ? bits16[k] : mine;
-    fbook[blk * 2 * LEVELS + LEVELS + tid] = mine;
-  }
-#pragma unroll
-  for (int k = 0; k < LEVELS - 1; ++k) b[k] = 0.5 * (m16[k] + m16[k + 1]);
-  for (int e = tid; e < r * (D / 2); e += THREADS) {
-    const int i = e / (D / 2), j = 2 * (e - i * (D / 2));
-    int code[2];
-    uint16_t outv[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const double x = (double)Vs[i * D + j + u];
-      code[u] = code_of(x, b);
-      uint16_t lev = 0;
-#pragma unroll
-      for (int k = 0; k < LEVELS; ++k) lev = ((code[u] & 7) == k) ? bits16[k] : lev;
-      outv[u] = (code[u] & 8) ? lev : (uint16_t)(lev | 0x8000u);
+  } else {
+    for (int i = 0; i < r; ++i) {
+      const float2 x = *reinterpret_cast<const float2*>(Vs + i * D + 2 * lane);
+      const int c0 = code_of(x.x, b), c1 = code_of(x.y, b);
+      const uint32_t o0 = float_to_half_bits((c0 & 8) ? book[wave][c0 & 7] : -book[wave][c0 & 7]);
+      const uint32_t o1 = float_to_half_bits((c1 & 8) ? book[wave][c1 & 7] : -book[wave][c1 & 7]);
+      *reinterpret_cast<uint32_t*>(rfac + (blk * r_max + i) * (size_t)D + 2 * lane) = o0 | (o1 << 16);
+      rcodes[(blk * r_max + i) * (size_t)(D / 2) + lane] = (uint8_t)(c0 | (c1 << 4));
     }
-    *reinterpret_cast<uint32_t*>(rfac + (blk * r_max + i) * (size_t)D + j) = (uint32_t)outv[0] | ((uint32_t)outv[1] << 16);
-    rcodes[(blk * r_max + i) * (size_t)(D / 2) + (j >> 1)] = (uint8_t)(code[0] | (code[1] << 4));
   }
   }  // blocks of this workgroup
 }
@@ -360,14 +334,30 @@ __global__ __launch_bounds__(THREADS) void eoq_factor_expand_kernel(
 
 }  // namespace
 
+// calls f(waves of U): a wave to 128 tokens, up to eight
+template <typename F>
+static hipError_t for_u_waves(int n, F&& f) {
+  if (n < 256) return f(std::integral_constant<int, 1>{});
+  if (n < 512) return f(std::integral_constant<int, 2>{});
+  if (n < 1024) return f(std::integral_constant<int, 4>{});
+  return f(std::integral_constant<int, 8>{});
+}
+
 // Largest LDS tables the two variants are ever launched with (n * r_max <= 32768, n <= 4096): raised once per device
 // at context creation, so that the hot call sets no function attribute.
 hipError_t eoq_factor_quant_prepare() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(eoq_factor_quant_kernel<8>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (4096 + D) * (int)sizeof(float));
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(eoq_factor_quant_kernel<32>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (32768 + EOQ_RMAX_CAP * D) * (int)sizeof(float));
+  for (int n = 128; n <= 1024; n *= 2) {
+    const hipError_t e = for_u_waves(n, [](auto uw) {
+      constexpr int UW = decltype(uw)::value;
+      const hipError_t e8 = hipFuncSetAttribute(reinterpret_cast<const void*>(eoq_factor_quant_kernel<8, UW>),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (4096 + D) * (int)sizeof(float));
+      if (e8 != hipSuccess) return e8;
+      return hipFuncSetAttribute(reinterpret_cast<const void*>(eoq_factor_quant_kernel<32, UW>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (32768 + EOQ_RMAX_CAP * D) * (int)sizeof(float));
+    });
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t eoq_launch_factor_quant(const EoqLaunch& L, const void* blocks_fp16, int64_t B, const float* wfac,
@@ -376,18 +366,20 @@ hipError_t eoq_launch_factor_quant(const EoqLaunch& L, const void* blocks_fp16, 
   for (int k = 0; k < LEVELS; ++k) g.c[k] = gauss_levels[k];
   // two launches over all blocks, each taking the blocks of its rank class: the table of the factors in LDS is
   // sized for 8 components (most blocks: many workgroups per CU) or for r_max
-  const size_t lds8 = (size_t)std::min(8, L.r_max) * (L.n + D) * sizeof(float);
-  hipError_t e = hipSuccess;
-  hipLaunchKernelGGL(eoq_factor_quant_kernel<8>, dim3((unsigned)B), dim3(THREADS), lds8, L.stream,
-                     static_cast<const uint16_t*>(blocks_fp16), L.map, B, L.n, L.r_max, g, out.rank, out.phi, out.sigma, wfac,
-                     out.rfac, out.lfac, fq.lcodes, fq.rcodes, fq.fbook, fq.phi16);
-  e = hipGetLastError();
-  if (e != hipSuccess || L.r_max <= 8) return e;
-  const size_t lds = (size_t)L.r_max * (L.n + D) * sizeof(float);
-  hipLaunchKernelGGL(eoq_factor_quant_kernel<32>, dim3((unsigned)(B < 512 ? B : 512)), dim3(THREADS), lds, L.stream,
-                     static_cast<const uint16_t*>(blocks_fp16), L.map, B, L.n, L.r_max, g, out.rank, out.phi, out.sigma, wfac,
-                     out.rfac, out.lfac, fq.lcodes, fq.rcodes, fq.fbook, fq.phi16);
-  return hipGetLastError();
+  return for_u_waves(L.n, [&](auto uw) {
+    constexpr int UW = decltype(uw)::value;
+    const size_t lds8 = (size_t)std::min(8, L.r_max) * (L.n + D) * sizeof(float);
+    hipLaunchKernelGGL((eoq_factor_quant_kernel<8, UW>), dim3((unsigned)B), dim3(64 * (UW + 1)), lds8, L.stream,
+                       static_cast<const uint16_t*>(blocks_fp16), L.map, B, L.n, L.r_max, g, out.rank, out.phi, out.sigma, wfac,
+                       out.rfac, out.lfac, fq.lcodes, fq.rcodes, fq.fbook, fq.phi16);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || L.r_max <= 8) return e;
+    const size_t lds = (size_t)L.r_max * (L.n + D) * sizeof(float);
+    hipLaunchKernelGGL((eoq_factor_quant_kernel<32, UW>), dim3((unsigned)(B < 512 ? B : 512)), dim3(64 * (UW + 1)), lds, L.stream,
+                       static_cast<const uint16_t*>(blocks_fp16), L.map, B, L.n, L.r_max, g, out.rank, out.phi, out.sigma, wfac,
+                       out.rfac, out.lfac, fq.lcodes, fq.rcodes, fq.fbook, fq.phi16);
+    return hipGetLastError();
+  });
 }
 
 hipError_t eoq_launch_factor_expand(const EoqLaunch& L, eoq_packed rec, eoq_factor_codes fq, int64_t B) {
