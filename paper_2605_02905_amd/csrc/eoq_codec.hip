@@ -19,7 +19,11 @@ constexpr int D = EOQ_D;
 // receives D[row = 8*(v/4) + 4*(l/32) + v%4][col = l%32] in register v.  The contraction index is permuted so that a lane's
 // entries of four consecutive instructions are four consecutive floats.
 // Float32 products run at twice the vector rate on the matrix cores, and the rotation no longer takes 64 KB of LDS and
-// twelve LDS reads per 32 multiply-adds, which left one workgroup per compute unit: 125 blocks of 512 rows 119 -> 39 us.
+// twelve LDS reads per 32 multiply-adds, which left one workgroup per compute unit.  The matrix instructions of a workgroup, 8 k
+// cycles, wait for its rows and its residual, so it is workgroups on a unit that fill them: W comes through the scalar cache, C
+// lies in LDS in the binary16 it is stored in, and the columns of Pi are read when the rows are done with their registers, which
+// leaves room for four a unit instead of two.  8192 workgroups of 64 rows at 1 bit 244 -> 200 us, 1000 at 4 bits 41 -> 36.5 (of
+// which 13 are the matrix cores' rate and 8 that of memory).
 // ---------------------------------------------------------------------------
 constexpr int ENC_ROWS = 64;
 constexpr int ENC_THREADS = 256;
@@ -28,55 +32,49 @@ constexpr int LDS_C = EOQ_RMAX_CAP + 1;
 typedef float float16v __attribute__((ext_vector_type(16)));
 
 template <int BITS>
-__global__ __launch_bounds__(ENC_THREADS, 2) void eoq_encode_kernel(
+__global__ __launch_bounds__(ENC_THREADS, 4) void eoq_encode_kernel(
     const float* __restrict__ blocks, EoqBlockMap map, int64_t b0, int n, int r_max, const float* __restrict__ pi,
     const float* __restrict__ tab, const float* __restrict__ wfac, const int32_t* __restrict__ rank_in,
     const uint16_t* __restrict__ rfac, uint16_t* __restrict__ lfac, uint16_t* __restrict__ norms,
     uint8_t* __restrict__ codes) {
   __shared__ __align__(16) float X[ENC_ROWS * LDS_X];      // rows of S, then sqrt(d) u
-  __shared__ __align__(16) float Wl[EOQ_RMAX_CAP * D];     // V diag(phi/sigma)
-  __shared__ float Cl[ENC_ROWS * LDS_C];
+  __shared__ uint16_t Cl[ENC_ROWS * LDS_C];                // C as stored
   constexpr int ROWB = BITS * D / 8;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
   const size_t blk = (size_t)b0 + blockIdx.y;
   const size_t slot = map.slot(blk);
   const int row0 = blockIdx.x * ENC_ROWS;
   const int r = rank_in[slot];
 
-  // rows and factors; then the wave's columns of the rotation, which are needed last
   {
     const float* src = blocks + map.in_base(blk) + (size_t)(row0 + (tid >> 5)) * (size_t)map.token_stride + 4 * (tid & 31);
     float4 x[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const float4*>(src + (size_t)(8 * k) * (size_t)map.token_stride);
-    for (int e = tid; e < r * (D / 4); e += ENC_THREADS)
-      reinterpret_cast<float4*>(Wl)[e] = reinterpret_cast<const float4*>(wfac + blk * r_max * D)[e];
 #pragma unroll
     for (int k = 0; k < 8; ++k) *reinterpret_cast<float4*>(X + (8 * k + (tid >> 5)) * LDS_X + 4 * (tid & 31)) = x[k];
   }
-  float4 P[16];
-#pragma unroll
-  for (int m = 0; m < 16; ++m) P[m] = *reinterpret_cast<const float4*>(pi + (32 * wave + l32) * D + 8 * m + 4 * hf);
   Bounds<BITS> bnd;
   bnd.load(tab + 16);
   __syncthreads();
 
   // C = S W^T (= U diag(phi)), rounded to the stored binary16 (Alg. 2 Return, Alg. 3 Store)
   for (int i = wave; i < r; i += 4) {
+    const float* w = wfac + (blk * r_max + i) * D;   // V diag(phi/sigma): the same for every lane, through the scalar cache
     float s0 = 0.0f, s1 = 0.0f;
-#pragma unroll 4
+#pragma unroll 8
     for (int j = 0; j < D; j += 4) {
-      const float4 x = *reinterpret_cast<const float4*>(X + lane * LDS_X + j), w = *reinterpret_cast<const float4*>(Wl + i * D + j);
-      s0 = fmaf(x.x, w.x, s0);
-      s1 = fmaf(x.y, w.y, s1);
-      s0 = fmaf(x.z, w.z, s0);
-      s1 = fmaf(x.w, w.w, s1);
+      const float4 x = *reinterpret_cast<const float4*>(X + lane * LDS_X + j);
+      s0 = fmaf(x.x, w[j], s0);
+      s1 = fmaf(x.y, w[j + 1], s1);
+      s0 = fmaf(x.z, w[j + 2], s0);
+      s1 = fmaf(x.w, w[j + 3], s1);
     }
     const uint16_t hb = float_to_half_bits(s0 + s1);
     lfac[(slot * r_max + i) * (size_t)n + row0 + lane] = hb;
-    Cl[lane * LDS_C + i] = half_bits_to_float(hb);
+    Cl[lane * LDS_C + i] = hb;
   }
   __syncthreads();
 
@@ -95,7 +93,7 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void eoq_encode_kernel(
       const float v2 = half_bits_to_float((uint16_t)(h.y & 0xFFFFu)), v3 = half_bits_to_float((uint16_t)(h.y >> 16));
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
-        const float c = Cl[(8 * tr + a) * LDS_C + i];
+        const float c = half_bits_to_float(Cl[(8 * tr + a) * LDS_C + i]);
         x[a].x = fmaf(-c, v0, x[a].x);
         x[a].y = fmaf(-c, v1, x[a].y);
         x[a].z = fmaf(-c, v2, x[a].z);
@@ -119,6 +117,9 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void eoq_encode_kernel(
   __syncthreads();
 
   // z = Pi u (Alg. 1 line 4) and index of the nearest centroid (line 5): two tiles of 32 rows
+  float4 P[16];
+#pragma unroll
+  for (int m = 0; m < 16; ++m) P[m] = *reinterpret_cast<const float4*>(pi + (32 * wave + l32) * D + 8 * m + 4 * hf);
   float16v acc[2];
   EOQ_SFOR(t, 2, EOQ_SFOR(v, 16, acc[t][v] = 0.0f;););
   EOQ_SFOR(m, 16,
