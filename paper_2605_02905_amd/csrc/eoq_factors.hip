@@ -88,12 +88,13 @@ __device__ __forceinline__ void boundaries(double level, float (&b)[LEVELS - 1])
   for (int k = 0; k < LEVELS - 1; ++k) b[k] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), k));
 }
 
-// One wave has V (r D entries), UW waves have U (r n entries, n / 128 of them up to 1024 tokens: the same share each).  A wave
-// walks its entries, which stay in its registers, and adds up for itself; its eight levels are all else that it keeps.  With
-// four waves on both matrices each of them went through both sums and both moves of the levels, and those, not the entries,
-// were most of its instructions.  4096 blocks of 128 x 128 (ranks 1 .. 6) took 246 us and take 121, 1024 of 512 x 128 154 and
-// 150, 16 blocks of 128 x 128 41 and 33.  What is left is bound by the reads of the rows of S, one to a lane: five waves to a
-// SIMD instead of four read them from further away and take 158.
+// One wave has V (r D entries), UW waves have U (r n entries).  A wave walks its entries, the first sixteen to a lane kept in
+// registers, and adds up for itself; its eight levels are all else that it keeps.  With four waves on both matrices each of
+// them went through both sums and both moves of the levels, and those, not the entries, were most of its instructions at
+// 128 tokens.  Ranks 1 .. 6: 4096 blocks of 128 x 128 took 246 us and take 118, 16 of them 41 and 33; 16384 blocks of 512 x 128
+// 1480 and 1065, 4096 of 1024 x 128 770 and 673.  The reads of the rows of S, one to a lane, keep it from more waves: five to a
+// SIMD instead of four read them from further away and take 158 where it is 118; on the fp64 matrix cores, sixteen rows
+// at a time, the product takes longer (128, 1240 and 710).
 template <int RCAP, int UW>
 __global__ __launch_bounds__(64 * (UW + 1), 4) void eoq_factor_quant_kernel(
     const uint16_t* __restrict__ blocks, EoqBlockMap map, int64_t B, int n, int r_max, GaussLevels g,
@@ -334,13 +335,14 @@ __global__ __launch_bounds__(THREADS) void eoq_factor_expand_kernel(
 
 }  // namespace
 
-// calls f(waves of U): a wave to 128 tokens, up to eight
+// Calls f(waves of U).  With the one of V they are two, four or eight, alike for the four SIMDs of a unit: at n / 128 waves of U,
+// that is five a workgroup at 512 tokens and nine at 1024, one SIMD had two or three of them and the others waited for it (16384
+// blocks of 512 x 128 1700 us instead of 1065, 4096 of 1024 x 128 914 instead of 673).
 template <typename F>
 static hipError_t for_u_waves(int n, F&& f) {
   if (n < 256) return f(std::integral_constant<int, 1>{});
-  if (n < 512) return f(std::integral_constant<int, 2>{});
-  if (n < 1024) return f(std::integral_constant<int, 4>{});
-  return f(std::integral_constant<int, 8>{});
+  if (n < 768) return f(std::integral_constant<int, 3>{});
+  return f(std::integral_constant<int, 7>{});
 }
 
 // Largest LDS tables the two variants are ever launched with (n * r_max <= 32768, n <= 4096): raised once per device

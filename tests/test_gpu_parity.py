@@ -672,10 +672,10 @@ def test_q4_shapes_rank0_and_clamp(n, B, r_max, rank_hi):
     _q4_case(blocks, 2, n, r_max, f"q4-n{n}-rmax{r_max}")
 
 
-@pytest.mark.parametrize("n,B,r_max,rank_hi", [(256, 6, 8, 8), (384, 6, 32, 12), (896, 4, 32, 12), (1152, 4, 16, 12), (2048, 3, 16, 12), (4096, 2, 8, 8)])
+@pytest.mark.parametrize("n,B,r_max,rank_hi", [(256, 6, 8, 8), (384, 6, 32, 12), (640, 4, 8, 8), (768, 4, 32, 12), (1152, 4, 16, 12), (2048, 3, 16, 12), (4096, 2, 8, 8)])
 def test_q4_entries_beyond_those_kept_in_registers(n, B, r_max, rank_hi):
-    """The waves of the codebook fit: one to 128 tokens up to eight, with token counts that they share unevenly and more
-    entries to a lane than its registers take."""
+    """The one, three and seven waves of the codebook fit of U, with token counts that they share unevenly and more entries
+    to a lane than its registers take."""
     spec = synth.BlockSpec("q4waves", n=n, n_tensors=1, blocks_per_tensor=B, rank_lo=1, rank_hi=rank_hi)
     blocks, _ = synth.make_blocks(spec, seed=47)
     blocks = torch.cat([blocks, blocks[:1]])
