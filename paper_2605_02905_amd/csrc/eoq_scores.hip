@@ -548,8 +548,10 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
 
   // Two register sets in turn: the next tile is on its way while this one is worked on.  The loop body has no branch
   // around a memory instruction (a wait can then name exactly the loads it needs): behind the wave's last tile a
-  // request fetches that tile once more.  Two exits: on every path back the younger requests are the other set's.  (With a
-  // pass that stored nothing behind an odd number of tiles, runs of five steps took as long as runs of six.)
+  // request fetches that tile once more.  The last tile of an odd number has a body of its own.  (With a pass that stored
+  // nothing there, runs of five steps took as long as runs of six; with an exit in the middle of the loop its trip count and
+  // its addresses passed through vector registers, 90 vector instructions a tile instead of 82 at 2 bits: 8 heads x 23 blocks
+  // of 128 5.88 us where it is 5.78, 8 heads x 64 blocks of 512 with the correction 13.8 and 13.7.)
   int tok_w = tok0 + 32 * wave, b_w = 0, end_w = n, r_w = rank_of(0);   // next tile to work on
 #define EOQ_SC_WORK(F)                       \
   if (tok_w >= end_w) {                      \
@@ -560,13 +562,14 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   work(F, tok_w, b_w, r_w);                  \
   tok_w += QUAD;
 #pragma unroll 1
-  for (int it = 1;; it += 2) {
+  for (int it = 1; it < count; it += 2) {
     EOQ_SC_REQUEST(f1)
     EOQ_SC_WORK(f0)
-    if (it == count) break;
     EOQ_SC_REQUEST(f0)
     EOQ_SC_WORK(f1)
-    if (it + 1 == count) break;
+  }
+  if (count & 1) {   // uniform
+    EOQ_SC_WORK(f0)
   }
 #undef EOQ_SC_REQUEST
 #undef EOQ_SC_WORK
