@@ -156,6 +156,7 @@ EoqLaunch make_launch(const eoq_ctx* ctx, void* stream) {
   L.solver = ctx->solver;
   L.loss = ctx->loss;
   std::memcpy(L.score_places, ctx->score_places, sizeof(L.score_places));
+  L.units = ctx->units;
   L.map = eoq_dense_map(ctx->n);
   return L;
 }
@@ -229,6 +230,8 @@ eoq_status eoq_create(eoq_ctx** out, int n, int d, int bits, uint64_t rot_seed, 
     if (e == hipSuccess) g_scratch_ptr[ctx->device] = p;
   }
   if (e == hipSuccess) e = eoq_factor_quant_prepare();
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&ctx->units, hipDeviceAttributeMultiprocessorCount, ctx->device);
+  if (e == hipSuccess && ctx->units <= 0) e = hipErrorInvalidDevice;
   for (int corrected = 0; corrected < 2; ++corrected)
     for (int wide = 0; wide < 2; ++wide) {
       const int places = e == hipSuccess ? eoq_scores_places(bits, corrected, wide ? 8 : 4) : 0;

@@ -34,6 +34,7 @@ struct eoq_ctx {
   std::string err;
   double gauss16[8] = {};  // Lloyd-Max magnitudes of N(0,1) at 16 levels: start of the per-block factor codebooks
   int score_places[2][2] = {};   // workgroups of the scores kernel the device holds: [corrected logits][more than 4 heads]
+  int units = 0;                 // compute units of the device
   int loss = 0;    // eoq_loss: which case of Eq. (shrinkers) Alg. 2 Step 3 evaluates
   int solver = 0;  // 0: tridiagonal eigensolver with Jacobi for repeated eigenvalues, 1: Jacobi for every block
   // optional per-kernel timing: events [2*i], [2*i+1] bracket stage i (spectral, encode, decode, scores, attend,
@@ -73,6 +74,7 @@ struct EoqLaunch {
   int solver;
   int loss;
   int score_places[2][2];
+  int units;
 };
 
 // Workspace layout for B blocks: lam[B][128] f64, then wfac[B][r_max][128] f32 (right singular vectors
@@ -98,6 +100,8 @@ hipError_t eoq_launch_factor_expand(const EoqLaunch& L, eoq_packed rec, eoq_fact
 hipError_t eoq_launch_decode(const EoqLaunch& L, eoq_packed in, int64_t B, void* out_fp16);
 // workgroups of the scores kernel that the current device holds at a time; 0 if it cannot be asked
 extern "C" int eoq_scores_places(int bits, int corrected, int group);
+// steps of 128 tokens that a workgroup of the scores kernel takes (the rule stands beside its definition)
+extern "C" int64_t eoq_scores_run(int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block, int64_t tails);
 // block_capacity / score_stride <= 0: the dense case (blocks_per_head slots per head, rows of blocks_per_head * n);
 // tail_len > 0 adds the scores of the binary16 tail behind the blocks' scores
 hipError_t eoq_launch_scores(const EoqLaunch& L, eoq_packed keys, int64_t n_seq, int n_kv_heads,

@@ -156,7 +156,7 @@ struct TileFetch {
 // kernel, 64 tokens each: a kernel of their own cost a launch, and with one workgroup per head 32 us at 12 heads and 389
 // tokens.
 constexpr int TAIL_TOK = 64;
-constexpr int SHORT_RUN = 6;   // see the launch
+constexpr int SHORT_RUN = 6;   // see eoq_scores_run
 constexpr int QUAD = 128;   // tokens of one tile of each of the four waves
 __device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, int t0, int tail_len,
                                             const uint16_t* __restrict__ q, int group, float* __restrict__ row, size_t T, float* qs,
@@ -193,7 +193,7 @@ __device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, i
 
 // One workgroup per (sequence, KV head, run of tokens); every wave works on 32-token tiles of its own (wave w takes the tiles
 // w, w + 4, ... of the run), the record bytes of the next tile on their way while this one is worked on.  A run is a number of
-// steps of 128 tokens, a tile for each wave, and may begin and end inside a block (see the rule at the launch).  NQ = query heads a lane finishes per token (2 for groups up to 4).
+// steps of 128 tokens, a tile for each wave, and may begin and end inside a block (eoq_scores_run).  NQ = query heads a lane finishes per token (2 for groups up to 4).
 // QJL: the logits get the correction of Eq. (qjl), |r_x| sqrt(pi/2)/d <Phi q, sign(Phi r_x)>, from one more bit plane
 // (the signs) and the stored residual norm; Phi q goes through the same fixed-point form as Pi q.
 template <int BITS, bool QJL, int NQ>
@@ -590,32 +590,9 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   if (score_stride <= 0) score_stride = blocks_per_head * L.n;
   if (L.ev) (void)hipEventRecord(L.ev[6], L.stream);
   const int64_t tail_groups = (tail_len + TAIL_TOK - 1) / TAIL_TOK;
-  // Tokens per workgroup, in steps of 128 (a tile for each of its waves).  The set-up is paid once per workgroup, so runs are
-  // as long as they can be, up to 16 blocks, while the grid still has a workgroup for each place on the chip (what
-  // eoq_scores_places found for the kernel that is launched), the tail's among them: a second, partly filled round of
-  // workgroups costs a set-up and a run.  Whole blocks would be too coarse a measure: 12 x 204 steps on 512 places at 4 bits
-  // 28 us with runs of two blocks (8 steps), 24 with 6; 16 x 400 on 768 at 3 bits 32 with 10, 29 with 9.  Where that would
-  // leave fewer than six steps to a run, the set-ups of the workgroups of a unit, one behind the other, take longer than
-  // their steps (2 bits, 2048 steps: 4 workgroups to a unit of 2 steps each 14.2 us, 2 of 4 10.8, 1 of 8 10.2): then fewer to a
-  // unit, down to one.
   const int group = n_q_heads / n_kv_heads;
-  const int64_t places = L.score_places[qjl ? 1 : 0][group <= 4 ? 0 : 1];
-  const int64_t spb = L.n / QUAD, steps = blocks_per_head * spb, most = SC_RUN_MAX * spb;
-  const int64_t tails = sg_total * tail_groups;
-  auto run_for = [&](int64_t grid) {   // the shortest run with which runs and tail have no more workgroups than that
-    const int64_t per_head = (grid - (tails < grid / 2 ? tails : grid / 2)) / sg_total;
-    const int64_t r = per_head < 1 ? most : (steps + per_head - 1) / per_head;
-    return r < 1 ? 1 : (r < most ? r : most);            // no block at all: the tail's workgroups only
-  };
-  int64_t run = run_for(places);
-  if (run < SHORT_RUN) {
-    // fewer workgroups, whole numbers of them to a unit
-    int64_t w = places / 256;
-    while (w > 1 && run_for(256 * w) < SHORT_RUN) --w;
-    run = run_for(256 * (w > 1 ? w : 1));
-  }
-  // a run that begins inside a block touches one block more
-  if (run % spb != 0 && run > most - spb + 1) run = most;
+  const int64_t spb = L.n / QUAD, steps = blocks_per_head * spb;
+  const int64_t run = eoq_scores_run(L.score_places[qjl ? 1 : 0][group <= 4 ? 0 : 1], L.units, sg_total, steps, spb, sg_total * tail_groups);
   const int64_t runs = (steps + run - 1) / run;
   if (sg_total > 65535 || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(runs + tail_groups), (unsigned)sg_total), block(THREADS);
@@ -653,6 +630,33 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
 }
 
 }  // namespace
+
+// Steps of 128 tokens (a tile for each of the four waves) that a workgroup takes, for `heads` (sequence, KV head) pairs of `steps`
+// steps each in blocks of `steps_per_block`, beside `tails` workgroups of the tail, on a device of `units` compute units that
+// holds `places` workgroups of the kernel.  The set-up is paid once per workgroup, so runs are as long as they can be, up to 16
+// blocks, while the grid still has a workgroup for each place on the chip, the tail's among them: a second, partly filled
+// round of workgroups costs a set-up and a run.  Whole blocks would be too coarse a measure: 12 x 204 steps on 512 places at 4
+// bits 28 us with runs of two blocks (8 steps), 24 with 6; 16 x 400 on 768 at 3 bits 32 with 10, 29 with 9.  Where that would
+// leave fewer than six steps to a run, the set-ups of the workgroups of a unit, one behind the other, take longer than
+// their steps (2 bits, 2048 steps: 4 workgroups to a unit of 2 steps each 14.2 us, 2 of 4 10.8, 1 of 8 10.2): then fewer to a
+// unit, down to one.
+extern "C" int64_t eoq_scores_run(int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block, int64_t tails) {
+  const int64_t most = SC_RUN_MAX * steps_per_block;
+  auto run_for = [&](int64_t grid) {   // the shortest run with which runs and tail have no more workgroups than that
+    const int64_t per_head = (grid - (tails < grid / 2 ? tails : grid / 2)) / heads;
+    const int64_t r = per_head < 1 ? most : (steps + per_head - 1) / per_head;
+    return r < 1 ? 1 : (r < most ? r : most);            // no block at all: the tail's workgroups only
+  };
+  int64_t run = run_for(places);
+  if (run < SHORT_RUN) {
+    // fewer workgroups, whole numbers of them to a unit
+    int64_t w = places / units;
+    while (w > 1 && run_for(units * w) < SHORT_RUN) --w;
+    run = run_for(units * (w > 1 ? w : 1));
+  }
+  // a run that begins inside a block touches one block more
+  return (run % steps_per_block != 0 && run > most - steps_per_block + 1) ? most : run;
+}
 
 // Workgroups of the kernel for `bits` that the current device holds at a time, by the compiled kernel's own registers and LDS
 // (a table of numbers beside the kernels was wrong at 4 bits with the correction, one per unit where two fit: 2048 blocks of

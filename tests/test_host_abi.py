@@ -111,3 +111,23 @@ def test_projection_table_matches_the_oracle_stream():
     want = oracle.gaussian_projection(128, 78).astype(np.float16).astype(np.float32)
     assert got.shape == (128, 128) and np.array_equal(got, got.astype(np.float16).astype(np.float32))
     assert np.count_nonzero(got != want) <= 2     # a libm difference in the last bit can only show at a rounding boundary
+
+
+def _scores_run(lib, places, units, heads, steps, steps_per_block, tails=0):
+    lib.eoq_scores_run.restype = C.c_int64
+    return lib.eoq_scores_run(*(C.c_int64(v) for v in (places, units, heads, steps, steps_per_block, tails)))
+
+
+@pytest.mark.parametrize("per_unit", [1, 2, 3, 4])
+def test_scores_runs_follow_the_units_of_the_device(lib, per_unit):
+    """The runs of the scores kernel depend on the work per compute unit alone: an eighth of the heads on an eighth of the
+    device is cut alike.  And no run touches more blocks than a workgroup has room for."""
+    rng = np.random.default_rng(7)
+    for _ in range(400):
+        heads, steps_per_block = int(rng.integers(1, 40)), int(2 ** rng.integers(0, 4))
+        steps, tails = int(np.exp(rng.uniform(0, 9))) * steps_per_block, int(rng.integers(0, 3)) * heads
+        run = _scores_run(lib, 32 * per_unit, 32, heads, steps, steps_per_block, tails)
+        assert run == _scores_run(lib, 256 * per_unit, 256, 8 * heads, steps, steps_per_block, 8 * tails), (heads, steps, tails)
+        # whole blocks begin where a block does, other runs anywhere
+        blocks = run // steps_per_block if run % steps_per_block == 0 else (steps_per_block + run - 2) // steps_per_block + 1
+        assert 1 <= run and blocks <= 16, (heads, steps, tails, run)
