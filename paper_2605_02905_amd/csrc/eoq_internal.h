@@ -101,7 +101,7 @@ hipError_t eoq_launch_decode(const EoqLaunch& L, eoq_packed in, int64_t B, void*
 // workgroups of the scores kernel that the current device holds at a time; 0 if it cannot be asked
 extern "C" int eoq_scores_places(int bits, int corrected, int group);
 // steps of 128 tokens that a workgroup of the scores kernel takes (the rule stands beside its definition)
-extern "C" int64_t eoq_scores_run(int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block, int64_t tails);
+extern "C" int64_t eoq_scores_run(int bits, int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block, int64_t tails);
 // block_capacity / score_stride <= 0: the dense case (blocks_per_head slots per head, rows of blocks_per_head * n);
 // tail_len > 0 adds the scores of the binary16 tail behind the blocks' scores
 hipError_t eoq_launch_scores(const EoqLaunch& L, eoq_packed keys, int64_t n_seq, int n_kv_heads,

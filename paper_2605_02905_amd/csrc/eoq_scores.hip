@@ -156,7 +156,6 @@ struct TileFetch {
 // kernel, 64 tokens each: a kernel of their own cost a launch, and with one workgroup per head 32 us at 12 heads and 389
 // tokens.
 constexpr int TAIL_TOK = 64;
-constexpr int SHORT_RUN = 6;   // see eoq_scores_run
 constexpr int QUAD = 128;   // tokens of one tile of each of the four waves
 __device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, int t0, int tail_len,
                                             const uint16_t* __restrict__ q, int group, float* __restrict__ row, size_t T, float* qs,
@@ -592,7 +591,7 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   const int64_t tail_groups = (tail_len + TAIL_TOK - 1) / TAIL_TOK;
   const int group = n_q_heads / n_kv_heads;
   const int64_t spb = L.n / QUAD, steps = blocks_per_head * spb;
-  const int64_t run = eoq_scores_run(L.score_places[qjl ? 1 : 0][group <= 4 ? 0 : 1], L.units, sg_total, steps, spb, sg_total * tail_groups);
+  const int64_t run = eoq_scores_run(L.bits, L.score_places[qjl ? 1 : 0][group <= 4 ? 0 : 1], L.units, sg_total, steps, spb, sg_total * tail_groups);
   const int64_t runs = (steps + run - 1) / run;
   if (sg_total > 65535 || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(runs + tail_groups), (unsigned)sg_total), block(THREADS);
@@ -633,29 +632,33 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
 
 // Steps of 128 tokens (a tile for each of the four waves) that a workgroup takes, for `heads` (sequence, KV head) pairs of `steps`
 // steps each in blocks of `steps_per_block`, beside `tails` workgroups of the tail, on a device of `units` compute units that
-// holds `places` workgroups of the kernel.  The set-up is paid once per workgroup, so runs are as long as they can be, up to 16
-// blocks, while the grid still has a workgroup for each place on the chip, the tail's among them: a second, partly filled
-// round of workgroups costs a set-up and a run.  Whole blocks would be too coarse a measure: 12 x 204 steps on 512 places at 4
-// bits 28 us with runs of two blocks (8 steps), 24 with 6; 16 x 400 on 768 at 3 bits 32 with 10, 29 with 9.  Where that would
-// leave fewer than six steps to a run, the set-ups of the workgroups of a unit, one behind the other, take longer than
-// their steps (2 bits, 2048 steps: 4 workgroups to a unit of 2 steps each 14.2 us, 2 of 4 10.8, 1 of 8 10.2): then fewer to a
-// unit, down to one.
-extern "C" int64_t eoq_scores_run(int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block, int64_t tails) {
-  const int64_t most = SC_RUN_MAX * steps_per_block;
-  auto run_for = [&](int64_t grid) {   // the shortest run with which runs and tail have no more workgroups than that
-    const int64_t per_head = (grid - (tails < grid / 2 ? tails : grid / 2)) / heads;
-    const int64_t r = per_head < 1 ? most : (steps + per_head - 1) / per_head;
-    return r < 1 ? 1 : (r < most ? r : most);            // no block at all: the tail's workgroups only
-  };
-  int64_t run = run_for(places);
-  if (run < SHORT_RUN) {
-    // fewer workgroups, whole numbers of them to a unit
-    int64_t w = places / units;
-    while (w > 1 && run_for(units * w) < SHORT_RUN) --w;
-    run = run_for(units * (w > 1 ? w : 1));
+// holds `places` workgroups of the kernel.  A second, partly filled round of workgroups costs a set-up and a run, so the grid, the
+// tail's workgroups among it, has no more than w workgroups for each unit, w up to what a unit holds; the unit that has w of
+// them decides.  Calls of one head with exactly w workgroups of `run` steps to a unit take, within 5 %,
+//   (run (w + 2.2) + s w) e + 4 us,  e = 0.13, 0.19, 0.35, 0.51 us and s = 15, 11, 6, 6 at 1 .. 4 bits (with the correction alike):
+// the waves of a unit work their steps off side by side, their set-ups pass one behind the other.  The w with the least of
+// it, in fifths, with s = 12 up to 2 bits and 6 above.  Against as many workgroups as there are places wherever that leaves
+// six steps to a run, else as few as it takes for six (us before and now): 24 heads x 64 blocks of 512, 2 bits 20.0, 18.0 (3
+// of 8 steps to a unit, not 4 of 7); 8 x 64 of 1024, 1 bit 13.4, 11.9 (2 of 8, not 3 of 6); 8 x 64 of 512, 3 bits 16.6, 15.1
+// (2 of 4, not 1 of 8).  Whole blocks are too coarse a measure: 12 x 204 steps on 512 places at 4 bits 28 us with runs of two
+// blocks (8 steps), 24 with 6.
+extern "C" int64_t eoq_scores_run(int bits, int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block,
+                                  int64_t tails) {
+  const int64_t most = SC_RUN_MAX * steps_per_block, setup = bits <= 2 ? 12 : 6;
+  int64_t run = most, least = INT64_MAX;
+  for (int64_t w = places / units; w >= 1; --w) {
+    const int64_t grid = w * units, per_head = (grid - (tails < grid / 2 ? tails : grid / 2)) / heads;
+    int64_t r = per_head < 1 ? most + 1 : (steps + per_head - 1) / per_head;   // the shortest run that does not exceed the grid
+    if (r > most) break;                                                       // more than one round, and so are fewer workgroups
+    r = r < 1 ? 1 : r;                                                         // no block at all: the tail's workgroups only
+    if (r % steps_per_block != 0 && r > most - steps_per_block + 1) r = most;  // begun inside a block it touches one block more
+    const int64_t cost = r * (5 * w + 11) + 5 * setup * w;
+    if (cost < least) {
+      least = cost;
+      run = r;
+    }
   }
-  // a run that begins inside a block touches one block more
-  return (run % steps_per_block != 0 && run > most - steps_per_block + 1) ? most : run;
+  return run;
 }
 
 // Workgroups of the kernel for `bits` that the current device holds at a time, by the compiled kernel's own registers and LDS

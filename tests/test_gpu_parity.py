@@ -3,6 +3,7 @@
 Bars (from the benchmark definition): estimated ranks and codebooks bit-exact; shrunk singular values within
 1e-3 relative; relative Frobenius reconstruction errors of the two paths agree within 1e-3; code indices may
 differ only at decision boundaries, at most 0.1 % of entries."""
+import ctypes as C
 import math
 
 import numpy as np
@@ -1275,8 +1276,11 @@ def test_scores_of_runs_that_begin_inside_a_block(bits, group, n, blocks, correc
         got = ctx.eoq_scores(rec, q, 1)
         want = ctx.eoq_scores(rec, each, blocks)
     torch.cuda.synchronize()
-    places = eoq.lib().eoq_scores_places(bits, int(corrected), group)
-    assert -(-blocks * (n // 128) // places) >= 6 and -(-blocks * (n // 128) // places) % (n // 128) != 0   # such runs they are
+    lib, units, steps = eoq.lib(), torch.cuda.get_device_properties(0).multi_processor_count, n // 128
+    lib.eoq_scores_run.restype = C.c_int64
+    run = lib.eoq_scores_run(C.c_int(bits), *(C.c_int64(v) for v in (lib.eoq_scores_places(bits, int(corrected), group), units, 1,
+                                                                     blocks * steps, steps, 0)))
+    assert run >= 6 and run % steps != 0   # such runs they are
     assert torch.equal(got.view(group, blocks, n), want.view(blocks, group, n).transpose(0, 1))
 
 

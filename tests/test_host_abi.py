@@ -113,21 +113,40 @@ def test_projection_table_matches_the_oracle_stream():
     assert np.count_nonzero(got != want) <= 2     # a libm difference in the last bit can only show at a rounding boundary
 
 
-def _scores_run(lib, places, units, heads, steps, steps_per_block, tails=0):
+def _scores_run(lib, bits, places, units, heads, steps, steps_per_block, tails=0):
     lib.eoq_scores_run.restype = C.c_int64
-    return lib.eoq_scores_run(*(C.c_int64(v) for v in (places, units, heads, steps, steps_per_block, tails)))
+    return lib.eoq_scores_run(C.c_int(bits), *(C.c_int64(v) for v in (places, units, heads, steps, steps_per_block, tails)))
 
 
 @pytest.mark.parametrize("per_unit", [1, 2, 3, 4])
 def test_scores_runs_follow_the_units_of_the_device(lib, per_unit):
     """The runs of the scores kernel depend on the work per compute unit alone: an eighth of the heads on an eighth of the
-    device is cut alike.  And no run touches more blocks than a workgroup has room for."""
+    device is cut alike.  They cover every step once, and none touches more blocks than a workgroup has room for."""
     rng = np.random.default_rng(7)
+    near = 0   # runs that would touch one block too many if they began inside a block
     for _ in range(400):
-        heads, steps_per_block = int(rng.integers(1, 40)), int(2 ** rng.integers(0, 4))
-        steps, tails = int(np.exp(rng.uniform(0, 9))) * steps_per_block, int(rng.integers(0, 3)) * heads
-        run = _scores_run(lib, 32 * per_unit, 32, heads, steps, steps_per_block, tails)
-        assert run == _scores_run(lib, 256 * per_unit, 256, 8 * heads, steps, steps_per_block, 8 * tails), (heads, steps, tails)
-        # whole blocks begin where a block does, other runs anywhere
-        blocks = run // steps_per_block if run % steps_per_block == 0 else (steps_per_block + run - 2) // steps_per_block + 1
-        assert 1 <= run and blocks <= 16, (heads, steps, tails, run)
+        heads, steps_per_block, bits = int(rng.integers(1, 40)), int(2 ** rng.integers(0, 4)), int(rng.integers(1, 5))
+        blocks, tails = int(np.exp(rng.uniform(0, 9))), int(rng.integers(0, 3)) * heads
+        if rng.random() < 0.3:
+            blocks = int(16 * 32 * per_unit / heads * rng.uniform(0.8, 1.0)) + 1
+        steps = blocks * steps_per_block
+        run = _scores_run(lib, bits, 32 * per_unit, 32, heads, steps, steps_per_block, tails)
+        assert run == _scores_run(lib, bits, 256 * per_unit, 256, 8 * heads, steps, steps_per_block, 8 * tails), (heads, steps, tails)
+        assert run >= 1
+        first = np.arange(0, steps, run)
+        last = np.minimum(first + run, steps) - 1
+        assert np.all(first[1:] == last[:-1] + 1) and last[-1] == steps - 1
+        assert np.max(last // steps_per_block - first // steps_per_block) < 16, (heads, steps, tails, run)
+        least = -(-steps * heads // (32 * per_unit))
+        near += 16 * steps_per_block >= least > 15 * steps_per_block + 1 and least % steps_per_block != 0
+    assert near > 0
+
+
+@pytest.mark.parametrize("bits,per_unit,heads,steps,steps_per_block,tails,run", [
+    (2, 4, 24, 256, 4, 0, 8), (1, 4, 8, 512, 8, 0, 8), (3, 3, 8, 256, 4, 0, 4), (4, 2, 8, 256, 4, 0, 4), (3, 3, 1, 4000, 4, 0, 8),
+    (2, 4, 8, 256, 4, 0, 8), (4, 2, 12, 204, 4, 84, 6), (3, 3, 16, 400, 4, 0, 9), (2, 4, 8, 23, 1, 8, 1),
+    (2, 4, 128, 512, 4, 0, 64), (2, 4, 4096, 4, 4, 0, 64), (2, 4, 8, 0, 4, 56, 1)])
+def test_scores_runs_that_measured_fastest(lib, bits, per_unit, heads, steps, steps_per_block, tails, run):
+    """On 256 units: the fullest grid is not the fastest where its last workgroups of a unit make the run of the others longer
+    than fewer workgroups would need, nor where set-ups are most of a run; and the ends of the range."""
+    assert _scores_run(lib, bits, 256 * per_unit, 256, heads, steps, steps_per_block, tails) == run
