@@ -81,6 +81,7 @@ struct AttendShape {
   static constexpr int RH = HALF ? 8 : GH;                   // heads of the codebook term
   static constexpr int JT = HALF ? 2 : 4;                    // coordinate tiles
   static_assert(!HALF || (BYTES && GH == 4), "byte terms");
+  static_assert(!HALF || RH == 2 * GH, "the halves of eight heads are as many sums as four heads");
   static constexpr int SETS_OF_BYTES = BYTES || SPLIT ? 1 : TERMS;   // how often the weights are cut into bytes
   // weight bytes: [row][64 tokens] and, where operand rows are left out, a row of zeros
   static constexpr int DIG_BYTES = BYTES || SPLIT ? (HALF ? 2 : 1) * 4 * 4 * PAIR + PAIR : TERMS * 32 * PAIR;
@@ -331,46 +332,54 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     // New units for the heads whose weights (sums of magnitudes tr, tw over four tokens each, with rho / without) do not
     // fit the ones they have.  The low-rank sums so far are brought to the new scale (a power of two).
     auto choose_units = [&](const float (&mr)[WSETS], const float (&mw)[SETS]) __attribute__((always_inline)) {
-      auto largest = [&](float t) __attribute__((always_inline)) {   // over the sixteen lanes of a head
-        EOQ_SFOR(x, 4,
-          constexpr int ctrl = x == 0 ? 0xB1 : (x == 1 ? 0x4E : (x == 2 ? 0x141 : 0x140));
+      float tr[WSETS];   // the largest over the sixteen lanes of a head, and of the low-rank term's
+      float tw[SETS];
+      EOQ_SFOR(s, WSETS, tr[s] = mr[s];);
+      EOQ_SFOR(s, SETS, tw[s] = mw[s];);
+      EOQ_SFOR(x, 4,
+        constexpr int ctrl = x == 0 ? 0xB1 : (x == 1 ? 0x4E : (x == 2 ? 0x141 : 0x140));
+        auto larger = [&](float& t) __attribute__((always_inline)) {
           const float a = dpp_mov<ctrl>(t);
           t = (a > t || !(a == a)) ? a : t;                // a NaN stays
-        );
-        return t;
-      };
+        };
+        EOQ_SFOR(s, WSETS, larger(tr[s]););
+        EOQ_SFOR(s, SETS, larger(tw[s]););
+      );
+      bool bad[WSETS];       // Inf or NaN among the weights: so is the head's output
+      bool bad_lr[SETS];
+      EOQ_SFOR(s, WSETS, bad[s] = !(tr[s] < INFINITY););
+      EOQ_SFOR(s, SETS,
+        bad_lr[s] = !(tw[s] < INFINITY);
+        if constexpr (!HALF) bad[s] = bad_lr[s] = bad[s] || bad_lr[s];   // the same head
+      );
       EOQ_SFOR(s, WSETS,
-        const float tr = largest(mr[s]);
-        const bool bad = !(tr < INFINITY);
-        const int er = min(max((int)(__float_as_uint(tr) >> 23) - 127, -90), 126);
-        if (bad || !(tr * inv[s] < 1.85f * 0x1.0p30f)) {
-          inv[s] = bad ? 0.0f : __uint_as_float((uint32_t)(28 - er + 127) << 23);     // integers below 2^29
-          if (l16 == 0) unit_s[4 * s + kg] = bad ? 0.0f : __uint_as_float((uint32_t)(er - 28 + 127) << 23);
-        }
-        if (bad) {   // Inf or NaN among the weights: so is the head's output
-          EOQ_SFOR(i, 8, rot[(4 * s + kg) * D + 16 * i + l16] = NAN;);
+        const int er = min(max((int)(__float_as_uint(tr[s]) >> 23) - 127, -90), 126);
+        if (bad[s] || !(tr[s] * inv[s] < 1.85f * 0x1.0p30f)) {
+          inv[s] = bad[s] ? 0.0f : __uint_as_float((uint32_t)(28 - er + 127) << 23);     // integers below 2^29
+          if (l16 == 0) unit_s[4 * s + kg] = bad[s] ? 0.0f : __uint_as_float((uint32_t)(er - 28 + 127) << 23);
         }
       );
       EOQ_SFOR(s, SETS,
-        const float tw = largest(mw[s]);
-        const bool bad = !(tw < INFINITY);
-        const int ew = min(max((int)(__float_as_uint(tw) >> 23) - 127, -90), 126);
+        const int ew = min(max((int)(__float_as_uint(tw[s]) >> 23) - 127, -90), 126);
         float turn = 1.0f;
-        if (bad || !(tw * sw[s] < 0x1.0p15f)) {
-          const float fresh = bad ? 0.0f : __uint_as_float((uint32_t)(12 - ew + 127) << 23);      // parts below 2^13
+        if (bad_lr[s] || !(tw[s] * sw[s] < 0x1.0p15f)) {
+          const float fresh = bad_lr[s] ? 0.0f : __uint_as_float((uint32_t)(12 - ew + 127) << 23);      // parts below 2^13
           turn = any ? fresh * winv_s[4 * s + kg] : 1.0f;
           sw[s] = fresh;
           __builtin_amdgcn_wave_barrier();
-          if (l16 == 0) winv_s[4 * s + kg] = bad ? 0.0f : __uint_as_float((uint32_t)(ew - 12 + 127) << 23);
+          if (l16 == 0) winv_s[4 * s + kg] = bad_lr[s] ? 0.0f : __uint_as_float((uint32_t)(ew - 12 + 127) << 23);
         }
         EOQ_SFOR(v, 4,
           const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(turn), 16 * v));
           EOQ_SFOR(k, 2, lr[s][k][v] *= f;);
         );
-        if (bad) {   // the weights alone, without rho: theirs is the low-rank term, but the output is one
+        if (bad_lr[s]) {
           EOQ_SFOR(i, 8, rot[(h0 - r0 + 4 * s + kg) * D + 16 * i + l16] = NAN;);
         }
       );
+      if constexpr (HALF) {
+        EOQ_SFOR(s, WSETS, if (bad[s]) { EOQ_SFOR(i, 8, rot[(4 * s + kg) * D + 16 * i + l16] = NAN;); });
+      }
       __builtin_amdgcn_wave_barrier();
     };
     // Two register sets in turn.  A pair's registers are free as soon as its weights are staged and its code nibbles
@@ -641,16 +650,17 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
   EOQ_SFOR(h, GH, *reinterpret_cast<float2*>(lin_m + h * D + c2) = make_float2(lin[h][0], lin[h][1]););
   __syncthreads();
   float* dst = partial + (sg * gridDim.x + blockIdx.x) * (size_t)(2 * MAXG * D);
+  // HALF: all heads of the codebook term, of their coordinates the 32 z .. + 31 of either 64
   for (int e = tid; e < GH * D; e += THREADS) {
-    float ls[4];
-    EOQ_SFOR(w, 4, ls[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES)[e];);
-    dst[(MAXG + h0) * D + e] = ((ls[0] + ls[1]) + ls[2]) + ls[3];
-  }
-  for (int i = tid; i < (HALF ? RH * D / 2 : RH * D); i += THREADS) {
-    const int e = HALF ? ((i >> 5) << 6) + 32 * z + (i & 31) : i;   // HALF: coordinates 32 z .. + 31 of either 64
+    const int er = HALF ? ((e >> 5) << 6) + 32 * z + (e & 31) : e;
     float rs[4];
-    EOQ_SFOR(w, 4, rs[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES + S::BASE_BYTES + S::BS_BYTES)[e];);
-    dst[r0 * D + e] = ((rs[0] + rs[1]) + rs[2]) + rs[3];
+    float ls[4];
+    EOQ_SFOR(w, 4,
+      ls[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES)[e];
+      rs[w] = reinterpret_cast<const float*>(mem + w * S::WAVE_BYTES + S::BASE_BYTES + S::BS_BYTES)[er];
+    );
+    dst[r0 * D + er] = ((rs[0] + rs[1]) + rs[2]) + rs[3];
+    dst[(MAXG + h0) * D + e] = ((ls[0] + ls[1]) + ls[2]) + ls[3];
   }
 }
 

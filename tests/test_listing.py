@@ -52,3 +52,16 @@ def test_state_of_the_scores_loop_stays_in_scalar_registers(tmp_path):
         loop = lines[first:last]
         assert sum(l.startswith("buffer_store_dword ") for l in loop) == 2 * heads   # two tiles a pass
         assert not [l for l in loop if l.startswith("v_readfirstlane")]
+
+
+@pytest.mark.skipif(not os.path.exists(g.HIPCC), reason="no compiler")
+def test_sums_of_attention_output_leave_in_one_loop(tmp_path):
+    """Behind the last barrier the four waves' sums of the codebook and of the low-rank term are added and stored side by side.
+    One behind the other they were a pass over LDS and memory more, which a call of a few tokens waits for."""
+    for shape in ("ILi1ELi4ELb0E", "ILi2ELi8ELb0E", "ILi4ELi4ELb0E", "ILi4ELi4ELb1E"):   # <bits, heads, coordinates shared>
+        lines = _kernel_lines("eoq_attend.hip", "eoq_attend_partial_kernel" + shape, tmp_path)
+        last = max(i for i, l in enumerate(lines) if l.startswith("s_barrier"))
+        label = {l[:-1]: i for i, l in enumerate(lines) if l.endswith(":")}
+        loops = [(label[l.split()[1]], i) for i, l in enumerate(lines) if re.match(r"s_c?branch", l) and last < label.get(l.split()[1], -1) < i]
+        assert len(loops) == 1
+        assert sum(l.startswith("global_store") for l in lines[loops[0][0]:loops[0][1]]) == 2
