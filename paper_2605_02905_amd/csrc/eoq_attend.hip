@@ -876,6 +876,15 @@ int64_t eoq_attend_runs(int64_t sg_total, int64_t blocks_per_head, int n, int* p
   return (pairs + 4 * ppw - 1) / (4 * ppw);
 }
 
+// At 4 bits with more than four heads the two sets of workgroups share the coordinates of the codebook term (AttendShape) where a
+// wave has more than one pair of tiles.  What is saved is work per pair; finding units and cutting weights for all heads
+// instead of four comes first and takes 2 us: seven heads, in us with coordinates / heads shared, 12.0 / 10.5 at one pair to a
+// wave (3 KV heads, 1 block of 512), 20.3 / 20.5 at two (128, 5 of 128), 24.6 / 25.0 at three (8, 64 of 384), 27.3 / 30.0 at
+// four (24, 23 of 384), 57.7 / 72.8 at twelve (8, 200 of 512).
+extern "C" int eoq_attend_shares_coordinates(int bits, int group, int pairs_per_wave) {
+  return bits == 4 && group > 4 && pairs_per_wave > 1;
+}
+
 int64_t eoq_attend_most_runs(int64_t sg_total, int64_t blocks_per_head, int n) {
   // The runs of a head are shorter the fuller the store is, so their number steps up AND down with the fill.  With one pair
   // per wave there are ceil(pairs / 4) of them; while a wave has up to 96 pairs, sg pairs <= 2048 ppw, hence at most
@@ -904,7 +913,7 @@ hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_se
   int ppw = 1;
   // up to 2 bits a wave takes all (up to eight) heads of the group; with byte terms the 32 operand rows hold four heads,
   // and a group of more is two sets of workgroups (the runs, at most as many as the workspace was sized for, are then
-  // twice as long), at 4 bits with the coordinates divided between them: see AttendShape
+  // twice as long), at 4 bits with the coordinates divided between them where a wave has several pairs
   const unsigned z = (L.bits >= 3 && group > 4) ? 2u : 1u;
   const int64_t runs = eoq_attend_runs(sg_total * z, blocks_per_head, L.n, &ppw);
   if (sg_total > 65535 || runs > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -917,7 +926,7 @@ hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_se
     case 1: if (group <= 4) EOQ_ATTEND(1, 4, 1); else EOQ_ATTEND(1, 8, 1); break;
     case 2: if (group <= 4) EOQ_ATTEND(2, 4, 1); else EOQ_ATTEND(2, 8, 1); break;
     case 3: EOQ_ATTEND(3, 4, z); break;
-    default: if (group <= 4) EOQ_ATTEND(4, 4, 1); else EOQ_ATTEND(4, 4, 2, true); break;
+    default: if (eoq_attend_shares_coordinates(L.bits, group, ppw)) EOQ_ATTEND(4, 4, 2, true); else EOQ_ATTEND(4, 4, z); break;
   }
 #undef EOQ_ATTEND
   hipError_t e = hipGetLastError();

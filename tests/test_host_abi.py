@@ -150,3 +150,12 @@ def test_scores_runs_that_measured_fastest(lib, bits, per_unit, heads, steps, st
     """On 256 units: the fullest grid is not the fastest where its last workgroups of a unit make the run of the others longer
     than fewer workgroups would need, nor where set-ups are most of a run; and the ends of the range."""
     assert _scores_run(lib, bits, 256 * per_unit, 256, heads, steps, steps_per_block, tails) == run
+
+
+def test_form_of_the_attention_output_at_4_bits(lib):
+    """Sharing coordinates saves work per pair of tiles and costs set-up: not where a wave has one pair."""
+    for group in range(1, 9):
+        assert not lib.eoq_attend_shares_coordinates(4, group, 1)
+        for pairs in (2, 3, 96):
+            assert bool(lib.eoq_attend_shares_coordinates(4, group, pairs)) == (group > 4)
+            assert not lib.eoq_attend_shares_coordinates(3, group, pairs)
