@@ -675,13 +675,40 @@ def test_q4_shapes_rank0_and_clamp(n, B, r_max, rank_hi):
 
 @pytest.mark.parametrize("n,B,r_max,rank_hi", [(256, 6, 8, 8), (384, 6, 32, 12), (640, 4, 8, 8), (768, 4, 32, 12), (1152, 4, 16, 12), (2048, 3, 16, 12), (4096, 2, 8, 8)])
 def test_q4_entries_beyond_those_kept_in_registers(n, B, r_max, rank_hi):
-    """The one, three and seven waves of the codebook fit of U, with token counts that they share unevenly and more entries
-    to a lane than its registers take."""
+    """The three and seven waves of the codebook fit of U, with token counts that they share unevenly and more entries to a
+    lane than its registers take."""
     spec = synth.BlockSpec("q4waves", n=n, n_tensors=1, blocks_per_tensor=B, rank_lo=1, rank_hi=rank_hi)
     blocks, _ = synth.make_blocks(spec, seed=47)
     blocks = torch.cat([blocks, blocks[:1]])
     blocks[-1] = synth.make_blocks(synth.BlockSpec("q4top", n=n, n_tensors=1, blocks_per_tensor=1, rank_lo=rank_hi, rank_hi=rank_hi), seed=53)[0][0]
     _q4_case(blocks, 2, n, r_max, f"q4-waves-n{n}")
+
+
+@pytest.mark.parametrize("n,B,r_max", [(128, 12, 32), (128, 12, 9), (256, 6, 32), (512, 4, 16), (1024, 4, 32)])
+def test_q4_more_than_eight_components(n, B, r_max):
+    """Blocks whose factors do not fit the small table: with one wave on each matrix (128 tokens) more entries to a lane than its
+    registers take, and a batch of so many that its workgroups walk several blocks each, among them blocks of eight
+    components and fewer, which they pass over."""
+    spec = synth.BlockSpec("q4ranks", n=n, n_tensors=1, blocks_per_tensor=B, rank_lo=7, rank_hi=11, channel_s=0.0,
+                           strengths=tuple(20.0 * 0.93**i for i in range(11)))
+    blocks, _ = synth.make_blocks(spec, seed=59)
+    ctx, rec, fq, _ = _q4_case(blocks, 2, n, r_max, f"q4-above8-n{n}-rmax{r_max}")
+    rank = rec.rank.cpu()
+    assert int((rank > 8).sum()) >= 2 and (n > 128 or int((rank <= 8).sum()) >= 2)
+    copies = 1100 // B if n == 128 else 3
+    many, mq, _ = ctx.eoq_compress_q4(blocks.to(DEV).repeat(copies, 1, 1))
+    torch.cuda.synchronize()
+    for name in ("rank", "phi", "lfac", "rfac", "codes", "norms"):
+        t = getattr(rec, name)
+        for b in range(B):
+            k = int(rank[b]) if name in ("phi", "lfac", "rfac") else None
+            got = getattr(many, name)[b::B]
+            assert torch.equal(got[:, :k] if k else got, (t[b, :k] if k else t[b]).expand_as(got[:, :k] if k else got)), (name, b)
+    for b in range(B):
+        for name in ("lcodes", "rcodes", "phi16"):
+            got = getattr(mq, name)[b::B, :int(rank[b])]
+            assert torch.equal(got, getattr(fq, name)[b, :int(rank[b])].expand_as(got)), (name, b)
+        assert torch.equal(mq.fbook[b::B], fq.fbook[b].expand_as(mq.fbook[b::B])), b
 
 
 @pytest.mark.parametrize("bits", [1, 4])
