@@ -192,7 +192,8 @@ __device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, i
 
 // One workgroup per (sequence, KV head, run of tokens); every wave works on 32-token tiles of its own (wave w takes the tiles
 // w, w + 4, ... of the run), the record bytes of the next tile on their way while this one is worked on.  A run is a number of
-// steps of 128 tokens, a tile for each wave, and may begin and end inside a block (eoq_scores_run).  NQ = query heads a lane finishes per token (2 for groups up to 4).
+// steps of 128 tokens, a tile for each wave, and may begin and end inside a block (eoq_scores_run).  NQ = query heads a lane
+// finishes per token (2 for groups up to 4).
 // QJL: the logits get the correction of Eq. (qjl), |r_x| sqrt(pi/2)/d <Phi q, sign(Phi r_x)>, from one more bit plane
 // (the signs) and the stored residual norm; Phi q goes through the same fixed-point form as Pi q.
 template <int BITS, bool QJL, int NQ>
@@ -633,15 +634,16 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
 // Steps of 128 tokens (a tile for each of the four waves) that a workgroup takes, for `heads` (sequence, KV head) pairs of `steps`
 // steps each in blocks of `steps_per_block`, beside `tails` workgroups of the tail, on a device of `units` compute units that
 // holds `places` workgroups of the kernel.  A second, partly filled round of workgroups costs a set-up and a run, so the grid, the
-// tail's workgroups among it, has no more than w workgroups for each unit, w up to what a unit holds; the unit that has w of
-// them decides.  Calls of one head with exactly w workgroups of `run` steps to a unit take, within 5 %,
-//   (run (w + 2.2) + s w) e + 4 us,  e = 0.13, 0.19, 0.35, 0.51 us and s = 15, 11, 6, 6 at 1 .. 4 bits (with the correction alike):
-// the waves of a unit work their steps off side by side, their set-ups pass one behind the other.  The w with the least of
-// it, in fifths, with s = 12 up to 2 bits and 6 above.  Against as many workgroups as there are places wherever that leaves
-// six steps to a run, else as few as it takes for six (us before and now): 24 heads x 64 blocks of 512, 2 bits 20.0, 18.0 (3
-// of 8 steps to a unit, not 4 of 7); 8 x 64 of 1024, 1 bit 13.4, 11.9 (2 of 8, not 3 of 6); 8 x 64 of 512, 3 bits 16.6, 15.1
-// (2 of 4, not 1 of 8).  Whole blocks are too coarse a measure: 12 x 204 steps on 512 places at 4 bits 28 us with runs of two
-// blocks (8 steps), 24 with 6.
+// tail's workgroups among it, has no more than w workgroups for each unit, w up to what a unit holds (more where the tail alone
+// takes over half of them, of which half is counted, and where heads of up to 16 blocks each are more than that); the unit that
+// has w of them decides.  Calls of one head with exactly w workgroups of `run` steps to a unit take, within 8 % from four steps on,
+//   (run (w + 2.2) + s w) e + 4 us,  e = 0.13, 0.19, 0.35, 0.51 us and s = 15, 11, 6, 6 at 1 .. 4 bits
+// (with the correction e = 0.26, 0.60 and s = 12, 7 at 2 and 4): the waves of a unit work their steps off side by side, their
+// set-ups pass one behind the other.  The w with the least of it, in fifths, with s = 12 up to 2 bits and 6 above.  Against as
+// many workgroups as there are places wherever that leaves six steps to a run, else as few as it takes for six (us before and
+// now): 24 heads x 64 blocks of 512, 2 bits 20.0, 18.5 (3 of 8 steps to a unit, not 4 of 7); 8 x 64 of 1024, 1 bit 13.4, 11.8 (2
+// of 8, not 3 of 6); 8 x 64 of 512, 3 bits 16.6, 15.6 (2 of 4, not 1 of 8).  Whole blocks are too coarse a measure: 12 x 204
+// steps on 512 places at 4 bits 28 us with runs of two blocks (8 steps), 24 with 6.
 extern "C" int64_t eoq_scores_run(int bits, int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block,
                                   int64_t tails) {
   const int64_t most = SC_RUN_MAX * steps_per_block, setup = bits <= 2 ? 12 : 6;
