@@ -203,8 +203,8 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
     const float* __restrict__ tab, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms,
     const int32_t* __restrict__ rank_in, const uint16_t* __restrict__ lfac, const uint16_t* __restrict__ rfac,
     const uint16_t* __restrict__ q, float* __restrict__ scores, const uint16_t* __restrict__ phih,
-    const uint8_t* __restrict__ qsigns, const uint16_t* __restrict__ qnorms, int runs, const uint16_t* __restrict__ tail,
-    int64_t tail_capacity, int tail_len) {
+    const uint8_t* __restrict__ qsigns, const uint16_t* __restrict__ qnorms, int run_heads, const uint16_t* __restrict__ tail,
+    int64_t tail_capacity, int tail_len, int heads) {
   constexpr int TYPES = 1 << (BITS - 1);
   constexpr int NMM = 4 * TYPES;   // matrix instructions per tile: 64 coordinates x TYPES bytes per lane, 16 at a time
   // One pool, used in turn: during the set-up the rotated query and the byte planes of coef[M] Pi q ([head][plane][k])
@@ -226,18 +226,22 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave: scalar
   const int l16 = lane & 15, g = lane >> 4;
   const int l32 = lane & 31, hf = lane >> 5;
-  const size_t sg = blockIdx.y;
-  const size_t sq = sg / n_kv_heads, kv = sg % n_kv_heads;
   const int n_q_heads = n_kv_heads * group;
-  const size_t q0 = (sq * n_q_heads + kv * group) * D;
   const size_t T = (size_t)score_stride;   // entries per score row (>= blocks_per_head * n)
   constexpr int ROWB = BITS * D / 8;
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
-  if ((int)blockIdx.x >= runs) {   // a workgroup of the tail
-    tail_scores(tail + sg * (size_t)tail_capacity * D, TAIL_TOK * ((int)blockIdx.x - runs), tail_len, q + q0, group,
-                scores + (sq * n_q_heads + kv * group) * T + (size_t)blocks_per_head * n, T, qrot, tid);
+  if ((int)blockIdx.y >= run_heads) {   // a workgroup of the tail, or none: see scores_grid
+    const uint32_t id = (blockIdx.y - (uint32_t)run_heads) * gridDim.x + blockIdx.x;
+    const uint32_t per_head = (uint32_t)(tail_len + TAIL_TOK - 1) / TAIL_TOK, head = id / per_head;
+    if (head >= (uint32_t)heads) return;
+    const size_t first = (size_t)(head / n_kv_heads) * n_q_heads + (head % n_kv_heads) * group;   // query head
+    tail_scores(tail + head * (size_t)tail_capacity * D, TAIL_TOK * (int)(id - head * per_head), tail_len, q + first * D, group,
+                scores + first * T + (size_t)blocks_per_head * n, T, qrot, tid);
     return;
   }
+  const size_t sg = blockIdx.y;
+  const size_t sq = sg / n_kv_heads, kv = sg % n_kv_heads;
+  const size_t q0 = (sq * n_q_heads + kv * group) * D;
 
   // the run: `run` steps of QUAD tokens from step number blockIdx.x * run of the head, which is token tok0 of block jb0; the
   // blocks it touches are numbers 0 .. nblk - 1 of the run (B n < 2^39: a step number fits 32 bits)
@@ -575,6 +579,30 @@ __global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scor
 #undef EOQ_SC_WORK
 }
 
+}  // namespace
+
+constexpr int64_t GRID_Y = 65535;
+struct ScoresGrid {
+  int64_t x, y, run_heads;   // workgroups (x, y): run x of head y below row run_heads, behind it the tail's in turn
+};
+// The launches for `runs` runs and `tail_groups` workgroups of the tail of each of `heads` heads: one, or two where the rows of a
+// grid do not suffice.  The runs come first: workgroups go to the eight XCDs in turn, and with each head's tail behind its
+// runs the runs of all heads met on one XCD in eight, four or two wherever runs and tail of a head were together a multiple of
+// eight and so on (128 heads, 23 blocks of 256 and 255 tokens, 4 bits: 2 runs and 4 tail workgroups a head 57 us, 4 and 4 65).
+extern "C" int eoq_scores_grids(int64_t heads, int64_t runs, int64_t tail_groups, ScoresGrid* out) {
+  const int64_t rows = runs > 0 ? (heads * tail_groups + runs - 1) / runs : 0;
+  if (runs > 0 && heads + rows <= GRID_Y) {
+    out[0] = {runs, heads + rows, heads};
+    return 1;
+  }
+  int k = 0;
+  if (runs > 0) out[k++] = {runs, heads, heads};
+  if (tail_groups > 0) out[k++] = {tail_groups, heads, 0};
+  return k;
+}
+
+namespace {
+
 template <int BITS>
 const void* scores_kernel(bool qjl, bool wide) {
   if (qjl) return wide ? (const void*)eoq_scores_i8_kernel<BITS, true, 4> : (const void*)eoq_scores_i8_kernel<BITS, true, 2>;
@@ -594,21 +622,21 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
   const int64_t spb = L.n / QUAD, steps = blocks_per_head * spb;
   const int64_t run = eoq_scores_run(L.bits, L.score_places[qjl ? 1 : 0][group <= 4 ? 0 : 1], L.units, sg_total, steps, spb, sg_total * tail_groups);
   const int64_t runs = (steps + run - 1) / run;
-  if (sg_total > 65535 || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(runs + tail_groups), (unsigned)sg_total), block(THREADS);
+  if (sg_total > GRID_Y || runs + tail_groups > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const dim3 block(THREADS);
   const uint16_t* q = static_cast<const uint16_t*>(q_fp16);
 #define EOQ_SCORES_ARGS                                                                                              \
-  grid, block, 0, L.stream, L.n, L.r_max, n_kv_heads, group, blocks_per_head, block_capacity, score_stride, (int)run, \
+  dim3((unsigned)G.x, (unsigned)G.y), block, 0, L.stream, L.n, L.r_max, n_kv_heads, group, blocks_per_head, block_capacity, score_stride, (int)run, \
       L.pih, L.tab, keys.codes, keys.norms, keys.rank, keys.lfac, keys.rfac, q, scores
 #define EOQ_SCORES(BITS, NQ)                                                                                         \
   do {                                                                                                               \
     if (qjl)                                                                                                         \
       hipLaunchKernelGGL((eoq_scores_i8_kernel<BITS, true, NQ>), EOQ_SCORES_ARGS, L.phih, qjl->signs, qjl->norms,  \
-                         (int)runs, (const uint16_t*)nullptr, (int64_t)0, 0);                                        \
+                         (int)G.run_heads, (const uint16_t*)nullptr, (int64_t)0, 0, (int)sg_total);                  \
     else                                                                                                             \
       hipLaunchKernelGGL((eoq_scores_i8_kernel<BITS, false, NQ>), EOQ_SCORES_ARGS, (const uint16_t*)nullptr,      \
-                         (const uint8_t*)nullptr, (const uint16_t*)nullptr, (int)runs,                              \
-                         static_cast<const uint16_t*>(tail_fp16), tail_capacity, tail_len);                          \
+                         (const uint8_t*)nullptr, (const uint16_t*)nullptr, (int)G.run_heads,                       \
+                         static_cast<const uint16_t*>(tail_fp16), tail_capacity, tail_len, (int)sg_total);           \
   } while (0)
 #define EOQ_SCORES_BITS(NQ)                 \
   switch (L.bits) {                         \
@@ -617,10 +645,15 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
     case 3: EOQ_SCORES(3, NQ); break;    \
     default: EOQ_SCORES(4, NQ); break;   \
   }
-  if (group <= 4) {
-    EOQ_SCORES_BITS(2)
-  } else {
-    EOQ_SCORES_BITS(4)
+  ScoresGrid grids[2];
+  const int launches = eoq_scores_grids(sg_total, runs, tail_groups, grids);
+  for (int i = 0; i < launches; ++i) {
+    const ScoresGrid& G = grids[i];
+    if (group <= 4) {
+      EOQ_SCORES_BITS(2)
+    } else {
+      EOQ_SCORES_BITS(4)
+    }
   }
 #undef EOQ_SCORES_BITS
 #undef EOQ_SCORES
@@ -633,9 +666,11 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
 
 // Steps of 128 tokens (a tile for each of the four waves) that a workgroup takes, for `heads` (sequence, KV head) pairs of `steps`
 // steps each in blocks of `steps_per_block`, beside `tails` workgroups of the tail, on a device of `units` compute units that
-// holds `places` workgroups of the kernel.  A second, partly filled round of workgroups costs a set-up and a run, so the grid, the
-// tail's workgroups among it, has no more than w workgroups for each unit, w up to what a unit holds (more where the tail alone
-// takes over half of them, of which half is counted, and where heads of up to 16 blocks each are more than that); the unit that
+// holds `places` workgroups of the kernel.  A second, partly filled round of workgroups costs a set-up and a run, so the grid has
+// no more than w workgroups for each unit, w up to what a unit holds (more where heads of up to 16 blocks each are more than
+// that); the tail's workgroups are among them, or, a layer of one to each unit at a time, beside them, where a layer costs what
+// a set-up does (8 heads x 23 blocks of 512 and 171 tokens, 24 workgroups of the tail, 2 bits: 7.5 us with 184 runs and 9.4 with
+// 248; 128 heads x 5 blocks of 1024 and 342 tokens, 768 of the tail, 1 bit: 17.8 with 512 runs and 27.6 with 256).  The unit that
 // has w of them decides.  Calls of one head with exactly w workgroups of `run` steps to a unit take, within 8 % from four steps on,
 //   (run (w + 2.2) + s w) e + 4 us,  e = 0.13, 0.19, 0.35, 0.51 us and s = 15, 11, 6, 6 at 1 .. 4 bits
 // (with the correction e = 0.26, 0.60 and s = 12, 7 at 2 and 4): the waves of a unit work their steps off side by side, their
@@ -647,17 +682,22 @@ hipError_t launch_scores_impl(const EoqLaunch& L, eoq_packed keys, const eoq_qjl
 extern "C" int64_t eoq_scores_run(int bits, int64_t places, int64_t units, int64_t heads, int64_t steps, int64_t steps_per_block,
                                   int64_t tails) {
   const int64_t most = SC_RUN_MAX * steps_per_block, setup = bits <= 2 ? 12 : 6;
+  const int64_t layers = (tails + units - 1) / units;   // of one tail workgroup to a unit
   int64_t run = most, least = INT64_MAX;
   for (int64_t w = places / units; w >= 1; --w) {
-    const int64_t grid = w * units, per_head = (grid - (tails < grid / 2 ? tails : grid / 2)) / heads;
-    int64_t r = per_head < 1 ? most + 1 : (steps + per_head - 1) / per_head;   // the shortest run that does not exceed the grid
-    if (r > most) break;                                                       // more than one round, and so are fewer workgroups
-    r = r < 1 ? 1 : r;                                                         // no block at all: the tail's workgroups only
-    if (r % steps_per_block != 0 && r > most - steps_per_block + 1) r = most;  // begun inside a block it touches one block more
-    const int64_t cost = r * (5 * w + 11) + 5 * setup * w;
-    if (cost < least) {
-      least = cost;
-      run = r;
+    for (int64_t beside = 0; beside <= layers && beside <= 4; ++beside) {
+      const int64_t among = (beside < 4 && tails > beside * units) ? tails - beside * units : 0;
+      const int64_t per_head = (w * units - among) / heads;
+      if (w * units - among < heads) continue;
+      int64_t r = (steps + per_head - 1) / per_head;                             // the shortest run that does not exceed the grid
+      if (r > most) continue;                                                    // more than one round
+      r = r < 1 ? 1 : r;                                                         // no block at all: the tail's workgroups only
+      if (r % steps_per_block != 0 && r > most - steps_per_block + 1) r = most;  // begun inside a block it touches one block more
+      const int64_t cost = r * (5 * w + 11) + 5 * setup * (w + beside);
+      if (cost < least) {
+        least = cost;
+        run = r;
+      }
     }
   }
   return run;

@@ -908,6 +908,36 @@ def test_scores_over_a_partly_filled_store_and_the_tail():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("n_seq,n_kv,n,filled,tail_len", [(3, 2, 512, 5, 171), (1, 1, 1024, 40, 1000), (16, 8, 256, 23, 255), (5000, 8, 128, 1, 70)])
+def test_scores_tail_workgroups_behind_the_runs(n_seq, n_kv, n, filled, tail_len):
+    """The tail's workgroups fill rows of the grid behind those of the runs: rows that are not full, more rows than heads, and
+    more heads than one grid has rows for both (two launches).  Blocks: the bits of the call without a tail.  Tail: sums of 128
+    products of binary16 numbers in float32, 128 roundings of 2^-24 of the sum of magnitudes at most."""
+    heads, group = n_seq * n_kv, 2
+    gen = torch.Generator(device=DEV).manual_seed(n + heads)
+    ctx = eoq.Context(n=n, bits=1, r_max=4)
+    rec = eoq.Packed.empty(heads * filled, n, 128, 1, 4, DEV)
+    rec.codes.random_(0, 256, generator=gen)
+    rec.norms.uniform_(0.5, 2.0, generator=gen)
+    rec.rank.random_(0, 4, generator=gen)
+    rec.lfac.normal_(0.0, 0.1, generator=gen)
+    rec.rfac.normal_(0.0, 0.1, generator=gen)
+    q = synth.make_queries(n_seq, n_kv * group, device=DEV)
+    tail = torch.randn(n_seq, n_kv, n, 128, generator=gen, device=DEV).half()
+    out = torch.full((n_seq, n_kv * group, filled * n + tail_len), float("nan"), device=DEV)
+    ctx.eoq_scores_stream(rec, q, n_kv, filled, filled, tail, tail_len, out)
+    blocks = ctx.eoq_scores(rec, q, n_kv)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:, :, :filled * n], blocks)
+    got = out[:, :, filled * n:].view(heads, group, tail_len)
+    qh, th = q.view(heads, group, 128), tail.view(heads, n, 128)
+    for a in range(0, heads, 2048):
+        for h in range(group):
+            terms = qh[a:a + 2048, h, None].double() * th[a:a + 2048, :tail_len].double()
+            bar = 128 * 2.0**-24 * terms.abs().sum(-1) / 128**0.5
+            assert bool(((got[a:a + 2048, h].double() - terms.sum(-1) / 128**0.5).abs() <= bar).all()), (a, h)
+
+
 def test_rank_fields_out_of_range_are_clamped_by_the_readers():
     """A record read back from storage may hold anything in its rank field.  eoq_decompress, eoq_scores and
     eoq_expand_factors bound it to 0 .. r_max before indexing the factor rows: the other blocks' results do not change

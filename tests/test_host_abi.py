@@ -145,7 +145,8 @@ def test_scores_runs_follow_the_units_of_the_device(lib, per_unit):
 @pytest.mark.parametrize("bits,per_unit,heads,steps,steps_per_block,tails,run", [
     (2, 4, 24, 256, 4, 0, 8), (1, 4, 8, 512, 8, 0, 8), (3, 3, 8, 256, 4, 0, 4), (4, 2, 8, 256, 4, 0, 4), (3, 3, 1, 4000, 4, 0, 8),
     (2, 4, 8, 256, 4, 0, 8), (4, 2, 12, 204, 4, 84, 6), (3, 3, 16, 400, 4, 0, 9), (2, 4, 8, 23, 1, 8, 1),
-    (2, 4, 128, 512, 4, 0, 64), (2, 4, 4096, 4, 4, 0, 64), (2, 4, 8, 0, 4, 56, 1)])
+    (2, 4, 128, 512, 4, 0, 64), (2, 4, 4096, 4, 4, 0, 64), (2, 4, 8, 0, 4, 56, 1), (2, 4, 8, 92, 4, 24, 4), (2, 4, 128, 92, 4, 1024, 16),
+    (1, 4, 128, 40, 8, 768, 10), (4, 2, 128, 46, 2, 512, 12)])
 def test_scores_runs_that_measured_fastest(lib, bits, per_unit, heads, steps, steps_per_block, tails, run):
     """On 256 units: the fullest grid is not the fastest where its last workgroups of a unit make the run of the others longer
     than fewer workgroups would need, nor where set-ups are most of a run; and the ends of the range."""
@@ -159,3 +160,25 @@ def test_form_of_the_attention_output_at_4_bits(lib):
         for pairs in (2, 3, 96):
             assert bool(lib.eoq_attend_shares_coordinates(4, group, pairs)) == (group > 4)
             assert not lib.eoq_attend_shares_coordinates(3, group, pairs)
+
+
+class _Grid(C.Structure):
+    _fields_ = [("x", C.c_int64), ("y", C.c_int64), ("run_heads", C.c_int64)]
+
+
+@pytest.mark.parametrize("heads,runs,tail_groups", [(128, 2, 6), (128, 4, 4), (8, 23, 1), (6, 1, 3), (1, 1024, 8), (3, 7, 0), (12, 0, 7), (65535, 3, 0),
+                                                    (65535, 3, 2), (40000, 1, 2), (30000, 1, 1), (65535, 0, 64)])
+def test_scores_grid_has_the_runs_in_front_of_the_tail(lib, heads, runs, tail_groups):
+    """Workgroups start in turn on eight dies: with the tail of a head behind the runs of that head, not behind those of all heads,
+    the runs met on some of the dies wherever a head's workgroups were a multiple of two."""
+    grids = (_Grid * 2)()
+    count = lib.eoq_scores_grids(C.c_int64(heads), C.c_int64(runs), C.c_int64(tail_groups), grids)
+    places = []
+    for g in grids[:count]:
+        assert 0 < g.x and 0 < g.y <= 65535 and 0 <= g.run_heads <= g.y
+        places += [("run", g.run_heads * g.x), ("tail", (g.y - g.run_heads) * g.x)]
+        assert g.run_heads in (0, heads) and (g.run_heads == 0 or g.x == runs)
+        assert g.y == g.run_heads or g.x * (g.y - g.run_heads) - heads * tail_groups in range(g.x)   # all of it, in the fewest rows
+    places = [p for p in places if p[1]]
+    assert places == sorted(places) and [p[0] for p in places] == ["run"] * (runs > 0) + ["tail"] * (tail_groups > 0)
+    assert sum(p[1] for p in places if p[0] == "run") == heads * runs
