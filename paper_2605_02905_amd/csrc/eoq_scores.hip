@@ -196,8 +196,12 @@ __device__ __forceinline__ void tail_scores(const uint16_t* __restrict__ tail, i
 // finishes per token (2 for groups up to 4).
 // QJL: the logits get the correction of Eq. (qjl), |r_x| sqrt(pi/2)/d <Phi q, sign(Phi r_x)>, from one more bit plane
 // (the signs) and the stored residual norm; Phi q goes through the same fixed-point form as Pi q.
+// (With the correction at 3 bits the compiler is told that two workgroups on a unit are what to schedule for: it went for a third,
+// which the registers do not allow, and gave every product of a tile the same operand registers, so that each waited for its own
+// reads of the table: one head of 1000 blocks of 512 26.5 us and now 24.4, 3 x 64 blocks 13.1 and 11.6.)
 template <int BITS, bool QJL, int NQ>
-__global__ __launch_bounds__(THREADS, (BITS <= 2 && !QJL) ? 4 : 1) void eoq_scores_i8_kernel(
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu((BITS <= 2 && !QJL) ? 4 : 1, (QJL && BITS == 3) ? 2 : 8)))
+void eoq_scores_i8_kernel(
     int n, int r_max, int n_kv_heads, int group, int64_t blocks_per_head, int64_t block_capacity, int64_t score_stride,
     int run, const uint16_t* __restrict__ pih,
     const float* __restrict__ tab, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ norms,

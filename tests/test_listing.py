@@ -65,3 +65,14 @@ def test_sums_of_attention_output_leave_in_one_loop(tmp_path):
         loops = [(label[l.split()[1]], i) for i, l in enumerate(lines) if re.match(r"s_c?branch", l) and last < label.get(l.split()[1], -1) < i]
         assert len(loops) == 1
         assert sum(l.startswith("global_store") for l in lines[loops[0][0]:loops[0][1]]) == 2
+
+
+@pytest.mark.skipif(not os.path.exists(g.HIPCC), reason="no compiler")
+def test_products_of_a_scores_tile_do_not_wait_for_each_other_s_reads(tmp_path):
+    """The operands of a tile's products come from a table in LDS.  If every product has the same operand registers, its reads can
+    only begin when the product before has taken them, and the products of a tile follow each other at the latency of a read."""
+    for kernel in ("ILi2ELb0ELi2E", "ILi3ELb0ELi2E", "ILi3ELb1ELi2E", "ILi3ELb1ELi4E", "ILi4ELb0ELi4E", "ILi4ELb1ELi2E"):   # <bits, correction, heads of a lane>
+        lines = _kernel_lines("eoq_scores.hip", "eoq_scores_i8_kernel" + kernel, tmp_path)
+        operands = [re.findall(r"[va]\[\d+:\d+\]", l)[2] for l in lines if l.startswith("v_mfma_i32_32x32x32_i8")]
+        repeats = sum(a == b for a, b in zip(operands, operands[1:]))
+        assert repeats <= len(operands) // 3, (kernel, repeats, len(operands))
