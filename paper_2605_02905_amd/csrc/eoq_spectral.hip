@@ -594,56 +594,43 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
 
 // Sum over the 16 lanes of a DPP row of the values p[S .. 7] of every lane (the values below S are dead),
 // transposing as it folds: on return lane tx holds the row total of value number fold_index<S>(tx), and the lanes
-// with fold_writer<S>(tx) hold each live total exactly once.  Partners: 15 - tx, tx ^ 7, tx ^ 2, tx ^ 1; at a
-// transposing fold a lane keeps the half of its values selected by one bit of tx and hands the other half to its
-// partner; once only half of the values are live that fold is a plain sum.
+// with fold_writer<S>(tx) hold each live total exactly once.  Partners: 15 - tx, tx ^ 7, tx ^ 2, tx ^ 1.  Two live values make
+// a transposing fold: a lane keeps the one that a bit of tx selects and hands the other to its partner (seven instructions); a
+// value without a live companion is summed as it is (three) and both lanes hold the sum.
 template <int S>
 __device__ __forceinline__ int fold_index(int tx) {
-  if constexpr (S < 4) return tx >> 1;
-  else if constexpr (S < 6) return 4 + ((tx >> 1) & 3);
-  else if constexpr (S == 6) return 6 + ((tx >> 1) & 1);
-  else return 7;
+  const int b3 = (tx >> 3) & 1, b2 = (tx >> 2) & 1, b1 = (tx >> 1) & 1;   // which of the values i and i + 4, i and i + 2, i and i + 1
+  const int i1 = (S < 7) ? b1 : 1;
+  const int i2 = i1 + 2 * ((S < 6) ? (4 + i1 >= S ? b2 : 1) : 1);
+  return i2 + 4 * ((S < 4) ? (i2 >= S ? b3 : 1) : 1);
 }
 template <int S>
 __device__ __forceinline__ bool fold_writer(int tx) {
-  if constexpr (S < 4) return (tx & 1) == 0;
-  else if constexpr (S < 6) return (tx & 9) == 0;
-  else if constexpr (S == 6) return (tx & 13) == 0;
-  else return tx == 0;
+  // of the lanes that hold the same total the one with the free bits clear
+  const int i = fold_index<S>(tx), i1 = i & 1, i2 = i & 3;
+  const int used = (S < 7 ? 2 : 0) | (S < 6 && 4 + i1 >= S ? 4 : 0) | (S < 4 && i2 >= S ? 8 : 0);
+  return (tx & ~used) == 0;
+}
+template <int CTRL>
+__device__ __forceinline__ double fold_pair(double lower, double upper, bool up) {
+  const double send = up ? lower : upper;
+  const double keep = up ? upper : lower;
+  return keep + dpp_mov<CTRL>(send);
 }
 template <int S>
 __device__ __forceinline__ double row16_fold(const double (&p)[8], int tx) {
   const bool b3 = (tx & 8) != 0, b2 = (tx & 4) != 0, b1 = (tx & 2) != 0;
   double r1[4], r2[2], r3;
-  if constexpr (S < 4) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const double send = b3 ? p[i] : p[4 + i];
-      const double keep = b3 ? p[4 + i] : p[i];
-      r1[i] = keep + dpp_mov<0x140>(send);  // row_mirror
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r1[i] = (4 + i >= S) ? p[4 + i] + dpp_mov<0x140>(p[4 + i]) : 0.0;
-  }
-  if constexpr (S < 6) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const double send = b2 ? r1[i] : r1[2 + i];
-      const double keep = b2 ? r1[2 + i] : r1[i];
-      r2[i] = keep + dpp_mov<0x141>(send);  // row_half_mirror
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) r2[i] = (6 + i >= S) ? r1[2 + i] + dpp_mov<0x141>(r1[2 + i]) : 0.0;
-  }
-  if constexpr (S < 7) {
-    const double send = b1 ? r2[0] : r2[1];
-    const double keep = b1 ? r2[1] : r2[0];
-    r3 = keep + dpp_mov<0x4E>(send);
-  } else {
-    r3 = r2[1] + dpp_mov<0x4E>(r2[1]);
-  }
+  EOQ_SFOR(i, 4,                                          // row_mirror
+    if constexpr (i >= S) r1[i] = fold_pair<0x140>(p[i], p[4 + i], b3);
+    else if constexpr (4 + i >= S) r1[i] = p[4 + i] + dpp_mov<0x140>(p[4 + i]);
+    else r1[i] = 0.0;);
+  EOQ_SFOR(i, 2,                                          // row_half_mirror
+    if constexpr (4 + i >= S) r2[i] = fold_pair<0x141>(r1[i], r1[2 + i], b2);
+    else if constexpr (6 + i >= S) r2[i] = r1[2 + i] + dpp_mov<0x141>(r1[2 + i]);
+    else r2[i] = 0.0;);
+  if constexpr (S < 7) r3 = fold_pair<0x4E>(r2[0], r2[1], b1);
+  else r3 = r2[1] + dpp_mov<0x4E>(r2[1]);
   return r3 + dpp_mov<0xB1>(r3);
 }
 
@@ -678,98 +665,124 @@ __device__ __forceinline__ double newton_rcp(double s) {
 // that forms the reflector therefore does nothing that another wave can do: the row goes to LDS as it is (one entry less alpha), and the
 // float copy of the reflector for the back-transformation is made one step later by the next wave, which would wait
 // otherwise.
-// p = beta A v in LDS: entry i = l + 16 g at pbuf[l + PB_LD g].  Its writers are four consecutive rows l of up to eight
-// groups g per wave; at a pitch of 20 doubles the groups start in eight different sets of eight banks.
-constexpr int PB_LD = 20;
+// What the waves exchange: v, in two buffers in turn (the float copy of reflector k is made during step k + 1), and p = beta A v.
+// Entry i = l + 16 g at l + VP_LD g.  The writers of p are four consecutive rows l of up to eight groups g per wave; at a pitch
+// of 20 doubles the groups start in eight different sets of eight banks.
+constexpr int VP_LD = 20;
+struct ReduceLds { double v[2][8 * VP_LD], p[8 * VP_LD]; };
 // float copy of reflector k (entries k + 1 .. 127 of v, in LDS as doubles) into the packed store, by one wave
 __device__ __forceinline__ void stash_reflector(const double* v, int k, int lane, float* refl) {
   float* dst = refl + refl_off(k) - (k + 1);   // entry j at dst[j]
-  if (lane > k) dst[lane] = (float)v[lane];
-  if (lane + 64 > k) dst[lane + 64] = (float)v[lane + 64];
+  if (lane > k) dst[lane] = (float)v[(lane & 15) + VP_LD * (lane >> 4)];
+  if (lane + 64 > k) dst[lane + 64] = (float)v[(lane & 15) + VP_LD * ((lane >> 4) + 4)];
 }
-template <int S>
-__device__ __forceinline__ void householder_stage(double (&A)[64], int tid, double (*vbuf)[D], double* pbuf,
-                                                  float* refl, double* dT, double* eT, double* betaT) {
+// acc += (the value of x in lane N of the lane's row of sixteen) * y, in one instruction
+template <int N>
+__device__ __forceinline__ void fmac_bcast(double& acc, double x, double y) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(y), "n"(N));
+}
+
+// One step.  A row's sums run over its eight entries in a lane, then over the sixteen lanes; the column views of v and p are a
+// lane's own eight entries of each.  The row views of v and q (eight values a row of lanes) are held once per row of
+// lanes, row ty + 16 (tx & 7) by lane tx, and fmac_bcast takes them from there: one read from LDS and one multiply-add in
+// place of eight.  With that, two steps to a round of the loop and no selects in the fold for values without a companion a block
+// takes 446 thousand cycles instead of 466 (8192 blocks of 512 x 128) and 338 instead of 364 (16 of 128 x 128).  Every wave
+// forming the reflector by itself from a published row, with one barrier a step, does the same for the short calls and is
+// slower in the long ones (467): waves that wait leave their issue slots to the unit's other workgroup.
+template <int S, int ODD>
+__device__ __forceinline__ void householder_step(int kk, double (&A)[64], int tid, ReduceLds& lds, float* refl, double* dT,
+                                                 double* eT, double* betaT) {
   const int lane = tid & 63, ty = tid >> 4, tx = tid & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr int KK_END = (S == 7) ? 14 : 16;
-#pragma unroll 1
-  for (int kk = 0; kk < KK_END; ++kk) {
-    const int k = 16 * S + kk;
-    double* vb = vbuf[kk & 1];
-    if (wave == (kk >> 2)) {
-      // every 16-lane row of this wave runs the arithmetic on its own matrix row; only the row k stores
-      const bool owner = ((lane >> 4) == (kk & 3));
-      const double xs = (tx > kk) ? A[S * 8 + S] : 0.0;  // columns j = tx + 16 b > k only
-      double s0 = xs * xs, s1 = 0.0;
-      EOQ_SFOR(b, 8,
-        if constexpr (b > S) {
-          if constexpr (((b - S) & 1) == 0) s0 = fma(A[S * 8 + b], A[S * 8 + b], s0);
-          else s1 = fma(A[S * 8 + b], A[S * 8 + b], s1);
-        });
-      const double ss = row16_sum_uniform(s0 + s1);   // the same bits in the sixteen lanes of a row
-      double xsel = xs;
-      if constexpr (S < 7) xsel = (kk == 15) ? A[S * 8 + S + 1] : xsel;
-      const double x0 = readlane_f64(xsel, 16 * (kk & 3) + ((kk + 1) & 15));  // x_{k+1} of row k
-      double alpha = 0.0, beta = 0.0;
-      if (ss > 0x1.0p-960) {
-        const double sigma = newton_sqrt(ss);
-        alpha = (x0 >= 0.0) ? -sigma : sigma;                 // H_k x = alpha e_1
-        beta = newton_rcp(fma(sigma, fabs(x0), ss));          // 2 / (v^T v), v = x - alpha e_1
-      }
-      if (owner) {
-        // v = x - alpha e_{k+1}: entry k + 1 sits in sub-tile S of lane kk + 1, or, at the last step of a stage, in
-        // sub-tile S + 1 of lane 0
-        const double fix = (tx == ((kk + 1) & 15)) ? alpha : 0.0;
-        vb[tx + 16 * S] = xs - ((kk < 15) ? fix : 0.0);
-        EOQ_SFOR(b, 8,
-          if constexpr (b > S) vb[tx + 16 * b] = (b == S + 1) ? A[S * 8 + b] - ((kk == 15) ? fix : 0.0) : A[S * 8 + b];);
-        if (tx == kk) {
-          dT[k] = A[S * 8 + S];
-          eT[k] = alpha;
-          betaT[k] = beta;
-        }
-      }
-    } else if (wave == (((kk >> 2) + 1) & 3) && k > 0) {
-      stash_reflector(vbuf[(kk + 1) & 1], k - 1, lane, refl);   // the reflector of the step before, complete since that step's first barrier
-    }
-    __syncthreads();
-    const double beta = betaT[k];
-    double vj[8];
-    EOQ_SFOR(b, 8, vj[b] = (b >= S) ? vb[tx + 16 * b] : 0.0;);
-    {
-      double part[8];
-      EOQ_SFOR(a, 8,
-        if constexpr (a >= S) {
-          // one chain per row: the chains of the live rows interleave, which is independent work enough
-          double s0 = 0.0;
-          EOQ_SFOR(b, 8, if constexpr (b >= S) s0 = fma(A[a * 8 + b], vj[b], s0););
-          part[a] = s0;
-        } else {
-          part[a] = 0.0;
-        });
-      const double tot = row16_fold<S>(part, tx);
-      if (fold_writer<S>(tx)) pbuf[ty + PB_LD * fold_index<S>(tx)] = beta * tot;
-    }
-    __syncthreads();
-    // v^T p from the column entries this lane holds anyway, summed over its DPP row (every row of 16 lanes covers
-    // all 128 columns and gets the same bits)
-    double wj[8], vi[8], wi[8];
-    EOQ_SFOR(b, 8, wj[b] = (b >= S) ? pbuf[tx + PB_LD * b] : 0.0;);
-    double dl0 = 0.0, dl1 = 0.0;
+  const int k = 16 * S + kk;
+  const bool last = ODD && kk == 15;
+  double* vb = lds.v[ODD];
+  if (wave == (kk >> 2)) {
+    // every 16-lane row of this wave runs the arithmetic on its own matrix row; only the row k stores
+    const double xs = (tx > kk) ? A[S * 8 + S] : 0.0;  // columns j = tx + 16 b > k only
+    double s0 = xs * xs, s1 = 0.0;
     EOQ_SFOR(b, 8,
-      if constexpr (b >= S) {
-        if constexpr ((b & 1) == 0) dl0 = fma(vj[b], wj[b], dl0);
-        else dl1 = fma(vj[b], wj[b], dl1);
+      if constexpr (b > S) {
+        if constexpr (((b - S) & 1) == 0) s0 = fma(A[S * 8 + b], A[S * 8 + b], s0);
+        else s1 = fma(A[S * 8 + b], A[S * 8 + b], s1);
       });
-    // v w^T + w v^T with w = p - K v is v p^T + q v^T with q = p - 2 K v: the correction is needed in the row view
-    // only, the column view of p goes into the update as it was read
-    const double K2 = beta * row16_sum_uniform(dl0 + dl1);
-    EOQ_SFOR(a, 8, vi[a] = (a >= S) ? vb[ty + 16 * a] : 0.0;);
-    EOQ_SFOR(a, 8, wi[a] = (a >= S) ? fma(-K2, vi[a], pbuf[ty + PB_LD * a]) : 0.0;);
-    EOQ_SFOR(e, 64,
-      if constexpr ((e >> 3) >= S && (e & 7) >= S)
-        A[e] = fma(-vi[e >> 3], wj[e & 7], fma(-wi[e >> 3], vj[e & 7], A[e])););
+    const double ss = row16_sum_uniform(s0 + s1);   // the same bits in the sixteen lanes of a row
+    double xsel = xs;
+    if constexpr (ODD) xsel = last ? A[S * 8 + S + 1] : xsel;
+    const double x0 = readlane_f64(xsel, 16 * (kk & 3) + ((kk + 1) & 15));  // x_{k+1} of row k
+    const bool some = ss > 0x1.0p-960;
+    const double sigma = newton_sqrt(ss);
+    const double alpha = some ? ((x0 >= 0.0) ? -sigma : sigma) : 0.0;        // H_k x = alpha e_1
+    const double beta = some ? newton_rcp(fma(sigma, fabs(x0), ss)) : 0.0;   // 2 / (v^T v), v = x - alpha e_1
+    if ((lane >> 4) == (kk & 3)) {
+      // v = x - alpha e_{k+1}: entry k + 1 sits in sub-tile S of lane kk + 1, or, at the last step of a stage, in
+      // sub-tile S + 1 of lane 0
+      vb[tx + VP_LD * S] = xs - ((tx == kk + 1) ? alpha : 0.0);
+      EOQ_SFOR(b, 8,
+        if constexpr (b > S) vb[tx + VP_LD * b] = (ODD && b == S + 1) ? A[S * 8 + b] - ((last && tx == 0) ? alpha : 0.0) : A[S * 8 + b];);
+      if (tx == kk) {
+        dT[k] = A[S * 8 + S];
+        eT[k] = alpha;
+        betaT[k] = beta;
+      }
+    }
+  } else if ((S > 0 || ODD || kk > 0) && wave == (((kk >> 2) + 1) & 3)) {
+    stash_reflector(lds.v[1 - ODD], k - 1, lane, refl);   // the reflector of the step before, complete since that step's first barrier
+  }
+  __syncthreads();
+  const double beta = betaT[k];
+  double vj[8];
+  EOQ_SFOR(b, 8, vj[b] = (b >= S) ? vb[tx + VP_LD * b] : 0.0;);
+  const int row = ty + VP_LD * (tx & 7);
+  const double vr = vb[row];
+  {
+    double part[8];
+    EOQ_SFOR(a, 8,
+      if constexpr (a >= S) {
+        // one chain per row: the chains of the live rows interleave, which is independent work enough
+        double s0 = 0.0;
+        EOQ_SFOR(b, 8, if constexpr (b >= S) s0 = fma(A[a * 8 + b], vj[b], s0););
+        part[a] = s0;
+      } else {
+        part[a] = 0.0;
+      });
+    const double tot = row16_fold<S>(part, tx);
+    if (fold_writer<S>(tx)) lds.p[ty + VP_LD * fold_index<S>(tx)] = beta * tot;
+  }
+  __syncthreads();
+  // v^T p from the column entries this lane holds anyway, summed over its DPP row (every row of 16 lanes covers
+  // all 128 columns and gets the same bits)
+  double wj[8];
+  EOQ_SFOR(b, 8, wj[b] = (b >= S) ? lds.p[tx + VP_LD * b] : 0.0;);
+  const double pr = lds.p[row];
+  double dl0 = 0.0, dl1 = 0.0;
+  EOQ_SFOR(b, 8,
+    if constexpr (b >= S) {
+      if constexpr ((b & 1) == 0) dl0 = fma(vj[b], wj[b], dl0);
+      else dl1 = fma(vj[b], wj[b], dl1);
+    });
+  // v w^T + w v^T with w = p - K v is v p^T + q v^T with q = p - 2 K v: the correction is needed in the row view
+  // only, the column view of p goes into the update as it was read
+  const double K2 = beta * row16_sum_uniform(dl0 + dl1);
+  double nv = -vr, nq = fma(K2, vr, -pr);   // rows of -v and -q
+  // a lane move must not follow within two instructions of the write of what it moves; the compiler keeps that distance for its
+  // own moves and does not see into fmac_bcast
+  asm volatile("s_nop 1" : "+v"(nq), "+v"(nv));
+  EOQ_SFOR(e, 64,
+    if constexpr ((e >> 3) >= S && (e & 7) >= S) {
+      fmac_bcast<(e >> 3)>(A[e], nq, vj[e & 7]);
+      fmac_bcast<(e >> 3)>(A[e], nv, wj[e & 7]);
+    });
+}
+
+// Steps 16 S .. 16 S + 15, two to a round of the loop: addresses in LDS are constants then
+template <int S>
+__device__ __forceinline__ void householder_stage(double (&A)[64], int tid, ReduceLds& lds, float* refl, double* dT, double* eT,
+                                                  double* betaT) {
+#pragma unroll 1
+  for (int kk = 0; kk < 16; kk += 2) {
+    householder_step<S, 0>(kk, A, tid, lds, refl, dT, eT, betaT);
+    householder_step<S, 1>(kk + 1, A, tid, lds, refl, dT, eT, betaT);
   }
 }
 
@@ -1051,8 +1064,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
   float* refl = reinterpret_cast<float*>(pool) + REFL_SLACK;
   unsigned char* u1 = pool + REFL_BYTES;
   double* wy = reinterpret_cast<double*>(u1 + TW_BYTES);   // triangular factors of the back-transformation
-  __shared__ __align__(16) double vbuf[2][D];
-  __shared__ __align__(16) double pbuf[8 * PB_LD];
+  __shared__ __align__(16) ReduceLds red;
   __shared__ __align__(16) double2 de[D + 1];  // (d_i, e_{i-1}^2) of the scaled tridiagonal matrix; de[D] = 0
   __shared__ double dT[D], eT[D], betaT[D];
   __shared__ double chain_s[EV_BATCH][2];  // sums of squares of the two halves of each vector
@@ -1080,8 +1092,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     else
       gram_f64(static_cast<const float*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, reinterpret_cast<double*>(pool), tid, A, &flag_s);
     __syncthreads();  // the pool changes hands
-    EOQ_SFOR(s, 6, householder_stage<s>(A, tid, vbuf, pbuf, refl, dT, eT, betaT););
-    if (wave == 1) stash_reflector(vbuf[1], 95, lane, refl);   // reflector 95: the stages stash one step behind
+    EOQ_SFOR(s, 6, householder_stage<s>(A, tid, red, refl, dT, eT, betaT););
+    if (wave == 1) stash_reflector(red.v[1], 95, lane, refl);   // reflector 95: the stages stash one step behind
     // the trailing 32 x 32 matrix (rows and columns 96 .. 127: sub-tiles a, b = 6, 7 of every lane) changes hands:
     // through LDS into the 64 lanes of wave 0, which finishes the reduction alone
     double* Ms = reinterpret_cast<double*>(u1);   // [32][33]
@@ -1095,7 +1107,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       const int ly = lane >> 3, lx = lane & 7;
       double T[16];
       EOQ_SFOR(e, 16, T[e] = Ms[(ly + 8 * (e >> 2)) * 33 + lx + 8 * (e & 3)];);
-      EOQ_SFOR(ao, 4, tail32_stage<ao>(T, lane, vring, pbuf, dT, eT, betaT););
+      EOQ_SFOR(ao, 4, tail32_stage<ao>(T, lane, vring, red.p, dT, eT, betaT););
       // the last 2x2 block of T: rows and columns 126, 127 = local 30, 31 = (ly, lx) in {6, 7}, a = b = 3
       if (ly == 6 && lx == 6) dT[D - 2] = T[15];
       if (ly == 7 && lx == 6) eT[D - 2] = T[15];
@@ -1173,7 +1185,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     {
       // every lane counts at one point of a grid; each eigenvalue then starts from its grid cell
       int* ce_s = reinterpret_cast<int*>(atoms);
-      float* gval_s = reinterpret_cast<float*>(&vbuf[0][0]);   // the reduction's buffers are free by now
+      float* gval_s = reinterpret_cast<float*>(red.v[0]);   // the reduction's buffers are free by now
       // grid point g at ((g + 1) / 257)^3: most eigenvalues of a block are noise eigenvalues far below the largest
       // one, so the points crowd towards zero (a cell near the top is 3 / 257 wide, a cell at 0.03 is 0.001 wide)
       const double step = 1.0 / (GRID_POINTS + 1);
@@ -1274,7 +1286,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
         atoms[2 * i_desc + 1] = hi;
         // the sign of det(T - x I) at the lower end as a value of its own; 0 where the sign does not tell the side
         const bool single = ((ce_hi - ce_lo) & 0xFF) == 1 && f_lo * f_hi < 0.0f;
-        reinterpret_cast<float*>(&vbuf[1][0])[i_desc] = single ? copysignf(1.0f, f_lo) : 0.0f;
+        reinterpret_cast<float*>(red.v[1])[i_desc] = single ? copysignf(1.0f, f_lo) : 0.0f;
       }
     }
     int rt;
@@ -1298,7 +1310,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       const int i_desc = !act ? 0 : (!wide ? jj : (jj <= rt ? jj : (jj == rt + 1 ? k_pilot : 2 * k_pilot)));
       const int jr = D - 1 - i_desc;
       double rlo = atoms[2 * i_desc], rhi = atoms[2 * i_desc + 1];
-      const float side = reinterpret_cast<const float*>(&vbuf[1][0])[i_desc];
+      const float side = reinterpret_cast<const float*>(red.v[1])[i_desc];
       const bool by_sign = __ballot(act && side == 0.0f) == 0ull;   // wave-uniform; the signs alone, as in the rounds above
       const int shift = (tid & 63) & ~(G - 1);
       const unsigned long long gmask = (lg == 6) ? ~0ull : ((1ull << G) - 1ull);

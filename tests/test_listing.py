@@ -76,3 +76,25 @@ def test_products_of_a_scores_tile_do_not_wait_for_each_other_s_reads(tmp_path):
         operands = [re.findall(r"[va]\[\d+:\d+\]", l)[2] for l in lines if l.startswith("v_mfma_i32_32x32x32_i8")]
         repeats = sum(a == b for a, b in zip(operands, operands[1:]))
         assert repeats <= len(operands) // 3, (kernel, repeats, len(operands))
+
+
+@pytest.mark.skipif(not os.path.exists(g.HIPCC), reason="no compiler")
+def test_rows_of_the_update_are_settled_before_they_are_moved_between_lanes(tmp_path):
+    """A lane move must not follow within two instructions of the vector instruction that writes what it moves.  The compiler
+    keeps that distance for its own moves; the multiply-adds of the reduction's update, which take one factor from another lane,
+    are statements that it does not see into, so nothing but the listing shows what it has put in front of them."""
+    def registers(operand):
+        m = re.match(r"-?\|?v\[(\d+):(\d+)\]", operand)
+        return set(range(int(m[1]), int(m[2]) + 1)) if m else ({int(operand[1:])} if re.match(r"v\d+$", operand) else set())
+    lines = [l for l in _kernel_lines("eoq_spectral.hip", "eoq_spectral_tridiag_kernel", tmp_path)]
+    moves = [i for i, l in enumerate(lines) if l.startswith("v_fmac_f64_dpp")]
+    live = 64 + 49 + 36 + 25 + 16 + 9   # entries of a lane in the six stages; two steps to a round, two multiply-adds an entry
+    assert len(moves) == 2 * 2 * live
+    for i in moves:
+        source, states, j = registers(lines[i].split()[2].rstrip(",")), 0, i
+        while states < 2:
+            j -= 1
+            if lines[j].endswith(":"):   # a jump ends here; nothing of the update may precede it
+                pytest.fail(f"label within two instructions of {lines[i]}")
+            assert not (lines[j].startswith("v_") and registers(lines[j].split()[1].rstrip(",")) & source), (lines[j], lines[i])
+            states += 1 + (int(lines[j].split()[1]) if lines[j].startswith("s_nop") else 0)
