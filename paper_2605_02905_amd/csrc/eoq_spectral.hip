@@ -795,80 +795,122 @@ __device__ __forceinline__ double oct_sum_uniform(double v) {
   return v;
 }
 
+// Sums over eight consecutive lanes of the values p[S .. 3] of every lane in the order of oct_sum_uniform, transposing as it
+// folds: lane lx holds the total of value number oct_fold_index<S>(lx), lanes lx and 7 - lx the same one.  The bits of lx that
+// select are taken relative to bit 2, so that the last partner, 7 - lx, has made the same choices.
+template <int S>
+__device__ __forceinline__ int oct_fold_index(int lx) {
+  const int b2 = (lx >> 2) & 1, c1 = ((lx >> 1) & 1) ^ b2, c0 = (lx & 1) ^ b2;
+  const int hi = (S < 2) ? c1 : 1;                    // level 2: values 0, 1 against 2, 3
+  return 2 * hi + ((2 * hi >= S) ? c0 : 1);           // level 1: even against odd ones
+}
+template <int S>
+__device__ __forceinline__ double oct_fold(const double (&p)[4], int lx) {
+  const bool c0 = (((lx >> 2) ^ lx) & 1) != 0, c1 = (((lx >> 2) ^ (lx >> 1)) & 1) != 0;
+  double r[2], t;
+  EOQ_SFOR(i, 2,
+    if constexpr (2 * i >= S) r[i] = fold_pair<0xB1>(p[2 * i], p[2 * i + 1], c0);
+    else if constexpr (2 * i + 1 >= S) r[i] = p[2 * i + 1] + dpp_mov<0xB1>(p[2 * i + 1]);
+    else r[i] = 0.0;);
+  if constexpr (S < 2) t = fold_pair<0x4E>(r[0], r[1], c1);
+  else t = r[1] + dpp_mov<0x4E>(r[1]);
+  return t + dpp_mov<0x141>(t);
+}
+
 // The last 30 steps of the reduction (k = 96 .. 125) on the trailing 32 x 32 matrix, by ONE wave: lane (ly, lx) =
 // (lane / 8, lane % 8) holds T[a][b] = M[ly + 8 a][lx + 8 b], a, b < 4 (rows and columns counted from 96).  With
 // the four waves on it a step of this size costs as many instructions per wave as a step on the full matrix
 // (reductions, exchanges and two barriers); here the other three waves issue nothing, the exchanges go through
 // LDS without a barrier (operations of one wave complete in order) and the sums run over eight lanes.
+//
+// A step is one chain through the wave, so what counts is its length.  Every group of eight lanes holds the row that the next
+// reflector is made of (x) and forms v, alpha and beta by itself: v is in the registers of its users at once.  For that row kq + 1
+// goes to LDS as it stands while the sums of step kq are formed, and is updated by everybody ahead of the matrix; the update of the
+// matrix fills the gaps in the chain of the next reflector.  One wave by itself issues an instruction in five to seven cycles
+// whatever it is, so the time is their number: 31.0 thousand cycles for the 30 steps, 34.0 with the reflector read back from LDS,
+// a sum of its own for every row and copies between the steps.  (Updates placed by hand between the links of the square root: 32.)
+struct Tail {
+  double x[4], v[4], p[4];    // columns lx + 8 b: the row of the next reflector, v and p of the step before
+  double vr[4], wr[4];        // rows ly + 8 a of v and of w = p - 2 K v of the step before
+};
+template <int AO>
+__device__ __forceinline__ void tail32_update(double (&T)[16], const Tail& h) {
+  // M <- M - v p^T - q v^T, q = p - 2 K v (= M - v w^T - w v^T with w = p - K v)
+  EOQ_SFOR(e, 16,
+    if constexpr ((e >> 2) >= AO && (e & 3) >= AO)
+      T[e] = fma(-h.vr[e >> 2], h.p[e & 3], fma(-h.wr[e >> 2], h.v[e & 3], T[e])););
+}
 // Steps 8 AO .. 8 AO + 7 (the last stage stops after local row 29): rows and columns below 8 AO are dead.
 template <int AO>
-__device__ __forceinline__ void tail32_stage(double (&T)[16], int lane, double* vring, double* pb, double* dT,
+__device__ __forceinline__ void tail32_stage(double (&T)[16], Tail& h, int lane, double* vring, double* pb, double* rowb, double* dT,
                                              double* eT, double* betaT) {
   const int ly = lane >> 3, lx = lane & 7;
   constexpr int KEND = (AO == 3) ? 6 : 8;
-#pragma unroll 1
+#pragma unroll 2   // what a step hands to the next changes registers: no copies
   for (int kk = 0; kk < KEND; ++kk) {
     const int kq = 8 * AO + kk, k = 96 + kq;
-    // ---- v, beta from row kq: every group of eight lanes runs the arithmetic on its own row, the owner stores ----
-    // (the reflector stays in LDS as doubles, every step in a slot of its own: `vring`; the float copy for the
-    // back-transformation is made afterwards by all four waves)
+    const bool last = AO < 3 && kk == 7;
+    // ---- v, alpha, beta from row kq (the reflectors stay in LDS as doubles, every step in a slot of its own: `vring`; the
+    // float copy for the back-transformation is made afterwards by all four waves) ----
     double* vb = vring + 32 * kq;
-    const bool owner = (ly == kk);
-    const double xs = (lx > kk) ? T[AO * 4 + AO] : 0.0;   // columns lx + 8 b > kq only
+    const double xs = (lx > kk) ? h.x[AO] : 0.0;   // columns lx + 8 b > kq only
     double ss = xs * xs;
-    EOQ_SFOR(b, 4, if constexpr (b > AO) ss = fma(T[AO * 4 + b], T[AO * 4 + b], ss););
+    EOQ_SFOR(b, 4, if constexpr (b > AO) ss = fma(h.x[b], h.x[b], ss););
     ss = oct_sum_uniform(ss);
     double xsel = xs;
-    if constexpr (AO < 3) xsel = (kk == 7) ? T[AO * 4 + AO + 1] : xsel;
-    const double x0 = readlane_f64(xsel, 8 * kk + ((kk + 1) & 7));   // M[kq][kq + 1]
-    double alpha = 0.0, beta = 0.0;
-    if (ss > 0x1.0p-960) {
-      const double sigma = newton_sqrt(ss);
-      alpha = (x0 >= 0.0) ? -sigma : sigma;
-      beta = newton_rcp(fma(sigma, fabs(x0), ss));
-    }
-    if (owner) {
-      // v = x - alpha e_{kq+1}: that entry sits in sub-tile AO of lane kk + 1, or, at the last step of a stage, in
-      // sub-tile AO + 1 of lane 0
-      const double fix = (lx == ((kk + 1) & 7)) ? alpha : 0.0;
-      vb[lx + 8 * AO] = xs - ((kk < 7) ? fix : 0.0);
-      EOQ_SFOR(b, 4,
-        if constexpr (b > AO) vb[lx + 8 * b] = (b == AO + 1) ? T[AO * 4 + b] - ((kk == 7) ? fix : 0.0) : T[AO * 4 + b];);
+    if constexpr (AO < 3) xsel = last ? h.x[AO + 1] : xsel;
+    const double x0 = readlane_f64(xsel, (kk + 1) & 7);   // M[kq][kq + 1]
+    const bool some = ss > 0x1.0p-960;
+    const double sigma = newton_sqrt(ss);
+    const double alpha = some ? ((x0 >= 0.0) ? -sigma : sigma) : 0.0;
+    const double beta = some ? newton_rcp(fma(sigma, fabs(x0), ss)) : 0.0;
+    // with one column left the compiler contracts the square into the first sum across lanes, and the lanes' beta may differ in the
+    // last bit: everybody takes the first one's
+    const double bq = AO == 3 ? readlane_f64(beta, 0) : beta;
+    tail32_update<AO>(T, h);
+    const double diag = h.x[AO];
+    // v = x - alpha e_{kq+1}: that entry sits in sub-tile AO of lane kk + 1, or, at the last step of a stage, in
+    // sub-tile AO + 1 of lane 0
+    h.v[AO] = xs - ((lx == kk + 1) ? alpha : 0.0);
+    EOQ_SFOR(b, 4,
+      if constexpr (b > AO) {
+        h.v[b] = h.x[b];
+        if constexpr (b == AO + 1) h.v[b] -= (last && lx == 0) ? alpha : 0.0;
+      });
+    if (ly == ((kk + 1) & 7)) {   // row kq + 1; in the last step the first row of the next sub-tile
+      EOQ_SFOR(b, 4, if constexpr (b >= AO) rowb[lx + 8 * b] = T[AO * 4 + b];);
+      if constexpr (AO < 3) {
+        if (last) { EOQ_SFOR(b, 4, if constexpr (b > AO) rowb[lx + 8 * b] = T[(AO + 1) * 4 + b];); }
+      }
+      EOQ_SFOR(b, 4, if constexpr (b >= AO) vb[lx + 8 * b] = h.v[b];);
       if (lx == kk) {
-        dT[k] = T[AO * 4 + AO];
+        dT[k] = diag;
         eT[k] = alpha;
         betaT[k] = beta;
       }
     }
+    // ---- p = beta M v: row sums over the eight lanes of a group, to LDS ----
+    {
+      double part[4];
+      EOQ_SFOR(a, 4,
+        part[a] = 0.0;
+        if constexpr (a >= AO) { EOQ_SFOR(b, 4, if constexpr (b >= AO) part[a] = fma(T[a * 4 + b], h.v[b], part[a]);); });
+      const double tot = oct_fold<AO>(part, lx);
+      if (lx < 4) pb[ly + 8 * oct_fold_index<AO>(lx)] = bq * tot;
+    }
     __builtin_amdgcn_wave_barrier();   // one wave: its LDS operations complete in order
-    const double bq = readlane_f64(beta, 8 * kk);
-    double vc[4], vr[4];
-    EOQ_SFOR(b, 4, vc[b] = (b >= AO) ? vb[lx + 8 * b] : 0.0;);
-    EOQ_SFOR(a, 4, vr[a] = (a >= AO) ? vb[ly + 8 * a] : 0.0;);
-    // ---- p = beta M v: row sums over the eight lanes of a group; the column view goes through LDS ----
-    double pr[4];
-    EOQ_SFOR(a, 4,
-      if constexpr (a >= AO) {
-        double acc = 0.0;
-        EOQ_SFOR(b, 4, if constexpr (b >= AO) acc = fma(T[a * 4 + b], vc[b], acc););
-        pr[a] = bq * oct_sum_uniform(acc);
-      } else {
-        pr[a] = 0.0;
-      });
-    if (lx == 0) { EOQ_SFOR(a, 4, if constexpr (a >= AO) pb[ly + 8 * a] = pr[a];); }
-    __builtin_amdgcn_wave_barrier();
-    double pc[4];
-    EOQ_SFOR(b, 4, pc[b] = (b >= AO) ? pb[lx + 8 * b] : 0.0;);
+    EOQ_SFOR(b, 4, h.p[b] = (b >= AO) ? pb[lx + 8 * b] : 0.0;);
+    const double p1 = pb[kq + 1], v1 = vb[kq + 1];
+    EOQ_SFOR(b, 4, if constexpr (b >= AO) h.x[b] = rowb[lx + 8 * b];);
+    EOQ_SFOR(a, 4, h.vr[a] = (a >= AO) ? vb[ly + 8 * a] : 0.0; h.wr[a] = (a >= AO) ? pb[ly + 8 * a] : 0.0;);
+    __builtin_amdgcn_wave_barrier();   // rewritten by the next step
     double dl = 0.0;
-    EOQ_SFOR(b, 4, if constexpr (b >= AO) dl = fma(vc[b], pc[b], dl););
+    EOQ_SFOR(b, 4, if constexpr (b >= AO) dl = fma(h.v[b], h.p[b], dl););
     const double K2 = bq * oct_sum_uniform(dl);
-    // ---- M <- M - v p^T - q v^T, q = p - 2 K v (= M - v w^T - w v^T with w = p - K v) ----
-    double wr[4];
-    EOQ_SFOR(a, 4, wr[a] = (a >= AO) ? fma(-K2, vr[a], pr[a]) : 0.0;);
-    EOQ_SFOR(e, 16,
-      if constexpr ((e >> 2) >= AO && (e & 3) >= AO)
-        T[e] = fma(-vr[e >> 2], pc[e & 3], fma(-wr[e >> 2], vc[e & 3], T[e])););
-    __builtin_amdgcn_wave_barrier();   // pb is rewritten by the next step
+    // ---- row kq + 1 of the updated matrix ----
+    const double q1 = fma(-K2, v1, p1);
+    EOQ_SFOR(b, 4, if constexpr (b >= AO) h.x[b] = fma(-v1, h.p[b], fma(-q1, h.v[b], h.x[b])););
+    EOQ_SFOR(a, 4, if constexpr (a >= AO) h.wr[a] = fma(-K2, h.vr[a], h.wr[a]););
   }
 }
 
@@ -1107,7 +1149,10 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       const int ly = lane >> 3, lx = lane & 7;
       double T[16];
       EOQ_SFOR(e, 16, T[e] = Ms[(ly + 8 * (e >> 2)) * 33 + lx + 8 * (e & 3)];);
-      EOQ_SFOR(ao, 4, tail32_stage<ao>(T, lane, vring, red.p, dT, eT, betaT););
+      Tail h;
+      EOQ_SFOR(b, 4, h.x[b] = Ms[lx + 8 * b]; h.v[b] = h.p[b] = h.vr[b] = h.wr[b] = 0.0;);
+      EOQ_SFOR(ao, 4, tail32_stage<ao>(T, h, lane, vring, red.p, red.v[0], dT, eT, betaT););
+      tail32_update<3>(T, h);
       // the last 2x2 block of T: rows and columns 126, 127 = local 30, 31 = (ly, lx) in {6, 7}, a = b = 3
       if (ly == 6 && lx == 6) dT[D - 2] = T[15];
       if (ly == 7 && lx == 6) eT[D - 2] = T[15];
