@@ -55,21 +55,50 @@ __device__ __forceinline__ void gram_tile(const void* __restrict__ blocks, int d
   }
 }
 
+// 1 / (2^{2/3} - 1) of the bulk-edge estimate, from the cube root of 4 in double
+constexpr double EDGE_COEF = 1.0 / (0x1.965fea53d6e3dp+0 - 1.0);
+
+// What rank_and_shrink keeps in LDS: the numbers 1 - (j / k)^{2/3}, j = 1 .. k, of the square-root edge law, which depend on
+// nothing of the block and are formed ahead of time (edge_law), and the two sums of every retained component.
+struct ShrinkLds { double law[D / 2], s1[EOQ_RMAX_CAP], s2[EOQ_RMAX_CAP]; };
+__device__ __forceinline__ double edge_law(int j, int k) { return 1.0 - pow((double)(j + 1) / (double)k, 2.0 / 3.0); }
+
+// Sum over the 64 lanes in the order of a butterfly lane ^ 32, ^ 16, .. ^ 1, without LDS: swaps of half waves and of rows of
+// sixteen lanes, then lane moves inside a row (lane ^ 4 as 3 - lane and 7 - lane).
+__device__ __forceinline__ double wave_sum_butterfly(double v) {
+  int lo = __double2loint(v), hi = __double2hiint(v);
+  {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  }
+  lo = __double2loint(v);
+  hi = __double2hiint(v);
+  {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  }
+  v += dpp_mov<0x128>(v);
+  v += dpp_mov<0x141>(dpp_mov<0x1B>(v));
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0xB1>(v);
+  return v;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Alg. 2 Steps 1-3 from the eigenvalues lam_s[0..127] (descending, in LDS, visible to all lanes).
 // Writes lam_out / phi / sigma for the block, fills atoms[] and scale_s[] (phi_i / sigma_i), sets flag
 // bits, returns the (clamped) rank to every lane.  Must be called by all 256 lanes.
 // ---------------------------------------------------------------------------------------------
-__device__ int rank_and_shrink(const double* lam_s, double* atoms, double* scale_s, unsigned* flag_s, int n, int k,
+// sh.law[0 .. k - 1] is filled before.
+__device__ int rank_and_shrink(const double* lam_s, double* atoms, double* scale_s, ShrinkLds& sh, unsigned* flag_s, int n, int k,
                                double rank_thr, int r_max, int loss, size_t blk, size_t slot, double* __restrict__ lam_out,
                                float* __restrict__ phi_out, float* __restrict__ sigma_out) {
   const int tid = threadIdx.x;
   if (tid < D) lam_out[blk * D + tid] = lam_s[tid];
 
   // Step 1: lambda_+ = lam_{k+1} + (lam_{k+1} - lam_{2k+1}) / (2^{2/3} - 1);  r = #{ lam_i / lambda_+ - 1 > d^{-1/3} }
-  const double edge_coef = 1.0 / (cbrt(4.0) - 1.0);
   const double lam_k1 = lam_s[k], lam_2k1 = lam_s[2 * k];
-  const double lam_plus = lam_k1 + edge_coef * (lam_k1 - lam_2k1);
+  const double lam_plus = lam_k1 + EDGE_COEF * (lam_k1 - lam_2k1);
   const int above = (tid < D) ? ((lam_s[tid] / lam_plus - 1.0 > rank_thr) ? 1 : 0) : 0;
   int r = __syncthreads_count(above);
   if (*flag_s & EOQ_FLAG_NONFINITE) r = 0;   // Inf or NaN in the block (set by the Gram stage, before several barriers)
@@ -84,8 +113,7 @@ __device__ int rank_and_shrink(const double* lam_s, double* atoms, double* scale
     double v;
     if (tid < k) {
       const double a = lam_s[k + r], b = lam_s[2 * k + r];
-      const double j = (double)(tid + 1);
-      v = a + (1.0 - pow(j / (double)k, 2.0 / 3.0)) * edge_coef * (a - b);
+      v = a + sh.law[tid] * EDGE_COEF * (a - b);
     } else {
       v = lam_s[r + tid];
     }
@@ -93,10 +121,12 @@ __device__ int rank_and_shrink(const double* lam_s, double* atoms, double* scale
   }
   __syncthreads();
 
-  // Step 3: Stieltjes transforms of the noise measure at each outlier, D-transform, shrinker of the chosen loss
+  // Step 3: Stieltjes transforms of the noise measure at each outlier, D-transform, shrinker of the chosen loss.  The sums by a
+  // wave for each outlier, what follows from them by a lane for each: one chain of divisions and roots for all, not one for each.
+  // (4.5 thousand cycles a block; 6.0 to 7.9 with a wave's lane 0 going through its outliers one after the other, the cube root
+  // and the powers of the edge law formed here, and sums over lanes by way of LDS.)
   {
     const int wave = tid >> 6, lane = tid & 63;
-    const double beta = (n >= D) ? (double)D / (double)n : (double)n / (double)D;
     for (int i = wave; i < r; i += THREADS / 64) {
       const double z = lam_s[i];
       double s1 = 0.0, s2 = 0.0;
@@ -105,49 +135,58 @@ __device__ int rank_and_shrink(const double* lam_s, double* atoms, double* scale
         s1 += inv;
         s2 = fma(inv, inv, s2);
       }
-      s1 = wave_sum_shfl(s1);
-      s2 = wave_sum_shfl(s2);
+      s1 = wave_sum_butterfly(s1);
+      s2 = wave_sum_butterfly(s2);
       if (lane == 0) {
-        // m_s: transform of the d x d Gram side; m_l: the n x n side, which has n - d more zero eigenvalues
-        const double m_s = s1 / (double)M, dm_s = s2 / (double)M;
-        const double m_l = beta * m_s - (1.0 - beta) / z;
-        const double dm_l = beta * dm_s + (1.0 - beta) / (z * z);
-        const double T = z * m_s * m_l;
-        const double dT = m_s * m_l + z * dm_s * m_l + z * m_s * dm_l;
-        const double sig = sqrt(fmax(z, 0.0));
-        double phi = 0.0;
-        bool ok = isfinite(T) && isfinite(dT) && T > 0.0 && dT < 0.0;
-        if (ok) {
-          // d = T^{-1/2}, a_x = m_x / (d^2 T'); Eq. (shrinkers): Frobenius d sqrt(a_1 a_2), operator
-          // d sqrt(min(a)/max(a)), nuclear d (sqrt(a_1 a_2) - sqrt((1 - a_1)(1 - a_2))), the overlaps clipped to [0, 1]
-          // before the last two take their roots
-          const double dh = 1.0 / sqrt(T);
-          const double a1 = m_l / (dh * dh * dT), a2 = m_s / (dh * dh * dT);
-          if (loss == EOQ_LOSS_FROBENIUS) {
-            phi = dh * sqrt(a1 * a2);
-          } else {
-            ok = isfinite(a1) && isfinite(a2);
-            const double c1 = fmin(fmax(a1, 0.0), 1.0), c2 = fmin(fmax(a2, 0.0), 1.0);
-            if (loss == EOQ_LOSS_OPERATOR) {
-              const double hi = fmax(c1, c2);
-              phi = (hi > 0.0) ? dh * sqrt(fmin(c1, c2) / hi) : 0.0;
-            } else {
-              phi = dh * (sqrt(c1 * c2) - sqrt((1.0 - c1) * (1.0 - c2)));
-            }
-          }
-          ok = ok && isfinite(phi);
-          if (ok) phi = fmin(fmax(phi, 0.0), sig);
-        }
-        if (!ok) {
-          phi = 0.0;
-          atomicOr(flag_s, EOQ_FLAG_SHRINK_GUARD);
-        }
-        phi_out[slot * r_max + i] = (float)phi;
-        sigma_out[slot * r_max + i] = (float)sig;
-        scale_s[i] = (sig > 0.0) ? phi / sig : 0.0;
+        sh.s1[i] = s1;
+        sh.s2[i] = s2;
       }
     }
-    for (int i = r + tid; i < r_max; i += THREADS) {
+  }
+  __syncthreads();
+  {
+    const double beta = (n >= D) ? (double)D / (double)n : (double)n / (double)D;
+    const int i = tid;
+    if (i < r) {
+      const double z = lam_s[i], s1 = sh.s1[i], s2 = sh.s2[i];
+      // m_s: transform of the d x d Gram side; m_l: the n x n side, which has n - d more zero eigenvalues
+      const double m_s = s1 / (double)M, dm_s = s2 / (double)M;
+      const double m_l = beta * m_s - (1.0 - beta) / z;
+      const double dm_l = beta * dm_s + (1.0 - beta) / (z * z);
+      const double T = z * m_s * m_l;
+      const double dT = m_s * m_l + z * dm_s * m_l + z * m_s * dm_l;
+      const double sig = sqrt(fmax(z, 0.0));
+      double phi = 0.0;
+      bool ok = isfinite(T) && isfinite(dT) && T > 0.0 && dT < 0.0;
+      if (ok) {
+        // d = T^{-1/2}, a_x = m_x / (d^2 T'); Eq. (shrinkers): Frobenius d sqrt(a_1 a_2), operator
+        // d sqrt(min(a)/max(a)), nuclear d (sqrt(a_1 a_2) - sqrt((1 - a_1)(1 - a_2))), the overlaps clipped to [0, 1]
+        // before the last two take their roots
+        const double dh = 1.0 / sqrt(T);
+        const double a1 = m_l / (dh * dh * dT), a2 = m_s / (dh * dh * dT);
+        if (loss == EOQ_LOSS_FROBENIUS) {
+          phi = dh * sqrt(a1 * a2);
+        } else {
+          ok = isfinite(a1) && isfinite(a2);
+          const double c1 = fmin(fmax(a1, 0.0), 1.0), c2 = fmin(fmax(a2, 0.0), 1.0);
+          if (loss == EOQ_LOSS_OPERATOR) {
+            const double hi = fmax(c1, c2);
+            phi = (hi > 0.0) ? dh * sqrt(fmin(c1, c2) / hi) : 0.0;
+          } else {
+            phi = dh * (sqrt(c1 * c2) - sqrt((1.0 - c1) * (1.0 - c2)));
+          }
+        }
+        ok = ok && isfinite(phi);
+        if (ok) phi = fmin(fmax(phi, 0.0), sig);
+      }
+      if (!ok) {
+        phi = 0.0;
+        atomicOr(flag_s, EOQ_FLAG_SHRINK_GUARD);
+      }
+      phi_out[slot * r_max + i] = (float)phi;
+      sigma_out[slot * r_max + i] = (float)sig;
+      scale_s[i] = (sig > 0.0) ? phi / sig : 0.0;
+    } else if (i < r_max) {
       phi_out[slot * r_max + i] = 0.0f;
       sigma_out[slot * r_max + i] = 0.0f;
     }
@@ -183,6 +222,7 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
   __shared__ double colnorm[D];
   __shared__ int slot_of[D];
   __shared__ double scale_s[EOQ_RMAX_CAP];
+  __shared__ ShrinkLds shrink_s;
   __shared__ unsigned flag_s;
 
   const int tid = threadIdx.x;
@@ -254,6 +294,7 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
       converged = (sweep_rot == 0);
     }
     if (!converged && tid == 0) flag_s |= EOQ_FLAG_NO_CONVERGE;
+    if (tid < k) shrink_s.law[tid] = edge_law(tid, k);
 
     // eigenvalues = column norms; order them
     {
@@ -281,7 +322,7 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
     }
     __syncthreads();
 
-    const int r = rank_and_shrink(lam_s, atoms, scale_s, &flag_s, n, k, rank_thr, r_max, loss, blk, slot, lam_out, phi_out,
+    const int r = rank_and_shrink(lam_s, atoms, scale_s, shrink_s, &flag_s, n, k, rank_thr, r_max, loss, blk, slot, lam_out, phi_out,
                                   sigma_out);
 
     // right singular vectors v_i = a_slot / lambda_i of the retained components
@@ -1113,6 +1154,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
   __shared__ int twist_s[EV_BATCH];
   __shared__ double lam_s[D], atoms[D];
   __shared__ double scale_s[EOQ_RMAX_CAP];
+  __shared__ ShrinkLds shrink_s;
   __shared__ double tscale_s;
   __shared__ unsigned flag_s;
 
@@ -1161,6 +1203,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
       // meanwhile the other waves form the triangular factors of the reflectors 0 .. 95, whose float copies are complete
       // (two blocks of sixteen each, one of many rows and one of few)
       wy_factors(wave - 1, 6 - wave, refl, betaT, wy, lane);
+      if (wave == 3 && lane < k_pilot) shrink_s.law[lane] = edge_law(lane, k_pilot);   // k <= 63: 2 k is a column
     }
     __syncthreads();
     // float copies of the last 30 reflectors (local entries c > kq of step kq), by everybody
@@ -1336,9 +1379,8 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     }
     int rt;
     {
-      const double edge_coef = 1.0 / (cbrt(4.0) - 1.0);
       const double lam_k1 = lam_s[k_pilot], lam_2k1 = lam_s[2 * k_pilot];
-      const double lam_plus = lam_k1 + edge_coef * (lam_k1 - lam_2k1);
+      const double lam_plus = lam_k1 + EDGE_COEF * (lam_k1 - lam_2k1);
       rt = __syncthreads_count((tid < D && lam_s[tid] / lam_plus - 1.0 > rank_thr) ? 1 : 0);   // also orders `atoms`
     }
     {
@@ -1382,7 +1424,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
   }
   __syncthreads();
 
-  const int r = rank_and_shrink(lam_s, atoms, scale_s, &flag_s, n, k_pilot, rank_thr, r_max, loss, blk, slot, lam_out,
+  const int r = rank_and_shrink(lam_s, atoms, scale_s, shrink_s, &flag_s, n, k_pilot, rank_thr, r_max, loss, blk, slot, lam_out,
                                 phi_out, sigma_out);
 
   // repeated retained eigenvalues: leave the block to the Jacobi solver
