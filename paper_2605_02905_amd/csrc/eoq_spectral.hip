@@ -707,15 +707,29 @@ __device__ __forceinline__ double newton_rcp(double s) {
 // float copy of the reflector for the back-transformation is made one step later by the next wave, which would wait
 // otherwise.
 // What the waves exchange: v, in two buffers in turn (the float copy of reflector k is made during step k + 1), and p = beta A v.
-// Entry i = l + 16 g at l + VP_LD g.  The writers of p are four consecutive rows l of up to eight groups g per wave; at a pitch
-// of 20 doubles the groups start in eight different sets of eight banks.
-constexpr int VP_LD = 20;
-struct ReduceLds { double v[2][8 * VP_LD], p[8 * VP_LD]; };
+// Entries l + 32 m and l + 32 m + 16 lie side by side, so that a lane reads two of its columns at once: a 16-byte read of four
+// waves takes 18 cycles, two 8-byte reads in one instruction 34.  The writers of p are four consecutive rows of all eight
+// sub-tiles; at a pitch of 40 doubles they use different banks.
+constexpr int VP_LD = 40, VP_LEN = D / 32 * VP_LD;
+struct ReduceLds { double v[2][VP_LEN], p[VP_LEN]; };
+__device__ __forceinline__ int vp_at(int i) { return VP_LD * (i >> 5) + 2 * (i & 15) + ((i >> 4) & 1); }
+// a lane's columns tx + 16 b, b >= S
+template <int S>
+__device__ __forceinline__ void vp_columns(const double* from, int tx, double (&to)[8]) {
+  EOQ_SFOR(m, 4,
+    if constexpr (2 * m + 1 >= S) {
+      const double2 t = *reinterpret_cast<const double2*>(from + VP_LD * m + 2 * tx);
+      to[2 * m] = t.x;
+      to[2 * m + 1] = t.y;
+    } else {
+      to[2 * m] = to[2 * m + 1] = 0.0;
+    });
+}
 // float copy of reflector k (entries k + 1 .. 127 of v, in LDS as doubles) into the packed store, by one wave
 __device__ __forceinline__ void stash_reflector(const double* v, int k, int lane, float* refl) {
   float* dst = refl + refl_off(k) - (k + 1);   // entry j at dst[j]
-  if (lane > k) dst[lane] = (float)v[(lane & 15) + VP_LD * (lane >> 4)];
-  if (lane + 64 > k) dst[lane + 64] = (float)v[(lane & 15) + VP_LD * ((lane >> 4) + 4)];
+  if (lane > k) dst[lane] = (float)v[vp_at(lane)];
+  if (lane + 64 > k) dst[lane + 64] = (float)v[vp_at(lane) + 2 * VP_LD];
 }
 // acc += (the value of x in lane N of the lane's row of sixteen) * y, in one instruction
 template <int N>
@@ -758,9 +772,13 @@ __device__ __forceinline__ void householder_step(int kk, double (&A)[64], int ti
     if ((lane >> 4) == (kk & 3)) {
       // v = x - alpha e_{k+1}: entry k + 1 sits in sub-tile S of lane kk + 1, or, at the last step of a stage, in
       // sub-tile S + 1 of lane 0
-      vb[tx + VP_LD * S] = xs - ((tx == kk + 1) ? alpha : 0.0);
-      EOQ_SFOR(b, 8,
-        if constexpr (b > S) vb[tx + VP_LD * b] = (ODD && b == S + 1) ? A[S * 8 + b] - ((last && tx == 0) ? alpha : 0.0) : A[S * 8 + b];);
+      double v[8];
+      EOQ_SFOR(b, 8, v[b] = b > S ? A[S * 8 + b] : 0.0;);
+      v[S] = xs - ((tx == kk + 1) ? alpha : 0.0);
+      if constexpr (ODD) v[S + 1] -= (last && tx == 0) ? alpha : 0.0;
+      EOQ_SFOR(m, 4,
+        if constexpr (2 * m >= S) *reinterpret_cast<double2*>(vb + VP_LD * m + 2 * tx) = make_double2(v[2 * m], v[2 * m + 1]);
+        else if constexpr (2 * m + 1 >= S) vb[VP_LD * m + 2 * tx + 1] = v[2 * m + 1];);
       if (tx == kk) {
         dT[k] = A[S * 8 + S];
         eT[k] = alpha;
@@ -773,8 +791,8 @@ __device__ __forceinline__ void householder_step(int kk, double (&A)[64], int ti
   __syncthreads();
   const double beta = betaT[k];
   double vj[8];
-  EOQ_SFOR(b, 8, vj[b] = (b >= S) ? vb[tx + VP_LD * b] : 0.0;);
-  const int row = ty + VP_LD * (tx & 7);
+  vp_columns<S>(vb, tx, vj);
+  const int row = VP_LD * ((tx & 7) >> 1) + 2 * ty + (tx & 1);   // vp_at(ty + 16 (tx & 7))
   const double vr = vb[row];
   {
     double part[8];
@@ -788,13 +806,13 @@ __device__ __forceinline__ void householder_step(int kk, double (&A)[64], int ti
         part[a] = 0.0;
       });
     const double tot = row16_fold<S>(part, tx);
-    if (fold_writer<S>(tx)) lds.p[ty + VP_LD * fold_index<S>(tx)] = beta * tot;
+    if (fold_writer<S>(tx)) lds.p[vp_at(ty + 16 * fold_index<S>(tx))] = beta * tot;
   }
   __syncthreads();
   // v^T p from the column entries this lane holds anyway, summed over its DPP row (every row of 16 lanes covers
   // all 128 columns and gets the same bits)
   double wj[8];
-  EOQ_SFOR(b, 8, wj[b] = (b >= S) ? lds.p[tx + VP_LD * b] : 0.0;);
+  vp_columns<S>(lds.p, tx, wj);
   const double pr = lds.p[row];
   double dl0 = 0.0, dl1 = 0.0;
   EOQ_SFOR(b, 8,
@@ -1022,8 +1040,9 @@ __device__ __forceinline__ int sturm_count(sc_double* de, double x, double* val 
 // for a batch of vectors y is a chain of products for v_mfma_f64_16x16x4_f64.  Its operands (wave64): lane l = 16 g + c
 // supplies A[row = c][k = g] and B[k = g][col = c] and receives D[row = 4 v + g][col = c] in register v: a result register v
 // is the B operand of the k-step that takes the rows 4 v .. 4 v + 3, nothing changes lanes.
-// position of T_ik in the 16 x 16 array of a block: an operand (row c, columns 4 v + g of lane 16 g + c) is 64 consecutive doubles
-__device__ __forceinline__ int wy_pos(int i, int k) { return 16 * k + i; }
+// position of T_ik in the 16 x 16 array of a block: row i, columns k = 4 v + g are the operand of lane 16 g + i in k-step v, two
+// steps side by side
+__device__ __forceinline__ int wy_pos(int i, int k) { return 128 * (k >> 3) + 2 * (16 * (k & 3) + i) + ((k >> 2) & 1); }
 
 // The factors T of the reflector blocks sg0 and sg1 into their places of `wy` (256 doubles per block), by one wave: V^T V on
 // the matrix cores (an entry of V is A and B operand alike), then lane 16 q + i < 32 forms row i of block q.
@@ -1580,18 +1599,21 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
               vc[tt][v] = (c > 4 * v + g && 16 * sg + 4 * v + g < D - 2) ? vc[tt][v] : 0.0f;);
           }
           if (t >= sg) { EOQ_SFOR(v, 4, d = mfma64((double)vr[tt][v], Y[tt][v], d);); });
-        double* x = xb + (sg & 1) * 1024;
-        EOQ_SFOR(v, 4, x[wave * 256 + 64 * v + lane] = d[v];);
-        double tm[4];
-        EOQ_SFOR(v, 4, tm[v] = wy[sg * 256 + 64 * v + lane];);   // wy_pos(c, 4 v + g)
+        // the waves' parts of V^T y, two registers side by side (16-byte accesses: half the time of two of 8 in one instruction)
+        double2* x = reinterpret_cast<double2*>(xb + (sg & 1) * 1024);
+        EOQ_SFOR(u, 2, x[wave * 128 + 64 * u + lane] = make_double2(d[2 * u], d[2 * u + 1]););
+        double2 tm[2];
+        EOQ_SFOR(u, 2, tm[u] = reinterpret_cast<const double2*>(wy + sg * 256)[64 * u + lane];);   // wy_pos(c, 8 u + g), + 4
         const int whole = 16 * (16 * sg) - 2152;
         row_at += row_step + whole;
         EOQ_SFOR(v, 4, col_at[v] += col_step + (whole + 64 * v););
         __syncthreads();
         double4v f = {0.0, 0.0, 0.0, 0.0};
-        EOQ_SFOR(v, 4,
-          const double sum = (x[64 * v + lane] + x[256 + 64 * v + lane]) + (x[512 + 64 * v + lane] + x[768 + 64 * v + lane]);
-          f = mfma64(tm[v], sum, f);
+        EOQ_SFOR(u, 2,
+          const double2 a0 = x[64 * u + lane]; const double2 a1 = x[128 + 64 * u + lane];
+          const double2 a2 = x[256 + 64 * u + lane]; const double2 a3 = x[384 + 64 * u + lane];
+          f = mfma64(tm[u].x, (a0.x + a1.x) + (a2.x + a3.x), f);
+          f = mfma64(tm[u].y, (a0.y + a1.y) + (a2.y + a3.y), f);
         );
         EOQ_SFOR(tt, 2,
           if (wave + 4 * tt >= sg) {
