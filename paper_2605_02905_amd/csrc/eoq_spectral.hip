@@ -343,10 +343,12 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
 // =============================================================================================
 // Tridiagonal solver
 // =============================================================================================
-// Cyclic layout of the working matrix: lane (ty, tx) = (tid / 16, tid % 16) owns the 8 x 8 entries
+// Cyclic layout of the working matrix: lane (ty, tx), ty = lane_row(tid), tx = tid % 16, owns the 8 x 8 entries
 // A[a * 8 + b] = G[ty + 16 a][tx + 16 b].  Rows and columns are dealt round-robin, so the trailing submatrix
 // of the reduction stays spread over all lanes while it shrinks: during steps 16 s .. 16 s + 15 every lane's
 // live part is the sub-tile a, b >= s.  The 16 lanes of one DPP row share ty.
+// Consecutive rows belong to different waves: lane's row number modulo 16.
+__device__ __forceinline__ int lane_row(int tid) { return (tid >> 6) + 4 * ((tid >> 4) & 3); }
 constexpr int XPAD = 17;  // row stride of a 16 x 16 exchange plane: transposed reads hit distinct banks
 // packed reflector storage: reflector k has entries i = k+1 .. 127 (24-bit products: full rate)
 __device__ __forceinline__ int refl_off(int k) { return (int)(__umul24(k, D - 1) - (__umul24(k, k - 1) >> 1)); }
@@ -417,7 +419,7 @@ constexpr int gi_tile_j(int w, int s) { return s < 6 ? 4 + w : (s == 6 && w >= 2
 // wave's tile wave + 4 s, in column lane % 16 and row `row(v)`.
 template <typename Get, typename Row>
 __device__ __forceinline__ void tiles_to_lanes(double* Tl, int tid, double (&A)[64], Get&& get, Row&& row) {
-  const int ty = tid >> 4, tx = tid & 15, wave = tid >> 6;
+  const int ty = lane_row(tid), tx = tid & 15, wave = tid >> 6;
   EOQ_SFOR(rd, 3,
     __syncthreads();
     EOQ_SFOR(s3, 3,
@@ -703,14 +705,16 @@ __device__ __forceinline__ double newton_rcp(double s) {
 // five, however independent they are (two waves per SIMD, which is what the registers allow: four to five cycles per
 // double-precision instruction between them), so what a step costs is the number of instructions of the wave the
 // others wait for, while the SIMDs of the waiting waves serve the other workgroup of the compute unit.  The wave
-// that forms the reflector therefore does nothing that another wave can do: the row goes to LDS as it is (one entry less alpha), and the
-// float copy of the reflector for the back-transformation is made one step later by the next wave, which would wait
-// otherwise.
+// that forms the reflector therefore does nothing that can wait: the row goes to LDS as it is (one entry less alpha) with beta, and
+// the entries of T and the float copy of the reflector for the back-transformation leave one step later, when another wave
+// forms the next reflector (consecutive rows belong to different waves).  A write to LDS costs a wave 14 to 20 cycles
+// whatever lanes are active: with four rows in turn in one wave, which wrote the entries of T at once, a block took 431.7 thousand
+// cycles instead of 424.6 (8192 blocks of 512 x 128), 325 instead of 316 with 16 blocks of 128 x 128.
 // What the waves exchange: v, in two buffers in turn (the float copy of reflector k is made during step k + 1), and p = beta A v.
 // Entries l + 32 m and l + 32 m + 16 lie side by side, so that a lane reads two of its columns at once: a 16-byte read of four
-// waves takes 18 cycles, two 8-byte reads in one instruction 34.  The writers of p are four consecutive rows of all eight
-// sub-tiles; at a pitch of 40 doubles they use different banks.
-constexpr int VP_LD = 40, VP_LEN = D / 32 * VP_LD;
+// waves takes 18 cycles, two 8-byte reads in one instruction 34.  The writers of p are every fourth row of all eight
+// sub-tiles; at a pitch of 34 doubles they use different banks.
+constexpr int VP_LD = 34, VP_LEN = D / 32 * VP_LD;
 struct ReduceLds { double v[2][VP_LEN], p[VP_LEN]; };
 __device__ __forceinline__ int vp_at(int i) { return VP_LD * (i >> 5) + 2 * (i & 15) + ((i >> 4) & 1); }
 // a lane's columns tx + 16 b, b >= S
@@ -725,8 +729,13 @@ __device__ __forceinline__ void vp_columns(const double* from, int tx, double (&
       to[2 * m] = to[2 * m + 1] = 0.0;
     });
 }
-// float copy of reflector k (entries k + 1 .. 127 of v, in LDS as doubles) into the packed store, by one wave
-__device__ __forceinline__ void stash_reflector(const double* v, int k, int lane, float* refl) {
+// What step k leaves behind, by the wave that formed its reflector: diagonal and off-diagonal entry of T, and a float copy of the
+// reflector (entries k + 1 .. 127 of v, in LDS as doubles) in the packed store.
+__device__ __forceinline__ void leave_reflector(const double* v, int k, int lane, double alpha, double diag, float* refl, double* dT, double* eT) {
+  if (lane == 16 * ((k & 15) >> 2) + (k & 15)) {
+    dT[k] = diag;
+    eT[k] = alpha;
+  }
   float* dst = refl + refl_off(k) - (k + 1);   // entry j at dst[j]
   if (lane > k) dst[lane] = (float)v[vp_at(lane)];
   if (lane + 64 > k) dst[lane + 64] = (float)v[vp_at(lane) + 2 * VP_LD];
@@ -744,15 +753,15 @@ __device__ __forceinline__ void fmac_bcast(double& acc, double x, double y) {
 // takes 446 thousand cycles instead of 466 (8192 blocks of 512 x 128) and 338 instead of 364 (16 of 128 x 128).  Every wave
 // forming the reflector by itself from a published row, with one barrier a step, does the same for the short calls and is
 // slower in the long ones (467): waves that wait leave their issue slots to the unit's other workgroup.
+// `alpha` and `diag` stay with the wave that formed the reflector until the step after, when it waits.
 template <int S, int ODD>
-__device__ __forceinline__ void householder_step(int kk, double (&A)[64], int tid, ReduceLds& lds, float* refl, double* dT,
-                                                 double* eT, double* betaT) {
-  const int lane = tid & 63, ty = tid >> 4, tx = tid & 15;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+__device__ __forceinline__ void householder_step(int kk, int wave, double (&A)[64], double& alpha, double& diag, int tid, ReduceLds& lds,
+                                                 float* refl, double* dT, double* eT, double* betaT) {
+  const int lane = tid & 63, ty = lane_row(tid), tx = tid & 15;
   const int k = 16 * S + kk;
   const bool last = ODD && kk == 15;
   double* vb = lds.v[ODD];
-  if (wave == (kk >> 2)) {
+  if (__builtin_expect(wave == (kk & 3), 1)) {   // falls through: a jump taken costs twenty cycles of the chain
     // every 16-lane row of this wave runs the arithmetic on its own matrix row; only the row k stores
     const double xs = (tx > kk) ? A[S * 8 + S] : 0.0;  // columns j = tx + 16 b > k only
     double s0 = xs * xs, s1 = 0.0;
@@ -764,12 +773,13 @@ __device__ __forceinline__ void householder_step(int kk, double (&A)[64], int ti
     const double ss = row16_sum_uniform(s0 + s1);   // the same bits in the sixteen lanes of a row
     double xsel = xs;
     if constexpr (ODD) xsel = last ? A[S * 8 + S + 1] : xsel;
-    const double x0 = readlane_f64(xsel, 16 * (kk & 3) + ((kk + 1) & 15));  // x_{k+1} of row k
+    const double x0 = readlane_f64(xsel, 16 * (kk >> 2) + ((kk + 1) & 15));  // x_{k+1} of row k
     const bool some = ss > 0x1.0p-960;
     const double sigma = newton_sqrt(ss);
-    const double alpha = some ? ((x0 >= 0.0) ? -sigma : sigma) : 0.0;        // H_k x = alpha e_1
+    alpha = some ? ((x0 >= 0.0) ? -sigma : sigma) : 0.0;                     // H_k x = alpha e_1
     const double beta = some ? newton_rcp(fma(sigma, fabs(x0), ss)) : 0.0;   // 2 / (v^T v), v = x - alpha e_1
-    if ((lane >> 4) == (kk & 3)) {
+    diag = A[S * 8 + S];
+    if (((lane >> 4) & 3) == (kk >> 2)) {
       // v = x - alpha e_{k+1}: entry k + 1 sits in sub-tile S of lane kk + 1, or, at the last step of a stage, in
       // sub-tile S + 1 of lane 0
       double v[8];
@@ -779,14 +789,10 @@ __device__ __forceinline__ void householder_step(int kk, double (&A)[64], int ti
       EOQ_SFOR(m, 4,
         if constexpr (2 * m >= S) *reinterpret_cast<double2*>(vb + VP_LD * m + 2 * tx) = make_double2(v[2 * m], v[2 * m + 1]);
         else if constexpr (2 * m + 1 >= S) vb[VP_LD * m + 2 * tx + 1] = v[2 * m + 1];);
-      if (tx == kk) {
-        dT[k] = A[S * 8 + S];
-        eT[k] = alpha;
-        betaT[k] = beta;
-      }
+      if (tx == kk) betaT[k] = beta;
     }
-  } else if ((S > 0 || ODD || kk > 0) && wave == (((kk >> 2) + 1) & 3)) {
-    stash_reflector(lds.v[1 - ODD], k - 1, lane, refl);   // the reflector of the step before, complete since that step's first barrier
+  } else if ((S > 0 || ODD || kk > 0) && wave == ((kk + 3) & 3)) {
+    leave_reflector(lds.v[1 - ODD], k - 1, lane, alpha, diag, refl, dT, eT);   // of the step before, complete since that step's first barrier
   }
   __syncthreads();
   const double beta = betaT[k];
@@ -836,12 +842,12 @@ __device__ __forceinline__ void householder_step(int kk, double (&A)[64], int ti
 
 // Steps 16 S .. 16 S + 15, two to a round of the loop: addresses in LDS are constants then
 template <int S>
-__device__ __forceinline__ void householder_stage(double (&A)[64], int tid, ReduceLds& lds, float* refl, double* dT, double* eT,
-                                                  double* betaT) {
+__device__ __forceinline__ void householder_stage(int wave, double (&A)[64], double& alpha, double& diag, int tid, ReduceLds& lds,
+                                                  float* refl, double* dT, double* eT, double* betaT) {
 #pragma unroll 1
   for (int kk = 0; kk < 16; kk += 2) {
-    householder_step<S, 0>(kk, A, tid, lds, refl, dT, eT, betaT);
-    householder_step<S, 1>(kk + 1, A, tid, lds, refl, dT, eT, betaT);
+    householder_step<S, 0>(kk, wave, A, alpha, diag, tid, lds, refl, dT, eT, betaT);
+    householder_step<S, 1>(kk + 1, wave, A, alpha, diag, tid, lds, refl, dT, eT, betaT);
   }
 }
 
@@ -1195,14 +1201,18 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     else
       gram_f64(static_cast<const float*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, reinterpret_cast<double*>(pool), tid, A, &flag_s);
     __syncthreads();  // the pool changes hands
-    EOQ_SFOR(s, 6, householder_stage<s>(A, tid, red, refl, dT, eT, betaT););
-    if (wave == 1) stash_reflector(red.v[1], 95, lane, refl);   // reflector 95: the stages stash one step behind
+    {
+      double alpha = 0.0, diag = 0.0;
+      const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+      EOQ_SFOR(s, 6, householder_stage<s>(w, A, alpha, diag, tid, red, refl, dT, eT, betaT););
+      if (w == 3) leave_reflector(red.v[1], 95, lane, alpha, diag, refl, dT, eT);   // a step is left behind in the next
+    }
     // the trailing 32 x 32 matrix (rows and columns 96 .. 127: sub-tiles a, b = 6, 7 of every lane) changes hands:
     // through LDS into the 64 lanes of wave 0, which finishes the reduction alone
     double* Ms = reinterpret_cast<double*>(u1);   // [32][33]
     double* vring = Ms + 32 * 33;                 // [30][32]: the reflectors of the last 30 steps as doubles
     {
-      const int ty = tid >> 4, tx = tid & 15;
+      const int ty = lane_row(tid), tx = tid & 15;
       EOQ_SFOR(a, 2, EOQ_SFOR(b, 2, Ms[(ty + 16 * a) * 33 + tx + 16 * b] = A[(6 + a) * 8 + 6 + b];););
     }
     __syncthreads();
