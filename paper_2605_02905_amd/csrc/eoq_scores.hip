@@ -16,8 +16,13 @@
 // f, 2 + f, 4 + f, 6 + f of ITS token, joins them, scales by its own stored norm and stores -- nothing changes lanes.
 // The low-rank term rides the f16 matrix cores the same way: rows e = 0 / 1 of head 2 q + f hold the binary16 hi / lo
 // parts of w_h = V_r^T q_h / sqrt(d), the B operand the token's stored coefficients.
-// The {-1, 0, +1} operands come out of a 256-entry LDS table indexed by one nibble of the sign plane and one nibble of a
-// magnitude plane: four coordinates of two terms per 8-byte read, in the order the matrix instruction takes them; the
+// The {-1, 0, +1} operands come out of tables in LDS.  Up to 2 bits one table of 256 entries, indexed by a nibble of the sign plane
+// and one of the magnitude plane: four coordinates of two terms per 8-byte read, in the order the matrix instruction takes
+// them.  From 3 bits on two tables of 16 words, the signs of a nibble and the byte mask of a nibble of a magnitude plane, and
+// an AND: sixteen words lie in sixteen banks, so the lanes' lookups, which collide at random in the large table, never do
+// (calls of more than 25 us: 9 % shorter at 3 and 4 bits, with the correction 8 and 9 %.  At 2 bits the additional lookups and
+// ANDs cost more than the collisions, 3 %; and with the correction at 4 bits and more than four heads, where 268 registers leave
+// one wave to a SIMD, the chain of lookup and AND does, 1 to 3 %: those have the table of pairs).  The
 // lane that owns a token reads its 8 bytes of every bit-plane straight from the record (lane half f: coordinates 64 f ..
 // 64 f + 63).
 #include "eoq_device.h"
@@ -224,7 +229,10 @@ void eoq_scores_i8_kernel(
   // A operands of the low-rank product, components 16 k2 .. + 15 of every block of the run: entry (16 f + 2 h + part) of a
   // block are components 8 f .. + 7 of head h, part 0 binary16(w), part 1 what that rounding lost
   __shared__ __align__(16) uint4 wop[2][SC_RUN_MAX * 32];
-  __shared__ __align__(16) uint2 nib_tab[256];
+  constexpr bool PAIRS = BITS <= 2 || (BITS == 4 && QJL && NQ == 4);   // one table of pairs
+  __shared__ __align__(PAIRS ? 16 : 64) uint2 nib_tab[PAIRS ? 256 : 16];   // PAIRS: signs, masked signs; else sign and mask words of a nibble: sign_tab, mask_tab
+  uint32_t* sign_tab = reinterpret_cast<uint32_t*>(nib_tab);
+  uint32_t* mask_tab = sign_tab + 16;
   __shared__ float qunit[SC_MAXG], punit[SC_MAXG];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave: scalar
@@ -276,9 +284,14 @@ void eoq_scores_i8_kernel(
     for (int e = 0; e < 4; ++e) {
       const uint32_t sb = ((tn >> e) & 1) ? 0x01u : 0xFFu;   // sign plane bit set: +1
       sd |= sb << (8 * e);
-      if ((xn >> e) & 1) td |= sb << (8 * e);
+      if constexpr (PAIRS) {
+        if ((xn >> e) & 1) td |= sb << (8 * e);
+      } else {
+        if ((tn >> e) & 1) td |= 0xFFu << (8 * e);
+      }
     }
-    nib_tab[tid] = make_uint2(sd, td);
+    if constexpr (PAIRS) nib_tab[tid] = make_uint2(sd, td);
+    else if (tid < 32) sign_tab[tid] = tid < 16 ? sd : td;
   }
   // coefficients of the multilinear form of the magnitudes: level number sum_p m_p 2^p is centroid L/2 + level of the
   // ascending N(0,1) table; coef[M] = sum over subsets S of M of (-1)^(|M| - |S|) centroid[L/2 + S]
@@ -452,6 +465,16 @@ void eoq_scores_i8_kernel(
     v16i acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0;
+    // byte j of the words made of a plane's word: four times the low / the high nibble of its byte j, a place in a table of words
+    auto places = [](uint32_t w, uint32_t (&at)[2]) __attribute__((always_inline)) {
+      at[0] = (w << 2) & 0x3C3C3C3Cu;
+      at[1] = (w >> 2) & 0x3C3C3C3Cu;
+      // opaque: otherwise every lookup shifts and masks the plane's word (two instructions) instead of taking a byte of these
+      asm("" : "+v"(at[0]), "+v"(at[1]));
+    };
+    auto entry = [](const uint32_t* table, const uint32_t (&at)[2], int nibble) __attribute__((always_inline)) {
+      return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const unsigned char*>(table) + __builtin_amdgcn_ubfe(at[nibble & 1], 8 * (nibble >> 1), 8));
+    };
     if constexpr (BITS <= 2) {
       // even / odd: byte j = (sign nibble | magnitude nibble << 4) of the low / high nibbles of byte j of the planes;
       // one table read gives the four sign bytes and the same bytes where the magnitude bit is set: 8 of the 16 bytes
@@ -477,7 +500,7 @@ void eoq_scores_i8_kernel(
           acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(Aq[i], B, acc, 0, 0, 0);
         );
       }
-    } else {
+    } else if constexpr (PAIRS) {
       // per nibble of four coordinates the TYPES terms, four bytes each: term 0 the signs, term 2^p from the table read
       // of magnitude plane p, the other terms (products of magnitude bits) as bitwise ANDs of those
       EOQ_SFOR(nb, 16,
@@ -498,6 +521,26 @@ void eoq_scores_i8_kernel(
           acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(Aq[nb * (TYPES / 4) + i], B, acc, 0, 0, 0);
         );
       );
+    } else {
+      // the same from the two small tables: term 2^p is the signs under the mask of magnitude plane p
+      EOQ_SFOR(wq, 2,
+        const uint32_t t = wq ? top1 : top0;
+        uint32_t sat[2], mat[BITS - 1][2];
+        places(t, sat);
+        EOQ_SFOR(p, BITS - 1, places(~(cur.pl[p][wq] ^ t), mat[p]););
+        EOQ_SFOR(nb, 8,
+          uint32_t term[TYPES];
+          term[0] = entry(sign_tab, sat, nb);
+          EOQ_SFOR(p, BITS - 1, term[1 << p] = term[0] & entry(mask_tab, mat[p], nb););
+          EOQ_SFOR(M, TYPES,
+            if constexpr ((M & (M - 1)) != 0) term[M] = term[M & -M] & term[M ^ (M & -M)];
+          );
+          EOQ_SFOR(i, TYPES / 4,
+            const v4i B = {(int)term[4 * i], (int)term[4 * i + 1], (int)term[4 * i + 2], (int)term[4 * i + 3]};
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(Aq[(8 * wq + nb) * (TYPES / 4) + i], B, acc, 0, 0, 0);
+          );
+        );
+      );
     }
     // ---- the planes of a head meet in the lane: registers 4 qq .. 4 qq + 3 are head 2 qq + hf; planes 0-1 and 2-3
     // are joined exactly in int32 (|register| < 2^18), the halves in float32 ----
@@ -509,15 +552,27 @@ void eoq_scores_i8_kernel(
       res[qq] = fmaf((float)hi, 65536.0f, (float)lo) * (Kq[qq] * rho);
     }
     if constexpr (QJL) {
-      // sign(Phi r_x) is one more plane of +-1: the table's first entry kind with the magnitude nibble at zero
+      // sign(Phi r_x) is one more plane of +-1: in the table of pairs the first entry kind with the magnitude nibble at zero
       v16i ac2;
 #pragma unroll
       for (int v = 0; v < 16; ++v) ac2[v] = 0;
-      EOQ_SFOR(i, 4,
-        const uint32_t sw = cur.sg[0][i >> 1] >> (16 * (i & 1));
-        const v4i B = {(int)nib_tab[sw & 0xFu].x, (int)nib_tab[(sw >> 4) & 0xFu].x, (int)nib_tab[(sw >> 8) & 0xFu].x, (int)nib_tab[(sw >> 12) & 0xFu].x};
-        ac2 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ap[i], B, ac2, 0, 0, 0);
-      );
+      if constexpr (PAIRS) {
+        EOQ_SFOR(i, 4,
+          const uint32_t sw = cur.sg[0][i >> 1] >> (16 * (i & 1));
+          const v4i B = {(int)nib_tab[sw & 0xFu].x, (int)nib_tab[(sw >> 4) & 0xFu].x, (int)nib_tab[(sw >> 8) & 0xFu].x, (int)nib_tab[(sw >> 12) & 0xFu].x};
+          ac2 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ap[i], B, ac2, 0, 0, 0);
+        );
+      } else {
+        EOQ_SFOR(wq, 2,
+          uint32_t sat[2];
+          places(cur.sg[0][wq], sat);
+          EOQ_SFOR(i, 2,
+            v4i B;
+            EOQ_SFOR(e, 4, B[e] = (int)entry(sign_tab, sat, 4 * i + e););
+            ac2 = __builtin_amdgcn_mfma_i32_32x32x32_i8(Ap[2 * wq + i], B, ac2, 0, 0, 0);
+          );
+        );
+      }
       const float gam = half_bits_to_float((uint16_t)cur.gam[0]);
 #pragma unroll
       for (int qq = 0; qq < NQ; ++qq) {
