@@ -24,6 +24,8 @@ constexpr int D = EOQ_D;
 // lies in LDS in the binary16 it is stored in, and the columns of Pi are read when the rows are done with their registers, which
 // leaves room for four a unit instead of two.  8192 workgroups of 64 rows at 1 bit 244 -> 200 us, 1000 at 4 bits 41 -> 36.5 (of
 // which 13 are the matrix cores' rate and 8 that of memory).
+// The product comes out with the coordinates of a row in a lane's registers (HalfBounds): 2 us less of a compress call of 125
+// blocks of 512 at 4 bits than with comparison masks dealt out to the rows.
 // ---------------------------------------------------------------------------
 constexpr int ENC_ROWS = 64;
 constexpr int ENC_THREADS = 256;
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void eoq_encode_kernel(
 #pragma unroll
     for (int k = 0; k < 8; ++k) *reinterpret_cast<float4*>(X + (8 * k + (tid >> 5)) * LDS_X + 4 * (tid & 31)) = x[k];
   }
-  Bounds<BITS> bnd;
+  HalfBounds<BITS> bnd;
   bnd.load(tab + 16);
   __syncthreads();
 
@@ -119,39 +121,36 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void eoq_encode_kernel(
   // z = Pi u (Alg. 1 line 4) and index of the nearest centroid (line 5): two tiles of 32 rows
   float4 P[16];
 #pragma unroll
-  for (int m = 0; m < 16; ++m) P[m] = *reinterpret_cast<const float4*>(pi + (32 * wave + l32) * D + 8 * m + 4 * hf);
+  for (int m = 0; m < 16; ++m) P[m] = *reinterpret_cast<const float4*>(pi + (32 * wave + plane_row(l32)) * D + 8 * m + 4 * hf);
   float16v acc[2];
   EOQ_SFOR(t, 2, EOQ_SFOR(v, 16, acc[t][v] = 0.0f;););
   EOQ_SFOR(m, 16,
     const float4 u0 = *reinterpret_cast<const float4*>(X + l32 * LDS_X + 8 * m + 4 * hf);
     const float4 u1 = *reinterpret_cast<const float4*>(X + (32 + l32) * LDS_X + 8 * m + 4 * hf);
-    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.x, P[m].x, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.x, P[m].x, acc[1], 0, 0, 0);
-    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.y, P[m].y, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.y, P[m].y, acc[1], 0, 0, 0);
-    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.z, P[m].z, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.z, P[m].z, acc[1], 0, 0, 0);
-    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(u0.w, P[m].w, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(u1.w, P[m].w, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].x, u0.x, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].x, u1.x, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].y, u0.y, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].y, u1.y, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].z, u0.z, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].z, u1.z, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].w, u0.w, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(P[m].w, u1.w, acc[1], 0, 0, 0);
   );
-  // every comparison mask holds one bit-plane of coordinates 32 w .. 32 w + 31 for the rows 8 q + e (low word) and
-  // 8 q + 4 + e (high word)
+  // bit-planes of row 32 t + l32, two half words at a time: the lower half of the wave stores the first, the upper half the second
+  uint32_t held = 0u;
   EOQ_SFOR(t, 2,
-    uint32_t outw[BITS];
-    EOQ_SFOR(p, BITS, outw[p] = 0u;);
-    EOQ_SFOR(v, 16,
-      unsigned long long m[BITS];
-      bnd.masks(acc[t][v], m);
-      constexpr int row_lo = 8 * (v >> 2) + (v & 3);
-      EOQ_SFOR(p, BITS,
-        outw[p] = write_lane<row_lo>(outw[p], (uint32_t)m[p]);
-        outw[p] = write_lane<row_lo + 4>(outw[p], (uint32_t)(m[p] >> 32));
-      );
+    uint32_t below[BITS];
+    bnd.planes(acc[t], below);
+    EOQ_SFOR(p, BITS,
+      constexpr int item = t * BITS + p;
+      if constexpr (item % 2 == 0) {
+        held = below[p];
+      } else {
+        constexpr int at_a = (item - 1) / BITS * 32 * ROWB + (item - 1) % BITS * 16; constexpr int at_b = 32 * t * ROWB + 16 * p;
+        uint8_t* dst = codes + (slot * (size_t)n + row0 + l32) * ROWB + 4 * wave + (hf ? at_b : at_a);
+        *reinterpret_cast<uint32_t*>(dst) = plane_words(held, below[p]);
+      }
     );
-    if (lane < 32) {
-      uint8_t* dst = codes + (slot * (size_t)n + row0 + 32 * t + lane) * ROWB + 4 * wave;
-      EOQ_SFOR(p, BITS, *reinterpret_cast<uint32_t*>(dst + 16 * p) = outw[p];);
-    }
   );
 }
 

@@ -149,60 +149,59 @@ __device__ __forceinline__ void static_for(F&& f) {
 #define EOQ_SFOR(var, n, ...) eoqdev::static_for<0, n>([&](auto var##_ic) __attribute__((always_inline)) { \
   constexpr int var = decltype(var##_ic)::value; __VA_ARGS__ })
 
-// old with lane LANE (a constant) replaced by the wave-uniform value val: one instruction (v_writelane_b32) where a
-// compare and a select per lane would be two.  Reached through the compiler's own intrinsic, not inline assembly:
-// a vector compare that has just written the scalar operand must be two instructions away, and only the compiler
-// sees both.
-extern "C" __device__ uint32_t eoq_llvm_writelane(uint32_t val, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
-template <int LANE>
-__device__ __forceinline__ uint32_t write_lane(uint32_t old, uint32_t val) {
-  return eoq_llvm_writelane(val, LANE, old);
-}
+// Bit-planes of the cells of a product Pi u^T (32 coordinates by 32 tokens).  A lane of half hf holds rows 8 (v / 4) + 4 hf + v % 4
+// of column l32: with Pi's rows in the order of plane_row, coordinate 16 hf + v of its token in register v.
+__device__ __forceinline__ int plane_row(int l32) { return 16 * ((l32 >> 2) & 1) + 4 * (l32 >> 3) + (l32 & 3); }
 
-// Decision boundaries of the codebook as separate values, not an array or a vector: the compiler turns a select between
-// two elements into an element at a selected index (scratch memory for an array, a chain of sixteen selects for a
-// register vector).
+// Index of a cell = number of boundaries <= z, found from the top bit down by signs, which are appended from below to words of the
+// lane: one instruction for the sign of z, three for every further bit (the boundary with the sign of z, the difference, its sign),
+// no mask in scalar registers.  The table is symmetric and its middle boundary 0 (lloyd_max), so the positive half of it is
+// enough.  A set bit stands for "below the boundary"; z is a sum that starts from +0 and never -0.  Which half of the remaining
+// cells comes next follows from the sign of the difference, not from |z|, or a negative z on a boundary would take the other one.
+// The boundaries are separate values, not an array or a vector: the compiler turns a select between two elements into an element
+// at a selected index (scratch memory for an array, a chain of sixteen selects for a register vector).
 template <int BITS>
-struct Bounds {
-  float b0, b1, b2, b3, b4, b5, b6, b7, b8, b9, b10, b11, b12, b13, b14;
+struct HalfBounds {
+  float c0, c1, c2, c3, c4, c5, c6;   // boundaries 2^(BITS-1) ..
   __device__ __forceinline__ void load(const float* __restrict__ bnd) {
-    constexpr int N = (1 << BITS) - 1;
-    b0 = bnd[0];
-    b1 = 1 < N ? bnd[1] : 0.0f; b2 = 2 < N ? bnd[2] : 0.0f;
-    b3 = 3 < N ? bnd[3] : 0.0f; b4 = 4 < N ? bnd[4] : 0.0f; b5 = 5 < N ? bnd[5] : 0.0f; b6 = 6 < N ? bnd[6] : 0.0f;
-    b7 = 7 < N ? bnd[7] : 0.0f; b8 = 8 < N ? bnd[8] : 0.0f; b9 = 9 < N ? bnd[9] : 0.0f; b10 = 10 < N ? bnd[10] : 0.0f;
-    b11 = 11 < N ? bnd[11] : 0.0f; b12 = 12 < N ? bnd[12] : 0.0f; b13 = 13 < N ? bnd[13] : 0.0f; b14 = 14 < N ? bnd[14] : 0.0f;
+    constexpr int N = (1 << (BITS - 1)) - 1;
+    const float* b = bnd + N + 1;
+    c0 = 0 < N ? b[0] : 0.0f; c1 = 1 < N ? b[1] : 0.0f; c2 = 2 < N ? b[2] : 0.0f;
+    c3 = 3 < N ? b[3] : 0.0f; c4 = 4 < N ? b[4] : 0.0f; c5 = 5 < N ? b[5] : 0.0f; c6 = 6 < N ? b[6] : 0.0f;
   }
-  // index = number of boundaries <= z, found from the top bit down; m[p] is bit p of the lanes' indices.  The candidates
-  // of the later levels are selected by the earlier decisions as soon as those are known, so the last comparison waits
-  // for one select only.
-  __device__ __forceinline__ void masks(float z, unsigned long long (&m)[BITS]) const {
-    if constexpr (BITS == 1) {
-      m[0] = __ballot(z >= b0);
-    } else if constexpr (BITS == 2) {
-      const bool t1 = z >= b1;
-      m[1] = __ballot(t1);
-      m[0] = __ballot(z >= (t1 ? b2 : b0));
+  __device__ __forceinline__ void append(float z, uint32_t (&below)[BITS]) const {
+    auto push = [](uint32_t& to, float x) __attribute__((always_inline)) { to = __builtin_amdgcn_alignbit(to, __float_as_uint(x), 31); };
+    auto outer = [&](float e) __attribute__((always_inline)) { return (int)(__float_as_uint(e) ^ __float_as_uint(z)) >= 0; };
+    push(below[BITS - 1], z);
+    if constexpr (BITS == 2) {
+      push(below[0], z - copysignf(c0, z));
     } else if constexpr (BITS == 3) {
-      const bool t2 = z >= b3;
-      m[2] = __ballot(t2);
-      const float lo0 = t2 ? b4 : b0, lo1 = t2 ? b6 : b2;
-      const bool t1 = z >= (t2 ? b5 : b1);
-      m[1] = __ballot(t1);
-      m[0] = __ballot(z >= (t1 ? lo1 : lo0));
-    } else {
-      const bool t3 = z >= b7;
-      m[3] = __ballot(t3);
-      const float q0 = t3 ? b8 : b0, q1 = t3 ? b10 : b2, q2 = t3 ? b12 : b4, q3 = t3 ? b14 : b6;
-      const float h0 = t3 ? b9 : b1, h1 = t3 ? b13 : b5;
-      const bool t2 = z >= (t3 ? b11 : b3);
-      m[2] = __ballot(t2);
-      const float lo0 = t2 ? q2 : q0, lo1 = t2 ? q3 : q1;
-      const bool t1 = z >= (t2 ? h1 : h0);
-      m[1] = __ballot(t1);
-      m[0] = __ballot(z >= (t1 ? lo1 : lo0));
+      const float e1 = z - copysignf(c1, z);
+      push(below[1], e1);
+      push(below[0], z - copysignf(outer(e1) ? c2 : c0, z));
+    } else if constexpr (BITS == 4) {
+      const float e2 = z - copysignf(c3, z);
+      push(below[2], e2);
+      const bool o2 = outer(e2);
+      const float mid = o2 ? c5 : c1, lo = o2 ? c4 : c0, hi = o2 ? c6 : c2;
+      const float e1 = z - copysignf(mid, z);
+      push(below[1], e1);
+      push(below[0], z - copysignf(outer(e1) ? hi : lo, z));
     }
   }
+  // bit v of below[p]: plane p of the lane's coordinate v
+  template <typename Acc>
+  __device__ __forceinline__ void planes(const Acc& z, uint32_t (&below)[BITS]) const {
+    EOQ_SFOR(p, BITS, below[p] = 0u;);
+    EOQ_SFOR(v, 16, append(z[15 - v], below););
+    const bool nan = z[0] != z[0];   // a token with a NaN: all its coordinates are, and lie in cell 0
+    EOQ_SFOR(p, BITS, below[p] = nan ? 0xFFFFu : below[p];);
+  }
 };
+// Half words a and b of the lanes: the lower half of the wave gets the plane's word of a, the upper half that of b.
+__device__ __forceinline__ uint32_t plane_words(uint32_t a, uint32_t b) {
+  const auto w = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return ~(w[0] | (w[1] << 16));
+}
 
 }  // namespace eoqdev

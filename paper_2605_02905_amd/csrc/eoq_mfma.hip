@@ -706,8 +706,12 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
 //     R^T = S^T - V16 C16^T  accumulator preloaded with S (the registers that were the B operand above)
 //     rho_t = |R_t|, u = R sqrt(d)/rho as binary16 into the LDS tile (in place of S)
 //   phase 2 (wave w = coordinates 32w .. 32w+31, rotation stationary in registers):
-//     z = u Pi^T with Pi as hi + lo, Lloyd-Max index by binary search on the boundaries; the comparison
-//     masks are the packed bit-planes (32 coordinates of two tokens per compare).
+//     z^T = Pi u^T with Pi as hi + lo (up to 3 bits its binary16 rounding): a lane gets sixteen coordinates in a row of ONE token,
+//     finds their Lloyd-Max cells by signs and appends the bits to half words of the bit-planes (HalfBounds); two half waves
+//     make whole words of them, one store for two planes.
+//     (z with the tokens in registers, comparison masks as bit-planes and a v_writelane for every token and plane took 7, 13 and
+//     23 instructions for 64 coordinates at 2, 3 and 4 bits instead of 4, 10 and 18: 2048 blocks of 1024 x 128 at 3 bits
+//     1146 -> 1098 us a compress call, 32768 of 512 x 128 at 2 bits 13282 -> 13211.)
 // ---------------------------------------------------------------------------------------------
 typedef _Float16 half4v __attribute__((ext_vector_type(4)));
 union H4 {
@@ -748,7 +752,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
   u32x4 pre[8];
   EOQ_SFOR(it, 8, pre[it] = *reinterpret_cast<const u32x4*>(src0 + (4 * it + (lane >> 4)) * tok + (lane & 15) * 8););
 
-  // stationary rotation operand: rows c = 32w + l32 of Pi.  Up to 3 bits the binary16 rounding of Pi alone (one
+  // stationary rotation operand: rows 32w .. 32w + 31 of Pi.  Up to 3 bits the binary16 rounding of Pi alone (one
   // matrix-core pass): it moves z sqrt(d) by a sum of 128 independent roundings, standard deviation 1.4e-4, the size of
   // what the binary16 rounding of u moves it by already; a coordinate that close to a cell boundary is reconstructed
   // equally well from either cell.  At 4 bits, where the cells are narrowest, the part that rounding lost goes through
@@ -756,14 +760,14 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
   constexpr bool ROT_LO = BITS == 4;
   H8 Bhi[8], Blo[ROT_LO ? 8 : 1];
   {
-    const int c = 32 * wave + l32;
+    const int c = 32 * wave + plane_row(l32);
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       Bhi[kk].u = *reinterpret_cast<const uint4*>(pih + c * D + 16 * kk + 8 * hf);
       if constexpr (ROT_LO) Blo[kk].u = *reinterpret_cast<const uint4*>(pih + D * D + c * D + 16 * kk + 8 * hf);
     }
   }
-  Bounds<BITS> bnd;
+  HalfBounds<BITS> bnd;
   bnd.load(tab + 16);
 
   // factors of the block: W = V diag(phi/sigma) split into hi + lo, and V16^T.  Only the rows below the rank
@@ -841,13 +845,15 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
             Cacc = mfma8(al, Sreg[kk], Cacc);
           }
           // stored coefficients C16 = binary16(U diag(phi)); their negatives are the next B operand
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int i = 8 * (v >> 2) + 4 * hf + (v & 3);
-            const uint16_t hb = float_to_half_bits_clamped_by_mode(Cacc[v]);
-            __builtin_amdgcn_raw_buffer_store_b16(hb, lbuf, cf_lane, (8 * (v >> 2) + (v & 3)) * n * 2, 0);
-            Cneg[v >> 2].s[v & 3] = (i < r) ? (uint16_t)(hb ^ 0x8000u) : (uint16_t)0;  // rows >= r of W are not initialised
-          }
+          EOQ_SFOR(q, 4,
+            if (8 * q < r) {   // uniform
+              EOQ_SFOR(e, 4,
+                const uint16_t hb = float_to_half_bits_clamped_by_mode(Cacc[4 * q + e]);
+                __builtin_amdgcn_raw_buffer_store_b16(hb, lbuf, cf_lane, (8 * q + e) * n * 2, 0);
+                Cneg[q].s[e] = (8 * q + 4 * hf + e < r) ? (uint16_t)(hb ^ 0x8000u) : (uint16_t)0;  // rows >= r of W are not initialised
+              );
+            }
+          );
         }
 #pragma unroll
         for (int k2 = 0; k2 < 4; ++k2) {
@@ -891,43 +897,31 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
     __syncthreads();
     // ---- phase 2 ---- (unrolled: a loop with stores in it would make the compiler wait for the rows requested above
     // before entering it)
-#pragma unroll
-    for (int tau = 0; tau < CHUNK / 32; ++tau) {
+    uint32_t held = 0u;
+    EOQ_SFOR(tau, CHUNK / 32,
       float16v acc;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        H8 a;
-        a.u = *reinterpret_cast<const uint4*>(X + (32 * tau + l32) * ZLD + 16 * kk + 8 * hf);
-        acc = mfma16(a, Bhi[kk], acc);
-        if constexpr (ROT_LO) acc = mfma16(a, Blo[kk], acc);
-      }
-      // index = number of boundaries <= z, found from the top bit down; every comparison mask holds one
-      // bit-plane of coordinates 32w..32w+31 for the tokens 8q+e (low word) and 8q+4+e (high word)
-      uint32_t outw[BITS];
-#pragma unroll
-      for (int p = 0; p < BITS; ++p) outw[p] = 0u;
-      EOQ_SFOR(v, 16,
-        const float z = acc[v];
-        unsigned long long m[BITS];
-        bnd.masks(z, m);
-        constexpr int row_lo = 8 * (v >> 2) + (v & 3);   // token of the low word; the high word is row_lo + 4
-        EOQ_SFOR(p, BITS,
-          outw[p] = write_lane<row_lo>(outw[p], (uint32_t)m[p]);
-          outw[p] = write_lane<row_lo + 4>(outw[p], (uint32_t)(m[p] >> 32));
-        );
+      EOQ_SFOR(v, 16, acc[v] = 0.0f;);
+      EOQ_SFOR(kk, 8,
+        H8 u;
+        u.u = *reinterpret_cast<const uint4*>(X + (32 * tau + l32) * ZLD + 16 * kk + 8 * hf);
+        acc = mfma16(Bhi[kk], u, acc);
+        if constexpr (ROT_LO) acc = mfma16(Blo[kk], u, acc);
       );
-      // lane t < 32 stores the words of token t; the other lanes aim past the end of the descriptor and are dropped
-      // (no branch: after a branch around the stores the compiler could not count them when it waits for the rows
-      // requested above, and would wait for everything)
-      {
-        const int off = (lane < 32) ? (t0 + 32 * tau + lane) * ROWB + 4 * wave : 0x7FFFFFF0;
-#pragma unroll
-        for (int p = 0; p < BITS; ++p) __builtin_amdgcn_raw_buffer_store_b32(outw[p], cbuf, off, p * 16, 0);
-      }
+      // bit-planes of token 32 tau + l32, half words of a lane, two at a time (number tau BITS + p of the chunk and the one before):
+      // the lower half of the wave stores the word of the earlier one, the upper half that of the later one
+      uint32_t below[BITS];
+      bnd.planes(acc, below);
+      EOQ_SFOR(p, BITS,
+        constexpr int item = tau * BITS + p;
+        if constexpr (item % 2 == 0) {
+          held = below[p];
+        } else {
+          constexpr int at_a = (item - 1) / BITS * 32 * ROWB + (item - 1) % BITS * 16; constexpr int at_b = 32 * tau * ROWB + 16 * p;
+          __builtin_amdgcn_raw_buffer_store_b32(plane_words(held, below[p]), cbuf, (t0 + l32) * ROWB + 4 * wave + (hf ? at_b - at_a : 0) + at_a, 0, 0);
+        }
+      );
       __builtin_amdgcn_sched_barrier(0);   // one tile at a time: keeps the registers of the rows in flight free
-    }
+    );
   }
 }
 

@@ -280,6 +280,34 @@ def test_blocks_with_inf_or_nan_are_flagged_and_stored_with_rank_zero(dtype, sol
     assert bool(torch.isfinite(x[0]).all()) and bool(torch.isfinite(x[2]).all())
 
 
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+def test_bit_planes_of_rows_without_a_direction(dtype, bits):
+    """A row of zeros is 0 in every coordinate, which is on the middle boundary: the cell above it.  A float32 row with a NaN has
+    a NaN in every coordinate, at or above no boundary: cell 0.  Every other row's planes are the oracle's, wherever in its tile
+    and half wave the row lies and whichever of the planes share a store."""
+    spec = synth.BlockSpec("planes", n=128, n_tensors=1, blocks_per_tensor=3, rank_lo=2, rank_hi=5)
+    blocks, _ = synth.make_blocks(spec, seed=29)
+    blocks = blocks.to(dtype)
+    rows = [0, 31, 32, 65, 127]
+    blocks[0, rows] = 0.0
+    blocks[1, rows, 5] = float("nan")
+    ctx = eoq.Context(n=128, bits=bits)
+    rec, _ = ctx.eoq_compress(blocks.to(DEV).contiguous())
+    torch.cuda.synchronize()
+    codes = rec.codes.cpu().reshape(3, 128, bits, 16)
+    want = torch.zeros(bits, 16, dtype=torch.uint8)
+    if dtype == torch.float32:
+        assert torch.equal(codes[1, rows], want.expand(5, bits, 16))
+    want[bits - 1] = 255
+    assert torch.equal(codes[0, rows], want.expand(5, bits, 16))
+    finite = blocks[[0, 2]]
+    b64 = finite.double().numpy()
+    _, sub, lam = _gpu_compress(finite, bits, 128)
+    U.compare_compress(b64, sub, lam, U.oracle_compress(b64, bits), bits)
+    assert torch.equal(sub.codes.cpu(), rec.codes.cpu()[[0, 2]])
+
+
 def test_repeated_singular_values_go_to_the_jacobi_solver():
     """Two exactly equal leading singular values: any orthonormal basis of their plane is a valid answer, so only
     what is unique is compared (spectrum, rank, shrunk values, the low-rank product) and the record is checked
