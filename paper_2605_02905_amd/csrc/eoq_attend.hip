@@ -36,17 +36,29 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, si
 }
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
+// Bits c of a and b side by side, those of even c in `even` (bits c, c + 1), those of odd c in `odd` (bits c - 1, c).  Both words
+// pass through an opaque statement together: the compiler (clang 22 of ROCm 7.2) otherwise let the first result take b's register
+// while the second still needed b, in one of the places this is expanded to, and the codes of odd coordinates were wrong there.
+__device__ __forceinline__ void interleave(uint32_t a, uint32_t b, uint32_t& even, uint32_t& odd) {
+  even = bfi(0x55555555u, a, b << 1);
+  odd = bfi(0x55555555u, a >> 1, b);
+  asm("" : "+v"(even), "+v"(odd));
+}
+
 // Partial sums of the attention output.  Every wave is a worker of its own: wave number w of a head takes the tokens
 // [w, w + 1) * 64 ppw of it, 64 at a time, without a barrier; the four waves of a workgroup meet once at the end.
 //
 // Codebook term, a_h[c] = sum_t w'_ht centroid[code_tc] with w' = w rho / sqrt(d): a contraction over TOKENS, on the
 // integer matrix cores and exact there.  The matrix instruction wants sixteen consecutive tokens of one coordinate in a
 // lane, the record holds eight coordinates of one token in a byte.  Matrix instructions turn the one into the other: the
-// lane that owns a token turns the nibbles of its bit-planes into the code numbers of its coordinates, one byte each
-// (one or two reads of a 256-entry LDS table per four coordinates), and v_mfma_i32_32x32x32_i8 multiplies 32 tokens x
-// 32 coordinates by the identity: lane (coordinate, half) receives the codes of sixteen tokens of ITS coordinate.  The
-// second tile of 32 tokens goes into the same accumulator with its codes in the second byte (table of 4 code, identity
-// of 64), so two registers make one word of four code bytes with one instruction.  v_perm_b32 with a table of eight
+// lane that owns a token puts the bits of a code side by side (interleave) and takes every eighth coordinate's code at once, a
+// byte each, with a shift and a mask: which coordinates an instruction gets is free as long as the sums are put where they
+// belong.  v_mfma_i32_32x32x32_i8 multiplies 32 tokens x 32 coordinates by the identity: lane (coordinate, half) receives the
+// codes of sixteen tokens of ITS coordinate.  (Four neighbouring coordinates by one or two reads of a table in LDS, which the
+// lanes' indices collide in: 8.4 M tokens of 2 bits 0.15 -> 0.14 ms; 1 M tokens, four and eight heads, 1 to 4 bits, us: 37 / 46,
+// 43 / 57, 62 / 107, 84 / 120 -> 35 / 44, 40 / 53, 57 / 96, 79 / 115.)  The second tile of 32 tokens goes into the same
+// accumulator with its codes in the second byte (4 code, identity of 64), so two registers make one word of four code bytes with
+// one instruction.  v_perm_b32 with a table of eight
 // bytes then turns four codes into four operand bytes at once:
 //   up to 2 bits  centroid = s (c_0 + m (c_1 - c_0)) with s = +-1, m = 0/1: terms s and s m in {-1, 0, 1}, the coefficient
 //                 is multiplied into the weights; with at most four heads (16 operand rows of 32) the second term has
@@ -97,7 +109,6 @@ struct AttendShape {
   static constexpr int BS_BYTES = PARTS3_BYTES + RING * RING_BYTES;
   static constexpr int BASE_BYTES = STAGE_BYTES > LIN_BYTES ? STAGE_BYTES : LIN_BYTES;
   static constexpr int WAVE_BYTES = BASE_BYTES + BS_BYTES + RH * D * 4 + 64;
-  static constexpr int NTAB = BITS <= 2 ? 2 : 3;
   static constexpr bool AHEAD = BITS == 1 || SPLIT;          // registers left to work ahead of a coordinate tile
 };
 
@@ -112,7 +123,6 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
   constexpr int TERMS = S::TERMS, NQ = S::NQ, SETS = S::SETS, WSETS = S::WSETS, RH = S::RH, JT = S::JT;
   constexpr int ROWB = BITS * D / 8;
   __shared__ __align__(16) unsigned char mem[4 * S::WAVE_BYTES];
-  __shared__ __align__(16) uint32_t tab_s[S::NTAB * 256];   // code bytes of four coordinates by two nibbles, times 1, 4 (and 16)
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5, l16 = lane & 15, kg = lane >> 4;
@@ -133,16 +143,9 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
   float* unit_s = rot + RH * D;                                               // value of one integer unit, per head
   float* winv_s = unit_s + RH;                                                // 1 / scale of the binary16 parts, per head
 
-  {
-    uint32_t v = 0u;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v |= (((tid >> e) & 1) | (BITS >= 2 ? ((tid >> (4 + e)) & 1) << 1 : 0)) << (8 * e);
-#pragma unroll
-    for (int k = 0; k < S::NTAB; ++k) tab_s[k * 256 + tid] = v << (2 * k);
-  }
   for (int e = lane; e < S::DIG_BYTES / 4; e += 64) reinterpret_cast<uint32_t*>(dig)[e] = 0u;
   for (int e = lane; e < RH * D; e += 64) rot[e] = 0.0f;
-  __syncthreads();
+  __builtin_amdgcn_wave_barrier();   // the wave's own memory
 
   // operand tables: four codes to four bytes of term t, entry i for code i (low register: codes 0 .. 3)
   uint32_t lut[TERMS][BITS == 4 ? 4 : 2];
@@ -239,7 +242,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
     };
 
     constexpr int ASETS = HALF ? 2 : 1;
-    v16i acc[ASETS][JT];       // coordinates 64 (l32 / 16) + 16 (2 z + j) + l32 % 16
+    v16i acc[ASETS][JT];       // coordinates 64 (l32 / 16) + 32 (t / 2) + t % 2 + 2 (l32 / 4 % 4) + 8 (l32 % 4), t = 2 z + j
     EOQ_SFOR(s, ASETS, EOQ_SFOR(j, JT, EOQ_SFOR(v, 16, acc[s][j][v] = 0;);););
     float4v lr[SETS][2];       // row 4 part + head, column = component l16 / 16 + l16
     EOQ_SFOR(s, SETS, EOQ_SFOR(k, 2, EOQ_SFOR(v, 4, lr[s][k][v] = 0.0f;);););
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
 
     auto flush_rot = [&]() __attribute__((always_inline)) {
       EOQ_SFOR(s, ASETS, EOQ_SFOR(j, JT,
-        const int c = 64 * (l32 >> 4) + 16 * (2 * z + j) + l16;
+        const int c = 64 * (l32 >> 4) + 32 * (z + (j >> 1)) + (j & 1) + 2 * ((l32 >> 2) & 3) + 8 * (l32 & 3);
         auto joined = [&](auto first) __attribute__((always_inline)) {   // the four bytes from register `first` on
           constexpr int v = decltype(first)::value;
           return fma(fma(fma((double)acc[s][j][v + 3], 256.0, (double)acc[s][j][v + 2]), 256.0, (double)acc[s][j][v + 1]), 256.0, (double)acc[s][j][v]);
@@ -471,19 +474,31 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       v4i A[TERMS][2];
       if constexpr (!HALF) { EOQ_SFOR(t, TERMS, EOQ_SFOR(m, 2, A[t][m] = weight_bytes(set0, t_ic, m_ic););); }
       // ---- codes: bytes, transposed, translated, multiplied ----
-      // even / odd: byte = (nibble of plane 0 | nibble of plane 1 << 4) of the low / high nibbles
-      uint32_t ev[2][HALF ? 1 : 2][BITS > 2 ? 2 : 1]; uint32_t od[2][HALF ? 1 : 2][BITS > 2 ? 2 : 1];
-      EOQ_SFOR(i, 2, EOQ_SFOR(w, (HALF ? 1 : 2), EOQ_SFOR(k, (BITS > 2 ? 2 : 1),
-        const uint32_t x = f.pl[i][2 * k][w];
-        if constexpr (2 * k + 1 < BITS) {
-          const uint32_t y = f.pl[i][2 * k + 1][w];
-          ev[i][w][k] = bfi(0x0F0F0F0Fu, x, y << 4);
-          od[i][w][k] = bfi(0x0F0F0F0Fu, x >> 4, y);
+      // The bits of a code side by side: word cw[i][w][t] holds codes of the plane words w, GROUP bits each, t % 2 the coordinate's
+      // lowest bit and, in groups of four bits, t / 2 the next one
+      uint32_t cw[2][HALF ? 1 : 2][BITS == 1 ? 1 : (BITS == 2 ? 2 : 4)];
+      EOQ_SFOR(i, 2, EOQ_SFOR(w, (HALF ? 1 : 2),
+        const uint32_t p0 = f.pl[i][0][w];
+        if constexpr (BITS == 1) {
+          cw[i][w][0] = p0;
         } else {
-          ev[i][w][k] = x & 0x0F0F0F0Fu;
-          od[i][w][k] = (x >> 4) & 0x0F0F0F0Fu;
+          const uint32_t p1 = f.pl[i][1][w];
+          uint32_t even; uint32_t odd;
+          interleave(p0, p1, even, odd);
+          if constexpr (BITS == 2) {
+            cw[i][w][0] = even;
+            cw[i][w][1] = odd;
+          } else {
+            const uint32_t p2 = f.pl[i][2][w]; const uint32_t p3 = BITS == 4 ? f.pl[i][BITS - 1][w] : 0u;
+            uint32_t even2; uint32_t odd2;
+            interleave(p2, p3, even2, odd2);
+            cw[i][w][0] = bfi(0x33333333u, even, even2 << 2);
+            cw[i][w][1] = bfi(0x33333333u, odd, odd2 << 2);
+            cw[i][w][2] = bfi(0x33333333u, even >> 2, even2);
+            cw[i][w][3] = bfi(0x33333333u, odd >> 2, odd2);
+          }
         }
-      );););
+      ););
       // ---- low-rank sums of this block ----
       if (r > 0) {
         EOQ_SFOR(s, SETS, EOQ_SFOR(i, 2,
@@ -502,19 +517,17 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       }
       if (last_in_block || last) flush_lin(b, last);
       request_next(f);
-      // coordinate tile j: where registers allow, the table reads of tile j + 2 and the transposing products of tile j + 1
-      // are issued before tile j is packed, so a wave has work while they are on their way
+      // coordinate tile j: where registers allow, the transposing products of tile j + 1 are issued before tile j is packed, so a
+      // wave has work while they are on their way
+      // word w of tile j: byte e is the code of coordinate 32 (j / 2) + j % 2 + 2 w + 8 e of the lane's, times 4 for the second 32
+      // tokens: one shift and one mask for four codes
       auto code_bytes = [&](auto jc, v4i (&X)[2]) __attribute__((always_inline)) {
         constexpr int j = decltype(jc)::value;
         EOQ_SFOR(i, 2, EOQ_SFOR(w, 4,
-          constexpr int sh = 8 * ((2 * j + (w >> 1)) & 3);
-          const uint32_t src0 = ((w & 1) ? od[i][j >> 1][0] : ev[i][j >> 1][0]) >> sh;
-          uint32_t x = tab_s[i * 256 + (src0 & 0xFFu)];
-          if constexpr (BITS > 2) {
-            const uint32_t src1 = ((w & 1) ? od[i][j >> 1][1] : ev[i][j >> 1][1]) >> sh;
-            x |= tab_s[(i + 1) * 256 + (src1 & 0xFFu)];
-          }
-          X[i][w] = (int)x;
+          constexpr int at = (BITS == 1 ? (j & 1) + 2 * w : (BITS == 2 ? 2 * w : 4 * (w >> 1))) - 2 * i;
+          constexpr uint32_t mask = (BITS == 1 ? 0x01010101u : (BITS == 2 ? 0x03030303u : 0x0F0F0F0Fu)) << (2 * i);
+          const uint32_t src = cw[i][j >> 1][BITS == 1 ? 0 : (BITS == 2 ? (j & 1) : (j & 1) + 2 * (w & 1))];
+          X[i][w] = (int)((at < 0 ? src << (at < 0 ? -at : 0) : src >> (at < 0 ? 0 : at)) & mask);
         ););
       };
       auto transpose = [&](const v4i (&X)[2]) __attribute__((always_inline)) {
@@ -523,12 +536,11 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
         cd = __builtin_amdgcn_mfma_i32_32x32x32_i8(X[0], id1, cd, 0, 0, 0);
         return __builtin_amdgcn_mfma_i32_32x32x32_i8(X[1], id64, cd, 0, 0, 0);
       };
-      v4i X[2][2];
+      v4i X[2];
       v16i cd[2];
       if constexpr (S::AHEAD) {
-        code_bytes(std::integral_constant<int, 0>{}, X[0]);
-        code_bytes(std::integral_constant<int, 1>{}, X[1]);
-        cd[0] = transpose(X[0]);
+        code_bytes(std::integral_constant<int, 0>{}, X);
+        cd[0] = transpose(X);
       }
       // register v: token 8 (v / 4) + 4 hf + v % 4 of the first tile in byte 0, of the second in byte 1
       auto pack = [&](const v16i& c, uint32_t (&pk)[8]) __attribute__((always_inline)) {
@@ -562,8 +574,9 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
         // both tiles first, then half by half: the weight bytes of one half for all heads are what the registers hold
         uint32_t pk[JT][8];
         EOQ_SFOR(j, JT,
-          code_bytes(j_ic, X[0]);
-          pack(transpose(X[0]), pk[j]);
+          code_bytes(j_ic, X);
+          pack(transpose(X), pk[j]);
+          __builtin_amdgcn_sched_barrier(0);   // one tile's code words at a time: registers
         );
         EOQ_SFOR(m, 2,
           EOQ_SFOR(s, 2, EOQ_SFOR(t, TERMS, A[t][s] = weight_bytes(s_ic, t_ic, m_ic);););
@@ -577,12 +590,14 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       } else {
         EOQ_SFOR(j, 4,
           if constexpr (S::AHEAD) {
-            if constexpr (j + 2 < 4) code_bytes(std::integral_constant<int, j + 2>{}, X[j & 1]);
-            if constexpr (j + 1 < 4) cd[(j + 1) & 1] = transpose(X[(j + 1) & 1]);
+            if constexpr (j + 1 < 4) {
+              code_bytes(std::integral_constant<int, j + 1>{}, X);
+              cd[(j + 1) & 1] = transpose(X);
+            }
             __builtin_amdgcn_sched_barrier(0);
           } else {
-            code_bytes(j_ic, X[j & 1]);
-            cd[j & 1] = transpose(X[j & 1]);
+            code_bytes(j_ic, X);
+            cd[j & 1] = transpose(X);
           }
           uint32_t pk[8];
           pack(cd[j & 1], pk);

@@ -98,3 +98,21 @@ def test_rows_of_the_update_are_settled_before_they_are_moved_between_lanes(tmp_
                 pytest.fail(f"label within two instructions of {lines[i]}")
             assert not (lines[j].startswith("v_") and registers(lines[j].split()[1].rstrip(",")) & source), (lines[j], lines[i])
             states += 1 + (int(lines[j].split()[1]) if lines[j].startswith("s_nop") else 0)
+
+
+@pytest.mark.skipif(not os.path.exists(g.HIPCC), reason="no compiler")
+def test_bits_of_two_planes_are_both_taken_from_the_planes(tmp_path):
+    """The attention output puts the bits of two planes side by side, even and odd coordinates by one instruction each.  The compiler
+    has let the first result take the register of a plane that the second still needed; no result may be made of another one."""
+    for shape in ("ILi2ELi4ELb0E", "ILi2ELi8ELb0E", "ILi3ELi4ELb0E", "ILi4ELi4ELb0E", "ILi4ELi4ELb1E"):   # <bits, heads, coordinates shared>
+        constant, made, found = {}, {}, 0
+        for l in _kernel_lines("eoq_attend.hip", "eoq_attend_partial_kernel" + shape, tmp_path):
+            if m := re.match(r"s_mov_b32 (s\d+), (0x\w+)", l):
+                constant[m[1]] = m[2]
+            m = re.match(r"v_bfi_b32 v\d+, (s\d+), (v\d+), (v\d+)", l)
+            if m and constant.get(m[1]) == "0x55555555":
+                found += 1
+                assert not made.get(m[2], "").startswith("v_bfi") and not made.get(m[3], "").startswith("v_bfi"), (shape, l)
+            if m := re.match(r"(v_\w+) (v\d+),", l):
+                made[m[2]] = m[1]
+        assert found >= 8
