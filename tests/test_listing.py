@@ -110,9 +110,10 @@ def test_bits_of_two_planes_are_both_taken_from_the_planes(tmp_path):
             if m := re.match(r"s_mov_b32 (s\d+), (0x\w+)", l):
                 constant[m[1]] = m[2]
             m = re.match(r"v_bfi_b32 v\d+, (s\d+), (v\d+), (v\d+)", l)
-            if m and constant.get(m[1]) == "0x55555555":
+            if m and constant.get(m[1]) in ("0x55555555", "0xaaaaaaaa"):   # the mask or its complement with the operands exchanged
                 found += 1
                 assert not made.get(m[2], "").startswith("v_bfi") and not made.get(m[3], "").startswith("v_bfi"), (shape, l)
-            if m := re.match(r"(v_\w+) (v\d+),", l):
-                made[m[2]] = m[1]
+            if m := re.match(r"((?:v|buffer_load|global_load|ds_read)_\w+) v(?:(\d+)|\[(\d+):(\d+)\]),", l):
+                for v in range(int(m[2] or m[3]), int(m[2] or m[4]) + 1):
+                    made[f"v{v}"] = m[1]
         assert found >= 8
