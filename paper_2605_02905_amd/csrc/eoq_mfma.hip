@@ -710,8 +710,9 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
 //     finds their Lloyd-Max cells by signs and appends the bits to half words of the bit-planes (HalfBounds); two half waves
 //     make whole words of them, one store for two planes.
 //     (z with the tokens in registers, comparison masks as bit-planes and a v_writelane for every token and plane took 7, 13 and
-//     23 instructions for 64 coordinates at 2, 3 and 4 bits instead of 4, 10 and 18: 2048 blocks of 1024 x 128 at 3 bits
-//     1146 -> 1098 us a compress call, 32768 of 512 x 128 at 2 bits 13282 -> 13211.)
+//     23 instructions for 64 coordinates at 2, 3 and 4 bits instead of 4, 10 and 18.  Compress calls, us, measured in turn on two
+//     machines: 2048 blocks of 1024 x 128 at 3 bits 1146 -> 1098 and 1189 -> 1185, 32768 of 512 x 128 at 2 bits 13282 -> 13211
+//     and 13419 -> 13393.)
 // ---------------------------------------------------------------------------------------------
 typedef _Float16 half4v __attribute__((ext_vector_type(4)));
 union H4 {
