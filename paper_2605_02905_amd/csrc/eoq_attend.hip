@@ -73,8 +73,8 @@ __device__ __forceinline__ void interleave(uint32_t a, uint32_t b, uint32_t& eve
 // Low-rank term: B_hi = sum_t w_ht C_ti per block on the f16 matrix cores (the coefficient rows are contiguous in t: the
 // operand is a 16-byte load), the weight as three binary16 parts of 11 bits each; then lin_h[c] += sum_i B_hi V_ic.
 //
-// What bounds it (2 bits, 4 heads, 8.4 M tokens: 0.15 ms, 0.36 ms in the float32 version this replaces, which spent 16
-// multiply-adds per token and lane): per pair of tiles 325 vector, 46 LDS and 26 matrix instructions, which take 0.10 ms
+// What bounds it (2 bits, 4 heads, 8.4 M tokens: 0.14 ms, 0.36 ms in the float32 version this replaces, which spent 16
+// multiply-adds per token and lane): per pair of tiles 325 vector, 14 LDS and 26 matrix instructions, which take 0.10 ms
 // by themselves, beside 0.49 GB from memory, which takes 0.11 ms by itself (4.5 TB/s): the two overlap in part only, at
 // the two waves per SIMD that the registers allow.
 // With byte terms and more than four heads two sets of workgroups (z = 0, 1) share the heads, 4 z .. 4 z + 3 each.  HALF: each
