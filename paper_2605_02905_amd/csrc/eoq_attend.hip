@@ -36,12 +36,22 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, si
 }
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
-// Bits c of a and b side by side, those of even c in `even` (bits c, c + 1), those of odd c in `odd` (bits c - 1, c).  Both words
-// pass through an opaque statement together: the compiler (clang 22 of ROCm 7.2) otherwise let the first result take b's register
-// while the second still needed b, in one of the places this is expanded to, and the codes of odd coordinates were wrong there.
+// A value of a register set in flight, read from it once: behind the opaque statement it is a register of its own.  The halves of an
+// 8-byte load are not: one way out of the loop leaves the pair undefined, the compiler (clang 22 of ROCm 7.2) computes anew where
+// such a pair is live when it has formed clauses of loads, and it lost the second of two reads of a half there ("no live subrange at
+// use" of its own check): something else took the register in between, and the codes of odd coordinates were wrong.
+__device__ __forceinline__ uint32_t read_once(uint32_t x) {
+  asm("" : "+v"(x));
+  return x;
+}
+// Groups of GROUP bits (1, 2) of a and b side by side, those in even places in `even` (a's below b's), those in odd places in `odd`.
+// (Opaque results: two bit-field inserts a pair; the compiler otherwise merges the levels into masks and more instructions, 4192 vector
+// instructions instead of 4118 in the kernel of 4 bits.)
+template <int GROUP>
 __device__ __forceinline__ void interleave(uint32_t a, uint32_t b, uint32_t& even, uint32_t& odd) {
-  even = bfi(0x55555555u, a, b << 1);
-  odd = bfi(0x55555555u, a >> 1, b);
+  constexpr uint32_t MASK = GROUP == 1 ? 0x55555555u : 0x33333333u;
+  even = bfi(MASK, a, b << GROUP);
+  odd = bfi(MASK, a >> GROUP, b);
   asm("" : "+v"(even), "+v"(odd));
 }
 
@@ -478,24 +488,22 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_attend_partial_kernel(
       // lowest bit and, in groups of four bits, t / 2 the next one
       uint32_t cw[2][HALF ? 1 : 2][BITS == 1 ? 1 : (BITS == 2 ? 2 : 4)];
       EOQ_SFOR(i, 2, EOQ_SFOR(w, (HALF ? 1 : 2),
-        const uint32_t p0 = f.pl[i][0][w];
+        const uint32_t p0 = read_once(f.pl[i][0][w]);
         if constexpr (BITS == 1) {
           cw[i][w][0] = p0;
         } else {
-          const uint32_t p1 = f.pl[i][1][w];
+          const uint32_t p1 = read_once(f.pl[i][1][w]);
           uint32_t even; uint32_t odd;
-          interleave(p0, p1, even, odd);
+          interleave<1>(p0, p1, even, odd);
           if constexpr (BITS == 2) {
             cw[i][w][0] = even;
             cw[i][w][1] = odd;
           } else {
-            const uint32_t p2 = f.pl[i][2][w]; const uint32_t p3 = BITS == 4 ? f.pl[i][BITS - 1][w] : 0u;
-            uint32_t even2; uint32_t odd2;
-            interleave(p2, p3, even2, odd2);
-            cw[i][w][0] = bfi(0x33333333u, even, even2 << 2);
-            cw[i][w][1] = bfi(0x33333333u, odd, odd2 << 2);
-            cw[i][w][2] = bfi(0x33333333u, even >> 2, even2);
-            cw[i][w][3] = bfi(0x33333333u, odd >> 2, odd2);
+            const uint32_t p2 = read_once(f.pl[i][2][w]);
+            uint32_t even2 = p2 & 0x55555555u; uint32_t odd2 = (p2 >> 1) & 0x55555555u;
+            if constexpr (BITS == 4) interleave<1>(p2, read_once(f.pl[i][BITS - 1][w]), even2, odd2);
+            interleave<2>(even, even2, cw[i][w][0], cw[i][w][2]);
+            interleave<2>(odd, odd2, cw[i][w][1], cw[i][w][3]);
           }
         }
       ););
