@@ -40,15 +40,7 @@ __device__ __forceinline__ T quad_sum(T v) {
   v += dpp_mov<0x4E>(v);
   return v;
 }
-// sum over a row of 16 lanes; every lane of the row gets a total (association may differ by lane)
-__device__ __forceinline__ double row16_sum(double v) {
-  v += dpp_mov<0xB1>(v);
-  v += dpp_mov<0x4E>(v);
-  v += dpp_mov<0x124>(v);
-  v += dpp_mov<0x128>(v);
-  return v;
-}
-// the same with a butterfly of commutative pair sums (lane^1, lane^2, 7-lane, 15-lane): bit-identical in all
+// sum over a row of 16 lanes by a butterfly of commutative pair sums (lane^1, lane^2, 7-lane, 15-lane): bit-identical in all
 // 16 lanes
 __device__ __forceinline__ double row16_sum_uniform(double v) {
   v += dpp_mov<0xB1>(v);
@@ -61,16 +53,6 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
   return __hiloint2double(hi, lo);
-}
-// sum over the 64 lanes of the wave; bit-identical in every lane
-__device__ __forceinline__ double wave_sum_uniform(double v) {
-  v = row16_sum(v);
-  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
-}
-__device__ __forceinline__ double wave_sum_shfl(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
 }
 
 // ---- number formats ---------------------------------------------------------------------------

@@ -353,8 +353,8 @@ constexpr int XPAD = 17;  // row stride of a 16 x 16 exchange plane: transposed 
 // packed reflector storage: reflector k has entries i = k+1 .. 127 (24-bit products: full rate)
 __device__ __forceinline__ int refl_off(int k) { return (int)(__umul24(k, D - 1) - (__umul24(k, k - 1) >> 1)); }
 constexpr int REFL_LEN = (D - 1) * D / 2;  // 8128
-constexpr int GRID_POINTS = 256;           // first localisation: one Sturm count per lane on a grid (cubically spaced)
-constexpr int MULTISECT_ITERS = 17;        // then two lanes per eigenvalue down to the width of 17 trisections of a uniform
+constexpr int GRID_POINTS = 256;           // first localisation: one Sturm count per lane on a grid (cubically spaced),
+                                           // then two lanes per eigenvalue down to the width of 17 trisections of a uniform
                                            // grid cell, 3^-17 / 257 < 2^-34.9 (plain trisection would take 18 rounds at most)
 constexpr int REFINE_COUNT = 32;           // at most this many eigenvalues go on to full precision (the reduction
                                            // itself is good to ~2^-48), with 256 / 32 = 8 lanes each or more
@@ -635,23 +635,23 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
                  [&](int v) { return 4 * kg + v; });
 }
 
-// Sum over the 16 lanes of a DPP row of the values p[S .. 7] of every lane (the values below S are dead),
-// transposing as it folds: on return lane tx holds the row total of value number fold_index<S>(tx), and the lanes
+// Sum over the 16 lanes of a DPP row of the values p[S .. 7] of every lane (the values below S are dead; S < 6, the last two stages
+// are the tail's), transposing as it folds: on return lane tx holds the row total of value number fold_index<S>(tx), and the lanes
 // with fold_writer<S>(tx) hold each live total exactly once.  Partners: 15 - tx, tx ^ 7, tx ^ 2, tx ^ 1.  Two live values make
 // a transposing fold: a lane keeps the one that a bit of tx selects and hands the other to its partner (seven instructions); a
 // value without a live companion is summed as it is (three) and both lanes hold the sum.
 template <int S>
 __device__ __forceinline__ int fold_index(int tx) {
-  const int b3 = (tx >> 3) & 1, b2 = (tx >> 2) & 1, b1 = (tx >> 1) & 1;   // which of the values i and i + 4, i and i + 2, i and i + 1
-  const int i1 = (S < 7) ? b1 : 1;
-  const int i2 = i1 + 2 * ((S < 6) ? (4 + i1 >= S ? b2 : 1) : 1);
+  static_assert(S < 6);
+  const int b3 = (tx >> 3) & 1, b2 = (tx >> 2) & 1, i1 = (tx >> 1) & 1;   // which of the values i and i + 4, i and i + 2, i and i + 1
+  const int i2 = i1 + 2 * (4 + i1 >= S ? b2 : 1);
   return i2 + 4 * ((S < 4) ? (i2 >= S ? b3 : 1) : 1);
 }
 template <int S>
 __device__ __forceinline__ bool fold_writer(int tx) {
   // of the lanes that hold the same total the one with the free bits clear
   const int i = fold_index<S>(tx), i1 = i & 1, i2 = i & 3;
-  const int used = (S < 7 ? 2 : 0) | (S < 6 && 4 + i1 >= S ? 4 : 0) | (S < 4 && i2 >= S ? 8 : 0);
+  const int used = 2 | (4 + i1 >= S ? 4 : 0) | (S < 4 && i2 >= S ? 8 : 0);
   return (tx & ~used) == 0;
 }
 template <int CTRL>
@@ -662,18 +662,17 @@ __device__ __forceinline__ double fold_pair(double lower, double upper, bool up)
 }
 template <int S>
 __device__ __forceinline__ double row16_fold(const double (&p)[8], int tx) {
+  static_assert(S < 6);
   const bool b3 = (tx & 8) != 0, b2 = (tx & 4) != 0, b1 = (tx & 2) != 0;
-  double r1[4], r2[2], r3;
+  double r1[4], r2[2];
   EOQ_SFOR(i, 4,                                          // row_mirror
     if constexpr (i >= S) r1[i] = fold_pair<0x140>(p[i], p[4 + i], b3);
     else if constexpr (4 + i >= S) r1[i] = p[4 + i] + dpp_mov<0x140>(p[4 + i]);
     else r1[i] = 0.0;);
   EOQ_SFOR(i, 2,                                          // row_half_mirror
     if constexpr (4 + i >= S) r2[i] = fold_pair<0x141>(r1[i], r1[2 + i], b2);
-    else if constexpr (6 + i >= S) r2[i] = r1[2 + i] + dpp_mov<0x141>(r1[2 + i]);
-    else r2[i] = 0.0;);
-  if constexpr (S < 7) r3 = fold_pair<0x4E>(r2[0], r2[1], b1);
-  else r3 = r2[1] + dpp_mov<0x4E>(r2[1]);
+    else r2[i] = r1[2 + i] + dpp_mov<0x141>(r1[2 + i]););
+  const double r3 = fold_pair<0x4E>(r2[0], r2[1], b1);
   return r3 + dpp_mov<0xB1>(r3);
 }
 
