@@ -13,15 +13,15 @@ constexpr int D = EOQ_D;
 // ---------------------------------------------------------------------------
 // encode kernel for float32 blocks: 64 rows of one block per workgroup, float32 arithmetic throughout.
 //   rows in LDS -> C = S W^T rounded to the stored binary16 -> R = S - C V^T, its norm and u in registers -> u in LDS
-//   -> z = u Pi^T with v_mfma_f32_32x32x2_f32, wave w the coordinates 32 w .. 32 w + 31 with its columns of Pi in 64
-//   registers -> comparison masks = packed bit-planes.
+//   -> z^T = Pi u^T with v_mfma_f32_32x32x2_f32, wave w the coordinates 32 w .. 32 w + 31 with its rows of Pi in 64
+//   registers -> cells by signs, appended to half words of the bit-planes (HalfBounds).
 // Operands of v_mfma_f32_32x32x2_f32 (wave64): lane l supplies A[row = l%32][k = l/32] and B[k = l/32][col = l%32] and
 // receives D[row = 8*(v/4) + 4*(l/32) + v%4][col = l%32] in register v.  The contraction index is permuted so that a lane's
 // entries of four consecutive instructions are four consecutive floats.
 // Float32 products run at twice the vector rate on the matrix cores, and the rotation no longer takes 64 KB of LDS and
 // twelve LDS reads per 32 multiply-adds, which left one workgroup per compute unit.  The matrix instructions of a workgroup, 8 k
 // cycles, wait for its rows and its residual, so it is workgroups on a unit that fill them: W comes through the scalar cache, C
-// lies in LDS in the binary16 it is stored in, and the columns of Pi are read when the rows are done with their registers, which
+// lies in LDS in the binary16 it is stored in, and Pi is read when the rows of the block are done with their registers, which
 // leaves room for four a unit instead of two.  8192 workgroups of 64 rows at 1 bit 244 -> 200 us, 1000 at 4 bits 41 -> 36.5 (of
 // which 13 are the matrix cores' rate and 8 that of memory).
 // The product comes out with the coordinates of a row in a lane's registers (HalfBounds): 2 us less of a compress call of 125

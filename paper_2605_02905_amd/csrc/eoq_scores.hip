@@ -20,7 +20,8 @@
 // and one of the magnitude plane: four coordinates of two terms per 8-byte read, in the order the matrix instruction takes
 // them.  From 3 bits on two tables of 16 words, the signs of a nibble and the byte mask of a nibble of a magnitude plane, and
 // an AND: sixteen words lie in sixteen banks, so the lanes' lookups, which collide at random in the large table, never do
-// (calls of more than 25 us: 9 % shorter at 3 and 4 bits, with the correction 8 and 9 %.  At 2 bits the additional lookups and
+// (3 and 4 bits, one to eight heads: logits of 1 M to 8.4 M tokens 10 to 16 % shorter, with the correction 8 to 13 %, of 262144
+// tokens 4 to 8 % and 3 to 5 %; 4.2 M tokens at four heads, us: 95.9 -> 83.8 and 149 -> 131, corrected 125 -> 109 and 170 -> 152.  At 2 bits the additional lookups and
 // ANDs cost more than the collisions, 3 %; and with the correction at 4 bits and more than four heads, where 268 registers leave
 // one wave to a SIMD, the chain of lookup and AND does, 1 to 3 %: those have the table of pairs).  The
 // lane that owns a token reads its 8 bytes of every bit-plane straight from the record (lane half f: coordinates 64 f ..
