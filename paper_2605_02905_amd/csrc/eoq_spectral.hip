@@ -441,8 +441,10 @@ __device__ __forceinline__ double4v mfma64(double a, double b, double4v c) { ret
 
 // Gram matrix of a float32 block on the fp64 matrix cores (products of float32 numbers are exact in double): nine of the 36
 // tiles per wave.  Lane l = 16 g + c supplies S[t + g][16 I + c] as operand of tile row or column I of v_mfma_f64_16x16x4_f64,
-// straight from memory, sixteen tokens ahead; result register v is row 4 v + g, column c.  As vector multiply-adds out
-// of LDS a compress call of 125 blocks of 512 x 128 took 272 us, now 244.
+// straight from memory; result register v is row 4 v + g, column c.  Eight tokens are 18 instructions of 64 cycles, less than a
+// row takes to come from HBM, so rows are requested 24 tokens ahead in four sets of registers: the stage takes 100 thousand
+// cycles for 512 tokens, of which the matrix cores need 74, and a compress call of 125 blocks of 512 x 128 209 us (220 with
+// rows requested eight tokens ahead).
 __device__ __forceinline__ void gram_f64(const float* __restrict__ src, size_t tok, int n, double* Tl, int tid, double (&A)[64],
                                          unsigned* flag_s) {
   const int lane = tid & 63, c = lane & 15, g = lane >> 4;
@@ -450,33 +452,39 @@ __device__ __forceinline__ void gram_f64(const float* __restrict__ src, size_t t
   double4v acc[9];
   EOQ_SFOR(s, 9, EOQ_SFOR(v, 4, acc[s][v] = 0.0;););
   const float* p = src + (size_t)g * tok + c;
-  float x[2][8], y[2][8];
+  float f0[2][8], f1[2][8], f2[2][8], f3[2][8];
   auto fetch = [&](int t, float (&f)[2][8]) __attribute__((always_inline)) {   // tokens t + g and t + 4 + g
     EOQ_SFOR(h, 2, EOQ_SFOR(I, 8, f[h][I] = p[(size_t)(t + 4 * h) * tok + 16 * I];););
   };
-  auto products = [&](const float (&f)[2][8]) __attribute__((always_inline)) {
-    EOQ_SFOR(h, 2,
-      double o[8];
-      EOQ_SFOR(I, 8, o[I] = (double)f[h][I];);
-      // the wave's tiles wave, wave + 4, ..: four cases, so that every operand is a register known at compile time
-      auto tiles = [&](auto w_ic) __attribute__((always_inline)) {
-        constexpr int w = decltype(w_ic)::value;
+  // the wave's tiles wave, wave + 4, ..: four cases, so that every operand is a register known at compile time
+  auto tiles = [&](auto w_ic) __attribute__((always_inline)) {
+    constexpr int w = decltype(w_ic)::value;
+    auto products = [&](const float (&f)[2][8]) __attribute__((always_inline)) {
+      EOQ_SFOR(h, 2,
+        double o[8];
+        EOQ_SFOR(I, 8, o[I] = (double)f[h][I];);
         EOQ_SFOR(s, 9, acc[s] = mfma64(o[gi_tile_i(w, s)], o[gi_tile_j(w, s)], acc[s]););
-      };
-      if (wave == 0) tiles(std::integral_constant<int, 0>{});
-      else if (wave == 1) tiles(std::integral_constant<int, 1>{});
-      else if (wave == 2) tiles(std::integral_constant<int, 2>{});
-      else tiles(std::integral_constant<int, 3>{});
-    );
-  };
-  fetch(0, x);
+      );
+    };
+    fetch(0, f0);
+    fetch(8, f1);
+    fetch(16, f2);
 #pragma unroll 1
-  for (int t = 0; t < n; t += 16) {
-    fetch(t + 8, y);
-    products(x);
-    fetch(min(t + 16, n - 8), x);
-    products(y);
-  }
+    for (int t = 0; t < n; t += 32) {
+      fetch(t + 24, f3);
+      products(f0);
+      fetch(min(t + 32, n - 8), f0);
+      products(f1);
+      fetch(min(t + 40, n - 8), f1);
+      products(f2);
+      fetch(min(t + 48, n - 8), f2);
+      products(f3);
+    }
+  };
+  if (wave == 0) tiles(std::integral_constant<int, 0>{});
+  else if (wave == 1) tiles(std::integral_constant<int, 1>{});
+  else if (wave == 2) tiles(std::integral_constant<int, 2>{});
+  else tiles(std::integral_constant<int, 3>{});
   bool bad = false;   // an Inf or NaN entry of the block reaches the diagonal of G, which the diagonal tiles hold
   EOQ_SFOR(v, 4, bad |= !(fabs(acc[0][v]) < INFINITY) || !(fabs(acc[7][v]) < INFINITY););
   if (bad) atomicOr(flag_s, EOQ_FLAG_NONFINITE);
