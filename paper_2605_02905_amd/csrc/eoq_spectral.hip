@@ -1,4 +1,4 @@
-// Spectral stage of eOptShrinkQ (Alg. 2) on gfx950, one workgroup of 256 lanes per block, double precision:
+// Spectral stage of eOptShrinkQ (Alg. 2) on gfx950, one workgroup per block, double precision:
 // Gram matrix G = S^T S, its eigenvalues (= squared singular values of the block, Sec. 2.3), bulk edge and
 // rank (Step 1), imputed noise spectrum (Step 2), D-transform shrinker (Step 3) and the right singular
 // vectors of the retained components.
@@ -60,7 +60,7 @@ constexpr double EDGE_COEF = 1.0 / (0x1.965fea53d6e3dp+0 - 1.0);
 
 // What rank_and_shrink keeps in LDS: the numbers 1 - (j / k)^{2/3}, j = 1 .. k, of the square-root edge law, which depend on
 // nothing of the block and are formed ahead of time (edge_law), and the two sums of every retained component.
-struct ShrinkLds { double law[D / 2], s1[EOQ_RMAX_CAP], s2[EOQ_RMAX_CAP]; };
+struct ShrinkLds { double law[D / 2], s1[EOQ_RMAX_CAP], s2[EOQ_RMAX_CAP]; int above[4]; };
 __device__ __forceinline__ double edge_law(int j, int k) { return 1.0 - pow((double)(j + 1) / (double)k, 2.0 / 3.0); }
 
 // Sum over the 64 lanes in the order of a butterfly lane ^ 32, ^ 16, .. ^ 1, without LDS: swaps of half waves and of rows of
@@ -84,6 +84,15 @@ __device__ __forceinline__ double wave_sum_butterfly(double v) {
   return v;
 }
 
+// How many of the lanes 0 .. 127 bring a true value; every lane of the workgroup gets the number.  (The library's
+// __syncthreads_count expects every wave that the workgroup was started with.)
+__device__ __forceinline__ int count_columns(bool mine, int* of_wave) {
+  const unsigned long long set = __ballot(mine);
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < D) of_wave[threadIdx.x >> 6] = __popcll(set);
+  __syncthreads();
+  return of_wave[0] + of_wave[1];
+}
+
 // ---------------------------------------------------------------------------------------------
 // Alg. 2 Steps 1-3 from the eigenvalues lam_s[0..127] (descending, in LDS, visible to all lanes).
 // Writes lam_out / phi / sigma for the block, fills atoms[] and scale_s[] (phi_i / sigma_i), sets flag
@@ -99,8 +108,7 @@ __device__ int rank_and_shrink(const double* lam_s, double* atoms, double* scale
   // Step 1: lambda_+ = lam_{k+1} + (lam_{k+1} - lam_{2k+1}) / (2^{2/3} - 1);  r = #{ lam_i / lambda_+ - 1 > d^{-1/3} }
   const double lam_k1 = lam_s[k], lam_2k1 = lam_s[2 * k];
   const double lam_plus = lam_k1 + EDGE_COEF * (lam_k1 - lam_2k1);
-  const int above = (tid < D) ? ((lam_s[tid] / lam_plus - 1.0 > rank_thr) ? 1 : 0) : 0;
-  int r = __syncthreads_count(above);
+  int r = count_columns(tid < D && lam_s[tid] / lam_plus - 1.0 > rank_thr, sh.above);
   if (*flag_s & EOQ_FLAG_NONFINITE) r = 0;   // Inf or NaN in the block (set by the Gram stage, before several barriers)
   if (r > r_max) {
     r = r_max;
@@ -208,6 +216,129 @@ constexpr int MAX_SWEEPS = 30;
 constexpr unsigned SHARERS = 251;
 constexpr double JACOBI_TOL = 5e-14;  // a pair is orthogonal when |<a_p,a_q>| <= tol |a_p||a_q|
 
+struct JacobiLds {
+  double A[D * LDA];            // column s of the working matrix at A[s*LDA ...]
+  float stage[STAGE_ROWS * D];
+  double lam[D], atoms[D], colnorm[D];
+  int slot_of[D];
+  double scale[EOQ_RMAX_CAP];
+  ShrinkLds shrink;
+  int rotated[THREADS / 64];
+  unsigned flag;
+};
+
+// One block, by the first 256 lanes of a workgroup, which are all that is left of it.
+__device__ void jacobi_block(JacobiLds& l, const void* __restrict__ blocks, const EoqBlockMap& map, int dtype, int n, int k,
+                             double rank_thr, int r_max, int loss, size_t blk, size_t slot, double* __restrict__ lam_out,
+                             float* __restrict__ wfac, int32_t* __restrict__ rank_out, float* __restrict__ phi_out,
+                             float* __restrict__ sigma_out, uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
+  const int tid = threadIdx.x;
+  __syncthreads();
+  if (tid == 0) l.flag = 0u;
+
+  {
+    double acc[64];
+    gram_tile(blocks, dtype, map.in_base(blk), (size_t)map.token_stride, n, l.stage, tid, acc);
+    bool bad = false;
+    EOQ_SFOR(e, 64, bad |= !(fabs(acc[e]) < INFINITY););
+    if (bad) atomicOr(&l.flag, EOQ_FLAG_NONFINITE);
+    const int ty = tid >> 4, tx = tid & 15;
+    EOQ_SFOR(e, 64, l.A[(tx * 8 + (e & 7)) * LDA + ty * 8 + (e >> 3)] = acc[e];);
+  }
+  __syncthreads();
+
+  // One-sided Jacobi on the columns of A = G: A V -> V Lambda.  64 pairs per step, one per group of 4
+  // lanes; pair p works on slots 2p, 2p+1 and writes its rotated columns to the slots the round-robin
+  // schedule pairs next.
+  const int pr = tid >> 2, ql = tid & 3;
+  const int m_pairs = D / 2;
+  const int dst_top = (pr == 0) ? 0 : (pr == m_pairs - 1 ? 2 * (m_pairs - 1) + 1 : 2 * (pr + 1));
+  const int dst_bot = (pr == 0) ? 2 : 2 * (pr - 1) + 1;
+  int sweeps = 0;
+  bool converged = false;
+  for (; sweeps < MAX_SWEEPS && !converged; ++sweeps) {
+    bool mine = false;   // a lane of this wave has rotated
+    for (int step = 0; step < D - 1; ++step) {
+      double xp[D / 4], xq[D / 4];
+      double alpha = 0.0, beta = 0.0, gamma = 0.0;
+#pragma unroll
+      for (int m = 0; m < D / 4; ++m) {
+        xp[m] = l.A[(2 * pr) * LDA + ql + 4 * m];
+        xq[m] = l.A[(2 * pr + 1) * LDA + ql + 4 * m];
+        alpha = fma(xp[m], xp[m], alpha);
+        beta = fma(xq[m], xq[m], beta);
+        gamma = fma(xp[m], xq[m], gamma);
+      }
+      alpha = quad_sum(alpha);
+      beta = quad_sum(beta);
+      gamma = quad_sum(gamma);
+      const bool rot = fabs(gamma) > JACOBI_TOL * sqrt(alpha * beta);
+      double c = 1.0, s = 0.0;
+      if (rot) {
+        const double zeta = (beta - alpha) / (2.0 * gamma);
+        const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
+        c = 1.0 / sqrt(1.0 + t * t);
+        s = c * t;
+      }
+      __syncthreads();  // every lane holds its operands; slots may now be overwritten
+#pragma unroll
+      for (int m = 0; m < D / 4; ++m) {
+        l.A[dst_top * LDA + ql + 4 * m] = c * xp[m] - s * xq[m];
+        l.A[dst_bot * LDA + ql + 4 * m] = s * xp[m] + c * xq[m];
+      }
+      mine |= __ballot(rot) != 0ull;
+      __syncthreads();
+    }
+    if ((tid & 63) == 0) l.rotated[tid >> 6] = mine;
+    __syncthreads();
+    converged = !(l.rotated[0] | l.rotated[1] | l.rotated[2] | l.rotated[3]);
+  }
+  if (!converged && tid == 0) l.flag |= EOQ_FLAG_NO_CONVERGE;
+  if (tid < k) l.shrink.law[tid] = edge_law(tid, k);
+
+  // eigenvalues = column norms; order them
+  {
+    double alpha = 0.0;
+#pragma unroll
+    for (int m = 0; m < D / 4; ++m) {
+      const double x = l.A[(tid >> 1) * LDA + (tid & 1) * 64 + m * 2 + 0];
+      const double y = l.A[(tid >> 1) * LDA + (tid & 1) * 64 + m * 2 + 1];
+      alpha = fma(x, x, alpha);
+      alpha = fma(y, y, alpha);
+    }
+    alpha = pair_sum(alpha);
+    if ((tid & 1) == 0) l.colnorm[tid >> 1] = sqrt(alpha);
+  }
+  __syncthreads();
+  if (tid < D) {
+    const double mine = l.colnorm[tid];
+    int pos = 0;
+    for (int t = 0; t < D; ++t) {
+      const double o = l.colnorm[t];
+      pos += (o > mine || (o == mine && t < tid)) ? 1 : 0;
+    }
+    l.lam[pos] = mine;
+    l.slot_of[pos] = tid;
+  }
+  __syncthreads();
+
+  const int r = rank_and_shrink(l.lam, l.atoms, l.scale, l.shrink, &l.flag, n, k, rank_thr, r_max, loss, blk, slot, lam_out, phi_out,
+                                sigma_out);
+
+  // right singular vectors v_i = a_slot / lambda_i of the retained components
+  for (int e = tid; e < r * D; e += THREADS) {
+    const int i = e >> 7, j = e & (D - 1);
+    const double li = l.lam[i];
+    const double v = (li > 0.0) ? l.A[l.slot_of[i] * LDA + j] / li : 0.0;
+    rfac[(slot * r_max + i) * D + j] = double_to_half_bits(v);
+    wfac[(blk * r_max + i) * D + j] = (float)(v * l.scale[i]);
+  }
+  if (tid == 0) {
+    rank_out[slot] = r;
+    flags_out[slot] = l.flag | ((unsigned)sweeps << EOQ_FLAG_SWEEPS_SHIFT);
+  }
+}
+
 // With `marks` non-null the workgroups share the batch and solve the blocks whose mark is set; otherwise workgroup b
 // handles block b.
 __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
@@ -215,16 +346,7 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
     const int* __restrict__ marks, double* __restrict__ lam_out,
     float* __restrict__ wfac, int32_t* __restrict__ rank_out, float* __restrict__ phi_out,
     float* __restrict__ sigma_out, uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
-  __shared__ double A[D * LDA];            // column s of the working matrix at A[s*LDA ...]
-  __shared__ float stage[STAGE_ROWS * D];
-  __shared__ double lam_s[D];
-  __shared__ double atoms[D];
-  __shared__ double colnorm[D];
-  __shared__ int slot_of[D];
-  __shared__ double scale_s[EOQ_RMAX_CAP];
-  __shared__ ShrinkLds shrink_s;
-  __shared__ unsigned flag_s;
-
+  __shared__ JacobiLds lds;
   const int tid = threadIdx.x;
   // blocks blockIdx.x, blockIdx.x + gridDim.x, ..: see SHARERS (B <= 2^24)
   const unsigned step = gridDim.x, total = (unsigned)B;
@@ -235,108 +357,8 @@ __global__ __launch_bounds__(THREADS) void eoq_spectral_jacobi_kernel(
     }
     if (marks && !marks[item]) continue;
     const size_t blk = (size_t)item;
-    const size_t slot = map.slot(blk);
-    __syncthreads();
-    if (tid == 0) flag_s = 0u;
-
-    {
-      double acc[64];
-      gram_tile(blocks, dtype, map.in_base(blk), (size_t)map.token_stride, n, stage, tid, acc);
-      bool bad = false;
-      EOQ_SFOR(e, 64, bad |= !(fabs(acc[e]) < INFINITY););
-      if (bad) atomicOr(&flag_s, EOQ_FLAG_NONFINITE);
-      const int ty = tid >> 4, tx = tid & 15;
-      EOQ_SFOR(e, 64, A[(tx * 8 + (e & 7)) * LDA + ty * 8 + (e >> 3)] = acc[e];);
-    }
-    __syncthreads();
-
-    // One-sided Jacobi on the columns of A = G: A V -> V Lambda.  64 pairs per step, one per group of 4
-    // lanes; pair p works on slots 2p, 2p+1 and writes its rotated columns to the slots the round-robin
-    // schedule pairs next.
-    const int pr = tid >> 2, ql = tid & 3;
-    const int m_pairs = D / 2;
-    const int dst_top = (pr == 0) ? 0 : (pr == m_pairs - 1 ? 2 * (m_pairs - 1) + 1 : 2 * (pr + 1));
-    const int dst_bot = (pr == 0) ? 2 : 2 * (pr - 1) + 1;
-    int sweeps = 0;
-    bool converged = false;
-    for (; sweeps < MAX_SWEEPS && !converged; ++sweeps) {
-      int sweep_rot = 0;
-      for (int step = 0; step < D - 1; ++step) {
-        double xp[D / 4], xq[D / 4];
-        double alpha = 0.0, beta = 0.0, gamma = 0.0;
-#pragma unroll
-        for (int m = 0; m < D / 4; ++m) {
-          xp[m] = A[(2 * pr) * LDA + ql + 4 * m];
-          xq[m] = A[(2 * pr + 1) * LDA + ql + 4 * m];
-          alpha = fma(xp[m], xp[m], alpha);
-          beta = fma(xq[m], xq[m], beta);
-          gamma = fma(xp[m], xq[m], gamma);
-        }
-        alpha = quad_sum(alpha);
-        beta = quad_sum(beta);
-        gamma = quad_sum(gamma);
-        const bool rot = fabs(gamma) > JACOBI_TOL * sqrt(alpha * beta);
-        double c = 1.0, s = 0.0;
-        if (rot) {
-          const double zeta = (beta - alpha) / (2.0 * gamma);
-          const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-          c = 1.0 / sqrt(1.0 + t * t);
-          s = c * t;
-        }
-        __syncthreads();  // every lane holds its operands; slots may now be overwritten
-#pragma unroll
-        for (int m = 0; m < D / 4; ++m) {
-          A[dst_top * LDA + ql + 4 * m] = c * xp[m] - s * xq[m];
-          A[dst_bot * LDA + ql + 4 * m] = s * xp[m] + c * xq[m];
-        }
-        sweep_rot |= __syncthreads_or(rot ? 1 : 0);
-      }
-      converged = (sweep_rot == 0);
-    }
-    if (!converged && tid == 0) flag_s |= EOQ_FLAG_NO_CONVERGE;
-    if (tid < k) shrink_s.law[tid] = edge_law(tid, k);
-
-    // eigenvalues = column norms; order them
-    {
-      double alpha = 0.0;
-#pragma unroll
-      for (int m = 0; m < D / 4; ++m) {
-        const double x = A[(tid >> 1) * LDA + (tid & 1) * 64 + m * 2 + 0];
-        const double y = A[(tid >> 1) * LDA + (tid & 1) * 64 + m * 2 + 1];
-        alpha = fma(x, x, alpha);
-        alpha = fma(y, y, alpha);
-      }
-      alpha = pair_sum(alpha);
-      if ((tid & 1) == 0) colnorm[tid >> 1] = sqrt(alpha);
-    }
-    __syncthreads();
-    if (tid < D) {
-      const double mine = colnorm[tid];
-      int pos = 0;
-      for (int t = 0; t < D; ++t) {
-        const double o = colnorm[t];
-        pos += (o > mine || (o == mine && t < tid)) ? 1 : 0;
-      }
-      lam_s[pos] = mine;
-      slot_of[pos] = tid;
-    }
-    __syncthreads();
-
-    const int r = rank_and_shrink(lam_s, atoms, scale_s, shrink_s, &flag_s, n, k, rank_thr, r_max, loss, blk, slot, lam_out, phi_out,
-                                  sigma_out);
-
-    // right singular vectors v_i = a_slot / lambda_i of the retained components
-    for (int e = tid; e < r * D; e += THREADS) {
-      const int i = e >> 7, j = e & (D - 1);
-      const double li = lam_s[i];
-      const double v = (li > 0.0) ? A[slot_of[i] * LDA + j] / li : 0.0;
-      rfac[(slot * r_max + i) * D + j] = double_to_half_bits(v);
-      wfac[(blk * r_max + i) * D + j] = (float)(v * scale_s[i]);
-    }
-    if (tid == 0) {
-      rank_out[slot] = r;
-      flags_out[slot] = flag_s | ((unsigned)sweeps << EOQ_FLAG_SWEEPS_SHIFT);
-    }
+    jacobi_block(lds, blocks, map, dtype, n, k, rank_thr, r_max, loss, blk, map.slot(blk), lam_out, wfac, rank_out, phi_out, sigma_out,
+                 rfac, flags_out);
   }
 }
 
@@ -738,14 +760,17 @@ __device__ __forceinline__ void vp_columns(const double* from, int tx, double (&
 }
 // What step k leaves behind, by the wave that formed its reflector: diagonal and off-diagonal entry of T, and a float copy of the
 // reflector (entries k + 1 .. 127 of v, in LDS as doubles) in the packed store.
+__device__ __forceinline__ void copy_reflector(const double* v, int k, int lane, float* refl) {
+  float* dst = refl + refl_off(k) - (k + 1);   // entry j at dst[j]
+  if (lane > k) dst[lane] = (float)v[vp_at(lane)];
+  if (lane + 64 > k) dst[lane + 64] = (float)v[vp_at(lane) + 2 * VP_LD];
+}
 __device__ __forceinline__ void leave_reflector(const double* v, int k, int lane, double alpha, double diag, float* refl, double* dT, double* eT) {
   if (lane == 16 * ((k & 15) >> 2) + (k & 15)) {
     dT[k] = diag;
     eT[k] = alpha;
   }
-  float* dst = refl + refl_off(k) - (k + 1);   // entry j at dst[j]
-  if (lane > k) dst[lane] = (float)v[vp_at(lane)];
-  if (lane + 64 > k) dst[lane + 64] = (float)v[vp_at(lane) + 2 * VP_LD];
+  copy_reflector(v, k, lane, refl);
 }
 // acc += (the value of x in lane N of the lane's row of sixteen) * y, in one instruction
 template <int N>
@@ -761,43 +786,106 @@ __device__ __forceinline__ void fmac_bcast(double& acc, double x, double y) {
 // forming the reflector by itself from a published row, with one barrier a step, does the same for the short calls and is
 // slower in the long ones (467): waves that wait leave their issue slots to the unit's other workgroup.
 // `alpha` and `diag` stay with the wave that formed the reflector until the step after, when it waits.
+//
+// The parts of a step.  Reflector k = 16 S + kk from row k, x[b] being its columns tx + 16 b in every row of lanes that holds it (the
+// others do the same on what they have): v goes to `vb` from the lanes with `store`, behind `half_vv(some, v^T v / 2)`, from which
+// beta = 2 / (v^T v) follows.
+template <int S, int ODD, bool LONE, typename F>
+__device__ __forceinline__ void form_reflector(int kk, const double (&x)[8], int tx, bool store, double* vb, double (&v)[8], double& alpha,
+                                               double& diag, F&& half_vv) {
+  const bool last = ODD && kk == 15;
+  const double xs = (tx > kk) ? x[S] : 0.0;  // columns j = tx + 16 b > k only
+  double s0 = xs * xs, s1 = 0.0;
+  EOQ_SFOR(b, 8,
+    if constexpr (b > S) {
+      if constexpr (((b - S) & 1) == 0) s0 = fma(x[b], x[b], s0);
+      else s1 = fma(x[b], x[b], s1);
+    });
+  const double ss = row16_sum_uniform(s0 + s1);   // the same bits in the sixteen lanes of a row
+  double xsel = xs;
+  if constexpr (ODD) xsel = last ? x[S + 1] : xsel;
+  const double x0 = readlane_f64(xsel, 16 * (kk >> 2) + ((kk + 1) & 15));  // x_{k+1} of row k
+  const bool some = ss > 0x1.0p-960;
+  const double sigma = newton_sqrt(ss);
+  alpha = some ? ((x0 >= 0.0) ? -sigma : sigma) : 0.0;              // H_k x = alpha e_1
+  diag = x[S];
+  if constexpr (!LONE) half_vv(some, fma(sigma, fabs(x0), ss));
+  // v = x - alpha e_{k+1}: entry k + 1 sits in sub-tile S of lane kk + 1, or, at the last step of a stage, in
+  // sub-tile S + 1 of lane 0
+  EOQ_SFOR(b, 8, v[b] = b > S ? x[b] : 0.0;);
+  v[S] = xs - ((tx == kk + 1) ? alpha : 0.0);
+  if constexpr (ODD) v[S + 1] -= (last && tx == 0) ? alpha : 0.0;
+  if (store) {
+    EOQ_SFOR(m, 4,
+      if constexpr (2 * m >= S) *reinterpret_cast<double2*>(vb + VP_LD * m + 2 * tx) = make_double2(v[2 * m], v[2 * m + 1]);
+      else if constexpr (2 * m + 1 >= S) vb[VP_LD * m + 2 * tx + 1] = v[2 * m + 1];);
+  }
+  if constexpr (LONE) half_vv(some, fma(sigma, fabs(x0), ss));
+}
+// a lane's parts of A v; vj: its columns of v
+template <int S>
+__device__ __forceinline__ void rows_times_v(const double (&A)[64], const double (&vj)[8], double (&part)[8]) {
+  EOQ_SFOR(a, 8,
+    if constexpr (a >= S) {
+      // one chain per row: the chains of the live rows interleave, which is independent work enough
+      double s0 = 0.0;
+      EOQ_SFOR(b, 8, if constexpr (b >= S) s0 = fma(A[a * 8 + b], vj[b], s0););
+      part[a] = s0;
+    } else {
+      part[a] = 0.0;
+    });
+}
+// p = beta A v into LDS
+template <int S>
+__device__ __forceinline__ void store_p(const double (&part)[8], double beta, int ty, int tx, double* p) {
+  const double tot = row16_fold<S>(part, tx);
+  if (fold_writer<S>(tx)) p[vp_at(ty + 16 * fold_index<S>(tx))] = beta * tot;
+}
+// 2 K = beta v^T p from the column entries a lane holds anyway, summed over its DPP row (every row of 16 lanes covers all 128
+// columns and gets the same bits)
+template <int S>
+__device__ __forceinline__ double beta_v_dot_p(const double (&vj)[8], const double (&wj)[8], double beta) {
+  double dl0 = 0.0, dl1 = 0.0;
+  EOQ_SFOR(b, 8,
+    if constexpr (b >= S) {
+      if constexpr ((b & 1) == 0) dl0 = fma(vj[b], wj[b], dl0);
+      else dl1 = fma(vj[b], wj[b], dl1);
+    });
+  return beta * row16_sum_uniform(dl0 + dl1);
+}
+// A <- A - v p^T - q v^T; vr, pr: row ty + 16 (tx & 7) of v and p in lane tx
+template <int S, typename F>
+__device__ __forceinline__ void rank_two_update(double (&A)[64], const double (&vj)[8], const double (&wj)[8], double vr, double pr, double K2, F&& first_rows_done) {
+  // v w^T + w v^T with w = p - K v is v p^T + q v^T with q = p - 2 K v: the correction is needed in the row view
+  // only, the column view of p goes into the update as it was read
+  double nv = -vr, nq = fma(K2, vr, -pr);   // rows of -v and -q
+  // a lane move must not follow within two instructions of the write of what it moves; the compiler keeps that distance for its
+  // own moves and does not see into fmac_bcast
+  asm volatile("s_nop 1" : "+v"(nq), "+v"(nv));
+  EOQ_SFOR(e, 64,
+    if constexpr ((e >> 3) >= S && (e & 7) >= S) {
+      fmac_bcast<(e >> 3)>(A[e], nq, vj[e & 7]);
+      fmac_bcast<(e >> 3)>(A[e], nv, wj[e & 7]);
+    }
+    if constexpr (e == 8 * S + 15) first_rows_done(););
+}
+
+// `alpha` and `diag` stay with the wave that formed the reflector until the step after, when it waits.
 template <int S, int ODD>
 __device__ __forceinline__ void householder_step(int kk, int wave, double (&A)[64], double& alpha, double& diag, int tid, ReduceLds& lds,
                                                  float* refl, double* dT, double* eT, double* betaT) {
   const int lane = tid & 63, ty = lane_row(tid), tx = tid & 15;
   const int k = 16 * S + kk;
-  const bool last = ODD && kk == 15;
   double* vb = lds.v[ODD];
   if (__builtin_expect(wave == (kk & 3), 1)) {   // falls through: a jump taken costs twenty cycles of the chain
+    double x[8], v[8];
+    EOQ_SFOR(b, 8, x[b] = A[S * 8 + b];);
     // every 16-lane row of this wave runs the arithmetic on its own matrix row; only the row k stores
-    const double xs = (tx > kk) ? A[S * 8 + S] : 0.0;  // columns j = tx + 16 b > k only
-    double s0 = xs * xs, s1 = 0.0;
-    EOQ_SFOR(b, 8,
-      if constexpr (b > S) {
-        if constexpr (((b - S) & 1) == 0) s0 = fma(A[S * 8 + b], A[S * 8 + b], s0);
-        else s1 = fma(A[S * 8 + b], A[S * 8 + b], s1);
-      });
-    const double ss = row16_sum_uniform(s0 + s1);   // the same bits in the sixteen lanes of a row
-    double xsel = xs;
-    if constexpr (ODD) xsel = last ? A[S * 8 + S + 1] : xsel;
-    const double x0 = readlane_f64(xsel, 16 * (kk >> 2) + ((kk + 1) & 15));  // x_{k+1} of row k
-    const bool some = ss > 0x1.0p-960;
-    const double sigma = newton_sqrt(ss);
-    alpha = some ? ((x0 >= 0.0) ? -sigma : sigma) : 0.0;                     // H_k x = alpha e_1
-    const double beta = some ? newton_rcp(fma(sigma, fabs(x0), ss)) : 0.0;   // 2 / (v^T v), v = x - alpha e_1
-    diag = A[S * 8 + S];
-    if (((lane >> 4) & 3) == (kk >> 2)) {
-      // v = x - alpha e_{k+1}: entry k + 1 sits in sub-tile S of lane kk + 1, or, at the last step of a stage, in
-      // sub-tile S + 1 of lane 0
-      double v[8];
-      EOQ_SFOR(b, 8, v[b] = b > S ? A[S * 8 + b] : 0.0;);
-      v[S] = xs - ((tx == kk + 1) ? alpha : 0.0);
-      if constexpr (ODD) v[S + 1] -= (last && tx == 0) ? alpha : 0.0;
-      EOQ_SFOR(m, 4,
-        if constexpr (2 * m >= S) *reinterpret_cast<double2*>(vb + VP_LD * m + 2 * tx) = make_double2(v[2 * m], v[2 * m + 1]);
-        else if constexpr (2 * m + 1 >= S) vb[VP_LD * m + 2 * tx + 1] = v[2 * m + 1];);
-      if (tx == kk) betaT[k] = beta;
-    }
+    const bool owner = ((lane >> 4) & 3) == (kk >> 2);
+    form_reflector<S, ODD, false>(kk, x, tx, owner, vb, v, alpha, diag, [&](bool some, double h) __attribute__((always_inline)) {
+      const double beta = some ? newton_rcp(h) : 0.0;
+      if (owner && tx == kk) betaT[k] = beta;
+    });
   } else if ((S > 0 || ODD || kk > 0) && wave == ((kk + 3) & 3)) {
     leave_reflector(lds.v[1 - ODD], k - 1, lane, alpha, diag, refl, dT, eT);   // of the step before, complete since that step's first barrier
   }
@@ -807,44 +895,14 @@ __device__ __forceinline__ void householder_step(int kk, int wave, double (&A)[6
   vp_columns<S>(vb, tx, vj);
   const int row = VP_LD * ((tx & 7) >> 1) + 2 * ty + (tx & 1);   // vp_at(ty + 16 (tx & 7))
   const double vr = vb[row];
-  {
-    double part[8];
-    EOQ_SFOR(a, 8,
-      if constexpr (a >= S) {
-        // one chain per row: the chains of the live rows interleave, which is independent work enough
-        double s0 = 0.0;
-        EOQ_SFOR(b, 8, if constexpr (b >= S) s0 = fma(A[a * 8 + b], vj[b], s0););
-        part[a] = s0;
-      } else {
-        part[a] = 0.0;
-      });
-    const double tot = row16_fold<S>(part, tx);
-    if (fold_writer<S>(tx)) lds.p[vp_at(ty + 16 * fold_index<S>(tx))] = beta * tot;
-  }
+  double part[8];
+  rows_times_v<S>(A, vj, part);
+  store_p<S>(part, beta, ty, tx, lds.p);
   __syncthreads();
-  // v^T p from the column entries this lane holds anyway, summed over its DPP row (every row of 16 lanes covers
-  // all 128 columns and gets the same bits)
   double wj[8];
   vp_columns<S>(lds.p, tx, wj);
   const double pr = lds.p[row];
-  double dl0 = 0.0, dl1 = 0.0;
-  EOQ_SFOR(b, 8,
-    if constexpr (b >= S) {
-      if constexpr ((b & 1) == 0) dl0 = fma(vj[b], wj[b], dl0);
-      else dl1 = fma(vj[b], wj[b], dl1);
-    });
-  // v w^T + w v^T with w = p - K v is v p^T + q v^T with q = p - 2 K v: the correction is needed in the row view
-  // only, the column view of p goes into the update as it was read
-  const double K2 = beta * row16_sum_uniform(dl0 + dl1);
-  double nv = -vr, nq = fma(K2, vr, -pr);   // rows of -v and -q
-  // a lane move must not follow within two instructions of the write of what it moves; the compiler keeps that distance for its
-  // own moves and does not see into fmac_bcast
-  asm volatile("s_nop 1" : "+v"(nq), "+v"(nv));
-  EOQ_SFOR(e, 64,
-    if constexpr ((e >> 3) >= S && (e & 7) >= S) {
-      fmac_bcast<(e >> 3)>(A[e], nq, vj[e & 7]);
-      fmac_bcast<(e >> 3)>(A[e], nv, wj[e & 7]);
-    });
+  rank_two_update<S>(A, vj, wj, vr, pr, beta_v_dot_p<S>(vj, wj, beta), []() {});
 }
 
 // Steps 16 S .. 16 S + 15, two to a round of the loop: addresses in LDS are constants then
@@ -855,6 +913,101 @@ __device__ __forceinline__ void householder_stage(int wave, double (&A)[64], dou
   for (int kk = 0; kk < 16; kk += 2) {
     householder_step<S, 0>(kk, wave, A, alpha, diag, tid, lds, refl, dT, eT, betaT);
     householder_step<S, 1>(kk + 1, wave, A, alpha, diag, tid, lds, refl, dT, eT, betaT);
+  }
+}
+
+// The same reduction where a workgroup has a compute unit to itself (LONE): a fifth wave, in the registers that a second workgroup
+// would take, has row k + 1 as it is before the update of step k, updates it by itself and forms reflector k + 1 while the four
+// others update the matrix, so that the two chains of a step run side by side.  The row takes the very operations that it takes in
+// the matrix: the same bits.  A sixth wave, on another SIMD, makes the float copies.  Two barriers a step: v complete (and row k + 2
+// there), p complete.  What bounds a step is the longer of the two chains, about 200 instructions of the fifth wave or the update of
+// the wave that shares its SIMD, behind the product and its fold: 2.2 thousand cycles on the full matrix, 1.2 on the last of the six
+// stages (2.3 and 1.3 with the reflector formed by the wave that owns the row).  The fifth wave issues first (s_setprio): in turn
+// with the wave beside it a step takes 2.5 and 1.4.  With beta handed over behind the barrier, by a word that the others poll, 2.3
+// and 1.3.
+struct LoneLds { ReduceLds red; double row[2][VP_LEN]; };   // row k in row[k & 1]
+__device__ __forceinline__ ReduceLds& reduce_part(ReduceLds& l) { return l; }
+__device__ __forceinline__ ReduceLds& reduce_part(LoneLds& l) { return l.red; }
+
+// columns of sub-tile row a, b >= S
+template <int S>
+__device__ __forceinline__ void leave_row(const double (&A)[64], bool next, int tx, double* to) {
+  EOQ_SFOR(m, 4,
+    if constexpr (2 * m + 1 >= S) {
+      double e0 = 2 * m >= S ? A[S * 8 + 2 * m] : 0.0; double e1 = A[S * 8 + 2 * m + 1];
+      if (next) {
+        e0 = A[(S + 1) * 8 + 2 * m];
+        e1 = A[(S + 1) * 8 + 2 * m + 1];
+      }
+      *reinterpret_cast<double2*>(to + VP_LD * m + 2 * tx) = make_double2(e0, e1);
+    });
+}
+template <int S, int ODD>
+__device__ __forceinline__ void lone_matrix_step(int kk, int wave, double (&A)[64], int tid, LoneLds& lds, const double* betaT) {
+  const int lane = tid & 63, ty = lane_row(tid), tx = tid & 15;
+  const double beta = betaT[16 * S + kk];
+  double vj[8], part[8];
+  vp_columns<S>(lds.red.v[ODD], tx, vj);
+  const int row = VP_LD * ((tx & 7) >> 1) + 2 * ty + (tx & 1);   // vp_at(ty + 16 (tx & 7))
+  const double vr = lds.red.v[ODD][row];
+  rows_times_v<S>(A, vj, part);
+  store_p<S>(part, beta, ty, tx, lds.red.p);
+  __syncthreads();
+  double wj[8];
+  vp_columns<S>(lds.red.p, tx, wj);
+  const double pr = lds.red.p[row];
+  rank_two_update<S>(A, vj, wj, vr, pr, beta_v_dot_p<S>(vj, wj, beta), [&]() __attribute__((always_inline)) {
+    if (wave == ((kk + 2) & 3) && (lane >> 4) == (((kk + 2) & 15) >> 2)) leave_row<S>(A, kk >= 14, tx, lds.row[ODD]);   // row k + 2
+  });
+  __syncthreads();
+}
+template <int S>
+__device__ __forceinline__ void lone_matrix_stage(int wave, double (&A)[64], int tid, LoneLds& lds, const double* betaT) {
+#pragma unroll 1
+  for (int kk = 0; kk < 16; kk += 2) {
+    lone_matrix_step<S, 0>(kk, wave, A, tid, lds, betaT);
+    lone_matrix_step<S, 1>(kk + 1, wave, A, tid, lds, betaT);
+  }
+}
+// The fifth wave, every row of whose lanes does the same: row k + 1 in x, reflector k in v, both by columns.
+struct Reflector { double x[8], v[8], alpha, beta, diag; };
+template <int S, int ODD>
+__device__ __forceinline__ void lone_form(int kk, Reflector& h, int lane, LoneLds& lds, double* betaT) {
+  form_reflector<S, ODD, true>(kk, h.x, lane & 15, lane < 16, lds.red.v[ODD], h.v, h.alpha, h.diag,
+                         [&](bool some, double t) __attribute__((always_inline)) {
+                           h.beta = some ? newton_rcp(t) : 0.0;
+                           if (lane == 0) betaT[16 * S + kk] = h.beta;
+                         });
+  __syncthreads();   // v complete
+}
+// Step k = 16 S + kk from there to row k + 1 behind its update
+template <int S, int ODD>
+__device__ __forceinline__ void lone_row_step(int kk, Reflector& h, int lane, LoneLds& lds, double* dT, double* eT) {
+  const int k = 16 * S + kk, tx = lane & 15;
+  vp_columns<S>(lds.row[1 - ODD], tx, h.x);
+  const double v1 = lds.red.v[ODD][vp_at(k + 1)];
+  if (lane == kk) {
+    dT[k] = h.diag;
+    eT[k] = h.alpha;
+  }
+  __syncthreads();   // p complete
+  const double p1 = lds.red.p[vp_at(k + 1)];
+  double wj[8];
+  vp_columns<S>(lds.red.p, tx, wj);
+  const double K2 = beta_v_dot_p<S>(h.v, wj, h.beta);
+  const double nv = -v1, nq = fma(K2, v1, -p1);
+  EOQ_SFOR(b, 8, if constexpr (b >= S) h.x[b] = fma(nv, wj[b], fma(nq, h.v[b], h.x[b])););
+}
+template <int S>
+__device__ __forceinline__ void lone_row_stage(Reflector& h, int lane, LoneLds& lds, double* dT, double* eT, double* betaT) {
+#pragma unroll 1
+  for (int kk = 0; kk < 16; kk += 2) {
+    lone_row_step<S, 0>(kk, h, lane, lds, dT, eT);
+    lone_form<S, 1>(kk + 1, h, lane, lds, betaT);
+    lone_row_step<S, 1>(kk + 1, h, lane, lds, dT, eT);
+    if (kk < 14) lone_form<S, 0>(kk + 2, h, lane, lds, betaT);
+    else if constexpr (S < 5) lone_form<S + 1, 0>(0, h, lane, lds, betaT);
+    else __syncthreads();
   }
 }
 
@@ -1168,27 +1321,48 @@ __device__ __forceinline__ void twisted_chain(double* F, const double* M, int rt
   *ssq_out = ssq;
 }
 
-__global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
+// One pool, used in turn by the Gram stage (byte planes, then the tiles on their way into the cyclic layout), the reduction
+// (reflectors) and the eigenvector stage (u1).
+template <bool LONE>
+struct TridiagLds {
+  __align__(16) unsigned char pool[POOL_BYTES];
+  __align__(16) std::conditional_t<LONE, LoneLds, ReduceLds> reduce;
+  __align__(16) double2 de[D + 1];   // (d_i, e_{i-1}^2) of the scaled tridiagonal matrix; de[D] = 0
+  double dT[D], eT[D], betaT[D];
+  double chain[EV_BATCH][2];         // sums of squares of the two halves of each vector
+  double lam[D], atoms[D];
+  double scale[EOQ_RMAX_CAP];
+  ShrinkLds shrink;
+  double tscale;
+  int twist[EV_BATCH];
+  unsigned flag;
+};
+// LONE: the batch has no more blocks than the device has compute units, and a workgroup the whole of one.  Six waves during the
+// reduction (see LoneLds), four behind it, and a block with repeated eigenvalues is solved on the spot, in the LDS that is free then:
+// no kernel behind this one looks for marks (4 us).
+constexpr int LONE_THREADS = THREADS + 128;
+template <bool LONE> struct SpectralLds { TridiagLds<false> t; };
+template <> struct SpectralLds<true> { union { TridiagLds<true> t; JacobiLds jacobi; }; };
+
+template <bool LONE>
+__device__ __forceinline__ void tridiag_block(SpectralLds<LONE>& lds,
     const void* __restrict__ blocks, EoqBlockMap map, int dtype, int n, int k_pilot, double rank_thr, int r_max, int loss,
     int* __restrict__ marks, double* __restrict__ lam_out, float* __restrict__ wfac,
     double* __restrict__ tri, int32_t* __restrict__ rank_out, float* __restrict__ phi_out, float* __restrict__ sigma_out,
     uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
-  // one pool, used in turn by the Gram stage (byte planes, then the tiles on their way into the cyclic layout), the
-  // reduction (reflectors) and the eigenvector stage (u1)
-  __shared__ __align__(16) unsigned char pool[POOL_BYTES];
+  unsigned char* pool = lds.t.pool;
   float* refl = reinterpret_cast<float*>(pool) + REFL_SLACK;
   unsigned char* u1 = pool + REFL_BYTES;
   double* wy = reinterpret_cast<double*>(u1 + TW_BYTES);   // triangular factors of the back-transformation
-  __shared__ __align__(16) ReduceLds red;
-  __shared__ __align__(16) double2 de[D + 1];  // (d_i, e_{i-1}^2) of the scaled tridiagonal matrix; de[D] = 0
-  __shared__ double dT[D], eT[D], betaT[D];
-  __shared__ double chain_s[EV_BATCH][2];  // sums of squares of the two halves of each vector
-  __shared__ int twist_s[EV_BATCH];
-  __shared__ double lam_s[D], atoms[D];
-  __shared__ double scale_s[EOQ_RMAX_CAP];
-  __shared__ ShrinkLds shrink_s;
-  __shared__ double tscale_s;
-  __shared__ unsigned flag_s;
+  ReduceLds& red = reduce_part(lds.t.reduce);
+  double2* de = lds.t.de;
+  double *dT = lds.t.dT, *eT = lds.t.eT, *betaT = lds.t.betaT;
+  double (&chain_s)[EV_BATCH][2] = lds.t.chain;
+  int* twist_s = lds.t.twist;
+  double *lam_s = lds.t.lam, *atoms = lds.t.atoms, *scale_s = lds.t.scale;
+  ShrinkLds& shrink_s = lds.t.shrink;
+  double& tscale_s = lds.t.tscale;
+  unsigned& flag_s = lds.t.flag;
 
   const int tid = threadIdx.x;
   const size_t blk = blockIdx.x;
@@ -1199,6 +1373,31 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     betaT[D - 2] = betaT[D - 1] = 0.0;  // reflectors 126, 127 do not exist
     de[D] = make_double2(0.0, 0.0);
   }
+  if constexpr (LONE) {
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (w >= 4) {
+      // the barriers of the Gram stage: three a group of tokens and the six of tiles_to_lanes; the pool changes hands
+      const int before = (dtype == EOQ_F16 ? 3 * (n / GI_TOK) : 0) + 6 + 1;
+      for (int i = 0; i < before; ++i) __syncthreads();
+      __syncthreads();   // rows 0 and 1
+      if (w == 5) {
+        __syncthreads();   // v complete
+#pragma unroll 1
+        for (int k = 0; k < D - 32; ++k) {
+          __syncthreads();   // p complete
+          copy_reflector(red.v[k & 1], k, lane, refl);
+          __syncthreads();   // the next v complete
+        }
+        return;
+      }
+      __builtin_amdgcn_s_setprio(3);
+      Reflector h;
+      vp_columns<0>(lds.t.reduce.row[0], lane & 15, h.x);
+      lone_form<0, 0>(0, h, lane, lds.t.reduce, betaT);
+      EOQ_SFOR(s, 6, lone_row_stage<s>(h, lane, lds.t.reduce, dT, eT, betaT););
+      return;   // a wave that has ended counts at no barrier
+    }
+  }
 
   {
     double A[64];
@@ -1208,9 +1407,15 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     else
       gram_f64(static_cast<const float*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, reinterpret_cast<double*>(pool), tid, A, &flag_s);
     __syncthreads();  // the pool changes hands
-    {
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if constexpr (LONE) {
+      if (tid < 16) leave_row<0>(A, false, tid, lds.t.reduce.row[0]);
+      if (w == 1 && lane < 16) leave_row<0>(A, false, lane, lds.t.reduce.row[1]);
+      __syncthreads();   // rows 0 and 1 are there
+      __syncthreads();   // and the first reflector
+      EOQ_SFOR(s, 6, lone_matrix_stage<s>(w, A, tid, lds.t.reduce, betaT););
+    } else {
       double alpha = 0.0, diag = 0.0;
-      const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
       EOQ_SFOR(s, 6, householder_stage<s>(w, A, alpha, diag, tid, red, refl, dT, eT, betaT););
       if (w == 3) leave_reflector(red.v[1], 95, lane, alpha, diag, refl, dT, eT);   // a step is left behind in the next
     }
@@ -1417,7 +1622,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     {
       const double lam_k1 = lam_s[k_pilot], lam_2k1 = lam_s[2 * k_pilot];
       const double lam_plus = lam_k1 + EDGE_COEF * (lam_k1 - lam_2k1);
-      rt = __syncthreads_count((tid < D && lam_s[tid] / lam_plus - 1.0 > rank_thr) ? 1 : 0);   // also orders `atoms`
+      rt = count_columns(tid < D && lam_s[tid] / lam_plus - 1.0 > rank_thr, shrink_s.above + 2);   // also orders `atoms`
     }
     {
       // rt + 3 eigenvalues when they fit 32 groups, else the 32 largest (all that can be retained)
@@ -1468,7 +1673,10 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
   for (int i = 0; i < r; ++i)
     if (lam_s[i] - lam_s[i + 1] <= CLUSTER_TOL * lam_s[0]) repeated = true;
   if (repeated) {
-    if (tid == 0) {
+    if constexpr (LONE) {
+      jacobi_block(lds.jacobi, blocks, map, dtype, n, k_pilot, rank_thr, r_max, loss, blk, slot, lam_out, wfac, rank_out, phi_out, sigma_out,
+                   rfac, flags_out);
+    } else if (tid == 0) {
       marks[blk] = 1;
       rank_out[slot] = r;
       flags_out[slot] = flag_s;
@@ -1653,10 +1861,28 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
     }
   }
   if (tid == 0) {
-    marks[blk] = 0;
+    if constexpr (!LONE) marks[blk] = 0;
     rank_out[slot] = r;
     flags_out[slot] = flag_s;
   }
+}
+
+__global__ __launch_bounds__(THREADS, 2) void eoq_spectral_tridiag_kernel(
+    const void* __restrict__ blocks, EoqBlockMap map, int dtype, int n, int k_pilot, double rank_thr, int r_max, int loss,
+    int* __restrict__ marks, double* __restrict__ lam_out, float* __restrict__ wfac,
+    double* __restrict__ tri, int32_t* __restrict__ rank_out, float* __restrict__ phi_out, float* __restrict__ sigma_out,
+    uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
+  __shared__ SpectralLds<false> lds;
+  tridiag_block<false>(lds, blocks, map, dtype, n, k_pilot, rank_thr, r_max, loss, marks, lam_out, wfac, tri, rank_out, phi_out,
+                       sigma_out, rfac, flags_out);
+}
+__global__ __launch_bounds__(LONE_THREADS) void eoq_spectral_lone_kernel(
+    const void* __restrict__ blocks, EoqBlockMap map, int dtype, int n, int k_pilot, double rank_thr, int r_max, int loss,
+    double* __restrict__ lam_out, float* __restrict__ wfac, double* __restrict__ tri, int32_t* __restrict__ rank_out,
+    float* __restrict__ phi_out, float* __restrict__ sigma_out, uint16_t* __restrict__ rfac, uint32_t* __restrict__ flags_out) {
+  __shared__ SpectralLds<true> lds;
+  tridiag_block<true>(lds, blocks, map, dtype, n, k_pilot, rank_thr, r_max, loss, nullptr, lam_out, wfac, tri, rank_out, phi_out,
+                      sigma_out, rfac, flags_out);
 }
 
 }  // namespace
@@ -1671,6 +1897,12 @@ hipError_t eoq_launch_spectral(const EoqLaunch& L, const void* blocks, int dtype
     hipLaunchKernelGGL(eoq_spectral_jacobi_kernel, dim3((unsigned)B), dim3(THREADS), 0, L.stream, blocks, L.map, dtype, L.n,
                        L.k, L.rank_thr, L.r_max, L.loss, B, (const int*)nullptr, lam, wfac, out.rank,
                        out.phi, out.sigma, out.rfac, out.flags);
+  } else if (B <= L.units) {
+    // A compute unit for every block.  Compress calls, us, here and with the two kernels below: 16 blocks of 128 x 128 136.5 and
+    // 145.1, 256 of them 137.6 and 145.8, 256 of 1024 x 128 211.8 and 220.7.  One block more and a unit has to hold two at a time
+    // (257 of 128 x 128: 190).
+    hipLaunchKernelGGL(eoq_spectral_lone_kernel, dim3((unsigned)B), dim3(LONE_THREADS), 0, L.stream, blocks, L.map, dtype, L.n,
+                       L.k, L.rank_thr, L.r_max, L.loss, lam, wfac, tri, out.rank, out.phi, out.sigma, out.rfac, out.flags);
   } else {
     hipLaunchKernelGGL(eoq_spectral_tridiag_kernel, dim3((unsigned)B), dim3(THREADS), 0, L.stream, blocks, L.map, dtype, L.n,
                        L.k, L.rank_thr, L.r_max, L.loss, marks, lam, wfac, tri, out.rank, out.phi, out.sigma, out.rfac,

@@ -372,6 +372,28 @@ def test_hand_over_to_the_jacobi_solver_in_large_batches():
     assert torch.equal(ctx.spectrum(ws, B), ref_lam[idx])
 
 
+@pytest.mark.parametrize("n,dtype", [(128, torch.float16), (384, torch.float16), (128, torch.float32), (384, torch.float32)])
+def test_blocks_with_a_compute_unit_each_are_those_of_larger_batches(n, dtype):
+    """Up to one block to a compute unit another kernel takes the batch: rows of the reduction are updated by a wave of their own,
+    and blocks with repeated singular values (two here) are solved on the spot.  Same operations, same bits."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    spec = synth.BlockSpec("units", n=n, n_tensors=1, blocks_per_tensor=units + 1, rank_lo=1, rank_hi=9, frac_rank0=0.1)
+    blocks, _ = synth.make_blocks(spec, seed=52)
+    blocks = blocks.to(dtype)
+    bank = _bank_with_repeated_values(n).to(dtype).cpu()
+    blocks[3], blocks[units - 1], blocks[7] = bank[0], bank[1], 0
+    _, many, lam = _gpu_compress(blocks, 2, n)
+    for count in (1, 5, units):
+        _, few, lam_few = _gpu_compress(blocks[:count], 2, n)
+        assert np.array_equal(lam_few, lam[:count])
+        rank = few.rank.cpu().tolist()
+        for f in ("codes", "norms", "rank", "flags"):
+            assert _bits_equal(getattr(few, f), getattr(many, f)[:count]), (f, count)
+        for b, r in enumerate(rank):
+            for f in ("phi", "sigma", "lfac", "rfac"):
+                assert _bits_equal(getattr(few, f)[b, :r], getattr(many, f)[b, :r]), (f, b, count)
+
+
 @pytest.mark.parametrize("distance", [1, 16, 20])
 def test_hand_over_to_the_jacobi_solver_uses_the_whole_chip(distance):
     """200 marked blocks, side by side or at a fixed distance, take about as long as one: there are more workgroups than

@@ -116,6 +116,37 @@ def test_rows_of_the_update_are_settled_before_they_are_moved_between_lanes(list
 
 
 @pytest.mark.skipif(not os.path.exists(g.HIPCC), reason="no compiler")
+def test_kernel_with_a_compute_unit_to_itself_keeps_both_orders(listings):
+    """The two orders above in the kernel of small batches, whose extra waves end early."""
+    lines = [l.split(";")[0].strip() for l in open(listings("eoq_spectral.hip"))]
+    first = next(i for i, l in enumerate(lines) if re.match(r"_Z\w*eoq_spectral_lone_kernel\w*:", l))
+    last = next(i for i in range(first, len(lines)) if lines[i].startswith(".Lfunc_end"))
+    lines = [l for l in lines[first:last] if l and not re.match(r"\.(?!LBB)", l)]
+    # stores of the tridiagonal matrix, the wait for them, the barrier, the 32 touches through the scalar cache
+    load = next(i for i, l in enumerate(lines) if l.startswith("s_load_dword ") and l.endswith(", 0x7c0"))
+    base = lines[load].split(",")[1].strip()
+    touch = next(i for i, l in enumerate(lines) if l.startswith("s_load_dword ") and l.endswith(f", {base}, 0x0"))
+    store = max(i for i in range(touch) if lines[i].startswith("global_store_dwordx4"))
+    barrier = next(i for i in range(store, touch) if lines[i] == "s_barrier")
+    waits = [i for i in range(store, barrier) if lines[i].startswith("s_waitcnt") and "vmcnt(0)" in lines[i]]
+    assert waits and not any("store" in l for l in lines[waits[0]:barrier])
+    # what a lane move takes is written two instructions before it or more, on every path
+    def registers(operand):
+        m = re.match(r"-?\|?v\[(\d+):(\d+)\]", operand)
+        return set(range(int(m[1]), int(m[2]) + 1)) if m else ({int(operand[1:])} if re.match(r"v\d+$", operand) else set())
+    moves = [i for i, l in enumerate(lines) if l.startswith("v_fmac_f64_dpp")]
+    assert len(moves) == 2 * 2 * (64 + 49 + 36 + 25 + 16 + 9)
+    for i in moves:
+        source, states, j = registers(lines[i].split()[2].rstrip(",")), 0, i
+        while states < 2:
+            j -= 1
+            if lines[j].endswith(":"):
+                continue   # what is jumped over stands in front of it: fewer instructions between, the same ones before
+            assert not (lines[j].startswith("v_") and registers(lines[j].split()[1].rstrip(",")) & source), (lines[j], lines[i])
+            states += 1 + (int(lines[j].split()[1]) if lines[j].startswith("s_nop") else 0)
+
+
+@pytest.mark.skipif(not os.path.exists(g.HIPCC), reason="no compiler")
 @pytest.mark.parametrize("source", SOURCES)
 def test_registers_pass_the_compiler_s_own_check(source, listings):
     """The compiler has lost a read of a register set in flight (one half of a loaded pair, read twice) and given the register away
