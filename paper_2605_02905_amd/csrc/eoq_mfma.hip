@@ -699,7 +699,8 @@ __global__ __launch_bounds__(64 * QWAVES, 2) void eoq_qjl_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// encode (binary16 blocks): one workgroup per block, 128 tokens per pass.
+// encode (binary16 blocks): one workgroup per block, or per share of a block where a batch has few (eoq_encode_shares), 128
+// tokens per pass.
 //   phase 1 (wave w, its own 32 tokens, v_mfma_f32_32x32x8_f16 so that every result feeds the next product
 //            without leaving the registers):
 //     C^T = W S^T          W = V diag(phi/sigma) as hi + lo binary16, S from the LDS tile
@@ -729,7 +730,7 @@ constexpr int VLD = EOQ_RMAX_CAP + 8;  // row stride (halfs) of V^T in LDS
 // projected, and the residual is taken against them.
 template <int BITS, bool FQ>
 __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
-    const uint16_t* __restrict__ blocks, EoqBlockMap map, int n, int r_max, const uint16_t* __restrict__ pih,
+    const uint16_t* __restrict__ blocks, EoqBlockMap map, int n, int share, int r_max, const uint16_t* __restrict__ pih,
     const float* __restrict__ tab, const float* __restrict__ wfac, const int32_t* __restrict__ rank_in,
     const uint16_t* __restrict__ rfac, uint16_t* lfac, uint16_t* __restrict__ norms,
     uint8_t* __restrict__ codes) {
@@ -749,9 +750,13 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
   // chunk ahead: the first chunk's here, before the tables
   const size_t tok = (size_t)map.token_stride;
   const uint16_t* src0 = blocks + map.in_base(blk) + (size_t)(32 * wave) * tok;
+  const int t_first = (int)blockIdx.y * share, t_end = min(t_first + share, n);   // this workgroup's tokens: whole chunks
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 pre[8];
-  EOQ_SFOR(it, 8, pre[it] = *reinterpret_cast<const u32x4*>(src0 + (4 * it + (lane >> 4)) * tok + (lane & 15) * 8););
+  {
+    const uint16_t* src = src0 + (size_t)t_first * tok;
+    EOQ_SFOR(it, 8, pre[it] = *reinterpret_cast<const u32x4*>(src + (4 * it + (lane >> 4)) * tok + (lane & 15) * 8););
+  }
 
   // stationary rotation operand: rows 32w .. 32w + 31 of Pi.  Up to 3 bits the binary16 rounding of Pi alone (one
   // matrix-core pass): it moves z sqrt(d) by a sum of 128 independent roundings, standard deviation 1.4e-4, the size of
@@ -803,7 +808,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
   const __amdgpu_buffer_rsrc_t lbuf = buffer_of(lfac + slot * r_max * (size_t)n, (size_t)r * n * 2);
   const __amdgpu_buffer_rsrc_t cbuf = buffer_of(codes + slot * (size_t)n * ROWB, (size_t)n * ROWB);
 
-  for (int t0 = 0; t0 < n; t0 += CHUNK) {
+  for (int t0 = t_first; t0 < t_end; t0 += CHUNK) {
     __syncthreads();  // previous chunk's tiles consumed (and the factor tables written)
     // ---- phase 1 ----
     {
@@ -891,7 +896,7 @@ __global__ __launch_bounds__(THREADS, 2) void eoq_encode_mfma_kernel(
     // the next chunk's rows travel while this one is rotated and quantised (requested here and not earlier: phase 1
     // has no registers to spare)
     __builtin_amdgcn_sched_barrier(0);
-    if (t0 + CHUNK < n) {
+    if (t0 + CHUNK < t_end) {
       const uint16_t* src = src0 + (size_t)(t0 + CHUNK) * tok;
       EOQ_SFOR(it, 8, pre[it] = *reinterpret_cast<const u32x4*>(src + (4 * it + (lane >> 4)) * tok + (lane & 15) * 8););
     }
@@ -981,17 +986,30 @@ hipError_t eoq_launch_qjl(const EoqLaunch& L, const void* blocks_fp16, int64_t B
   return hipGetLastError();
 }
 
+// Workgroups that share the `chunks` chunks of 128 tokens of a block: as many as fit one round of the chip, two to each of its
+// `units` compute units, whole chunks each and none without.  Every share sets its tables up again, which costs as much as a chunk
+// (11 of 23 thousand cycles), so a batch that fills the chip keeps whole blocks.  Compress calls at 2 bits, us, whole blocks and
+// shared: 16 blocks of 1024 x 128 195.8 and 173.9, 100 of 512 x 128 176.3 and 168.1.
+extern "C" int eoq_encode_shares(int64_t B, int chunks, int units) {
+  const int64_t most = B > 0 ? 2 * (int64_t)units / B : 1;
+  const int shares = most < 1 ? 1 : (most < chunks ? (int)most : chunks);
+  const int each = (chunks + shares - 1) / shares;
+  return (chunks + each - 1) / each;
+}
+
 hipError_t eoq_launch_encode_f16(const EoqLaunch& L, const void* blocks, int64_t B, const float* wfac,
                                  eoq_packed out, bool stored_factors) {
-  const dim3 grid((unsigned)B), block(THREADS);
+  const int chunks = L.n / CHUNK, shares = eoq_encode_shares(B, chunks, L.units);
+  const int share = (chunks + shares - 1) / shares * CHUNK;
+  const dim3 grid((unsigned)B, (unsigned)shares), block(THREADS);
   const uint16_t* src = static_cast<const uint16_t*>(blocks);
 #define EOQ_ENCODE(BITS)                                                                                            \
   do {                                                                                                              \
     if (stored_factors)                                                                                             \
-      hipLaunchKernelGGL((eoq_encode_mfma_kernel<BITS, true>), grid, block, 0, L.stream, src, L.map, L.n, L.r_max,  \
+      hipLaunchKernelGGL((eoq_encode_mfma_kernel<BITS, true>), grid, block, 0, L.stream, src, L.map, L.n, share, L.r_max, \
                          L.pih, L.tab, wfac, out.rank, out.rfac, out.lfac, out.norms, out.codes);                   \
     else                                                                                                            \
-      hipLaunchKernelGGL((eoq_encode_mfma_kernel<BITS, false>), grid, block, 0, L.stream, src, L.map, L.n, L.r_max, \
+      hipLaunchKernelGGL((eoq_encode_mfma_kernel<BITS, false>), grid, block, 0, L.stream, src, L.map, L.n, share, L.r_max, \
                          L.pih, L.tab, wfac, out.rank, out.rfac, out.lfac, out.norms, out.codes);                   \
   } while (0)
   switch (L.bits) {

@@ -394,6 +394,27 @@ def test_blocks_with_a_compute_unit_each_are_those_of_larger_batches(n, dtype):
                 assert _bits_equal(getattr(few, f)[b, :r], getattr(many, f)[b, :r]), (f, b, count)
 
 
+@pytest.mark.parametrize("n,bits,q4", [(640, 1, False), (640, 4, False), (1024, 3, True)])
+def test_blocks_shared_by_several_workgroups_of_the_encoder(n, bits, q4):
+    """Few blocks are encoded by several workgroups each (all chunks apart, an even and an odd share), many by one: the same bits."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    spec = synth.BlockSpec("shares", n=n, n_tensors=1, blocks_per_tensor=2 * units + 1, rank_lo=1, rank_hi=11, frac_rank0=0.1)
+    blocks = synth.make_blocks(spec, seed=57)[0].cuda()
+    ctx = eoq.Context(n=n, bits=bits)
+    compress = (lambda x: ctx.eoq_compress_q4(x)[0]) if q4 else (lambda x: ctx.eoq_compress(x)[0])
+    many = compress(blocks)
+    shares = eoq.lib().eoq_encode_shares
+    assert shares(C.c_int64(2 * units + 1), n // 128, units) == 1
+    for count in (1, units // 2 - 28, units - 56):
+        assert shares(C.c_int64(count), n // 128, units) > 1
+        few = compress(blocks[:count].contiguous())
+        rank = few.rank.cpu().tolist()
+        for f in ("codes", "norms", "rank"):
+            assert _bits_equal(getattr(few, f), getattr(many, f)[:count]), (f, count)
+        for b, r in enumerate(rank):
+            assert _bits_equal(few.lfac[b, :r], many.lfac[b, :r]), (b, count)
+
+
 @pytest.mark.parametrize("distance", [1, 16, 20])
 def test_hand_over_to_the_jacobi_solver_uses_the_whole_chip(distance):
     """200 marked blocks, side by side or at a fixed distance, take about as long as one: there are more workgroups than

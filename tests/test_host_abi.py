@@ -182,3 +182,14 @@ def test_scores_grid_has_the_runs_in_front_of_the_tail(lib, heads, runs, tail_gr
     places = [p for p in places if p[1]]
     assert places == sorted(places) and [p[0] for p in places] == ["run"] * (runs > 0) + ["tail"] * (tail_groups > 0)
     assert sum(p[1] for p in places if p[0] == "run") == heads * runs
+
+
+def test_shares_of_a_block_are_whole_chunks_and_none_is_empty():
+    shares = eoq.lib().eoq_encode_shares
+    for units in (1, 104, 256):
+        for chunks in range(1, 33):
+            for B in (0, 1, 2, 3, units // 3, units - 1, units, units + 1, 2 * units - 1, 2 * units, 2 * units + 1, 1 << 24):
+                k = shares(C.c_int64(B), chunks, units)
+                each = -(-chunks // k)
+                assert 1 <= k <= chunks and (k - 1) * each < chunks <= k * each
+                assert k == 1 or B * k <= 2 * units
