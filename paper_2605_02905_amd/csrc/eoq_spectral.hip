@@ -528,55 +528,52 @@ __device__ __forceinline__ float scale_high_half(uint32_t w, float s) {
   asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(s));
   return r;
 }
-// cmax: 4 x 64 words (the waves' column maxima), cexp: 128 ints (exponent of the integer unit of each column); both
-// outside the pool, which the planes fill.  n is a multiple of 128.
+// cmax: twice 4 x 64 words (the waves' column maxima, by turns), cexp: 128 ints (exponent of the integer unit of each column);
+// both outside the pool, which the planes fill.  n is a multiple of 128.
 __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size_t tok, int n, unsigned char* pool,
                                           uint32_t* cmax, int* cexp, int tid, double (&A)[64], unsigned* flag_s) {
   const int lane = tid & 63, l16 = lane & 15, kg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = tid & 15, q = tid >> 4;  // loader: columns 8m .. 8m+7, tokens 64 h + 4q .. 64 h + 4q + 3 of the group
+  // loader: columns 4 m .. 4 m + 3, tokens 16 q .. 16 q + 15 of the group: the sixteen bytes of a column and plane are one write
+  const int m = tid & 31, q = tid >> 5;
   double Gacc[9][4];  // tile number wave + 4 s, rows 4 kg + v, column l16
   EOQ_SFOR(s, 9, EOQ_SFOR(v, 4, Gacc[s][v] = 0.0;););
 
-  // gi_place of the loader's column 8 m, chunk q / 4 (bits 4 .. 6 and 7 .. 9 flipped by c for column 8 m + c), and of the operands
-  const int w_base = gi_place(8 * m, q >> 2) + 4 * (q & 3), r_base = gi_place(l16, kg);
+  // gi_place of the loader's column 4 m, chunk q (bits 4, 5 and 7, 8 flipped by c for column 4 m + c), and of the operands
+  const int w_base = gi_place(4 * m, q), r_base = gi_place(l16, kg);
   uint32_t top = 0u;  // largest |binary16 pattern| this lane has seen in its columns: 0x7C00 and above is Inf / NaN
-  uint4 raw[8];
+  const uint16_t* mine = src + (size_t)(16 * q) * tok + 4 * m;
+  uint2 raw[16];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    raw[i] = *reinterpret_cast<const uint4*>(src + (size_t)(64 * (i >> 2) + 4 * q + (i & 3)) * tok + 8 * m);
+  for (int i = 0; i < 16; ++i) raw[i] = *reinterpret_cast<const uint2*>(mine + (size_t)i * tok);
 
 #pragma unroll 1
   for (int t0 = 0; t0 < n; t0 += GI_TOK) {
-    // ---- column maxima of the group: over the lane's eight tokens, the wave's four loader rows, the four waves ----
-    uint32_t mx[4] = {0u, 0u, 0u, 0u};
+    // ---- column maxima of the group: over the lane's sixteen tokens, the two halves of the wave, the four waves ----
+    uint32_t mx[2] = {0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 16; ++i) {
       mx[0] = pk_max_u16(mx[0], raw[i].x & 0x7FFF7FFFu);
       mx[1] = pk_max_u16(mx[1], raw[i].y & 0x7FFF7FFFu);
-      mx[2] = pk_max_u16(mx[2], raw[i].z & 0x7FFF7FFFu);
-      mx[3] = pk_max_u16(mx[3], raw[i].w & 0x7FFF7FFFu);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      mx[i] = pk_max_u16(mx[i], (uint32_t)__shfl_xor((int)mx[i], 16, 64));
-      mx[i] = pk_max_u16(mx[i], (uint32_t)__shfl_xor((int)mx[i], 32, 64));
+    for (int i = 0; i < 2; ++i) {
+      const auto o = __builtin_amdgcn_permlane32_swap(mx[i], mx[i], false, false);
+      mx[i] = pk_max_u16(o[0], o[1]);
     }
-    __syncthreads();  // the previous group no longer reads planes, maxima or exponents
-    if (kg == 0) *reinterpret_cast<uint4*>(cmax + wave * 64 + m * 4) = make_uint4(mx[0], mx[1], mx[2], mx[3]);
-    __syncthreads();
+    uint32_t* cm = cmax + ((t0 / GI_TOK) & 1) * 256;   // the other half may still be read
+    if (lane < 32) *reinterpret_cast<uint2*>(cm + wave * 64 + m * 2) = make_uint2(mx[0], mx[1]);
+    __syncthreads();  // maxima complete; the previous group no longer reads planes or exponents
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const uint4 o = *reinterpret_cast<const uint4*>(cmax + w * 64 + m * 4);
+      const uint2 o = *reinterpret_cast<const uint2*>(cm + w * 64 + m * 2);
       mx[0] = pk_max_u16(mx[0], o.x);
       mx[1] = pk_max_u16(mx[1], o.y);
-      mx[2] = pk_max_u16(mx[2], o.z);
-      mx[3] = pk_max_u16(mx[3], o.w);
     }
-    top = pk_max_u16(top, pk_max_u16(pk_max_u16(mx[0], mx[1]), pk_max_u16(mx[2], mx[3])));
+    top = pk_max_u16(top, pk_max_u16(mx[0], mx[1]));
     // ---- integers, byte planes ----
-    int ex[8];
-    EOQ_SFOR(c, 8,
+    int ex[4];
+    EOQ_SFOR(c, 4,
       const uint32_t hmax = (mx[c >> 1] >> (16 * (c & 1))) & 0xFFFFu;
       const int ef = max((int)(hmax >> 10), 1);               // biased exponent of the column maximum (subnormals: 1)
       const float scale = __int_as_float((171 - ef) << 23);   // 2^(29 - (ef - 15))
@@ -584,32 +581,23 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
       // I = sum_k d_k 256^k with balanced digits d_k in [-128, 127]: adding 128 to every digit place makes them the
       // plain bytes of I + 0x80808080 (|I| < 2^30: no carry out of the top), and flipping the top bit of each byte
       // takes the 128 off again, as a two's-complement byte.  The four planes are those bytes.
-      EOQ_SFOR(h, 2,
+      uint32_t pl[4][4];   // [four tokens][plane]
+      EOQ_SFOR(h, 4,
         uint32_t dg[4];
         EOQ_SFOR(it, 4,
-          const uint4 rw = raw[4 * h + it];
-          const uint32_t w = (c >> 1) == 0 ? rw.x : ((c >> 1) == 1 ? rw.y : ((c >> 1) == 2 ? rw.z : rw.w));
+          const uint32_t w = (c >> 1) == 0 ? raw[4 * h + it].x : raw[4 * h + it].y;
           const int I = (int)((c & 1) ? scale_high_half(w, scale) : scale_low_half(w, scale));   // truncation towards zero
           dg[it] = ((uint32_t)I + 0x80808080u) ^ 0x80808080u;
         );
-        uint32_t pl[4];
-        transpose_bytes(dg[0], dg[1], dg[2], dg[3], pl);
-        unsigned char* dst = pool + (w_base ^ (c << 4) ^ (h << 6) ^ (c * GI_ROW));
-        *reinterpret_cast<uint32_t*>(dst) = pl[0];
-        *reinterpret_cast<uint32_t*>(dst + GI_PLANE) = pl[1];
-        *reinterpret_cast<uint32_t*>(dst + 2 * GI_PLANE) = pl[2];
-        *reinterpret_cast<uint32_t*>(dst + 3 * GI_PLANE) = pl[3];
+        transpose_bytes(dg[0], dg[1], dg[2], dg[3], pl[h]);
       );
+      unsigned char* dst = pool + (w_base ^ (c << 4) ^ (c * GI_ROW));
+      EOQ_SFOR(p, 4, *reinterpret_cast<uint4*>(dst + p * GI_PLANE) = make_uint4(pl[0][p], pl[1][p], pl[2][p], pl[3][p]););
     );
-    if (q == 0) {
-      int4* to = reinterpret_cast<int4*>(cexp + 8 * m);
-      to[0] = make_int4(ex[0], ex[1], ex[2], ex[3]);
-      to[1] = make_int4(ex[4], ex[5], ex[6], ex[7]);
-    }
+    if (q == 0) *reinterpret_cast<int4*>(cexp + 4 * m) = make_int4(ex[0], ex[1], ex[2], ex[3]);
     if (t0 + GI_TOK < n) {  // next group on its way during the products
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        raw[i] = *reinterpret_cast<const uint4*>(src + (size_t)(t0 + GI_TOK + 64 * (i >> 2) + 4 * q + (i & 3)) * tok + 8 * m);
+      for (int i = 0; i < 16; ++i) raw[i] = *reinterpret_cast<const uint2*>(mine + (size_t)(t0 + GI_TOK + i) * tok);
     }
     __syncthreads();
     // ---- products: lane supplies row / column l16 of the tile, tokens 64 h + 16 kg .. + 15 ----
@@ -1376,8 +1364,8 @@ __device__ __forceinline__ void tridiag_block(SpectralLds<LONE>& lds,
   if constexpr (LONE) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (w >= 4) {
-      // the barriers of the Gram stage: three a group of tokens and the six of tiles_to_lanes; the pool changes hands
-      const int before = (dtype == EOQ_F16 ? 3 * (n / GI_TOK) : 0) + 6 + 1;
+      // the barriers of the Gram stage: two a group of tokens and the six of tiles_to_lanes; the pool changes hands
+      const int before = (dtype == EOQ_F16 ? 2 * (n / GI_TOK) : 0) + 6 + 1;
       for (int i = 0; i < before; ++i) __syncthreads();
       __syncthreads();   // rows 0 and 1
       if (w == 5) {
@@ -1403,7 +1391,7 @@ __device__ __forceinline__ void tridiag_block(SpectralLds<LONE>& lds,
     double A[64];
     if (dtype == EOQ_F16)
       gram_int8(static_cast<const uint16_t*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, pool,
-                reinterpret_cast<uint32_t*>(lam_s), reinterpret_cast<int*>(atoms), tid, A, &flag_s);
+                reinterpret_cast<uint32_t*>(lam_s) /* and atoms */, reinterpret_cast<int*>(dT), tid, A, &flag_s);
     else
       gram_f64(static_cast<const float*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, reinterpret_cast<double*>(pool), tid, A, &flag_s);
     __syncthreads();  // the pool changes hands
