@@ -293,6 +293,15 @@ eoq_status eoq_scores_prod(eoq_ctx* ctx, eoq_packed keys, eoq_qjl qjl, int64_t n
 eoq_status eoq_softmax(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, int64_t row_stride, void* hip_stream);
 
 /*
+ * eoq_softmax with DEVICE workspace, which lets several workgroups share a row where there are few long ones.
+ * eoq_softmax_workspace_bytes says how much such a call takes, and 0 where it gains nothing; with a NULL workspace, or where
+ * it is 0, the call is eoq_softmax.
+ */
+size_t eoq_softmax_workspace_bytes(const eoq_ctx* ctx, int64_t rows, int64_t len);
+eoq_status eoq_softmax_ws(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, int64_t row_stride, void* workspace,
+                          size_t workspace_bytes, void* hip_stream);
+
+/*
  * Attention output on compressed values without materialising them (Sec. 2.1 with V replaced by its
  * reconstruction; the split of Remark 6.5 applied to the values): out[s][h] = sum_t weights[s][h][t] x_hat_t over
  * the tokens of the first blocks_filled blocks of KV head h / (n_q_heads / n_kv_heads) of sequence s.

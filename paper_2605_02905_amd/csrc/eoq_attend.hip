@@ -767,6 +767,47 @@ __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_hea
   }
 }
 
+// A row of the softmax as accesses of four consecutive elements on 16-byte boundaries of the buffer.  What an access covers beside
+// the row reads as -inf and is not written.
+struct SoftmaxRow {
+  float* row;             // elements head .. end - 1 of this pointer are the row
+  int head;               // elements between the 16-byte boundary and the row
+  int64_t end, items;     // items: accesses
+  __device__ __forceinline__ SoftmaxRow(float* x, size_t number, int64_t len, int64_t stride) {
+    const size_t first = number * (size_t)stride;
+    head = (int)(first & 3);
+    row = x + (first - head);
+    end = head + len;
+    items = (end + 3) >> 2;
+  }
+  template <typename E> __device__ __forceinline__ bool whole(E e) const { return e >= (head ? 1 : 0) && e < (end >> 2); }   // nothing but the row
+  __device__ __forceinline__ bool has(int64_t at) const { return at >= head && at < end; }
+  template <typename E> __device__ __forceinline__ float4 load(E e) const {
+    float4 v = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (whole(e)) {
+      v = reinterpret_cast<const float4*>(row)[e];
+    } else {
+      const int64_t b = 4 * (int64_t)e;
+      if (has(b)) v.x = row[b];
+      if (has(b + 1)) v.y = row[b + 1];
+      if (has(b + 2)) v.z = row[b + 2];
+      if (has(b + 3)) v.w = row[b + 3];
+    }
+    return v;
+  }
+  template <typename E> __device__ __forceinline__ void store(E e, const float4& v) const {
+    if (whole(e)) {
+      reinterpret_cast<float4*>(row)[e] = v;
+    } else {
+      const int64_t b = 4 * (int64_t)e;
+      if (has(b)) row[b] = v.x;
+      if (has(b + 1)) row[b + 1] = v.y;
+      if (has(b + 2)) row[b + 2] = v.z;
+      if (has(b + 3)) row[b + 3] = v.w;
+    }
+  }
+};
+
 // Row-wise softmax in place (the attention weights of Sec. 2.1), one workgroup of NT lanes per row.  The row passes
 // through registers once: up to 4 NV elements per lane are loaded (all loads in flight), their maximum is met, they are
 // exponentiated and summed, met again, scaled and stored -- one read and one write of the row instead of three reads and
@@ -777,15 +818,9 @@ __global__ __launch_bounds__(THREADS) void eoq_attend_finish_kernel(int n_kv_hea
 template <int NT, int NV>
 __global__ __launch_bounds__(NT) void eoq_softmax_kernel(float* __restrict__ x, int64_t len, int64_t stride) {
   __shared__ float red[NT / 64];
-  const size_t first = blockIdx.x * (size_t)stride;
-  const int head = (int)(first & 3);              // elements between the 16-byte boundary and the row
-  float* row = x + (first - head);                // elements head .. end - 1 of this pointer are the row
-  const int64_t end = head + len;
-  const int64_t items = (end + 3) >> 2;
+  const SoftmaxRow r(x, blockIdx.x, len, stride);
+  const int64_t items = r.items;
   const int n_reg = (int)(items < NV * NT ? items : NV * NT);      // accesses of the register part
-  // accesses e_first .. e_last - 1 cover nothing but the row
-  const int e_first = head ? 1 : 0;
-  const int64_t e_last = end >> 2;
   const int tid = threadIdx.x;
   auto meet = [&](float v, bool maximum) __attribute__((always_inline)) {
 #pragma unroll
@@ -803,30 +838,8 @@ __global__ __launch_bounds__(NT) void eoq_softmax_kernel(float* __restrict__ x, 
     }
     return v;
   };
-  auto load = [&](auto e) __attribute__((always_inline)) {
-    float4 v = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    if (e >= e_first && e < e_last) {
-      v = reinterpret_cast<const float4*>(row)[e];
-    } else {
-      const int64_t b = 4 * (int64_t)e;
-      if (b >= head && b < end) v.x = row[b];
-      if (b + 1 >= head && b + 1 < end) v.y = row[b + 1];
-      if (b + 2 >= head && b + 2 < end) v.z = row[b + 2];
-      if (b + 3 >= head && b + 3 < end) v.w = row[b + 3];
-    }
-    return v;
-  };
-  auto store = [&](auto e, const float4& v) __attribute__((always_inline)) {
-    if (e >= e_first && e < e_last) {
-      reinterpret_cast<float4*>(row)[e] = v;
-    } else {
-      const int64_t b = 4 * (int64_t)e;
-      if (b >= head && b < end) row[b] = v.x;
-      if (b + 1 >= head && b + 1 < end) row[b + 1] = v.y;
-      if (b + 2 >= head && b + 2 < end) row[b + 2] = v.z;
-      if (b + 3 >= head && b + 3 < end) row[b + 3] = v.w;
-    }
-  };
+  auto load = [&](auto e) __attribute__((always_inline)) { return r.load(e); };
+  auto store = [&](auto e, const float4& v) __attribute__((always_inline)) { r.store(e, v); };
   float4 v[NV];
   float m = -INFINITY;
 #pragma unroll
@@ -885,6 +898,63 @@ __global__ __launch_bounds__(NT) void eoq_softmax_kernel(float* __restrict__ x, 
     o.w *= inv;
     store(e, o);
   }
+}
+
+// Softmax of few long rows: PART_ITEMS accesses of a row to a workgroup, in two kernels.  With a compute unit to a row most of the
+// chip is idle, the exponentials of 65536 elements alone take a unit 8 us, and what does not fit its registers is read three
+// times.  The first kernel leaves the maximum of every part and the sum of the exponentials against it, the second forms the row's
+// from those and scales its part: two reads and one write.
+constexpr int PART_THREADS = 256, PART_NV = 4, PART_ITEMS = PART_THREADS * PART_NV;
+__global__ __launch_bounds__(PART_THREADS) void eoq_softmax_parts_kernel(float* __restrict__ x, int64_t len, int64_t stride,
+                                                                         float2* __restrict__ stats) {
+  __shared__ float red[2][PART_THREADS / 64];
+  const SoftmaxRow r(x, blockIdx.y, len, stride);
+  const int tid = threadIdx.x;
+  const int64_t e0 = (int64_t)blockIdx.x * PART_ITEMS + tid;
+  float4 v[PART_NV];
+  EOQ_SFOR(k, PART_NV, v[k] = r.load(e0 + k * PART_THREADS););   // behind the row: -inf
+  float m = -INFINITY;
+  EOQ_SFOR(k, PART_NV, m = fmaxf(fmaxf(m, fmaxf(v[k].x, v[k].y)), fmaxf(v[k].z, v[k].w)););
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
+  if ((tid & 63) == 0) red[0][tid >> 6] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+  const float ref = m == -INFINITY ? 0.0f : m;   // a part of -inf alone adds nothing to a row that has more
+  float sum = 0.0f;
+  EOQ_SFOR(k, PART_NV, sum += (expf(v[k].x - ref) + expf(v[k].y - ref)) + (expf(v[k].z - ref) + expf(v[k].w - ref)););
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s, 64);
+  if ((tid & 63) == 0) red[1][tid >> 6] = sum;
+  __syncthreads();
+  if (tid == 0)
+    stats[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = make_float2(m, (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
+}
+// Every wave forms the row's maximum and sum by itself, in the same order.  A row of -inf alone, or with a NaN or +inf, is NaN.
+__global__ __launch_bounds__(PART_THREADS) void eoq_softmax_scale_kernel(float* __restrict__ x, int64_t len, int64_t stride,
+                                                                         const float2* __restrict__ stats) {
+  const SoftmaxRow r(x, blockIdx.y, len, stride);
+  const int tid = threadIdx.x, lane = tid & 63, parts = (int)gridDim.x;
+  const int64_t e0 = (int64_t)blockIdx.x * PART_ITEMS + tid;
+  float4 v[PART_NV];
+  EOQ_SFOR(k, PART_NV, v[k] = r.load(e0 + k * PART_THREADS););
+  __builtin_amdgcn_sched_barrier(0);   // on their way while the row's numbers are formed
+  const float2* st = stats + (size_t)blockIdx.y * parts;
+  float m = -INFINITY, sum = 0.0f;
+  for (int p = lane; p < parts; p += 64) m = fmaxf(m, st[p].x);
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
+  for (int p = lane; p < parts; p += 64) sum += st[p].y * expf(st[p].x - m);
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s, 64);
+  const float inv = 1.0f / sum;
+  EOQ_SFOR(k, PART_NV,
+    v[k].x = expf(v[k].x - m) * inv;
+    v[k].y = expf(v[k].y - m) * inv;
+    v[k].z = expf(v[k].z - m) * inv;
+    v[k].w = expf(v[k].w - m) * inv;
+    r.store(e0 + k * PART_THREADS, v[k]);
+  );
 }
 
 }  // namespace
@@ -960,8 +1030,27 @@ hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_se
   return hipGetLastError();
 }
 
-hipError_t eoq_launch_softmax(const EoqLaunch& L, float* x, int64_t rows, int64_t len, int64_t stride) {
+// Parts of a row that the two kernels take, 0 where one workgroup takes it whole.  The second launch costs 2 to 3 us, so the row has
+// to be long, and the more rows there are the busier the chip is with one each.  us, a workgroup to a row / in parts: 32 rows of
+// 16380 5.6 / 7.3, of 32768 8.9 / 8.0, of 65536 14.4 / 9.0, of 131072 32.6 / 11.3; one row of 400000 91.6 / 7.1; 84 rows of 50001
+// 13.4 / 12.2; 128 of 50001 14.1 / 14.5, of 98304 33.4 / 29.3; 256 of 65536 28.7 / 36.7, of 98304 48.8 / 50.4, of 131072
+// 78.0 / 64.1.  (At 32768 and below the caller's second launch takes the host what the GPU gains.)  Against 64 bits both are off by
+// 4e-8 to 2e-7 in the 2-norm, the parts by less more often than not.
+extern "C" int64_t eoq_softmax_row_parts(int64_t rows, int64_t len) {
+  const int64_t from = rows <= 96 ? 32769 : (rows <= 160 ? 65537 : 131072);
+  if (rows < 1 || rows > 65535 || len < from || len > (int64_t)1 << 40) return 0;
+  return ((len + 3 + 3) / 4 + PART_ITEMS - 1) / PART_ITEMS;
+}
+
+hipError_t eoq_launch_softmax(const EoqLaunch& L, float* x, int64_t rows, int64_t len, int64_t stride, float* stats) {
   if (L.ev) (void)hipEventRecord(L.ev[10], L.stream);
+  if (stats) {
+    const dim3 grid((unsigned)eoq_softmax_row_parts(rows, len), (unsigned)rows);
+    hipLaunchKernelGGL(eoq_softmax_parts_kernel, grid, dim3(PART_THREADS), 0, L.stream, x, len, stride, reinterpret_cast<float2*>(stats));
+    hipLaunchKernelGGL(eoq_softmax_scale_kernel, grid, dim3(PART_THREADS), 0, L.stream, x, len, stride, reinterpret_cast<const float2*>(stats));
+    if (L.ev) (void)hipEventRecord(L.ev[11], L.stream);
+    return hipGetLastError();
+  }
   // as many lanes as it takes to hold the row in registers (64 elements per lane are what 1024 lanes have room for);
   // rows of up to 4096 with few elements per lane: the latency of a lane's chain is what counts there
   const int64_t span = len + 3;

@@ -539,7 +539,12 @@ size_t eoq_attend_workspace_bytes(const eoq_ctx* ctx, int64_t n_seq, int n_kv_he
   return (size_t)eoq_attend_most_runs(n_seq * n_kv_heads, blocks_per_head, ctx->n) * eoq_attend_run_bytes();
 }
 
-eoq_status eoq_softmax(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, int64_t row_stride, void* hip_stream) {
+size_t eoq_softmax_workspace_bytes(const eoq_ctx* ctx, int64_t rows, int64_t len) {
+  return ctx ? (size_t)(rows * eoq_softmax_row_parts(rows, len)) * 2 * sizeof(float) : 0;
+}
+
+static eoq_status softmax_impl(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, int64_t row_stride, void* workspace,
+                               size_t workspace_bytes, void* hip_stream) {
   if (!ctx) return EOQ_ERR_ARG;
   ctx->err.clear();
   if (ctx->device < 0) return fail(ctx, EOQ_ERR_HIP, "context was created without a HIP device");
@@ -547,14 +552,27 @@ eoq_status eoq_softmax(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, i
   if (rows == 0 || len == 0) return EOQ_OK;
   if (!scores || !aligned16(scores)) return fail(ctx, EOQ_ERR_ARG, "null or misaligned score pointer");
   if (rows > 0x7FFFFFFF) return fail(ctx, EOQ_ERR_UNSUPPORTED, "more than 2^31 - 1 rows");
+  const size_t need = eoq_softmax_workspace_bytes(ctx, rows, len);
+  if (need == 0) workspace = nullptr;   // a row to a workgroup
+  if (workspace && !aligned16(workspace)) return fail(ctx, EOQ_ERR_ARG, "misaligned workspace");
+  if (workspace && workspace_bytes < need) return fail(ctx, EOQ_ERR_WORKSPACE, "workspace too small");
   const EoqLaunch L = make_launch(ctx, hip_stream);
-  const hipError_t e = eoq_launch_softmax(L, scores, rows, len, row_stride);
+  const hipError_t e = eoq_launch_softmax(L, scores, rows, len, row_stride, static_cast<float*>(workspace));
   if (ctx->profile) ctx->ev_valid[5] = (e == hipSuccess);
   if (e != hipSuccess) {
     ctx->err = std::string("HIP: ") + hipGetErrorString(e);
     return EOQ_ERR_HIP;
   }
   return EOQ_OK;
+}
+
+eoq_status eoq_softmax(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, int64_t row_stride, void* hip_stream) {
+  return softmax_impl(ctx, scores, rows, len, row_stride, nullptr, 0, hip_stream);
+}
+
+eoq_status eoq_softmax_ws(eoq_ctx* ctx, float* scores, int64_t rows, int64_t len, int64_t row_stride, void* workspace,
+                          size_t workspace_bytes, void* hip_stream) {
+  return softmax_impl(ctx, scores, rows, len, row_stride, workspace, workspace_bytes, hip_stream);
 }
 
 static eoq_status attend_impl(eoq_ctx* ctx, eoq_packed values, int64_t n_seq, int n_kv_heads, int64_t block_capacity,

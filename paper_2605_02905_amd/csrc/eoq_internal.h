@@ -119,7 +119,9 @@ hipError_t eoq_launch_attend(const EoqLaunch& L, eoq_packed values, int64_t n_se
                              int64_t blocks_per_head, int64_t block_capacity, const float* weights,
                              int64_t weight_stride, int n_q_heads, float* out, float* partial,
                              const void* tail_fp16 = nullptr, int64_t tail_capacity = 0, int tail_len = 0);
-hipError_t eoq_launch_softmax(const EoqLaunch& L, float* x, int64_t rows, int64_t len, int64_t stride);
+extern "C" int64_t eoq_softmax_row_parts(int64_t rows, int64_t len);
+// stats: two floats for every part of a row, or null: a row to a workgroup
+hipError_t eoq_launch_softmax(const EoqLaunch& L, float* x, int64_t rows, int64_t len, int64_t stride, float* stats);
 
 // TQ_prod side information of stored records and scores with the correction of Eq. (qjl)
 hipError_t eoq_launch_qjl(const EoqLaunch& L, const void* blocks_fp16, int64_t B, eoq_packed rec, eoq_qjl out);

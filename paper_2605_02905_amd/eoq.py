@@ -21,7 +21,7 @@ FLAG_RANK_CLAMPED, FLAG_SHRINK_GUARD, FLAG_NO_CONVERGE, FLAG_NONFINITE = 1, 2, 4
 
 EXPORTS = ["eoq_create", "eoq_destroy", "eoq_pilot_k", "eoq_workspace_bytes", "eoq_rotation", "eoq_projection",
            "eoq_codebook", "eoq_qjl_encode", "eoq_scores_prod",
-           "eoq_compress", "eoq_compress_static", "eoq_static_max_blocks", "eoq_compress_q4", "eoq_compress_chunk", "eoq_expand_factors", "eoq_decompress", "eoq_scores", "eoq_scores_stream", "eoq_softmax", "eoq_attend_workspace_bytes", "eoq_attend", "eoq_attend_stream", "eoq_set_solver", "eoq_set_loss", "eoq_profile", "eoq_stage_ms", "eoq_ceiling", "eoq_last_error"]
+           "eoq_compress", "eoq_compress_static", "eoq_static_max_blocks", "eoq_compress_q4", "eoq_compress_chunk", "eoq_expand_factors", "eoq_decompress", "eoq_scores", "eoq_scores_stream", "eoq_softmax", "eoq_softmax_workspace_bytes", "eoq_softmax_ws", "eoq_attend_workspace_bytes", "eoq_attend", "eoq_attend_stream", "eoq_set_solver", "eoq_set_loss", "eoq_profile", "eoq_stage_ms", "eoq_ceiling", "eoq_last_error"]
 
 
 class EoqError(RuntimeError):
@@ -103,6 +103,10 @@ def lib():
         L.eoq_scores_stream.restype = C.c_int
         L.eoq_softmax.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_void_p]
         L.eoq_softmax.restype = C.c_int
+        L.eoq_softmax_workspace_bytes.argtypes = [C.c_void_p, C.c_int64, C.c_int64]
+        L.eoq_softmax_workspace_bytes.restype = C.c_size_t
+        L.eoq_softmax_ws.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_void_p, C.c_size_t, C.c_void_p]
+        L.eoq_softmax_ws.restype = C.c_int
         L.eoq_attend_workspace_bytes.argtypes = [C.c_void_p, C.c_int64, C.c_int, C.c_int64]
         L.eoq_attend_workspace_bytes.restype = C.c_size_t
         L.eoq_attend.argtypes = [C.c_void_p, _Packed, C.c_int64, C.c_int, C.c_int64, C.c_int64, C.c_void_p, C.c_int64,
@@ -404,8 +408,15 @@ class Context:
         assert scores.is_cuda and scores.is_contiguous() and scores.dtype == torch.float32
         stride = scores.size(-1)
         rows = scores.numel() // stride if stride else 0
-        self._check(lib().eoq_softmax(self._h, scores.data_ptr(), rows, stride if length is None else length, stride,
-                                      _stream_ptr(scores.device)))
+        if length is None:
+            length = stride
+        need = lib().eoq_softmax_workspace_bytes(self._h, rows, length) if length > 32768 else 0
+        if need:   # few long rows: several workgroups share one
+            ws = torch.empty(need, dtype=torch.uint8, device=scores.device)
+            self._check(lib().eoq_softmax_ws(self._h, scores.data_ptr(), rows, length, stride, ws.data_ptr(), need,
+                                             _stream_ptr(scores.device)))
+        else:
+            self._check(lib().eoq_softmax(self._h, scores.data_ptr(), rows, length, stride, _stream_ptr(scores.device)))
         return scores
 
     def eoq_attend_workspace_bytes(self, n_seq: int, n_kv_heads: int, blocks_per_head: int) -> int:

@@ -415,6 +415,51 @@ def test_blocks_shared_by_several_workgroups_of_the_encoder(n, bits, q4):
             assert _bits_equal(few.lfac[b, :r], many.lfac[b, :r]), (b, count)
 
 
+@pytest.mark.parametrize("rows,length,stride", [(1, 32769, 32769), (3, 36865, 36870), (5, 131071, 131073), (96, 32769, 32772),
+                                                (97, 65537, 65541), (161, 131072, 131072)])
+def test_softmax_of_rows_in_parts(rows, length, stride):
+    """Rows shared by several workgroups: against float64, entries behind the length untouched, replays of a graph, -inf, NaN, inf."""
+    ctx = eoq.Context(n=128, bits=2)
+    L = eoq.lib()
+    parts = -(-(length + 3) // 4096)
+    assert L.eoq_softmax_workspace_bytes(ctx._h, rows, length) == 8 * rows * parts
+    assert L.eoq_softmax_workspace_bytes(ctx._h, rows, length - 1) in (0, 8 * rows * -(-(length + 2) // 4096))
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = 4.0 * torch.randn(rows, stride, device="cuda", generator=g)
+    x[0, :min(length - 7, 9000)] = -float("inf")            # whole parts
+    if rows > 2:
+        x[1, :length] = -float("inf")                       # a row without a number, as torch has it
+        x[2, length - 1] = float("nan")
+    if rows > 4:
+        x[3, 5000] = float("inf")
+        x[4, 17] = 90.0
+    want = torch.softmax(x[:, :length].double(), dim=-1)
+    one = x.clone()
+    assert L.eoq_softmax(ctx._h, one.data_ptr(), rows, length, stride, torch.cuda.current_stream().cuda_stream) == 0
+    have = ctx.eoq_softmax(x.clone(), length)
+    assert _bits_equal(have[:, length:], x[:, length:])
+    nan = want.isnan()
+    for y in (one, have):
+        assert torch.equal(y[:, :length].isnan(), nan)
+    # float32 exponentials (one unit) of differences rounded once (up to 2^-24 |x - max|, here at most 2^-24 * 100 for terms that
+    # matter not at all, 2^-24 * 8 for those that do) over a sum that is off by less: 1e-6 of a weight's own size and the row's
+    good = ~nan
+    err = lambda y: ((y[:, :length].double() - want)[good].norm() / want[good].norm()).item()
+    assert err(have) <= max(1.5 * err(one), 2e-7) and max(err(have), err(one)) <= 1e-6
+    ws = torch.empty(8 * rows * parts, dtype=torch.uint8, device="cuda")
+    bad = lambda p, n: L.eoq_softmax_ws(ctx._h, one.data_ptr(), rows, length, stride, p, n, None)
+    assert bad(ws.data_ptr(), ws.numel() - 1) == eoq.EOQ_ERR_WORKSPACE and bad(ws.data_ptr() + 8, ws.numel()) == eoq.EOQ_ERR_ARG
+    buf = x.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.eoq_softmax(buf, length)
+    for _ in range(3):
+        buf.copy_(x)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _bits_equal(buf, have)
+
+
 @pytest.mark.parametrize("distance", [1, 16, 20])
 def test_hand_over_to_the_jacobi_solver_uses_the_whole_chip(distance):
     """200 marked blocks, side by side or at a fixed distance, take about as long as one: there are more workgroups than

@@ -184,6 +184,16 @@ def test_scores_grid_has_the_runs_in_front_of_the_tail(lib, heads, runs, tail_gr
     assert sum(p[1] for p in places if p[0] == "run") == heads * runs
 
 
+def test_parts_of_a_softmax_row_cover_it_wherever_it_starts():
+    parts = eoq.lib().eoq_softmax_row_parts
+    parts.restype = C.c_int64
+    for rows in (0, 1, 96, 97, 160, 161, 65535, 65536, 1 << 31):
+        lengths = [k for k in range(1, 150000, 1021)] + [32768, 32769, 65536, 65537, 131071, 131072, 1 << 22, 1 << 31]
+        taken = [l for l in lengths if parts(C.c_int64(rows), C.c_int64(l))]
+        assert all(parts(C.c_int64(rows), C.c_int64(l)) * 4096 >= l + 3 for l in taken)
+        assert (not taken) == (rows < 1 or rows > 65535) and all(l > 32768 for l in taken)
+
+
 def test_shares_of_a_block_are_whole_chunks_and_none_is_empty():
     shares = eoq.lib().eoq_encode_shares
     for units in (1, 104, 256):
