@@ -964,6 +964,12 @@ int64_t eoq_attend_runs(int64_t sg_total, int64_t blocks_per_head, int n, int* p
   // 96 pairs (6144 tokens) per wave, where a second round costs little
   const int64_t pairs = blocks_per_head * (n / PAIR);
   int64_t ppw = (sg_total * pairs + 2047) / 2048;
+  // and at most 128 runs to a head while that is fewer: the finishing kernel has one workgroup for every query head, which
+  // reads 1 KB of every run.  Attention output, us, without and with this bound: one KV head of 131072 tokens, eight query
+  // heads, 2 bits 22.5 and 17.9; two of 76800, three, 4 bits 23.4 and 20.0.  (A bound of 64, in a build that differed in the
+  // finishing kernel: 25 where 128 took 17.8 and 20.5.)
+  const int64_t few = (pairs + 4 * 128 - 1) / (4 * 128);
+  ppw = ppw < few ? few : ppw;
   ppw = ppw < 1 ? 1 : (ppw > 96 ? 96 : ppw);
   *pairs_per_wave = (int)ppw;
   return (pairs + 4 * ppw - 1) / (4 * ppw);

@@ -1193,6 +1193,26 @@ def test_attention_output_weights_of_any_size(n, bits, group, filled, tail_len):
     assert np.all(np.max(np.abs(out2[0, keep].double().cpu().numpy() - want[keep]), axis=1) <= ATTEND_TOL * norm[keep])
 
 
+@pytest.mark.parametrize("n,bits,group,filled", [(512, 2, 8, 64), (128, 1, 3, 257), (512, 3, 1, 131), (1024, 4, 6, 130)])
+def test_attention_output_of_a_long_row_of_runs(n, bits, group, filled):
+    """One KV head of many blocks: 128 runs, the first length that takes two pairs of tiles to a wave, three and five.  Reference and
+    bar as above; in a workspace of exactly the size that is asked for, whose end stays as it was."""
+    ctx = eoq.Context(n=n, bits=bits)
+    spec = synth.BlockSpec("vals", n=n, n_tensors=1, blocks_per_tensor=filled, rank_lo=0, rank_hi=9)
+    blocks, _ = synth.make_blocks(spec, seed=277 + n, device=DEV)
+    store, _ = ctx.eoq_compress(blocks)
+    x = U.reconstruct64(store, bits).view(filled * n, 128)
+    T = filled * n
+    w = torch.softmax(3.0 * torch.randn(1, group, T, device=DEV, generator=torch.Generator(DEV).manual_seed(n)), dim=-1)
+    need = ctx.eoq_attend_workspace_bytes(1, 1, filled)
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+    out = ctx.eoq_attend(store, w, 1, workspace=ws[:need])
+    want = w[0].double() @ x.to(DEV)
+    norm = (w[0].double().square() @ x.to(DEV).square().sum(1)).sqrt()
+    assert bool(((out[0].double() - want).abs().amax(1) <= ATTEND_TOL * norm + 2.0 * 2.0**-24 * want.abs().amax(1)).all())
+    assert bool((ws[need:] == 0x5A).all())
+
+
 @pytest.mark.parametrize("n,group,filled", [(128, 5, 1), (512, 8, 3), (1024, 6, 37), (256, 7, 90)])
 def test_attention_output_of_wide_groups_at_4_bits(n, group, filled):
     """More than four heads per KV head at 4 bits: two workgroups share the heads where a wave has one token pair, and the
