@@ -439,22 +439,27 @@ constexpr int gi_tile_j(int w, int s) { return s < 6 ? 4 + w : (s == 6 && w >= 2
 // The 36 tiles, three rounds of twelve through LDS, into the cyclic layout: lane (ty, tx) takes element (ty, tx) of tile
 // (a, b) as A[a * 8 + b] and, for a < b, element (tx, ty) as A[b * 8 + a].  `get(s, v)` is this lane's entry number v of the
 // wave's tile wave + 4 s, in column lane % 16 and row `row(v)`.
-template <typename Get, typename Row>
+// A wave leaves the numbers FIRST .. LAST - 1 of the tiles of w = wave % 4; the first four waves read.
+template <int FIRST = 0, int LAST = 9, bool READ = true, typename Get, typename Row>
 __device__ __forceinline__ void tiles_to_lanes(double* Tl, int tid, double (&A)[64], Get&& get, Row&& row) {
-  const int ty = lane_row(tid), tx = tid & 15, wave = tid >> 6;
+  const int ty = lane_row(tid), tx = tid & 15, wave = LAST - FIRST == 9 ? tid >> 6 : (tid >> 6) & 3;
   EOQ_SFOR(rd, 3,
     __syncthreads();
     EOQ_SFOR(s3, 3,
-      double* dst = Tl + (wave + 4 * s3) * 16 * XPAD;
-      EOQ_SFOR(v, 4, dst[row(v) * XPAD + tx] = get(std::integral_constant<int, 3 * rd + s3>{}, v_ic););
+      if constexpr (3 * rd + s3 >= FIRST && 3 * rd + s3 < LAST) {
+        double* dst = Tl + (wave + 4 * s3) * 16 * XPAD;
+        EOQ_SFOR(v, 4, dst[row(v) * XPAD + tx] = get(std::integral_constant<int, 3 * rd + s3>{}, v_ic););
+      }
     );
     __syncthreads();
-    EOQ_SFOR(pp, 12,
-      constexpr int tile = 12 * rd + pp;
-      constexpr int a = gi_tile_i(tile & 3, tile >> 2); constexpr int b = gi_tile_j(tile & 3, tile >> 2);
-      A[a * 8 + b] = Tl[pp * 16 * XPAD + ty * XPAD + tx];
-      if constexpr (a != b) A[b * 8 + a] = Tl[pp * 16 * XPAD + tx * XPAD + ty];
-    );
+    if constexpr (READ) {
+      EOQ_SFOR(pp, 12,
+        constexpr int tile = 12 * rd + pp;
+        constexpr int a = gi_tile_i(tile & 3, tile >> 2); constexpr int b = gi_tile_j(tile & 3, tile >> 2);
+        A[a * 8 + b] = Tl[pp * 16 * XPAD + ty * XPAD + tx];
+        if constexpr (a != b) A[b * 8 + a] = Tl[pp * 16 * XPAD + tx * XPAD + ty];
+      );
+    }
   );
 }
 
@@ -528,31 +533,40 @@ __device__ __forceinline__ float scale_high_half(uint32_t w, float s) {
   asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(s));
   return r;
 }
-// cmax: twice 4 x 64 words (the waves' column maxima, by turns), cexp: 128 ints (exponent of the integer unit of each column);
+// SHARE 0: four waves, all nine tiles of w each.  Where a workgroup has a compute unit to itself eight waves form it, every one
+// half of the tokens' integers and, of the nine tiles of w = wave % 4, five (SHARE 1, the first four waves) or four (SHARE 2, which
+// get no part of A): the same sums of the same tiles.  One wave to a SIMD waits for its own instructions half of the time; with
+// two, compress calls, us: 16 blocks of 1024 x 128 173.6 -> 164.7, of 512 x 128 165.3 -> 160.9, of 128 x 128 138.7 -> 137.6.
+// cmax: twice WAVES x 64 words (the waves' column maxima, by turns), cexp: 128 ints (exponent of the integer unit of each column);
 // both outside the pool, which the planes fill.  n is a multiple of 128.
+template <int SHARE>
 __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size_t tok, int n, unsigned char* pool,
                                           uint32_t* cmax, int* cexp, int tid, double (&A)[64], unsigned* flag_s) {
   const int lane = tid & 63, l16 = lane & 15, kg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // loader: columns 4 m .. 4 m + 3, tokens 16 q .. 16 q + 15 of the group: the sixteen bytes of a column and plane are one write
-  const int m = tid & 31, q = tid >> 5;
-  double Gacc[9][4];  // tile number wave + 4 s, rows 4 kg + v, column l16
-  EOQ_SFOR(s, 9, EOQ_SFOR(v, 4, Gacc[s][v] = 0.0;););
+  constexpr int WAVES = SHARE == 0 ? 4 : 8, TOKENS = 64 / WAVES;
+  constexpr int FIRST = SHARE == 2 ? 5 : 0, LAST = SHARE == 1 ? 5 : 9;   // numbers of the tiles
+  const int w = SHARE == 0 ? wave : wave & 3;
+  // loader: columns 4 m .. 4 m + 3, tokens TOKENS q .. + TOKENS - 1 of the group: the sixteen (eight) bytes of a column and plane
+  // are one write, and the halves of a wave write neighbouring chunks, which spreads them over all banks
+  const int m = tid & 31, q = SHARE == 0 ? tid >> 5 : 4 * (wave >> 1) + 2 * (lane >> 5) + (wave & 1);
+  double Gacc[LAST - FIRST][4];  // tile number FIRST + s of w, rows 4 kg + v, column l16
+  EOQ_SFOR(s, LAST - FIRST, EOQ_SFOR(v, 4, Gacc[s][v] = 0.0;););
 
-  // gi_place of the loader's column 4 m, chunk q (bits 4, 5 and 7, 8 flipped by c for column 4 m + c), and of the operands
-  const int w_base = gi_place(4 * m, q), r_base = gi_place(l16, kg);
+  // gi_place of the loader's column 4 m, its tokens' chunk (bits 4, 5 and 7, 8 flipped by c for column 4 m + c), and of the operands
+  const int w_base = gi_place(4 * m, TOKENS * q >> 4) + (TOKENS * q & 15), r_base = gi_place(l16, kg);
   uint32_t top = 0u;  // largest |binary16 pattern| this lane has seen in its columns: 0x7C00 and above is Inf / NaN
-  const uint16_t* mine = src + (size_t)(16 * q) * tok + 4 * m;
-  uint2 raw[16];
+  const uint16_t* mine = src + (size_t)(TOKENS * q) * tok + 4 * m;
+  uint2 raw[TOKENS];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) raw[i] = *reinterpret_cast<const uint2*>(mine + (size_t)i * tok);
+  for (int i = 0; i < TOKENS; ++i) raw[i] = *reinterpret_cast<const uint2*>(mine + (size_t)i * tok);
 
 #pragma unroll 1
   for (int t0 = 0; t0 < n; t0 += GI_TOK) {
-    // ---- column maxima of the group: over the lane's sixteen tokens, the two halves of the wave, the four waves ----
+    // ---- column maxima of the group: over the lane's tokens, the two halves of the wave, the waves ----
     uint32_t mx[2] = {0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < TOKENS; ++i) {
       mx[0] = pk_max_u16(mx[0], raw[i].x & 0x7FFF7FFFu);
       mx[1] = pk_max_u16(mx[1], raw[i].y & 0x7FFF7FFFu);
     }
@@ -561,12 +575,12 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
       const auto o = __builtin_amdgcn_permlane32_swap(mx[i], mx[i], false, false);
       mx[i] = pk_max_u16(o[0], o[1]);
     }
-    uint32_t* cm = cmax + ((t0 / GI_TOK) & 1) * 256;   // the other half may still be read
+    uint32_t* cm = cmax + ((t0 / GI_TOK) & 1) * (WAVES * 64);   // the other half may still be read
     if (lane < 32) *reinterpret_cast<uint2*>(cm + wave * 64 + m * 2) = make_uint2(mx[0], mx[1]);
     __syncthreads();  // maxima complete; the previous group no longer reads planes or exponents
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint2 o = *reinterpret_cast<const uint2*>(cm + w * 64 + m * 2);
+    for (int o_wave = 0; o_wave < WAVES; ++o_wave) {
+      const uint2 o = *reinterpret_cast<const uint2*>(cm + o_wave * 64 + m * 2);
       mx[0] = pk_max_u16(mx[0], o.x);
       mx[1] = pk_max_u16(mx[1], o.y);
     }
@@ -581,23 +595,26 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
       // I = sum_k d_k 256^k with balanced digits d_k in [-128, 127]: adding 128 to every digit place makes them the
       // plain bytes of I + 0x80808080 (|I| < 2^30: no carry out of the top), and flipping the top bit of each byte
       // takes the 128 off again, as a two's-complement byte.  The four planes are those bytes.
-      uint32_t pl[4][4];   // [four tokens][plane]
-      EOQ_SFOR(h, 4,
+      uint32_t pl[TOKENS / 4][4];   // [four tokens][plane]
+      EOQ_SFOR(h, TOKENS / 4,
         uint32_t dg[4];
         EOQ_SFOR(it, 4,
-          const uint32_t w = (c >> 1) == 0 ? raw[4 * h + it].x : raw[4 * h + it].y;
-          const int I = (int)((c & 1) ? scale_high_half(w, scale) : scale_low_half(w, scale));   // truncation towards zero
+          const uint32_t pair = (c >> 1) == 0 ? raw[4 * h + it].x : raw[4 * h + it].y;
+          const int I = (int)((c & 1) ? scale_high_half(pair, scale) : scale_low_half(pair, scale));   // truncation towards zero
           dg[it] = ((uint32_t)I + 0x80808080u) ^ 0x80808080u;
         );
         transpose_bytes(dg[0], dg[1], dg[2], dg[3], pl[h]);
       );
       unsigned char* dst = pool + (w_base ^ (c << 4) ^ (c * GI_ROW));
-      EOQ_SFOR(p, 4, *reinterpret_cast<uint4*>(dst + p * GI_PLANE) = make_uint4(pl[0][p], pl[1][p], pl[2][p], pl[3][p]););
+      EOQ_SFOR(p, 4,
+        if constexpr (TOKENS == 16) *reinterpret_cast<uint4*>(dst + p * GI_PLANE) = make_uint4(pl[0][p], pl[1][p], pl[2][p], pl[3][p]);
+        else *reinterpret_cast<uint2*>(dst + p * GI_PLANE) = make_uint2(pl[0][p], pl[1][p]);
+      );
     );
     if (q == 0) *reinterpret_cast<int4*>(cexp + 4 * m) = make_int4(ex[0], ex[1], ex[2], ex[3]);
     if (t0 + GI_TOK < n) {  // next group on its way during the products
 #pragma unroll
-      for (int i = 0; i < 16; ++i) raw[i] = *reinterpret_cast<const uint2*>(mine + (size_t)(t0 + GI_TOK + i) * tok);
+      for (int i = 0; i < TOKENS; ++i) raw[i] = *reinterpret_cast<const uint2*>(mine + (size_t)(t0 + GI_TOK + i) * tok);
     }
     __syncthreads();
     // ---- products: lane supplies row / column l16 of the tile, tokens 64 h + 16 kg .. + 15 ----
@@ -608,8 +625,8 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
     v4i acc[7];   // acc[c]: plane pairs (p, q) with p + q = c, weight 2^(8 c)
     auto tile_product = [&](auto s_ic) __attribute__((always_inline)) {
       constexpr int s = decltype(s_ic)::value;
-      const int tI = gi_tile_i(wave, s); const int tJ = gi_tile_j(wave, s);
-      if constexpr (s == 0 || s == 7) { EOQ_SFOR(h, 2, EOQ_SFOR(p, 4, kept[h][p] = operand(tJ, h, p););); }
+      const int tI = gi_tile_i(w, s); const int tJ = gi_tile_j(w, s);
+      if constexpr (s == FIRST || s == 7) { EOQ_SFOR(h, 2, EOQ_SFOR(p, 4, kept[h][p] = operand(tJ, h, p););); }
       EOQ_SFOR(cc, 7, EOQ_SFOR(v, 4, acc[cc][v] = 0;););
       EOQ_SFOR(h, 2,
         v4i a[4]; v4i b[4];
@@ -628,7 +645,7 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
     };
     auto tile_sum = [&](auto s_ic) __attribute__((always_inline)) {
       constexpr int s = decltype(s_ic)::value;
-      const int tI = gi_tile_i(wave, s); const int tJ = gi_tile_j(wave, s);
+      const int tI = gi_tile_i(w, s); const int tJ = gi_tile_j(w, s);
       // into double precision with the exponents of rows 4 kg + v (tile I) and column l16 (tile J)
       const int ej = cexp[16 * tJ + l16];
       const int4 ei = *reinterpret_cast<const int4*>(cexp + 16 * tI + 4 * kg);
@@ -642,14 +659,15 @@ __device__ __forceinline__ void gram_int8(const uint16_t* __restrict__ src, size
         const int m01 = acc[0][v] + (acc[1][v] << 8), m23 = acc[2][v] + (acc[3][v] << 8);
         const int m45 = acc[4][v] + (acc[5][v] << 8);
         const double val = fma(fma(fma((double)acc[6][v], 65536.0, (double)m45), 65536.0, (double)m23), 65536.0, (double)m01);
-        Gacc[s][v] += ldexp(val, eiv[v] + ej);
+        Gacc[s - FIRST][v] += ldexp(val, eiv[v] + ej);
       );
     };
-    EOQ_SFOR(s, 9, tile_product(s_ic); tile_sum(s_ic););
+    EOQ_SFOR(s, 9, if constexpr (s >= FIRST && s < LAST) { tile_product(s_ic); tile_sum(s_ic); });
   }
   // a column maximum with all exponent bits set: the integer conversion of that pass saturated, G is meaningless
   if (q == 0 && (((top & 0xFFFFu) >= 0x7C00u) || ((top >> 16) >= 0x7C00u))) atomicOr(flag_s, EOQ_FLAG_NONFINITE);
-  tiles_to_lanes(reinterpret_cast<double*>(pool), tid, A, [&](auto s, auto v) { return Gacc[decltype(s)::value][decltype(v)::value]; },
+  tiles_to_lanes<FIRST, LAST, SHARE != 2>(reinterpret_cast<double*>(pool), tid, A,
+                 [&](auto s, auto v) { return Gacc[decltype(s)::value - FIRST][decltype(v)::value]; },
                  [&](int v) { return 4 * kg + v; });
 }
 
@@ -1325,10 +1343,11 @@ struct TridiagLds {
   int twist[EV_BATCH];
   unsigned flag;
 };
-// LONE: the batch has no more blocks than the device has compute units, and a workgroup the whole of one.  Six waves during the
-// reduction (see LoneLds), four behind it, and a block with repeated eigenvalues is solved on the spot, in the LDS that is free then:
+// LONE: the batch has no more blocks than the device has compute units, and a workgroup the whole of one.  Eight waves form the Gram
+// matrix of a binary16 block, six reduce it (see LoneLds), four do the rest, and a block with repeated eigenvalues is solved on the spot, in the LDS that is free then:
 // no kernel behind this one looks for marks (4 us).
-constexpr int LONE_THREADS = THREADS + 128;
+constexpr int LONE_THREADS = 2 * THREADS;
+static_assert(sizeof(LoneLds) >= 2 * 8 * 64 * 4, "column maxima of eight waves");
 template <bool LONE> struct SpectralLds { TridiagLds<false> t; };
 template <> struct SpectralLds<true> { union { TridiagLds<true> t; JacobiLds jacobi; }; };
 
@@ -1364,9 +1383,15 @@ __device__ __forceinline__ void tridiag_block(SpectralLds<LONE>& lds,
   if constexpr (LONE) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (w >= 4) {
-      // the barriers of the Gram stage: two a group of tokens and the six of tiles_to_lanes; the pool changes hands
-      const int before = (dtype == EOQ_F16 ? 2 * (n / GI_TOK) : 0) + 6 + 1;
-      for (int i = 0; i < before; ++i) __syncthreads();
+      if (dtype == EOQ_F16) {
+        double none[64];
+        gram_int8<2>(static_cast<const uint16_t*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, pool,
+                     reinterpret_cast<uint32_t*>(&lds.t.reduce), reinterpret_cast<int*>(dT), tid, none, &flag_s);
+      } else {
+        for (int i = 0; i < 6; ++i) __syncthreads();   // the barriers of tiles_to_lanes
+      }
+      __syncthreads();   // the pool changes hands
+      if (w >= 6) return;
       __syncthreads();   // rows 0 and 1
       if (w == 5) {
         __syncthreads();   // v complete
@@ -1390,8 +1415,9 @@ __device__ __forceinline__ void tridiag_block(SpectralLds<LONE>& lds,
   {
     double A[64];
     if (dtype == EOQ_F16)
-      gram_int8(static_cast<const uint16_t*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, pool,
-                reinterpret_cast<uint32_t*>(lam_s) /* and atoms */, reinterpret_cast<int*>(dT), tid, A, &flag_s);
+      gram_int8<LONE ? 1 : 0>(static_cast<const uint16_t*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, pool,
+                              LONE ? reinterpret_cast<uint32_t*>(&lds.t.reduce) : reinterpret_cast<uint32_t*>(lam_s) /* and atoms */,
+                              reinterpret_cast<int*>(dT), tid, A, &flag_s);
     else
       gram_f64(static_cast<const float*>(blocks) + map.in_base(blk), (size_t)map.token_stride, n, reinterpret_cast<double*>(pool), tid, A, &flag_s);
     __syncthreads();  // the pool changes hands
