@@ -1912,8 +1912,8 @@ hipError_t eoq_launch_spectral(const EoqLaunch& L, const void* blocks, int dtype
                        L.k, L.rank_thr, L.r_max, L.loss, B, (const int*)nullptr, lam, wfac, out.rank,
                        out.phi, out.sigma, out.rfac, out.flags);
   } else if (B <= L.units) {
-    // A compute unit for every block.  Compress calls, us, here and with the two kernels below: 16 blocks of 128 x 128 136.5 and
-    // 145.1, 256 of them 137.6 and 145.8, 256 of 1024 x 128 211.8 and 220.7.  One block more and a unit has to hold two at a time
+    // A compute unit for every block.  Compress calls, us, here and with the two kernels below: 16 blocks of 128 x 128 135.9 and
+    // 145.1, 256 of them 137.9 and 145.8, 256 of 1024 x 128 203.0 and 220.7.  One block more and a unit has to hold two at a time
     // (257 of 128 x 128: 190).
     hipLaunchKernelGGL(eoq_spectral_lone_kernel, dim3((unsigned)B), dim3(LONE_THREADS), 0, L.stream, blocks, L.map, dtype, L.n,
                        L.k, L.rank_thr, L.r_max, L.loss, lam, wfac, tri, out.rank, out.phi, out.sigma, out.rfac, out.flags);
